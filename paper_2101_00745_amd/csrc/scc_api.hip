@@ -206,11 +206,11 @@ int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* d
                                                         (float*)dw, (float*)workspace, p, (hipStream_t)stream));
     // layers both matrix-core kernels take: their two grids as one launch
     if (dtype == SCC_F32) {
-        if (scc::backward_merged_applicable((const float*)x, (const float*)dy, (const float*)dx, p))
+        if (scc::backward_merged_applicable<float>(p))
             return launch_status(scc::launch_backward_merged((const float*)x, (const float*)dy, (const float*)w,
                                                              (float*)dx, (float*)dw, (float*)workspace, p,
                                                              (hipStream_t)stream));
-    } else if (scc::backward_merged_applicable((const scc::bf16_t*)x, (const scc::bf16_t*)dy, (const scc::bf16_t*)dx, p)) {
+    } else if (scc::backward_merged_applicable<scc::bf16_t>(p)) {
         return launch_status(scc::launch_backward_merged((const scc::bf16_t*)x, (const scc::bf16_t*)dy,
                                                          (const scc::bf16_t*)w, (scc::bf16_t*)dx, (float*)dw,
                                                          (float*)workspace, p, (hipStream_t)stream));

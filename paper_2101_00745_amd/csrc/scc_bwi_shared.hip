@@ -25,7 +25,7 @@
 // lane f of a half-wave is channel c0 + f, and consecutive channels read consecutive weights of a filter's row
 // (one coalesced 128-byte read per half-wave and K value); weights outside the window are masked to zero.
 //
-// fp32 tensors, planes whose size is a multiple of 4 and 16-byte aligned dy/dx only; the products are the
+// fp32 tensors and planes of at least 4 pixels only (a lane owns a group of 4 consecutive columns); the products are the
 // six-of-nine bf16 partial products of scc_common.h, sums binary32.
 #include <type_traits>
 
@@ -38,6 +38,7 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef int i32x4 __attribute__((ext_vector_type(4)));
@@ -56,6 +57,7 @@ struct BwiSharedTiling {
     int FG;        // workgroups per column tile: ceil(CB / 4)
     int total;     // workgroups with work
     int chunk;     // consecutive workgroups given to one XCD
+    Groups q;      // column groups of 4 pixels; a workgroup owns 32 of them
 };
 
 __host__ __device__ inline int floor_div_g(int a, int b)  // b > 0
@@ -161,9 +163,9 @@ __global__ __launch_bounds__(kWavesG * 64, 2) void backward_input_shared32(const
     const int lq = tid & 31, lu = tid >> 5;
     uint32_t lcol;                                           // byte offset of this thread's 4 columns in plane 0 of their sample
     {
-        const uint32_t q = (uint32_t)ct * kColsG + 4u * (uint32_t)lq;
-        const uint32_t qq = q < (uint32_t)P.NQ ? q : 0u;     // columns past the end read column 0 and are never stored
-        const uint32_t n = qq / (uint32_t)P.HW, p = qq % (uint32_t)P.HW;
+        const uint32_t u = (uint32_t)ct * 32u + (uint32_t)lq;
+        uint32_t n, p;
+        column_of_group(u < (uint32_t)T.q.count ? u : 0u, T.q, n, p);   // past the end: group 0, never stored
         lcol = (n * (uint32_t)P.Cout * (uint32_t)P.HW + p) * 4u;
     }
     const int b_dst = (((lu >> 2) * 2 + ((lu >> 1) & 1)) * kColsG + lq) * 16 + 8 * (lu & 1);
@@ -174,7 +176,7 @@ __global__ __launch_bounds__(kWavesG * 64, 2) void backward_input_shared32(const
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             const uint32_t rowb = (uint32_t)table[kRoundG * r + 4 * lu + e][2];   // plane 0 for positions without a filter
-            braw[set][e] = *(const f32x4*)(gb + (lcol + rowb));
+            braw[set][e] = *(const f32x4u*)(gb + (lcol + rowb));
         }
     };
     auto commit_b = [&](auto SET) {                          // set s -> LDS buffer s
@@ -267,16 +269,17 @@ __global__ __launch_bounds__(kWavesG * 64, 2) void backward_input_shared32(const
     if (!tvalid) return;
 
     // ---- store: accumulator register v holds channel c0 + 8*(v/4) + 4*h + v%4, columns 4f .. 4f+3 of the tile ----
-    const uint32_t q = (uint32_t)ct * kColsG + 4u * (uint32_t)f;
-    if (q >= (uint32_t)P.NQ) return;
-    const uint32_t n = q / (uint32_t)P.HW, p = q % (uint32_t)P.HW;
+    const uint32_t u = (uint32_t)ct * 32u + (uint32_t)f;
+    if (u >= (uint32_t)T.q.count) return;
+    uint32_t n, p;
+    column_of_group(u, T.q, n, p);
     float* db = dx + (size_t)n * P.Cin * P.HW + p;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int cr = c0 + 8 * (v >> 2) + 4 * h + (v & 3);
         if (cr < P.Cin) {
             const f32x4 o = {acc[0][v], acc[1][v], acc[2][v], acc[3][v]};
-            __builtin_nontemporal_store(o, (f32x4*)(db + (size_t)cr * P.HW));   // written once, never re-read here
+            __builtin_nontemporal_store(o, (f32x4u*)(db + (size_t)cr * P.HW));   // written once, never re-read here
         }
     }
 }
@@ -287,7 +290,8 @@ BwiSharedTiling make_bwi_shared_tiling(const Problem& p)
     t.b = make_band(p);
     t.CB = (p.Cin + 31) / 32;
     t.FG = (t.CB + kWavesG - 1) / kWavesG;
-    const long long nct = (p.NQ + kColsG - 1) / kColsG;
+    t.q = column_groups(p, 4);
+    const long long nct = (t.q.count + 31) / 32;
     t.total = (int)(nct * t.FG);
     t.chunk = (t.total + 7) / 8;
     return t;
@@ -317,17 +321,16 @@ void walk_stats(const Problem& p, const BwiSharedTiling& t, int* longest, double
 
 }  // namespace
 
-bool backward_input_shared_eligible(const float* dy, const float* dx, const Problem& p)
+bool backward_input_shared_eligible(const Problem& p)
 {
-    const uintptr_t addr = (uintptr_t)dy | (uintptr_t)dx;
-    if (!backward_input_mfma_eligible(p) || p.HW % 4 != 0 || (addr & 15) != 0) return false;
+    if (!backward_input_mfma_eligible(p) || p.HW < 4) return false;
     const BwiSharedTiling t = make_bwi_shared_tiling(p);
     int longest;
     double gain;
     walk_stats(p, t, &longest, &gain);
     // the table holds the walk and one more round; weight offsets k*L + j fit an int (checked by the caller's eligibility)
     return (longest + kRoundG - 1) / kRoundG * kRoundG + kRoundG <= kMaxPos &&
-           (long long)((p.NQ + kColsG - 1) / kColsG) * t.FG < (1ll << 28);
+           (t.q.count + 31) / 32 * t.FG < (1ll << 28);
 }
 
 // Measured: the shared walk wins where the per-block kernel loses the re-reads of dy to HBM, i.e. where windows
@@ -336,12 +339,12 @@ bool backward_input_shared_eligible(const float* dy, const float* dx, const Prob
 // three times, 124 against 133 us), and where four blocks walk nearly the same filters (cg = 1 at the metric
 // shape, 4x: 40 against 44 us); the grid has to fill the chip (two workgroups per CU).  With fewer shared filters
 // or fewer columns the per-block kernel is faster (cg = 2: 27 against 30 us; the stack's layers).
-bool backward_input_shared_preferred(const float* dy, const float* dx, const Problem& p)
+bool backward_input_shared_preferred(const Problem& p)
 {
 #ifdef SCC_SHARED_ALWAYS
-    return backward_input_shared_eligible(dy, dx, p);
+    return backward_input_shared_eligible(p);
 #else
-    if (!backward_input_shared_eligible(dy, dx, p)) return false;
+    if (!backward_input_shared_eligible(p)) return false;
     const BwiSharedTiling t = make_bwi_shared_tiling(p);
     int longest;
     double gain;

@@ -22,6 +22,33 @@ struct DwGeom {
     int H, W, Ho, Wo, s;
 };
 
+// Columns in groups of CT consecutive pixels of one sample, so that a lane moves a group of a plane with one load or
+// store whatever the plane's size: a sample has per = ceil(HW / CT) groups, group i of them the pixels
+// min(CT*i, HW - CT) .. + CT-1.  When CT does not divide HW the last group overlaps the one before it: forward and
+// grad-input compute the shared pixels twice, from the same operands in the same order, and store the same bits;
+// grad-weight, which sums over pixels, counts them once.  Needs HW >= CT.  (One 4-byte access per column, which
+// planes of a size like 7x7 took before, costs an instruction of the same address time as one of 16 bytes: forward and
+// backward of 64 x 512 -> 1024 channels on 7x7 maps, fp32, 162 us with single columns, 103 with groups.)
+struct Groups {
+    int per;          // groups per sample
+    int last;         // first pixel of a sample's last group
+    int ct;           // pixels per group
+    long long count;  // groups of the batch
+};
+
+inline __host__ __device__ void column_of_group(uint32_t u, const Groups& q, uint32_t& n, uint32_t& p)
+{
+    n = u / (uint32_t)q.per;
+    const uint32_t i = (u - n * (uint32_t)q.per) * (uint32_t)q.ct;
+    p = i < (uint32_t)q.last ? i : (uint32_t)q.last;
+}
+
+inline Groups column_groups(const Problem& p, int ct)
+{
+    const int per = (p.HW + ct - 1) / ct;
+    return {per, p.HW - ct, ct, (long long)p.N * per};
+}
+
 typedef uint16_t bf16_t;  // bfloat16 storage: the upper 16 bits of a binary32
 
 __device__ __forceinline__ float to_f32(float v) { return v; }
@@ -100,15 +127,15 @@ template <typename T> hipError_t launch_backward_weight_generic(const T* x, cons
 bool forward_mfma_eligible(const Problem& p);
 template <typename T> hipError_t launch_forward_mfma(const T* x, const T* w, T* y, const Problem& p, hipStream_t st);
 // Forward with the activation operand shared by four tiles through LDS, fp32 (scc_fwd_shared.hip)
-bool forward_shared_eligible(const float* x, const float* w, const float* y, const Problem& p);
+bool forward_shared_eligible(const Problem& p);
 double forward_shared_gain(const Problem& p);   // channel fetches saved: own spans / shared walks
-bool forward_shared_preferred(const float* x, const float* w, const float* y, const Problem& p);   // ... and faster
+bool forward_shared_preferred(const Problem& p);   // ... and faster
 hipError_t launch_forward_shared(const float* x, const float* w, float* y, const Problem& p, hipStream_t st);
 bool backward_input_mfma_eligible(const Problem& p);
 template <typename T> hipError_t launch_backward_input_mfma(const T* dy, const T* w, T* dx, const Problem& p, hipStream_t st);
 // Grad-input with the dy operand shared by four channel blocks through LDS, fp32 (scc_bwi_shared.hip)
-bool backward_input_shared_eligible(const float* dy, const float* dx, const Problem& p);
-bool backward_input_shared_preferred(const float* dy, const float* dx, const Problem& p);   // ... and faster
+bool backward_input_shared_eligible(const Problem& p);
+bool backward_input_shared_preferred(const Problem& p);   // ... and faster
 hipError_t launch_backward_input_shared(const float* dy, const float* w, float* dx, const Problem& p, hipStream_t st);
 bool backward_weight_mfma_eligible(const Problem& p);
 size_t backward_weight_mfma_workspace(const Problem& p);  // bytes of K-split partials (0 when not split)
@@ -127,7 +154,7 @@ hipError_t launch_backward_fused(const float* x, const float* dy, const float* w
 
 // Both gradients in one launch, the two matrix-core kernels side by side in one grid (scc_bwd_merged.hip);
 // needs the workspace of the grad-weight pass
-template <typename T> bool backward_merged_applicable(const T* x, const T* dy, const T* dx, const Problem& p);
+template <typename T> bool backward_merged_applicable(const Problem& p);
 template <typename T>
 hipError_t launch_backward_merged(const T* x, const T* dy, const T* w, T* dx, float* dw, float* workspace,
                                   const Problem& p, hipStream_t st);

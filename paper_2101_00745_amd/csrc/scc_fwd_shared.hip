@@ -17,8 +17,7 @@
 // zeros outside the filter's window, parked in a wavefront-private LDS block.  Two B buffers and two register
 // sets: the loads of rounds r+1 and r+2 are in flight while round r is multiplied, one barrier per round.
 //
-// fp32 tensors, planes whose size is a multiple of 4 and 16-byte aligned tensors only (a lane owns 4 consecutive
-// columns); the products are the six-of-nine bf16 partial products of scc_common.h, sums binary32.
+// fp32 tensors and planes of at least 4 pixels only (a lane owns a group of 4 consecutive columns); the products are the six-of-nine bf16 partial products of scc_common.h, sums binary32.
 #include <type_traits>
 
 #include "scc_band.h"
@@ -30,6 +29,7 @@ namespace {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
 typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -51,6 +51,7 @@ struct SharedTiling {
     int FG;        // workgroups per column tile: ceil(IB*MB / 4)
     int total;     // workgroups with work
     int chunk;     // consecutive workgroups given to one XCD
+    Groups q;      // column groups of 4 pixels; a workgroup owns 32 of them
 };
 
 // AL4: g and L are multiples of 4, so a group of four consecutive weights is wholly inside or outside a window
@@ -117,7 +118,7 @@ __global__ __launch_bounds__(kWavesS * 64, 2) void forward_shared32(const float*
             const int j0 = kRound * r + 4 * sc - sro[it];
             if (AL4) {
                 const bool in = j0 >= 0 && j0 < P.L;
-                ga[set][it] = *(const f32x4*)(w + (in ? srw[it] + j0 : 0));
+                ga[set][it] = *(const f32x4u*)(w + (in ? srw[it] + j0 : 0));
                 gam[set] |= in ? (0xfu << (4 * it)) : 0u;
             } else {
                 // windows that start anywhere: the four weights are masked one by one, but still fetched with one
@@ -128,8 +129,7 @@ __global__ __launch_bounds__(kWavesS * 64, 2) void forward_shared32(const float*
                 for (int q = 0; q < 4; ++q) m4 |= (j0 + q >= 0 && j0 + q < P.L) ? (1u << q) : 0u;
                 const int e0 = srw[it] + j0;
                 if (m4 == 0u || (e0 >= 0 && e0 + 4 <= P.Cout * P.L)) {
-                    typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
-                    ga[set][it] = *(const f32x4u*)(w + (m4 ? e0 : 0));
+                        ga[set][it] = *(const f32x4u*)(w + (m4 ? e0 : 0));
                 } else {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) ga[set][it][q] = w[(m4 >> q) & 1u ? e0 + q : 0];
@@ -161,9 +161,9 @@ __global__ __launch_bounds__(kWavesS * 64, 2) void forward_shared32(const float*
     const uint32_t plane = (uint32_t)P.HW * 4u, wrapb = (uint32_t)P.Cin * plane;
     uint32_t lcol;                                             // byte offset of this thread's 4 columns in plane 0 of their sample
     {
-        const uint32_t q = (uint32_t)ct * kColsS + 4u * (uint32_t)lq;
-        const uint32_t qq = q < (uint32_t)P.NQ ? q : 0u;       // columns past the end read column 0 and are never stored
-        const uint32_t n = qq / (uint32_t)P.HW, p = qq % (uint32_t)P.HW;
+        const uint32_t u = (uint32_t)ct * 32u + (uint32_t)lq;
+        uint32_t n, p;
+        column_of_group(u < (uint32_t)T.q.count ? u : 0u, T.q, n, p);   // past the end: group 0, never stored
         lcol = (n * (uint32_t)P.Cin * (uint32_t)P.HW + p) * 4u;
     }
     uint32_t lrow[4];
@@ -177,7 +177,7 @@ __global__ __launch_bounds__(kWavesS * 64, 2) void forward_shared32(const float*
         constexpr int set = decltype(SET)::value;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            braw[set][e] = *(const f32x4*)(xb + (lcol + lrow[e]));
+            braw[set][e] = *(const f32x4u*)(xb + (lcol + lrow[e]));
             lrow[e] += round_b;
             lrow[e] -= lrow[e] >= wrapb ? wrapb : 0u;
         }
@@ -281,10 +281,10 @@ __global__ __launch_bounds__(kWavesS * 64, 2) void forward_shared32(const float*
 
     // ---- store: accumulator register v holds tile row 8*(v/4) + 4*h + v%4, columns 4f .. 4f+3 of the tile ----
     // (every lane stays for the shuffles: lane fr holds the filter of tile row fr)
-    const uint32_t q = (uint32_t)ct * kColsS + 4u * (uint32_t)f;
-    const bool qlive = q < (uint32_t)P.NQ;
-    const uint32_t qq = qlive ? q : 0u;
-    const uint32_t n = qq / (uint32_t)P.HW, p = qq % (uint32_t)P.HW;
+    const uint32_t u = (uint32_t)ct * 32u + (uint32_t)f;
+    const bool qlive = u < (uint32_t)T.q.count;
+    uint32_t n, p;
+    column_of_group(qlive ? u : 0u, T.q, n, p);
     float* yb = y + (size_t)n * P.Cout * P.HW + p;
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
@@ -293,7 +293,7 @@ __global__ __launch_bounds__(kWavesS * 64, 2) void forward_shared32(const float*
         const bool rvalid = __shfl((int)fvalid, fr, 64) != 0;
         if (rvalid && qlive) {
             const f32x4 o = {acc[0][v], acc[1][v], acc[2][v], acc[3][v]};
-            __builtin_nontemporal_store(o, (f32x4*)(yb + (size_t)kr * P.HW));   // written once, never re-read here
+            __builtin_nontemporal_store(o, (f32x4u*)(yb + (size_t)kr * P.HW));   // written once, never re-read here
         }
     }
 }
@@ -315,7 +315,8 @@ SharedTiling make_shared_tiling(const Problem& p)
     t.MB = (t.b.P + t.TM - 1) / t.TM;
     t.U = p.L + t.b.g * (t.TM - 1);
     t.FG = (t.IB * t.MB + kWavesS - 1) / kWavesS;
-    const long long nct = (p.NQ + kColsS - 1) / kColsS;
+    t.q = column_groups(p, 4);
+    const long long nct = (t.q.count + 31) / 32;
     t.total = (int)(nct * t.FG);
     t.chunk = (t.total + 7) / 8;
     return t;
@@ -323,12 +324,11 @@ SharedTiling make_shared_tiling(const Problem& p)
 
 }  // namespace
 
-bool forward_shared_eligible(const float* x, const float* w, const float* y, const Problem& p)
+bool forward_shared_eligible(const Problem& p)
 {
-    const uintptr_t addr = (uintptr_t)x | (uintptr_t)y | (uintptr_t)w;
-    if (!forward_mfma_eligible(p) || p.HW % 4 != 0 || (addr & 15) != 0) return false;
+    if (!forward_mfma_eligible(p) || p.HW < 4) return false;
     const SharedTiling t = make_shared_tiling(p);
-    return (long long)((p.NQ + kColsS - 1) / kColsS) * t.FG < (1ll << 28);
+    return (t.q.count + 31) / 32 * t.FG < (1ll << 28);
 }
 
 // Channels fetched by the tiles of a layer when every tile fetches its own span, over the channels fetched when
@@ -351,12 +351,12 @@ double forward_shared_gain(const Problem& p)
 // common walk (c4 channel-expanding layer 3.3x: 115 against 137-160 us; cg = 1 at the metric shape 4x: 39 against
 // 45 us) and the grid still fills the chip (two workgroups per CU); at 2.7x and below (cg = 2, co = 0.25, the
 // metric layer) and on the few-column layers of the stack the per-tile kernel is as fast or faster.
-bool forward_shared_preferred(const float* x, const float* w, const float* y, const Problem& p)
+bool forward_shared_preferred(const Problem& p)
 {
 #ifdef SCC_SHARED_ALWAYS
-    return forward_shared_eligible(x, w, y, p);
+    return forward_shared_eligible(p);
 #else
-    if (!forward_shared_eligible(x, w, y, p)) return false;
+    if (!forward_shared_eligible(p)) return false;
     const SharedTiling t = make_shared_tiling(p);
     return t.total >= 512 && forward_shared_gain(p) >= 3.0;
 #endif

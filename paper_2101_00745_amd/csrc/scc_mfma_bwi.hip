@@ -18,11 +18,11 @@ namespace scc {
 
 namespace {
 
-template <typename T_, int CT, int KC, bool VEC, int S, int WPB>
+template <typename T_, int CT, int KC, int S, int WPB>
 __global__ __launch_bounds__(WPB * 64) void backward_input_mfma32(const T_* __restrict__ dy, const T_* __restrict__ w,
                                                              T_* __restrict__ dx, Problem P, bwi::BwiTiling T)
 {
-    bwi::backward_input_body<T_, CT, KC, VEC, S, WPB>(dy, w, dx, P, T, (int)blockIdx.x);
+    bwi::backward_input_body<T_, CT, KC, S, WPB>(dy, w, dx, P, T, (int)blockIdx.x);
 }
 
 }  // namespace
@@ -41,13 +41,12 @@ template <typename T_>
 hipError_t launch_backward_input_mfma(const T_* dy, const T_* w, T_* dx, const Problem& p, hipStream_t st)
 {
     if constexpr (sizeof(T_) == 4) {
-        if (backward_input_shared_preferred((const float*)dy, (const float*)dx, p))
+        if (backward_input_shared_preferred(p))
             return launch_backward_input_shared((const float*)dy, (const float*)w, (float*)dx, p, st);
     }
-    bwi::select_backward_input(dy, dx, p, [&](auto ct, auto vec, auto s, auto wpb, const bwi::BwiTiling& t, long long blocks) {
+    bwi::select_backward_input<T_>(p, [&](auto ct, auto s, auto wpb, const bwi::BwiTiling& t, long long blocks) {
         constexpr int CT = decltype(ct)::value, S = decltype(s)::value, WPB = decltype(wpb)::value;
-        constexpr bool VEC = decltype(vec)::value;
-        backward_input_mfma32<T_, CT, 8, VEC, S, WPB><<<dim3((unsigned)blocks), dim3(WPB * 64), 0, st>>>(dy, w, dx, p, t);
+        backward_input_mfma32<T_, CT, 8, S, WPB><<<dim3((unsigned)blocks), dim3(WPB * 64), 0, st>>>(dy, w, dx, p, t);
     });
     return hipGetLastError();
 }

@@ -30,6 +30,7 @@ struct BwiTiling {
     int FG;     // workgroups per column tile = ceil(CB / 4)
     int total;  // workgroups with work: column tiles * FG, channel-block group fastest
     int chunk;  // consecutive workgroups of that order given to one XCD: ceil(total / 8)
+    Groups q;   // column groups of CT pixels
 };
 
 __device__ __forceinline__ int floor_div(int a, int b)  // b > 0
@@ -49,12 +50,12 @@ constexpr size_t reduce_bytes() { return S > 1 ? (size_t)(WPB / S) * (S - 1) * C
 
 // `shared_red`: LDS of at least reduce_bytes<CT, S, WPB>() that the caller provides for that sum (a kernel that
 // holds dynamic LDS for other workgroups of its grid lends it); null: the body declares its own.
-template <typename T_, int CT, int KC, bool VEC, int S, int WPB, bool LENT = false>
+template <typename T_, int CT, int KC, int S, int WPB, bool LENT = false>
 __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, const T_* __restrict__ w,
                                                     T_* __restrict__ dx, const Problem& P, const BwiTiling& T,
                                                     const int bid, float* shared_red = nullptr)
 {
-    typedef T_ bvec __attribute__((ext_vector_type(CT)));
+    typedef T_ bvec __attribute__((ext_vector_type(CT), aligned(sizeof(T_))));   // CT consecutive columns of one plane
     constexpr uint32_t ES = sizeof(T_);
     // bid is the workgroup's index in a launch whose first workgroup is a multiple of 8: bid % 8 names the XCD; each XCD takes a contiguous run of the (column tile, group) order, so the
     // channel blocks of a column tile, which re-read the same dy planes, share an XCD and its L2
@@ -84,16 +85,14 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
     const char* wb = (const char*)w;
     const char* gb = (const char*)dy;
 
-    uint32_t gcol[CT], dcol[CT];
-    bool live[CT];
-#pragma unroll
-    for (int cc = 0; cc < CT; ++cc) {
-        const uint32_t q = (uint32_t)ct * (32 * CT) + (VEC ? f * CT + cc : cc * 32 + f);
-        live[cc] = q < (uint32_t)P.NQ;
-        const uint32_t qq = live[cc] ? q : 0u;
-        const uint32_t n = qq / (uint32_t)P.HW, p = qq % (uint32_t)P.HW;
-        gcol[cc] = (n * (uint32_t)P.Cout * (uint32_t)P.HW + p) * ES;
-        dcol[cc] = n * (uint32_t)P.Cin * (uint32_t)P.HW + p;
+    const uint32_t u = (uint32_t)ct * 32u + (uint32_t)f;       // this lane's group of CT columns
+    const bool live = u < (uint32_t)T.q.count;
+    uint32_t gcol, dcol;
+    {
+        uint32_t n, p;
+        column_of_group(live ? u : 0u, T.q, n, p);
+        gcol = (n * (uint32_t)P.Cout * (uint32_t)P.HW + p) * ES;
+        dcol = n * (uint32_t)P.Cin * (uint32_t)P.HW + p;
     }
 
     // K-slot state of this half-wave: slot u = h*Uh + t  <->  (mm, i) = (u / F, u % F)
@@ -121,12 +120,7 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
             ad[s] = *(const T_*)(wb + (uint32_t)(in ? (k * P.L + ju) : 0) * ES);
             am |= in ? (1u << s) : 0u;
             const uint32_t rowofs = (uint32_t)(kvalid ? k : 0) * plane;
-            if (VEC) {
-                bd[s] = *(const bvec*)(gb + (uint32_t)(gcol[0] + rowofs));
-            } else {
-#pragma unroll
-                for (int cc = 0; cc < CT; ++cc) bd[s][cc] = *(const T_*)(gb + (uint32_t)(gcol[cc] + rowofs));
-            }
+            bd[s] = *(const bvec*)(gb + (uint32_t)(gcol + rowofs));
             // next slot: next filter of this window, or the first filter of the next window
             ++i;
             const bool nextw = (i == T.b.F);
@@ -225,19 +219,11 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int cr = c0 + 8 * (v >> 2) + 4 * h + (v & 3);
-        if (cr < P.Cin) {
-            if (VEC) {
-                if (live[0]) {
-                    bvec o;
+        if (cr < P.Cin && live) {
+            bvec o;
 #pragma unroll
-                    for (int cc = 0; cc < CT; ++cc) o[cc] = from_f32<T_>(acc[cc][v]);
-                    __builtin_nontemporal_store(o, (bvec*)(dx + (size_t)dcol[0] + (size_t)cr * P.HW));  // written once, not re-read here
-                }
-            } else {
-#pragma unroll
-                for (int cc = 0; cc < CT; ++cc)
-                    if (live[cc]) __builtin_nontemporal_store(from_f32<T_>(acc[cc][v]), dx + (size_t)dcol[cc] + (size_t)cr * P.HW);
-            }
+            for (int cc = 0; cc < CT; ++cc) o[cc] = from_f32<T_>(acc[cc][v]);
+            __builtin_nontemporal_store(o, (bvec*)(dx + (size_t)dcol + (size_t)cr * P.HW));  // written once, not re-read here
         }
     }
 }
@@ -251,7 +237,8 @@ inline BwiTiling make_tiling(const Problem& p, long long* blocks)
     BwiTiling t;
     t.b = make_band(p);
     t.CB = (p.Cin + 31) / 32;
-    const long long nct = (p.NQ + 32 * CT - 1) / (32 * CT);
+    t.q = column_groups(p, CT);
+    const long long nct = (t.q.count + 31) / 32;
     t.FG = (t.CB * S + WPB - 1) / WPB;
     t.total = (int)(nct * t.FG);
     t.chunk = (t.total + 7) / 8;
@@ -259,57 +246,53 @@ inline BwiTiling make_tiling(const Problem& p, long long* blocks)
     return t;
 }
 
-// Calls f(CT, VEC, S, WPB, tiling, blocks) with the first four as std::integral_constant / std::bool_constant
-// values: the variant backward_input_body<T_, CT, 8, VEC, S, WPB> that the layer takes, and its launch shape
+// Calls f(CT, S, WPB, tiling, blocks) with the first three as std::integral_constant
+// values: the variant backward_input_body<T_, CT, 8, S, WPB> that the layer takes, and its launch shape
 // (blocks workgroups of WPB * 64 threads).
 template <typename T_, typename F>
-void select_backward_input(const T_* dy, const T_* dx, const Problem& p, F&& f)
+void select_backward_input(const Problem& p, F&& f)
 {
-    using std::bool_constant;
     using std::integral_constant;
     // workgroups of 8 wavefronts (0.6 us faster at the metric layer; delaying half of them, which pays in the
     // forward, does not here): only for grids that fill the chip exactly once with two wavefronts per SIMD, fp32,
     // windows that start on multiples of 32 channels, and at most 16 flop per byte, the shapes it was measured on
-    auto with_wpb = [&](auto ct, auto vec, auto s) {
+    auto with_wpb = [&](auto ct, auto s) {
         constexpr int CT = decltype(ct)::value, S = decltype(s)::value;
-        constexpr bool VEC = decltype(vec)::value;
         long long blocks = 0;
-        if constexpr (sizeof(T_) == 4 && CT == 4 && VEC && S == 1) {
+        if constexpr (sizeof(T_) == 4 && CT == 4 && S == 1) {
             const Band b = make_band(p);
-            const long long cbs = (p.Cin + 31) / 32, nct = (p.NQ + 32 * CT - 1) / (32 * CT), waves = nct * cbs;
+            const long long cbs = (p.Cin + 31) / 32, nct = (column_groups(p, CT).count + 31) / 32, waves = nct * cbs;
             const bool once = waves >= 2048 && waves < 2048 + 256;
             const bool light = (long long)p.Cout * p.L <= 32ll * (p.Cin + p.Cout);
             if (b.g % 32 == 0 && p.Cin % 32 == 0 && cbs % 8 == 0 && once && light) {
                 const BwiTiling t = make_tiling<CT, S, 8>(p, &blocks);
-                f(ct, vec, s, integral_constant<int, 8>{}, t, blocks);
+                f(ct, s, integral_constant<int, 8>{}, t, blocks);
                 return;
             }
         }
         const BwiTiling t = make_tiling<CT, S, 4>(p, &blocks);
-        f(ct, vec, s, integral_constant<int, 4>{}, t, blocks);
+        f(ct, s, integral_constant<int, 4>{}, t, blocks);
     };
     // share a tile between 2 or 4 wavefronts while there are fewer than two wavefronts per SIMD and each slice
     // keeps at least 32 K-steps; a block of 32 channels sees about (L+31)/g windows of F filters each
-    auto with_split = [&](auto ct, auto vec, long long waves) {
+    auto with_split = [&](auto ct, long long waves) {
         constexpr int CT = decltype(ct)::value;
         const Band b = make_band(p);
         const long long slots = ((long long)(p.L + 31) / b.g + 1) * b.F;
         int split = 1;
         while (split < 4 && waves * split < 2048 && slots / (4 * split) >= 32) split *= 2;
         if (split == 1)
-            with_wpb(ct, vec, integral_constant<int, 1>{});
+            with_wpb(ct, integral_constant<int, 1>{});
         else if (split == 2)
-            with_wpb(ct, vec, integral_constant<int, 2>{});
+            with_wpb(ct, integral_constant<int, 2>{});
         else
-            with_wpb(ct, vec, integral_constant<int, 4>{});
+            with_wpb(ct, integral_constant<int, 4>{});
     };
-    // columns per wavefront: 128 when that still gives every SIMD a wavefront, else 64 or 32; vector plane
-    // accesses need planes whose size is a multiple of the vector and tensors aligned to it
+    // columns per wavefront: 128 when that still gives every SIMD a wavefront, else 64 or 32; a plane has to hold at
+    // least one group of columns
     constexpr long long kEnoughWaves = 1024;
     const long long blocks32 = (p.Cin + 31) / 32;
-    auto waves = [&](int ct) { return (p.NQ + 32 * ct - 1) / (32 * ct) * blocks32; };
-    const uintptr_t addr = (uintptr_t)dy | (uintptr_t)dx;
-    auto vec_ok = [&](int ct) { return p.HW % ct == 0 && (addr & (ct * sizeof(T_) - 1)) == 0; };
+    auto waves = [&](int ct) { return (column_groups(p, ct).count + 31) / 32 * blocks32; };
     // a tile's contraction can be shared by up to 4 wavefronts (with_split): wide tiles, whose loads move 16 bytes
     // per lane and instruction, are kept as long as that sharing still gives every SIMD a wavefront
     auto shared = [&](long long wv) {
@@ -319,14 +302,12 @@ void select_backward_input(const T_* dy, const T_* dx, const Problem& p, F&& f)
         while (sp < 4 && wv * sp < 2048 && slots / (4 * sp) >= 32) sp *= 2;
         return wv * sp;
     };
-    if (vec_ok(4) && shared(waves(4)) >= kEnoughWaves)
-        with_split(integral_constant<int, 4>{}, bool_constant<true>{}, waves(4));
-    else if (vec_ok(2) && shared(waves(2)) >= kEnoughWaves)
-        with_split(integral_constant<int, 2>{}, bool_constant<true>{}, waves(2));
-    else if (waves(2) >= kEnoughWaves)
-        with_split(integral_constant<int, 2>{}, bool_constant<false>{}, waves(2));
+    if (p.HW >= 4 && shared(waves(4)) >= kEnoughWaves)
+        with_split(integral_constant<int, 4>{}, waves(4));
+    else if (p.HW >= 2 && shared(waves(2)) >= kEnoughWaves)
+        with_split(integral_constant<int, 2>{}, waves(2));
     else
-        with_split(integral_constant<int, 1>{}, bool_constant<false>{}, waves(1));
+        with_split(integral_constant<int, 1>{}, waves(1));
 }
 
 }  // namespace bwi

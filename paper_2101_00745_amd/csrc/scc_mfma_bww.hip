@@ -109,8 +109,7 @@ hipError_t launch_backward_weight_mfma(const T_* x, const T_* dy, float* dw, flo
     float* out = t.KS > 1 ? workspace : dw;
     const dim3 grid((unsigned)blocks), block(kWaves * 64);
     hipError_t e = hipSuccess;
-    // vector loads of 4 columns need planes whose size is a multiple of 4 and tensors aligned to 4 elements
-    const bool vec = p.HW % 4 == 0 && (((uintptr_t)x | (uintptr_t)dy) & (4 * sizeof(T_) - 1)) == 0;
+    const bool vec = p.HW >= 4;
     if (t.NPT == 1)
         e = vec ? launch_tile<T_, 1, true>(grid, block, st, x, dy, out, p, t)
                 : launch_tile<T_, 1, false>(grid, block, st, x, dy, out, p, t);

@@ -58,7 +58,8 @@ struct BwwTiling {
     int NPT;      // span positions per wavefront tile / 32
     int NSC;      // span chunks of 32*NPT positions
     int KS;       // K-splits (workgroups per tile and span chunk)
-    int NQ4;      // groups of 4 consecutive columns: ceil(N*HW / 4)
+    Groups q;     // column groups of 4 pixels (planes of at least 4 pixels)
+    int NQ4;      // groups of 4 consecutive columns: q.count, or ceil(N*HW / 4) for smaller planes
     int per_ks;   // column groups per K-split: ceil(NQ4 / KS)
     int chunk;    // consecutive workgroups of the (K-split, tile) order given to one XCD: ceil(KS * tiles / 8)
 };
@@ -74,14 +75,16 @@ __device__ __forceinline__ void tile_filter(const BwwTiling& T, const Problem& P
 }
 
 // T_ is the storage type of x and dy (float or bf16_t); staged values, products, sums and dw are binary32.
-// VEC: H*W is a multiple of 4 and the tensors are aligned to 4 elements, so a lane's 4 consecutive columns
-// lie in one sample and are one vector load; otherwise they are 4 scalar loads with their own addresses.
+// VEC: planes of at least 4 pixels: a lane's 4 columns are a group of consecutive pixels of one sample
+// (column_groups in scc_common.h) and one vector load; the pixels a sample's last group shares with the one before it
+// are zeroed when they are parked.  Otherwise the columns are 4 scalar loads with their own addresses.
 template <typename T_, int kPosTiles, bool VEC>
 __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, const T_* __restrict__ dy,
                                                      float* __restrict__ out, const Problem& P, const BwwTiling& T,
                                                      const int bid)
 {
-    typedef T_ ldvec __attribute__((ext_vector_type(4)));   // 4 consecutive columns of one row, as stored
+    typedef T_ ldvec __attribute__((ext_vector_type(4), aligned(sizeof(T_))));   // 4 consecutive columns of one row, as stored
+    typedef T_ stvec __attribute__((ext_vector_type(4)));
     constexpr uint32_t ES = sizeof(T_);
     constexpr int kRows = rows_of(kPosTiles);
     constexpr int kRowB = row_bytes_of((int)ES);
@@ -153,19 +156,30 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
     // this lane's column group in chunk 0, advanced by 8 groups (32 columns) per chunk; one (sample, pixel)
     // position for the whole group when it is a vector, one per column otherwise
     constexpr int NE = VEC ? 1 : 4;
+    const uint32_t sampA = (uint32_t)P.Cout * plane, sampB = (uint32_t)P.Cin * plane;   // bytes of one sample
+    // vector: group index inside the sample and byte offset of the sample; scalar: pixel and byte offset per column
     uint32_t cp[NE], offA[NE], offB[NE];
+    if (VEC) {
+        const uint32_t u = (uint32_t)(qb + lc), n = u / (uint32_t)T.q.per;
+        cp[0] = u - n * (uint32_t)T.q.per;
+        offA[0] = n * sampA;
+        offB[0] = n * sampB;
+    } else {
 #pragma unroll
-    for (int e = 0; e < NE; ++e) {
-        const uint32_t col = (uint32_t)(qb + lc) * 4u + e;
-        const uint32_t cn = col / (uint32_t)P.HW;
-        cp[e] = col % (uint32_t)P.HW;
-        offA[e] = (cn * (uint32_t)P.Cout * (uint32_t)P.HW + cp[e]) * ES;
-        offB[e] = (cn * (uint32_t)P.Cin * (uint32_t)P.HW + cp[e]) * ES;
+        for (int e = 0; e < NE; ++e) {
+            const uint32_t col = (uint32_t)(qb + lc) * 4u + e;
+            const uint32_t cn = col / (uint32_t)P.HW;
+            cp[e] = col % (uint32_t)P.HW;
+            offA[e] = cn * sampA + cp[e] * ES;
+            offB[e] = cn * sampB + cp[e] * ES;
+        }
     }
-    const uint32_t dn = 32u / (uint32_t)P.HW, dp = 32u % (uint32_t)P.HW;
-    const uint32_t stepA = (dn * (uint32_t)P.Cout * (uint32_t)P.HW + dp) * ES;
-    const uint32_t stepB = (dn * (uint32_t)P.Cin * (uint32_t)P.HW + dp) * ES;
-    const uint32_t wrapA = ((uint32_t)P.Cout - 1u) * plane, wrapB = ((uint32_t)P.Cin - 1u) * plane;
+    // a chunk further: 8 groups = 32 columns
+    const uint32_t per = VEC ? (uint32_t)T.q.per : (uint32_t)P.HW, ahead = VEC ? 8u : 32u;
+    const uint32_t dn = ahead / per, dp = ahead % per;
+    const uint32_t stepA = dn * sampA + (VEC ? 0u : dp * ES), wrapA = VEC ? sampA : sampA - plane;
+    const uint32_t stepB = dn * sampB + (VEC ? 0u : dp * ES), wrapB = VEC ? sampB : sampB - plane;
+    const uint32_t dup = VEC ? 4u * per - (uint32_t)P.HW : 0u;   // pixels the last group shares with the one before
     int qnext = qb + lc;                       // column group the next load_chunk call takes
 
     const char* ab = (const char*)dy;
@@ -182,8 +196,9 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
     auto load_chunk = [&](ldvec (&r)[kRows / 8], uint32_t& rin) {
         const bool gin = qnext < qe;
         if (VEC) {
-            rin = gin ? 0xfu : 0u;
-            const uint32_t ca = gin ? offA[0] : 0u, cb = gin ? offB[0] : 0u;
+            rin = gin ? (0xfu << (cp[0] == per - 1u ? dup : 0u)) : 0u;
+            const uint32_t p4 = 4u * cp[0] < (uint32_t)T.q.last ? 4u * cp[0] : (uint32_t)T.q.last;
+            const uint32_t ca = gin ? offA[0] + p4 * ES : 0u, cb = gin ? offB[0] + p4 * ES : 0u;
 #pragma unroll
             for (int it = 0; it < kRows / 8; ++it)
                 r[it] = it < 4 ? *(const ldvec*)(ab + (ca + rowoff[it])) : *(const ldvec*)(bb + (cb + rowoff[it]));
@@ -203,8 +218,8 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
 #pragma unroll
         for (int e = 0; e < NE; ++e) {
             cp[e] += dp;
-            const bool wr = cp[e] >= (uint32_t)P.HW;             // crossed into the next sample
-            cp[e] -= wr ? (uint32_t)P.HW : 0u;
+            const bool wr = cp[e] >= per;                        // crossed into the next sample
+            cp[e] -= wr ? per : 0u;
             offA[e] += stepA + (wr ? wrapA : 0u);
             offB[e] += stepB + (wr ? wrapB : 0u);
         }
@@ -219,7 +234,7 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
 #pragma unroll
                     for (int e = 0; e < 4; ++e) v[e] = (rin >> e) & 1u ? r[it][e] : (T_)0;
                 }
-                *(ldvec*)dst = v;
+                *(stvec*)dst = v;
             } else {                                             // fp32 (or widened): zeros past the range
                 f32x4 v;
                 if (full) {
@@ -271,7 +286,8 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
     uint32_t in = 0;
     if (nchunk > 0) load_chunk(r, in);
     for (int ci = 0; ci < nchunk; ++ci) {
-        park_chunk(r, in, qb + 8 * (ci + 1) <= qe && (long long)(qb + 8 * (ci + 1)) * 4 <= P.NQ);
+        const int done = qb + 8 * (ci + 1);   // every column of the chunk exists and is counted once
+        park_chunk(r, in, done <= qe && (VEC ? dup == 0u : (long long)done * 4 <= P.NQ));
         if (ci + 1 < nchunk) load_chunk(r, in);
         mma_chunk();
     }
@@ -337,7 +353,8 @@ inline BwwTiling make_tiling(const Problem& p, bool side_by_side = false)
     // the 2x2 to 8x8 layers of the stack: 1-3 us per pass, except for spans of 512 channels)
     if (p.NQ <= 8192 && t.U <= 256) t.NPT = 1;
     t.NSC = (t.U + 32 * t.NPT - 1) / (32 * t.NPT);
-    t.NQ4 = (int)((p.NQ + 3) / 4);   // the last group is partial when N*H*W is not a multiple of 4
+    t.q = column_groups(p, 4);
+    t.NQ4 = p.HW >= 4 ? (int)t.q.count : (int)((p.NQ + 3) / 4);   // HW < 4: the last group may be partial
     // about one workgroup per CU (one wavefront per SIMD, deep prefetch), at least 32 column groups per wavefront
     const long long tiles = (long long)t.IB * t.MB * t.NSC;
     long long ks = (256 + tiles - 1) / tiles;

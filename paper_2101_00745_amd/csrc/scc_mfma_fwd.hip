@@ -35,13 +35,14 @@ struct FwdTiling {
     int total;     // workgroups with work: column tiles (of 32*CT columns) * FG, filter-tile group fastest
     int chunk;     // consecutive workgroups of that order given to one XCD: ceil(total / 8)
     int stagger;   // ticks of the 100 MHz clock the second half of an 8-wavefront workgroup waits after kernel start
+    Groups q;      // column groups of CT pixels
 };
 
 // CT   column groups of 32 per wavefront (the tile is 32 filters x 32*CT columns)
 // KC   K-steps per pipelined chunk of B loads
 // AL4  g and L are multiples of 4: groups of four weights are wholly inside or outside a window
-// VEC  H*W is a multiple of CT: a lane owns CT CONSECUTIVE columns (one CT*4-byte load per plane,
-//      one CT*4-byte store per output row); otherwise a lane owns columns f, f+32, ...
+//      A lane owns one group of CT CONSECUTIVE columns of a sample (column_groups in scc_common.h: one load per
+//      plane, one store per output row, whatever the size of the plane)
 // T    storage type of x, w, y (float or bf16_t); sums are binary32 either way, products go through the
 //      bf16 matrix instruction (bf16 values as stored, fp32 values as three bf16 pieces each)
 // S    wavefronts sharing one tile (1, 2 or 4), each taking a slice of the contraction; their partial
@@ -52,11 +53,11 @@ struct FwdTiling {
 //      resident at once, and without the stagger all of them load, then all multiply, then all store; with
 //      it one half's stores and arithmetic overlap the other half's loads (17 against 19-21 us at the metric
 //      layer; used only where it wins, see launch_chunk).
-template <typename T_, int CT, int KC, bool AL4, bool VEC, int S, int WPB>
+template <typename T_, int CT, int KC, bool AL4, int S, int WPB>
 __global__ __launch_bounds__(WPB * 64) void forward_mfma32(const T_* __restrict__ x, const T_* __restrict__ w,
                                                       T_* __restrict__ y, Problem P, FwdTiling T)
 {
-    typedef T_ bvec __attribute__((ext_vector_type(CT)));               // CT consecutive columns of one plane
+    typedef T_ bvec __attribute__((ext_vector_type(CT), aligned(sizeof(T_))));   // CT consecutive columns of one plane
     typedef T_ avec __attribute__((ext_vector_type(4), aligned(sizeof(T_))));  // 4 consecutive weights
     constexpr uint32_t ES = sizeof(T_);
     constexpr int KA = 2 * KC;   // K-steps per round: two chunks of B loads
@@ -190,17 +191,15 @@ __global__ __launch_bounds__(WPB * 64) void forward_mfma32(const T_* __restrict_
     if (t0 < t1) stage_issue(t0, nb0);
     __builtin_amdgcn_sched_barrier(0);
 
-    // ---- B side: this lane's columns (byte offsets from x; the launcher checked they fit 32 bits) ----
-    uint32_t xcol[CT], ycol[CT];
-    bool live[CT];
-#pragma unroll
-    for (int c = 0; c < CT; ++c) {
-        const uint32_t q = (uint32_t)ct * (32 * CT) + (VEC ? f * CT + c : c * 32 + f);
-        live[c] = q < (uint32_t)P.NQ;
-        const uint32_t qq = live[c] ? q : 0u;
-        const uint32_t n = qq / (uint32_t)P.HW, p = qq % (uint32_t)P.HW;
-        xcol[c] = (n * (uint32_t)P.Cin * (uint32_t)P.HW + p) * ES;
-        ycol[c] = n * (uint32_t)P.Cout * (uint32_t)P.HW + p;
+    // ---- B side: this lane's columns (byte offset from x; the launcher checked it fits 32 bits) ----
+    const uint32_t u = (uint32_t)ct * 32u + (uint32_t)f;
+    const bool live = u < (uint32_t)T.q.count;
+    uint32_t xcol, ycol;
+    {
+        uint32_t n, p;
+        column_of_group(live ? u : 0u, T.q, n, p);
+        xcol = (n * (uint32_t)P.Cin * (uint32_t)P.HW + p) * ES;
+        ycol = n * (uint32_t)P.Cout * (uint32_t)P.HW + p;
     }
     const uint32_t plane = (uint32_t)P.HW * ES;                  // bytes between channel planes
     const uint32_t wrap = (uint32_t)P.Cin * plane;               // bytes of one sample's channels
@@ -215,12 +214,7 @@ __global__ __launch_bounds__(WPB * 64) void forward_mfma32(const T_* __restrict_
     auto load_b = [&](bvec (&bd)[KC]) {
 #pragma unroll
         for (int s = 0; s < KC; ++s) {
-            if (VEC) {
-                bd[s] = *(const bvec*)(xb + (uint32_t)(xcol[0] + rowofs));
-            } else {
-#pragma unroll
-                for (int c = 0; c < CT; ++c) bd[s][c] = *(const T_*)(xb + (uint32_t)(xcol[c] + rowofs));
-            }
+            bd[s] = *(const bvec*)(xb + (uint32_t)(xcol + rowofs));
             rowofs += plane;
             rowofs = (rowofs == wrap) ? 0u : rowofs;             // cyclic wrap past channel Cin-1
         }
@@ -324,19 +318,11 @@ __global__ __launch_bounds__(WPB * 64) void forward_mfma32(const T_* __restrict_
         const int fr = 8 * (v >> 2) + 4 * h + (v & 3);
         const int kr = __shfl(k, fr, 64);            // filter of tile row fr lives in lane fr's registers
         const bool rvalid = __shfl((int)fvalid, fr, 64) != 0;
-        if (rvalid) {
-            if (VEC) {
-                if (live[0]) {                        // CT divides H*W: the CT columns are live together
-                    bvec o;
+        if (rvalid && live) {
+            bvec o;
 #pragma unroll
-                    for (int c = 0; c < CT; ++c) o[c] = from_f32<T_>(acc[c][v]);
-                    __builtin_nontemporal_store(o, (bvec*)(y + (size_t)ycol[0] + (size_t)kr * P.HW));  // written once, not re-read here
-                }
-            } else {
-#pragma unroll
-                for (int c = 0; c < CT; ++c)
-                    if (live[c]) __builtin_nontemporal_store(from_f32<T_>(acc[c][v]), y + (size_t)ycol[c] + (size_t)kr * P.HW);
-            }
+            for (int c = 0; c < CT; ++c) o[c] = from_f32<T_>(acc[c][v]);
+            __builtin_nontemporal_store(o, (bvec*)(y + (size_t)ycol + (size_t)kr * P.HW));  // written once, not re-read here
         }
     }
 }
@@ -377,11 +363,12 @@ FwdTiling filter_tiling(const Problem& p)
     return t;
 }
 
-template <typename T_, int CT, bool VEC, int S, int KC, int WPB>
+template <typename T_, int CT, int S, int KC, int WPB>
 void launch_wpb(const T_* x, const T_* w, T_* y, const Problem& p, hipStream_t st)
 {
     FwdTiling t = filter_tiling(p);
-    const long long nct = (p.NQ + 32 * CT - 1) / (32 * CT);
+    t.q = column_groups(p, CT);
+    const long long nct = (t.q.count + 31) / 32;
     t.Us = ((t.Uh + S - 1) / S + 2 * KC - 1) / (2 * KC) * (2 * KC);
     t.FG = (t.IB * t.MB * S + WPB - 1) / WPB;
     t.total = (int)(nct * t.FG);
@@ -389,12 +376,12 @@ void launch_wpb(const T_* x, const T_* w, T_* y, const Problem& p, hipStream_t s
     const long long blocks = (long long)8 * t.chunk;
     const bool al4 = (t.b.g % 4 == 0) && (p.L % 4 == 0);
     if (al4)
-        forward_mfma32<T_, CT, KC, true, VEC, S, WPB><<<dim3((unsigned)blocks), dim3(WPB * 64), 0, st>>>(x, w, y, p, t);
+        forward_mfma32<T_, CT, KC, true, S, WPB><<<dim3((unsigned)blocks), dim3(WPB * 64), 0, st>>>(x, w, y, p, t);
     else
-        forward_mfma32<T_, CT, KC, false, VEC, S, WPB><<<dim3((unsigned)blocks), dim3(WPB * 64), 0, st>>>(x, w, y, p, t);
+        forward_mfma32<T_, CT, KC, false, S, WPB><<<dim3((unsigned)blocks), dim3(WPB * 64), 0, st>>>(x, w, y, p, t);
 }
 
-template <typename T_, int CT, bool VEC, int S, int KC>
+template <typename T_, int CT, int S, int KC>
 void launch_chunk(const T_* x, const T_* w, T_* y, const Problem& p, hipStream_t st)
 {
     // Workgroups of 8 wavefronts with staggered halves: only for grids that fill the chip exactly once with two
@@ -402,31 +389,31 @@ void launch_chunk(const T_* x, const T_* w, T_* y, const Problem& p, hipStream_t
     // and at most 16 flop per byte.  Measured on other shapes it loses: larger grids run in generations that are
     // out of phase anyway, bf16 and single-round tiles have too little arithmetic to overlap, and layers with
     // more arithmetic per byte are slowed by the followers' late start.
-    if constexpr (sizeof(T_) == 4 && CT == 4 && VEC && KC == 8 && S == 1) {
+    if constexpr (sizeof(T_) == 4 && CT == 4 && KC == 8 && S == 1) {
         const FwdTiling t = filter_tiling(p);
-        const long long nct = (p.NQ + 32 * CT - 1) / (32 * CT), waves = nct * t.IB * t.MB;
+        const long long nct = (column_groups(p, CT).count + 31) / 32, waves = nct * t.IB * t.MB;
         const bool once = waves >= 2 * kEnoughWaves && waves < 2 * kEnoughWaves + kEnoughWaves / 4;
         const bool light = (long long)p.Cout * p.L <= 32ll * (p.Cin + p.Cout);
         if (t.TM == 1 && (t.IB * t.MB) % 8 == 0 && t.Uh >= 32 && once && light) {
-            launch_wpb<T_, CT, VEC, S, KC, 8>(x, w, y, p, st);
+            launch_wpb<T_, CT, S, KC, 8>(x, w, y, p, st);
             return;
         }
     }
-    launch_wpb<T_, CT, VEC, S, KC, 4>(x, w, y, p, st);
+    launch_wpb<T_, CT, S, KC, 4>(x, w, y, p, st);
 }
 
-template <typename T_, int CT, bool VEC, int S>
+template <typename T_, int CT, int S>
 void launch_split(const T_* x, const T_* w, T_* y, const Problem& p, hipStream_t st)
 {
     const Band b = make_band(p);
     const int ti = pow2_floor(b.F < 32 ? b.F : 32), tm = 32 / ti < b.P ? 32 / ti : b.P;
     if (chunk_steps(p.L + b.g * (tm - 1)) == 4)
-        launch_chunk<T_, CT, VEC, S, 4>(x, w, y, p, st);
+        launch_chunk<T_, CT, S, 4>(x, w, y, p, st);
     else
-        launch_chunk<T_, CT, VEC, S, 8>(x, w, y, p, st);
+        launch_chunk<T_, CT, S, 8>(x, w, y, p, st);
 }
 
-template <typename T_, int CT, bool VEC>
+template <typename T_, int CT>
 void launch_cfg(const T_* x, const T_* w, T_* y, const Problem& p, hipStream_t st, long long waves)
 {
     // share a tile between 2 or 4 wavefronts while there are fewer than two wavefronts per SIMD and each
@@ -435,11 +422,11 @@ void launch_cfg(const T_* x, const T_* w, T_* y, const Problem& p, hipStream_t s
     int split = 1;
     while (split < 4 && waves * split < 2 * kEnoughWaves && t.Uh / (2 * split) >= 32) split *= 2;
     if (split == 1)
-        launch_split<T_, CT, VEC, 1>(x, w, y, p, st);
+        launch_split<T_, CT, 1>(x, w, y, p, st);
     else if (split == 2)
-        launch_split<T_, CT, VEC, 2>(x, w, y, p, st);
+        launch_split<T_, CT, 2>(x, w, y, p, st);
     else
-        launch_split<T_, CT, VEC, 4>(x, w, y, p, st);
+        launch_split<T_, CT, 4>(x, w, y, p, st);
 }
 
 }  // namespace
@@ -457,17 +444,14 @@ template <typename T_>
 hipError_t launch_forward_mfma(const T_* x, const T_* w, T_* y, const Problem& p, hipStream_t st)
 {
     // Columns per wavefront: 128 when that still gives every SIMD a wavefront, else 64 or 32 (layers with
-    // few columns and many filters).  Vector plane accesses (CT consecutive columns per lane) need planes whose
-    // size is a multiple of CT and tensors aligned to the vector; otherwise a lane owns strided single columns.
+    // few columns and many filters); a plane has to hold at least one group.
     if constexpr (sizeof(T_) == 4) {
-        if (forward_shared_preferred((const float*)x, (const float*)w, (const float*)y, p))
+        if (forward_shared_preferred(p))
             return launch_forward_shared((const float*)x, (const float*)w, (float*)y, p, st);
     }
     const FwdTiling ft = filter_tiling(p);
     const long long tiles = (long long)ft.IB * ft.MB;
-    auto waves = [&](int ct) { return (p.NQ + 32 * ct - 1) / (32 * ct) * tiles; };
-    const uintptr_t addr = (uintptr_t)x | (uintptr_t)y | (uintptr_t)w;
-    auto vec_ok = [&](int ct) { return p.HW % ct == 0 && (addr & (ct * sizeof(T_) - 1)) == 0; };
+    auto waves = [&](int ct) { return (column_groups(p, ct).count + 31) / 32 * tiles; };
     // a tile's contraction can be shared by up to 4 wavefronts (launch_cfg): wide tiles, whose loads move 16 bytes
     // per lane and instruction, are kept as long as that sharing still gives every SIMD a wavefront
     auto shared = [&](long long wv) {
@@ -475,14 +459,12 @@ hipError_t launch_forward_mfma(const T_* x, const T_* w, T_* y, const Problem& p
         while (sp < 4 && wv * sp < 2 * kEnoughWaves && ft.Uh / (2 * sp) >= 32) sp *= 2;
         return wv * sp;
     };
-    if (vec_ok(4) && shared(waves(4)) >= kEnoughWaves)
-        launch_cfg<T_, 4, true>(x, w, y, p, st, waves(4));
-    else if (vec_ok(2) && shared(waves(2)) >= kEnoughWaves)
-        launch_cfg<T_, 2, true>(x, w, y, p, st, waves(2));
-    else if (waves(2) >= kEnoughWaves)
-        launch_cfg<T_, 2, false>(x, w, y, p, st, waves(2));
+    if (p.HW >= 4 && shared(waves(4)) >= kEnoughWaves)
+        launch_cfg<T_, 4>(x, w, y, p, st, waves(4));
+    else if (p.HW >= 2 && shared(waves(2)) >= kEnoughWaves)
+        launch_cfg<T_, 2>(x, w, y, p, st, waves(2));
     else
-        launch_cfg<T_, 1, false>(x, w, y, p, st, waves(1));
+        launch_cfg<T_, 1>(x, w, y, p, st, waves(1));
     return hipGetLastError();
 }
 
