@@ -100,6 +100,18 @@ int scc_forward(const void* x, const void* w, void* y,
                 scc_dtype dtype, void* stream);
 
 /*
+ * The same with device scratch: layers with enough arithmetic per byte pack their weights into it in the operand
+ * layout of the matrix cores first, which pays for itself; on these layers, and only there, the query is not 0.
+ * workspace: at least scc_forward_workspace_bytes(...) bytes, 256-byte aligned, owned by the caller, contents
+ * undefined before and after; NULL runs the kernels that need none, as scc_forward does.  The results of the two
+ * differ by the order of their binary32 sums.
+ */
+size_t scc_forward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype);
+int scc_forward_ws(const void* x, const void* w, void* y,
+                   int N, int Cin, int Cout, int H, int W, int cg, double co,
+                   scc_dtype dtype, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * Gradient with respect to the input (Section 4.2, "Input-Centric Backward Pass"):
  * each input-gradient element gathers from the filters whose window covers its channel,
  *     dx[n,c,h,w] = sum_{k : (c - s_k) mod Cin < L} w[k, (c - s_k) mod Cin] * dy[n,k,h,w]
@@ -109,6 +121,11 @@ int scc_forward(const void* x, const void* w, void* y,
 int scc_backward_input(const void* dy, const void* w, void* dx,
                        int N, int Cin, int Cout, int H, int W, int cg, double co,
                        scc_dtype dtype, void* stream);
+/* The same with device scratch, as scc_forward_ws. */
+size_t scc_backward_input_workspace_bytes(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype);
+int scc_backward_input_ws(const void* dy, const void* w, void* dx,
+                          int N, int Cin, int Cout, int H, int W, int cg, double co,
+                          scc_dtype dtype, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * Bytes of device scratch scc_backward_weight needs for this problem (may be 0).

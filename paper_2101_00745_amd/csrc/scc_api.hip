@@ -82,6 +82,34 @@ int scratch_of_current_device(void** out)
     return SCC_OK;
 }
 
+// f(T()) with T the storage type of `dtype`
+template <typename F>
+int with_type(scc_dtype dtype, F&& f)
+{
+    return dtype == SCC_F32 ? f(float()) : f(scc::bf16_t());
+}
+
+// Forward (FWD) or grad-input: with a workspace, the layers that packed_workspace names take the product with packed
+// weights; without one, and every other layer, the kernels that need none.
+template <typename T, bool FWD>
+int run_product(const T* src, const T* w, T* out, const Problem& p, void* workspace, size_t workspace_bytes, hipStream_t st)
+{
+    const size_t need = workspace ? scc::packed_workspace<FWD>(p, (int)sizeof(T)) : 0;
+    if (need > 0 && (workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0)) return SCC_ERR_WORKSPACE;
+    drop_stale_error();
+    if (need > 0) return launch_status(scc::launch_packed<T, FWD>(src, w, out, workspace, p, st));
+    if constexpr (FWD) {
+        if (scc::forward_mfma_eligible(p)) return launch_status(scc::launch_forward_mfma(src, w, out, p, st));
+        return launch_status(scc::launch_forward_generic(src, w, out, p, st));
+    } else {
+        if (scc::backward_input_mfma_eligible(p)) return launch_status(scc::launch_backward_input_mfma(src, w, out, p, st));
+        return launch_status(scc::launch_backward_input_generic(src, w, out, p, st));
+    }
+}
+
+// The workspace of scc_backward: grad-weight's partial sums first, then grad-input's packed weights.
+size_t align256(size_t v) { return (v + 255) / 256 * 256; }
+
 }  // namespace
 
 extern "C" {
@@ -97,48 +125,58 @@ int scc_window_params(int Cin, int Cout, int cg, double co, int* L, int* stride,
     return SCC_OK;
 }
 
-int scc_forward(const void* x, const void* w, void* y, int N, int Cin, int Cout, int H, int W, int cg, double co,
-                scc_dtype dtype, void* stream)
+size_t scc_forward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype)
+{
+    Problem p;
+    if (make_problem(N, Cin, Cout, H, W, cg, co, &p) != SCC_OK || !dtype_ok(dtype)) return 0;
+    return scc::packed_workspace<true>(p, dtype == SCC_F32 ? 4 : 2);
+}
+
+int scc_forward_ws(const void* x, const void* w, void* y, int N, int Cin, int Cout, int H, int W, int cg, double co,
+                   scc_dtype dtype, void* workspace, size_t workspace_bytes, void* stream)
 {
     if (!x || !w || !y) return SCC_ERR_NULL;
     Problem p;
     const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    drop_stale_error();
-    hipStream_t st = (hipStream_t)stream;
-    if (dtype == SCC_F32) {
-        if (scc::forward_mfma_eligible(p))
-            return launch_status(scc::launch_forward_mfma((const float*)x, (const float*)w, (float*)y, p, st));
-        return launch_status(scc::launch_forward_generic((const float*)x, (const float*)w, (float*)y, p, st));
-    }
-    if (scc::forward_mfma_eligible(p))
-        return launch_status(
-            scc::launch_forward_mfma((const scc::bf16_t*)x, (const scc::bf16_t*)w, (scc::bf16_t*)y, p, st));
-    return launch_status(
-        scc::launch_forward_generic((const scc::bf16_t*)x, (const scc::bf16_t*)w, (scc::bf16_t*)y, p, st));
+    return with_type(dtype, [&](auto t) {
+        typedef decltype(t) T;
+        return run_product<T, true>((const T*)x, (const T*)w, (T*)y, p, workspace, workspace_bytes, (hipStream_t)stream);
+    });
 }
 
-int scc_backward_input(const void* dy, const void* w, void* dx, int N, int Cin, int Cout, int H, int W, int cg,
-                       double co, scc_dtype dtype, void* stream)
+int scc_forward(const void* x, const void* w, void* y, int N, int Cin, int Cout, int H, int W, int cg, double co,
+                scc_dtype dtype, void* stream)
+{
+    return scc_forward_ws(x, w, y, N, Cin, Cout, H, W, cg, co, dtype, nullptr, 0, stream);
+}
+
+size_t scc_backward_input_workspace_bytes(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype)
+{
+    Problem p;
+    if (make_problem(N, Cin, Cout, H, W, cg, co, &p) != SCC_OK || !dtype_ok(dtype)) return 0;
+    return scc::packed_workspace<false>(p, dtype == SCC_F32 ? 4 : 2);
+}
+
+int scc_backward_input_ws(const void* dy, const void* w, void* dx, int N, int Cin, int Cout, int H, int W, int cg,
+                          double co, scc_dtype dtype, void* workspace, size_t workspace_bytes, void* stream)
 {
     if (!dy || !w || !dx) return SCC_ERR_NULL;
     Problem p;
     const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    drop_stale_error();
-    hipStream_t st = (hipStream_t)stream;
-    if (dtype == SCC_F32) {
-        if (scc::backward_input_mfma_eligible(p))
-            return launch_status(scc::launch_backward_input_mfma((const float*)dy, (const float*)w, (float*)dx, p, st));
-        return launch_status(scc::launch_backward_input_generic((const float*)dy, (const float*)w, (float*)dx, p, st));
-    }
-    if (scc::backward_input_mfma_eligible(p))
-        return launch_status(
-            scc::launch_backward_input_mfma((const scc::bf16_t*)dy, (const scc::bf16_t*)w, (scc::bf16_t*)dx, p, st));
-    return launch_status(
-        scc::launch_backward_input_generic((const scc::bf16_t*)dy, (const scc::bf16_t*)w, (scc::bf16_t*)dx, p, st));
+    return with_type(dtype, [&](auto t) {
+        typedef decltype(t) T;
+        return run_product<T, false>((const T*)dy, (const T*)w, (T*)dx, p, workspace, workspace_bytes, (hipStream_t)stream);
+    });
+}
+
+int scc_backward_input(const void* dy, const void* w, void* dx, int N, int Cin, int Cout, int H, int W, int cg,
+                       double co, scc_dtype dtype, void* stream)
+{
+    return scc_backward_input_ws(dy, w, dx, N, Cin, Cout, H, W, cg, co, dtype, nullptr, 0, stream);
 }
 
 size_t scc_backward_weight_workspace_bytes(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype)
@@ -183,9 +221,9 @@ size_t scc_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int 
     size_t need = scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype);
     if (dtype == SCC_F32 && scc::backward_fused_eligible(p)) {
         const size_t fused = scc::backward_fused_workspace(p);
-        need = fused > need ? fused : need;
+        return fused > need ? fused : need;
     }
-    return need;
+    return align256(need) + scc::packed_workspace<false>(p, dtype == SCC_F32 ? 4 : 2);
 }
 
 int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* dw, int N, int Cin, int Cout, int H,
@@ -200,10 +238,19 @@ int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* d
     if (need > 0 && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0))
         return SCC_ERR_WORKSPACE;
     drop_stale_error();
-    const bool aligned = (((uintptr_t)x | (uintptr_t)dy | (uintptr_t)dx) & 15u) == 0;
-    if (dtype == SCC_F32 && aligned && scc::backward_fused_eligible(p))
-        return launch_status(scc::launch_backward_fused((const float*)x, (const float*)dy, (const float*)w, (float*)dx,
-                                                        (float*)dw, (float*)workspace, p, (hipStream_t)stream));
+    if (dtype == SCC_F32 && scc::backward_fused_eligible(p)) {
+        const bool aligned = (((uintptr_t)x | (uintptr_t)dy | (uintptr_t)dx) & 15u) == 0;
+        if (aligned)
+            return launch_status(scc::launch_backward_fused((const float*)x, (const float*)dy, (const float*)w,
+                                                            (float*)dx, (float*)dw, (float*)workspace, p,
+                                                            (hipStream_t)stream));
+    } else if (scc::packed_workspace<false>(p, dtype == SCC_F32 ? 4 : 2) > 0) {
+        const size_t at = align256(scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype));
+        const int r = scc_backward_input_ws(dy, w, dx, N, Cin, Cout, H, W, cg, co, dtype, (char*)workspace + at,
+                                            workspace_bytes - at, stream);
+        if (r != SCC_OK) return r;
+        return scc_backward_weight(x, dy, dw, N, Cin, Cout, H, W, cg, co, dtype, workspace, workspace_bytes, stream);
+    }
     // layers both matrix-core kernels take: their two grids as one launch
     if (dtype == SCC_F32) {
         if (scc::backward_merged_applicable<float>(p))

@@ -137,6 +137,11 @@ template <typename T> hipError_t launch_backward_input_mfma(const T* dy, const T
 bool backward_input_shared_eligible(const Problem& p);
 bool backward_input_shared_preferred(const Problem& p);   // ... and faster
 hipError_t launch_backward_input_shared(const float* dy, const float* w, float* dx, const Problem& p, hipStream_t st);
+// Forward (FWD) and grad-input as one product with weights packed by a pass of their own (scc_packed.hip): bytes of
+// workspace they are packed into, 0 for layers that do not take this path; es is the storage type's size
+template <bool FWD> size_t packed_workspace(const Problem& p, int es);
+template <typename T, bool FWD>
+hipError_t launch_packed(const T* src, const T* w, T* out, void* workspace, const Problem& p, hipStream_t st);
 bool backward_weight_mfma_eligible(const Problem& p);
 size_t backward_weight_mfma_workspace(const Problem& p);  // bytes of K-split partials (0 when not split)
 template <typename T>

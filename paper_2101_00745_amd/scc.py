@@ -6,6 +6,7 @@ nothing else.  There is no CPU path: if the library is missing or a tensor is no
 GPU the call raises.
 """
 import ctypes
+import functools
 import os
 
 import torch
@@ -14,7 +15,8 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libscc_hip.so")
 
 SCC_F32, SCC_BF16 = 0, 1
-SYMBOLS = ("scc_window_params", "scc_forward", "scc_backward_input",
+SYMBOLS = ("scc_window_params", "scc_forward", "scc_forward_workspace_bytes", "scc_forward_ws", "scc_backward_input",
+           "scc_backward_input_workspace_bytes", "scc_backward_input_ws",
            "scc_backward_weight_workspace_bytes", "scc_backward_weight", "scc_backward_weight_static",
            "scc_backward_workspace_bytes", "scc_backward",
            "scc_depthwise3x3_out", "scc_depthwise3x3_forward", "scc_depthwise3x3_backward_workspace_bytes",
@@ -49,6 +51,10 @@ def load():
     lib.scc_forward.restype = c_int
     lib.scc_backward_input.argtypes = [c_vp, c_vp, c_vp] + shape + [c_vp]
     lib.scc_backward_input.restype = c_int
+    for name in ("scc_forward", "scc_backward_input"):
+        query, call = getattr(lib, name + "_workspace_bytes"), getattr(lib, name + "_ws")
+        query.argtypes, query.restype = shape, c_sz
+        call.argtypes, call.restype = [c_vp, c_vp, c_vp] + shape + [c_vp, c_sz, c_vp], c_int
     lib.scc_backward_weight_workspace_bytes.argtypes = shape
     lib.scc_backward_weight_workspace_bytes.restype = c_sz
     lib.scc_backward_weight.argtypes = [c_vp, c_vp, c_vp] + shape + [c_vp, c_sz, c_vp]
@@ -120,6 +126,20 @@ def _stream(dev):
     return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
 
 
+@functools.lru_cache(maxsize=4096)
+def _workspace_need(query, *shape):
+    """Bytes the library's query function of that name answers; it depends on its integer arguments and co alone."""
+    return int(getattr(load(), query)(*shape))
+
+
+def _scratch(need, dev):
+    """(tensor to keep alive until the call has been enqueued, its address, its size); nothing where nothing is needed."""
+    if need == 0:
+        return None, None, 0
+    t = torch.empty(need, dtype=torch.uint8, device=dev)
+    return t, t.data_ptr(), need
+
+
 def scc_forward(x, w, cg, co, out=None):
     """y = SCC(x; w): x [N,Cin,H,W], w [Cout,Cin//cg] -> y [N,Cout,H,W] (same dtype)."""
     dev = _dev(x, w)
@@ -131,9 +151,10 @@ def scc_forward(x, w, cg, co, out=None):
     if out is not None:
         _dev(out)
         assert out.shape == (N, Cout, H, W) and out.dtype == x.dtype
+    shape = (N, Cin, Cout, H, W, cg, float(co), _dtype_code(x))
+    ws, ws_ptr, ws_len = _scratch(_workspace_need("scc_forward_workspace_bytes", *shape), dev)
     with torch.cuda.device(dev):
-        _check(load().scc_forward(x.data_ptr(), w.data_ptr(), y.data_ptr(), N, Cin, Cout, H, W, cg, float(co),
-                                  _dtype_code(x), _stream(dev)))
+        _check(load().scc_forward_ws(x.data_ptr(), w.data_ptr(), y.data_ptr(), *shape, ws_ptr, ws_len, _stream(dev)))
     return y
 
 
@@ -148,9 +169,11 @@ def scc_backward_input(dy, w, Cin, cg, co, out=None):
     if out is not None:
         _dev(out)
         assert out.shape == (N, Cin, H, W) and out.dtype == dy.dtype
+    shape = (N, Cin, Cout, H, W, cg, float(co), _dtype_code(dy))
+    ws, ws_ptr, ws_len = _scratch(_workspace_need("scc_backward_input_workspace_bytes", *shape), dev)
     with torch.cuda.device(dev):
-        _check(load().scc_backward_input(dy.data_ptr(), w.data_ptr(), dx.data_ptr(), N, Cin, Cout, H, W, cg,
-                                         float(co), _dtype_code(dy), _stream(dev)))
+        _check(load().scc_backward_input_ws(dy.data_ptr(), w.data_ptr(), dx.data_ptr(), *shape, ws_ptr, ws_len,
+                                            _stream(dev)))
     return dx
 
 

@@ -1,0 +1,69 @@
+"""Forward and grad-input as a product with packed weights (scc_forward_ws, scc_backward_input_ws) against the fp64 oracle on
+layers that take this path: row groups, column tiles, rounds and walks that are full, ragged or wrap; both tile widths;
+planes of any remainder.  Bars: those of the suite (2e-5 of the largest value in fp32, 1e-2 in bf16)."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2101_00745_amd as S
+import scc_workloads as Wk
+from oracle import scc_oracle as O
+from paper_2101_00745_amd import scc as B
+
+BANDED = (130, 120, 500, 11, 9, 2, 0.33)     # 120 window starts x 5 filters, 100 of the 600 rows empty; 99 pixels
+CIRCLE = (20, 104, 400, 46, 44, 1, 0.3)      # every window reaches every channel block: walks are once around the circle
+NARROW = (64, 512, 1000, 7, 7, 2, 0.33)      # 64-column tiles; last row group of 104 rows; walk of 23 rounds
+DENSE = (110, 336, 330, 16, 18, 1, 0.5)       # two windows x 165 filters; last row group of 74 rows
+GAPS = (190, 320, 160, 37, 28, 4, 0.0)        # four windows side by side: grad-input's blocks see one or two of them
+ROUND = (60, 96, 190, 30, 44, 4, 0.76)       # windows of 24 channels, 6 apart; a forward walk of two rounds
+CASES = [("forward", "f32", s) for s in (BANDED, CIRCLE, NARROW, DENSE, ROUND)] + \
+        [("forward", "bf16", s) for s in (BANDED, CIRCLE, NARROW, DENSE, ROUND)] + \
+        [("backward_input", "f32", s) for s in (CIRCLE, DENSE, GAPS)] + \
+        [("backward_input", "bf16", s) for s in (BANDED, CIRCLE, NARROW, DENSE, GAPS)]
+
+
+def need(which, dtype, shape):
+    return getattr(S.load(), "scc_%s_workspace_bytes" % which)(*shape, 0 if dtype == "f32" else 1)
+
+
+@pytest.mark.parametrize("which,dtype,shape", CASES)
+def test_layers_here_take_the_path_and_a_short_workspace_is_refused(which, dtype, shape):
+    n = need(which, dtype, shape)
+    assert n > 0
+    call = getattr(S.load(), "scc_%s_ws" % which)
+    fake, code = ctypes.c_void_p(0x1000), 0 if dtype == "f32" else 1
+    for ws, size in ((0x1000, n - 1), (0x1010, n)):              # too small; not 256-byte aligned
+        assert call(fake, fake, fake, *shape, code, ws, size, None) == -5
+    assert call(fake, None, fake, *shape, code, 0x1000, n, None) == -1
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which,dtype,shape", CASES)
+def test_parity(which, dtype, shape):
+    N, Cin, Cout, H, W, cg, co = shape
+    layer = Wk.Layer("packed", 9, N=N, Cin=Cin, Cout=Cout, H=H, W=W, cg=cg, co=co)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    xd, wd, dyd = (torch.from_numpy(a).to(td).cuda() for a in Wk.make_inputs(layer))
+    x, w, dy = (t.float().cpu().numpy() for t in (xd, wd, dyd))
+    if which == "forward":
+        got, ref = S.scc_forward(xd, wd, cg, co), O.forward(x, w, cg, co)
+    else:
+        got, ref = S.scc_backward_input(dyd, wd, Cin, cg, co), O.backward_input(dy, w, Cin, cg, co)
+    err = np.max(np.abs(got.float().cpu().numpy() - ref)) / np.max(np.abs(ref))
+    assert err <= (2e-5 if dtype == "f32" else 1e-2), err
+    # without a workspace: the other kernels, the same definition
+    out = torch.empty_like(got)
+    src = xd if which == "forward" else dyd
+    shp = shape + (0 if dtype == "f32" else 1,)
+    assert getattr(S.load(), "scc_" + which)(src.data_ptr(), wd.data_ptr(), out.data_ptr(), *shp,
+                                             torch.cuda.current_stream().cuda_stream) == 0
+    err = np.max(np.abs(out.float().cpu().numpy() - ref)) / np.max(np.abs(ref))
+    assert err <= (2e-5 if dtype == "f32" else 1e-2), err
+
+
+def test_queries_of_bad_arguments_are_zero():
+    for bad in ((0, 8, 8, 4, 4, 2, 0.5, 0), (1, 9, 8, 4, 4, 2, 0.5, 0), (1, 8, 8, 4, 4, 2, 1.5, 0), (1, 8, 8, 4, 4, 2, 0.5, 7)):
+        assert B.load().scc_forward_workspace_bytes(*bad) == 0
+        assert B.load().scc_backward_input_workspace_bytes(*bad) == 0
