@@ -107,6 +107,33 @@ int run_product(const T* src, const T* w, T* out, const Problem& p, void* worksp
     }
 }
 
+// Grad-weight: the kernel that shares its operands between filter tiles on the layers that gain from it (`shared`), else
+// the one with a tile per wavefront, else the one for any shape.  `workspace`: weight_workspace bytes.
+bool weight_shared(const Problem& p, scc_dtype dtype)
+{
+    return scc::backward_weight_shared_preferred(p, dtype == SCC_F32 ? 4 : 2);
+}
+
+size_t weight_workspace(const Problem& p, scc_dtype dtype, bool shared)
+{
+    if (shared) return scc::backward_weight_shared_workspace(p, dtype == SCC_F32 ? 4 : 2);
+    return scc::backward_weight_mfma_eligible(p) ? scc::backward_weight_mfma_workspace(p) : 0;
+}
+
+int run_weight(const void* x, const void* dy, void* dw, const Problem& p, scc_dtype dtype, bool shared, void* workspace,
+               hipStream_t st)
+{
+    drop_stale_error();
+    return with_type(dtype, [&](auto t) {
+        typedef const decltype(t)* In;
+        if (shared)
+            return launch_status(scc::launch_backward_weight_shared((In)x, (In)dy, (float*)dw, (float*)workspace, p, st));
+        if (scc::backward_weight_mfma_eligible(p))
+            return launch_status(scc::launch_backward_weight_mfma((In)x, (In)dy, (float*)dw, (float*)workspace, p, st));
+        return launch_status(scc::launch_backward_weight_generic((In)x, (In)dy, (float*)dw, p, st));
+    });
+}
+
 // The workspace of scc_backward: grad-weight's partial sums first, then grad-input's packed weights.
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
@@ -183,8 +210,7 @@ size_t scc_backward_weight_workspace_bytes(int N, int Cin, int Cout, int H, int 
 {
     Problem p;
     if (make_problem(N, Cin, Cout, H, W, cg, co, &p) != SCC_OK || !dtype_ok(dtype)) return 0;
-    if (scc::backward_weight_mfma_eligible(p)) return scc::backward_weight_mfma_workspace(p);
-    return 0;
+    return weight_workspace(p, dtype, weight_shared(p, dtype));
 }
 
 int scc_backward_weight(const void* x, const void* dy, void* dw, int N, int Cin, int Cout, int H, int W, int cg,
@@ -195,22 +221,11 @@ int scc_backward_weight(const void* x, const void* dy, void* dw, int N, int Cin,
     const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    const size_t need = scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype);
+    const bool shared = weight_shared(p, dtype);
+    const size_t need = weight_workspace(p, dtype, shared);
     if (need > 0 && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0))
         return SCC_ERR_WORKSPACE;
-    drop_stale_error();
-    hipStream_t st = (hipStream_t)stream;
-    if (dtype == SCC_F32) {
-        if (scc::backward_weight_mfma_eligible(p))
-            return launch_status(scc::launch_backward_weight_mfma((const float*)x, (const float*)dy, (float*)dw,
-                                                                  (float*)workspace, p, st));
-        return launch_status(scc::launch_backward_weight_generic((const float*)x, (const float*)dy, (float*)dw, p, st));
-    }
-    if (scc::backward_weight_mfma_eligible(p))
-        return launch_status(scc::launch_backward_weight_mfma((const scc::bf16_t*)x, (const scc::bf16_t*)dy, (float*)dw,
-                                                              (float*)workspace, p, st));
-    return launch_status(
-        scc::launch_backward_weight_generic((const scc::bf16_t*)x, (const scc::bf16_t*)dy, (float*)dw, p, st));
+    return run_weight(x, dy, dw, p, dtype, shared, workspace, (hipStream_t)stream);
 }
 
 size_t scc_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype)
@@ -244,7 +259,7 @@ int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* d
             return launch_status(scc::launch_backward_fused((const float*)x, (const float*)dy, (const float*)w,
                                                             (float*)dx, (float*)dw, (float*)workspace, p,
                                                             (hipStream_t)stream));
-    } else if (scc::packed_workspace<false>(p, dtype == SCC_F32 ? 4 : 2) > 0) {
+    } else if (scc::packed_workspace<false>(p, dtype == SCC_F32 ? 4 : 2) > 0 || weight_shared(p, dtype)) {
         const size_t at = align256(scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype));
         const int r = scc_backward_input_ws(dy, w, dx, N, Cin, Cout, H, W, cg, co, dtype, (char*)workspace + at,
                                             workspace_bytes - at, stream);
@@ -401,14 +416,17 @@ int scc_backward_weight_static(const void* x, const void* dy, void* dw, int N, i
     const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    const size_t need = scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype);
+    // where the shared kernel's partial sums do not fit the buffer, the other kernel's do, and it runs as it always has
+    bool shared = weight_shared(p, dtype);
+    if (shared && weight_workspace(p, dtype, true) > (size_t)SCC_STATIC_SCRATCH_BYTES) shared = false;
+    const size_t need = weight_workspace(p, dtype, shared);
     if (need > (size_t)SCC_STATIC_SCRATCH_BYTES) return SCC_ERR_SCRATCH;
     void* ptr = nullptr;
     if (need > 0) {
         const int sc = scratch_of_current_device(&ptr);
         if (sc != SCC_OK) return sc;
     }
-    return scc_backward_weight(x, dy, dw, N, Cin, Cout, H, W, cg, co, dtype, ptr, need, stream);
+    return run_weight(x, dy, dw, p, dtype, shared, ptr, (hipStream_t)stream);
 }
 
 const char* scc_status_string(int status)

@@ -148,6 +148,13 @@ template <typename T>
 hipError_t launch_backward_weight_mfma(const T* x, const T* dy, float* dw, float* workspace, const Problem& p,
                                        hipStream_t st);
 
+// Grad-weight with both operands shared by four filter tiles through LDS (scc_shared_bww.hip)
+bool backward_weight_shared_preferred(const Problem& p, int es);
+size_t backward_weight_shared_workspace(const Problem& p, int es);  // bytes of partial sums (0 when not split)
+template <typename T>
+hipError_t launch_backward_weight_shared(const T* x, const T* dy, float* dw, float* workspace, const Problem& p,
+                                         hipStream_t st);
+
 // dw[e] = sum over K-splits of part[ks][e], e < count, in a fixed order (scc_mfma_bww.hip)
 hipError_t launch_weight_reduce(const float* part, float* dw, int count, int KS, hipStream_t st);
 

@@ -212,7 +212,9 @@ __global__ __launch_bounds__(256, 2) void packed_product(const T_* __restrict__ 
     };
 
     // ---- B, loading role: lane (quad lu + 8z, column group lq) fetches CT columns of 4 planes ------------------
-    const int lq = tid & 31, lu = tid >> 5;
+    // (eight lanes with one quad, the next eight with the other quad of the same eight positions: the 8-byte LDS stores of
+    // 16 lanes then cover 128 contiguous bytes; with 16 lanes on one quad they conflict two by two)
+    const int lq = (lane & 7) | (lane >> 4) << 3, lu = 2 * wave + (lane >> 3 & 1);
     const int srows = FWD ? P.Cin : P.Cout, drows = FWD ? P.Cout : P.Cin;
     uint32_t lcol;
     {

@@ -1,0 +1,49 @@
+"""Grad-weight with both operands shared by four filter tiles, on layers that take this path, against the fp64 oracle: row
+groups and position chunks that are full, ragged and wrap, 2, 3 and 4 position tiles per workgroup, slices whose last round
+is partial, planes of any remainder.  Bar: the suite's 2e-5 of the largest value (dw is binary32 in both data types); and the
+error's 2-norm, which grows with the square root of the number of columns, 2**-24 * sqrt(N*H*W / 16) for one rounding per K group
+of 16 columns, with a factor of 4 for the six products of a group."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2101_00745_amd as S
+import scc_workloads as Wk
+from oracle import scc_oracle as O
+
+CASES = [("f32", (330, 120, 500, 11, 9, 2, 0.33)),      # 99 pixels: the last group of a sample overlaps; 5 row groups, the last of 88 rows
+         ("f32", (100, 104, 400, 23, 22, 1, 0.3)),      # walks once around the circle, entered past its end; last chunk of 8 positions
+         ("f32", (37, 336, 330, 20, 41, 1, 0.5)),       # last row group of 74 rows; three chunks
+         ("f32", (131, 96, 380, 30, 30, 2, 0.5)),       # 24 channels between starts; one chunk of 72 positions or more
+         ("bf16", (330, 120, 500, 11, 9, 2, 0.33)), ("bf16", (100, 104, 400, 23, 22, 1, 0.3)),
+         ("bf16", (37, 336, 330, 20, 41, 1, 0.5)), ("bf16", (131, 96, 380, 30, 30, 2, 0.5))]
+
+
+def workspace(dtype, shape):
+    return S.load().scc_backward_weight_workspace_bytes(*shape, 0 if dtype == "f32" else 1)
+
+
+@pytest.mark.parametrize("dtype,shape", CASES)
+def test_layers_here_take_the_path(dtype, shape):
+    # the per-tile kernel cuts the columns into at most 256 slices of all tiles and asks for 4 MiB at most
+    assert workspace(dtype, shape) > 4 << 20
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,shape", CASES)
+def test_parity_and_repeat(dtype, shape):
+    N, Cin, Cout, H, W, cg, co = shape
+    layer = Wk.Layer("shared_weight", 9, N=N, Cin=Cin, Cout=Cout, H=H, W=W, cg=cg, co=co)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    xd, wd, dyd = (torch.from_numpy(a).to(td).cuda() for a in Wk.make_inputs(layer))
+    ref = O.backward_weight(xd.float().cpu().numpy(), dyd.float().cpu().numpy(), cg, co)
+    dw = S.scc_backward_weight(xd, dyd, cg, co)
+    got = dw.cpu().numpy().astype(np.float64)
+    assert np.max(np.abs(got - ref)) <= 2e-5 * np.max(np.abs(ref))
+    assert np.linalg.norm(got - ref) <= 4 * 2.0 ** -24 * np.sqrt(N * H * W / 16) * np.linalg.norm(ref)
+    assert torch.equal(dw, S.scc_backward_weight(xd, dyd, cg, co))
+    dx, dw2 = S.scc_backward(xd, dyd, wd, cg, co)
+    assert torch.equal(dw, dw2) and torch.equal(dx, S.scc_backward_input(dyd, wd, Cin, cg, co))
+    static = torch.empty_like(dw)
+    S.scc_backward_weight_static(xd, dyd, cg, co, static)       # its buffer holds 8 MiB: either kernel
+    assert np.max(np.abs(static.cpu().numpy() - ref)) <= 2e-5 * np.max(np.abs(ref))
