@@ -236,6 +236,19 @@ int scc_dw_forward(const void* x, const void* kdw, const void* w, void* y,
                    scc_dtype dtype, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * All gradients of that block in one call (the depthwise output is computed again, never kept):
+ *     z = scc_depthwise3x3_forward(x, kdw);  (dz, dw) = scc_backward(z, dy, w);  (dx, dkdw) = scc_depthwise3x3_backward(x, kdw, dz)
+ * with the results of these three, bit for bit.  dy: in, N*Cout*Ho*Wo.  dx: out, as x.  dkdw: out, Cin*9, dw: out, Cout*L,
+ * binary32 values in both dtypes.  workspace: at least scc_dw_backward_workspace_bytes(...) bytes, 256-byte aligned, owned
+ * by the caller, contents undefined before and after.
+ */
+size_t scc_dw_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co,
+                                       scc_dtype dtype);
+int scc_dw_backward(const void* x, const void* kdw, const void* w, const void* dy, void* dx, void* dkdw, void* dw,
+                    int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype,
+                    void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * scc_backward_weight for callers that cannot allocate device memory or hand over a workspace:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments, kernels, arithmetic and summation order as scc_backward_weight (results are bitwise

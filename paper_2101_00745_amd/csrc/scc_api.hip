@@ -408,6 +408,48 @@ int scc_dw_forward(const void* x, const void* kdw, const void* w, void* y, int N
     return scc_forward(workspace, w, y, N, Cin, Cout, g.Ho, g.Wo, cg, co, dtype, stream);
 }
 
+// The workspace of scc_dw_backward: the depthwise output, its gradient, then the scratch of whichever stage runs.
+static size_t dw_backward_plane_bytes(const Problem& p, scc_dtype dtype)
+{
+    return align256((size_t)p.NQ * p.Cin * (dtype == SCC_F32 ? 4 : 2));
+}
+
+size_t scc_dw_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co,
+                                       scc_dtype dtype)
+{
+    Problem p;
+    scc::DwGeom g;
+    if (make_dw_problem(N, Cin, Cout, H, W, dw_stride, cg, co, &p, &g) != SCC_OK || !dtype_ok(dtype)) return 0;
+    const size_t a = scc_backward_workspace_bytes(N, Cin, Cout, g.Ho, g.Wo, cg, co, dtype);
+    const size_t b = scc_depthwise3x3_backward_workspace_bytes(N, Cin, H, W, dw_stride, dtype);
+    return 2 * dw_backward_plane_bytes(p, dtype) + (a > b ? a : b);
+}
+
+int scc_dw_backward(const void* x, const void* kdw, const void* w, const void* dy, void* dx, void* dkdw, void* dw, int N,
+                    int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype, void* workspace,
+                    size_t workspace_bytes, void* stream)
+{
+    if (!x || !kdw || !w || !dy || !dx || !dkdw || !dw) return SCC_ERR_NULL;
+    Problem p;
+    scc::DwGeom g;
+    const int rc = make_dw_problem(N, Cin, Cout, H, W, dw_stride, cg, co, &p, &g);
+    if (rc != SCC_OK) return rc;
+    if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
+    if (!workspace || workspace_bytes < scc_dw_backward_workspace_bytes(N, Cin, Cout, H, W, dw_stride, cg, co, dtype) ||
+        ((uintptr_t)workspace & 255u) != 0)
+        return SCC_ERR_WORKSPACE;
+    const size_t plane = dw_backward_plane_bytes(p, dtype);
+    char* z = (char*)workspace;
+    char* dz = z + plane;
+    char* rest = dz + plane;
+    int r = scc_depthwise3x3_forward(x, kdw, z, N, Cin, H, W, dw_stride, dtype, stream);
+    if (r != SCC_OK) return r;
+    r = scc_backward(z, dy, w, dz, dw, N, Cin, Cout, g.Ho, g.Wo, cg, co, dtype, rest, workspace_bytes - 2 * plane, stream);
+    if (r != SCC_OK) return r;
+    return scc_depthwise3x3_backward(x, kdw, dz, dx, dkdw, N, Cin, H, W, dw_stride, dtype, rest,
+                                     workspace_bytes - 2 * plane, stream);
+}
+
 int scc_backward_weight_static(const void* x, const void* dy, void* dw, int N, int Cin, int Cout, int H, int W, int cg,
                                double co, scc_dtype dtype, void* stream)
 {

@@ -21,7 +21,7 @@ SYMBOLS = ("scc_window_params", "scc_forward", "scc_forward_workspace_bytes", "s
            "scc_backward_workspace_bytes", "scc_backward",
            "scc_depthwise3x3_out", "scc_depthwise3x3_forward", "scc_depthwise3x3_backward_workspace_bytes",
            "scc_depthwise3x3_backward", "scc_dw_forward_workspace_bytes", "scc_dw_forward_fusable", "scc_dw_forward",
-           "scc_status_string")
+           "scc_dw_backward_workspace_bytes", "scc_dw_backward", "scc_status_string")
 STATIC_SCRATCH_BYTES = 8 << 20    # SCC_STATIC_SCRATCH_BYTES of include/scc.h
 
 _lib = None
@@ -80,6 +80,10 @@ def load():
     lib.scc_dw_forward_fusable.restype = c_int
     lib.scc_dw_forward.argtypes = [c_vp] * 4 + dw_shape + [c_vp, c_sz, c_vp]
     lib.scc_dw_forward.restype = c_int
+    lib.scc_dw_backward_workspace_bytes.argtypes = dw_shape
+    lib.scc_dw_backward_workspace_bytes.restype = c_sz
+    lib.scc_dw_backward.argtypes = [c_vp] * 7 + dw_shape + [c_vp, c_sz, c_vp]
+    lib.scc_dw_backward.restype = c_int
     lib.scc_status_string.argtypes = [c_int]
     lib.scc_status_string.restype = ctypes.c_char_p
     _lib = lib
@@ -102,12 +106,14 @@ def scc_window_params(Cin, Cout, cg, co):
     return L.value, s.value, p.value
 
 
+_CODES = {torch.float32: SCC_F32, torch.bfloat16: SCC_BF16}
+
+
 def _dtype_code(t):
-    if t.dtype == torch.float32:
-        return SCC_F32
-    if t.dtype == torch.bfloat16:
-        return SCC_BF16
-    raise TypeError("SCC tensors must be float32 or bfloat16, got %s" % t.dtype)
+    code = _CODES.get(t.dtype)
+    if code is None:
+        raise TypeError("SCC tensors must be float32 or bfloat16, got %s" % t.dtype)
+    return code
 
 
 def _dev(*tensors):
@@ -117,13 +123,27 @@ def _dev(*tensors):
         if not t.is_contiguous():
             raise ValueError("SCC tensors must be dense and contiguous (NCHW)")
     dev = tensors[0].device
-    if any(t.device != dev for t in tensors):
-        raise ValueError("SCC tensors must share one device")
+    for t in tensors[1:]:
+        if t.device != dev:
+            raise ValueError("SCC tensors must share one device")
     return dev
 
 
-def _stream(dev):
-    return ctypes.c_void_p(torch.cuda.current_stream(dev).cuda_stream)
+_raw_stream = torch._C._cuda_getCurrentRawStream    # the address alone: torch.cuda.current_stream builds a Stream object around it
+
+
+def _launch(dev, call, *args):
+    """call(*args, current stream of dev) with dev as the current device.  A small layer's pass is bound by the host, so the
+    device is switched only where it is another one and no Stream object is made (one 8x8 image, 32 channels, forward and
+    scc_backward: 28 us with both, 22 without)."""
+    index = dev.index
+    if torch.cuda.current_device() == index:
+        status = call(*args, _raw_stream(index))
+    else:
+        with torch.cuda.device(index):
+            status = call(*args, _raw_stream(index))
+    if status != 0:
+        _check(status)
 
 
 @functools.lru_cache(maxsize=4096)
@@ -147,14 +167,13 @@ def scc_forward(x, w, cg, co, out=None):
     Cout = w.shape[0]
     if w.dtype != x.dtype or w.dim() != 2 or (cg >= 1 and Cin % cg == 0 and w.shape[1] != Cin // cg):
         raise ValueError("w must be [Cout, Cin//cg] with the dtype of x")
-    y = torch.empty((N, Cout, H, W), dtype=x.dtype, device=dev) if out is None else out
+    y = x.new_empty((N, Cout, H, W)) if out is None else out
     if out is not None:
         _dev(out)
         assert out.shape == (N, Cout, H, W) and out.dtype == x.dtype
     shape = (N, Cin, Cout, H, W, cg, float(co), _dtype_code(x))
     ws, ws_ptr, ws_len = _scratch(_workspace_need("scc_forward_workspace_bytes", *shape), dev)
-    with torch.cuda.device(dev):
-        _check(load().scc_forward_ws(x.data_ptr(), w.data_ptr(), y.data_ptr(), *shape, ws_ptr, ws_len, _stream(dev)))
+    _launch(dev, load().scc_forward_ws, x.data_ptr(), w.data_ptr(), y.data_ptr(), *shape, ws_ptr, ws_len)
     return y
 
 
@@ -165,15 +184,13 @@ def scc_backward_input(dy, w, Cin, cg, co, out=None):
     if w.dtype != dy.dtype or w.dim() != 2 or w.shape[0] != Cout or \
             (cg >= 1 and Cin % cg == 0 and w.shape[1] != Cin // cg):
         raise ValueError("w must be [Cout, Cin//cg] with the dtype of dy")
-    dx = torch.empty((N, Cin, H, W), dtype=dy.dtype, device=dev) if out is None else out
+    dx = dy.new_empty((N, Cin, H, W)) if out is None else out
     if out is not None:
         _dev(out)
         assert out.shape == (N, Cin, H, W) and out.dtype == dy.dtype
     shape = (N, Cin, Cout, H, W, cg, float(co), _dtype_code(dy))
     ws, ws_ptr, ws_len = _scratch(_workspace_need("scc_backward_input_workspace_bytes", *shape), dev)
-    with torch.cuda.device(dev):
-        _check(load().scc_backward_input_ws(dy.data_ptr(), w.data_ptr(), dx.data_ptr(), *shape, ws_ptr, ws_len,
-                                            _stream(dev)))
+    _launch(dev, load().scc_backward_input_ws, dy.data_ptr(), w.data_ptr(), dx.data_ptr(), *shape, ws_ptr, ws_len)
     return dx
 
 
@@ -189,8 +206,8 @@ def scc_backward_weight(x, dy, cg, co, out=None, workspace=None):
     Cout = dy.shape[1]
     if dy.dtype != x.dtype or dy.shape != (N, Cout, H, W):
         raise ValueError("dy must be [N,Cout,H,W] with the dtype of x")
-    code = _dtype_code(x)
-    need = int(load().scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, float(co), code))
+    shape = (N, Cin, Cout, H, W, cg, float(co), _dtype_code(x))
+    need = _workspace_need("scc_backward_weight_workspace_bytes", *shape) if workspace is None else 0
     if workspace is None and need > 0:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     L = Cin // cg if cg >= 1 and Cin % cg == 0 else 1
@@ -200,9 +217,7 @@ def scc_backward_weight(x, dy, cg, co, out=None, workspace=None):
         assert out.shape == (Cout, L) and out.dtype == torch.float32
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    with torch.cuda.device(dev):
-        _check(load().scc_backward_weight(x.data_ptr(), dy.data_ptr(), dw.data_ptr(), N, Cin, Cout, H, W, cg,
-                                          float(co), code, ws_ptr, ws_len, _stream(dev)))
+    _launch(dev, load().scc_backward_weight, x.data_ptr(), dy.data_ptr(), dw.data_ptr(), *shape, ws_ptr, ws_len)
     return dw
 
 
@@ -217,9 +232,8 @@ def scc_backward_weight_static(x, dy, cg, co, out):
     L = Cin // cg if cg >= 1 and Cin % cg == 0 else 1
     if out.shape != (Cout, L) or out.dtype != torch.float32:
         raise ValueError("out must be float32 [Cout, Cin//cg]")
-    with torch.cuda.device(dev):
-        _check(load().scc_backward_weight_static(x.data_ptr(), dy.data_ptr(), out.data_ptr(), N, Cin, Cout, H, W, cg,
-                                                 float(co), _dtype_code(x), _stream(dev)))
+    _launch(dev, load().scc_backward_weight_static, x.data_ptr(), dy.data_ptr(), out.data_ptr(), N, Cin, Cout, H, W, cg,
+            float(co), _dtype_code(x))
     return out
 
 
@@ -238,8 +252,8 @@ def scc_backward(x, dy, w, cg, co, out_dx=None, out_dw=None, workspace=None):
     if w.dtype != x.dtype or w.dim() != 2 or w.shape[0] != Cout or \
             (cg >= 1 and Cin % cg == 0 and w.shape[1] != Cin // cg):
         raise ValueError("w must be [Cout, Cin//cg] with the dtype of x")
-    code = _dtype_code(x)
-    need = int(load().scc_backward_workspace_bytes(N, Cin, Cout, H, W, cg, float(co), code))
+    shape = (N, Cin, Cout, H, W, cg, float(co), _dtype_code(x))
+    need = _workspace_need("scc_backward_workspace_bytes", *shape) if workspace is None else 0
     if workspace is None and need > 0:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     L = Cin // cg if cg >= 1 and Cin % cg == 0 else 1
@@ -251,9 +265,8 @@ def scc_backward(x, dy, w, cg, co, out_dx=None, out_dw=None, workspace=None):
             assert o.shape == shp and o.dtype == dt
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    with torch.cuda.device(dev):
-        _check(load().scc_backward(x.data_ptr(), dy.data_ptr(), w.data_ptr(), dx.data_ptr(), dw.data_ptr(), N, Cin, Cout,
-                                   H, W, cg, float(co), code, ws_ptr, ws_len, _stream(dev)))
+    _launch(dev, load().scc_backward, x.data_ptr(), dy.data_ptr(), w.data_ptr(), dx.data_ptr(), dw.data_ptr(), *shape,
+            ws_ptr, ws_len)
     return dx, dw
 
 
@@ -264,20 +277,25 @@ def scc_depthwise3x3_out(size, dw_stride):
     return r
 
 
+def _out(size, dw_stride):
+    """scc_depthwise3x3_out without a call into the library, which only speaks up where there is an error."""
+    return (size - 1) // dw_stride + 1 if size > 0 and dw_stride >= 1 else scc_depthwise3x3_out(size, dw_stride)
+
+
 def scc_depthwise3x3_forward(x, kdw, dw_stride=1, out=None):
     """z = DW3x3(x; kdw): x [N,C,H,W], kdw [C,3,3] -> z [N,C,Ho,Wo] (Eq. 2: centred taps, zero outside the map)."""
     dev = _dev(x, kdw)
     N, C, H, W = x.shape
     if kdw.dtype != x.dtype or tuple(kdw.shape) != (C, 3, 3):
         raise ValueError("kdw must be [C, 3, 3] with the dtype of x")
-    Ho, Wo = scc_depthwise3x3_out(H, dw_stride), scc_depthwise3x3_out(W, dw_stride)
-    z = torch.empty((N, C, Ho, Wo), dtype=x.dtype, device=dev) if out is None else out
+    dw_stride = int(dw_stride)
+    Ho, Wo = _out(H, dw_stride), _out(W, dw_stride)
+    z = x.new_empty((N, C, Ho, Wo)) if out is None else out
     if out is not None:
         _dev(out)
         assert out.shape == (N, C, Ho, Wo) and out.dtype == x.dtype
-    with torch.cuda.device(dev):
-        _check(load().scc_depthwise3x3_forward(x.data_ptr(), kdw.data_ptr(), z.data_ptr(), N, C, H, W, int(dw_stride),
-                                               _dtype_code(x), _stream(dev)))
+    _launch(dev, load().scc_depthwise3x3_forward, x.data_ptr(), kdw.data_ptr(), z.data_ptr(), N, C, H, W, dw_stride,
+            _dtype_code(x))
     return z
 
 
@@ -287,7 +305,8 @@ def scc_depthwise3x3_backward(x, kdw, dz, dw_stride=1, need_dx=True, need_dk=Tru
     A gradient that is not needed comes back as None."""
     dev = _dev(x, kdw, dz)
     N, C, H, W = x.shape
-    Ho, Wo = scc_depthwise3x3_out(H, dw_stride), scc_depthwise3x3_out(W, dw_stride)
+    dw_stride = int(dw_stride)
+    Ho, Wo = _out(H, dw_stride), _out(W, dw_stride)
     if kdw.dtype != x.dtype or tuple(kdw.shape) != (C, 3, 3):
         raise ValueError("kdw must be [C, 3, 3] with the dtype of x")
     if dz.dtype != x.dtype or tuple(dz.shape) != (N, C, Ho, Wo):
@@ -295,7 +314,7 @@ def scc_depthwise3x3_backward(x, kdw, dz, dw_stride=1, need_dx=True, need_dk=Tru
     if not (need_dx or need_dk):
         return None, None
     code = _dtype_code(x)
-    need = int(load().scc_depthwise3x3_backward_workspace_bytes(N, C, H, W, int(dw_stride), code)) if need_dk else 0
+    need = _workspace_need("scc_depthwise3x3_backward_workspace_bytes", N, C, H, W, dw_stride, code) if need_dk else 0
     if workspace is None and need > 0:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
     dx = (torch.empty_like(x) if out_dx is None else out_dx) if need_dx else None
@@ -306,11 +325,9 @@ def scc_depthwise3x3_backward(x, kdw, dz, dw_stride=1, need_dx=True, need_dk=Tru
             assert o.shape == shp and o.dtype == dt
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    with torch.cuda.device(dev):
-        _check(load().scc_depthwise3x3_backward(x.data_ptr(), kdw.data_ptr(), dz.data_ptr(),
-                                                dx.data_ptr() if dx is not None else None,
-                                                dk.data_ptr() if dk is not None else None, N, C, H, W, int(dw_stride),
-                                                code, ws_ptr, ws_len, _stream(dev)))
+    _launch(dev, load().scc_depthwise3x3_backward, x.data_ptr(), kdw.data_ptr(), dz.data_ptr(),
+            dx.data_ptr() if dx is not None else None, dk.data_ptr() if dk is not None else None, N, C, H, W, dw_stride,
+            code, ws_ptr, ws_len)
     return dx, dk
 
 
@@ -339,23 +356,45 @@ def scc_dw_forward(x, kdw, w, cg, co, dw_stride=1, out=None, workspace=None, fus
         raise ValueError("kdw must be [Cin, 3, 3] with the dtype of x")
     if w.dtype != x.dtype or w.dim() != 2 or (cg >= 1 and Cin % cg == 0 and w.shape[1] != Cin // cg):
         raise ValueError("w must be [Cout, Cin//cg] with the dtype of x")
-    Ho, Wo = scc_depthwise3x3_out(H, dw_stride), scc_depthwise3x3_out(W, dw_stride)
+    dw_stride = int(dw_stride)
+    Ho, Wo = _out(H, dw_stride), _out(W, dw_stride)
     if fused is False:
         z = scc_depthwise3x3_forward(x, kdw, dw_stride)
         return scc_forward(z, w, cg, co, out=out)
-    code = _dtype_code(x)
-    need = int(load().scc_dw_forward_workspace_bytes(N, Cin, Cout, H, W, int(dw_stride), cg, float(co), code))
+    shape = (N, Cin, Cout, H, W, dw_stride, cg, float(co), _dtype_code(x))
+    need = _workspace_need("scc_dw_forward_workspace_bytes", *shape)
     if fused:
         workspace = None
     elif workspace is None and need > 0:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
-    y = torch.empty((N, Cout, Ho, Wo), dtype=x.dtype, device=dev) if out is None else out
+    y = x.new_empty((N, Cout, Ho, Wo)) if out is None else out
     if out is not None:
         _dev(out)
         assert out.shape == (N, Cout, Ho, Wo) and out.dtype == x.dtype
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    with torch.cuda.device(dev):
-        _check(load().scc_dw_forward(x.data_ptr(), kdw.data_ptr(), w.data_ptr(), y.data_ptr(), N, Cin, Cout, H, W,
-                                     int(dw_stride), cg, float(co), code, ws_ptr, ws_len, _stream(dev)))
+    _launch(dev, load().scc_dw_forward, x.data_ptr(), kdw.data_ptr(), w.data_ptr(), y.data_ptr(), *shape, ws_ptr, ws_len)
     return y
+
+
+def scc_dw_backward(x, kdw, w, dy, cg, co, dw_stride=1):
+    """(dx, dkdw, dw), all gradients of a DW + SCC block in one call: x [N,Cin,H,W], kdw [Cin,3,3], w [Cout,Cin//cg],
+    dy [N,Cout,Ho,Wo]; dkdw and dw are float32."""
+    dev = _dev(x, kdw, w, dy)
+    N, Cin, H, W = x.shape
+    Cout = w.shape[0]
+    if kdw.dtype != x.dtype or tuple(kdw.shape) != (Cin, 3, 3):
+        raise ValueError("kdw must be [Cin, 3, 3] with the dtype of x")
+    if w.dtype != x.dtype or w.dim() != 2 or (cg >= 1 and Cin % cg == 0 and w.shape[1] != Cin // cg):
+        raise ValueError("w must be [Cout, Cin//cg] with the dtype of x")
+    dw_stride = int(dw_stride)
+    if dy.dtype != x.dtype or tuple(dy.shape) != (N, Cout, _out(H, dw_stride), _out(W, dw_stride)):
+        raise ValueError("dy must be [N, Cout, Ho, Wo] with the dtype of x")
+    shape = (N, Cin, Cout, H, W, dw_stride, cg, float(co), _dtype_code(x))
+    ws, ws_ptr, ws_len = _scratch(_workspace_need("scc_dw_backward_workspace_bytes", *shape), dev)
+    dx = torch.empty_like(x)
+    dk = torch.empty((Cin, 3, 3), dtype=torch.float32, device=dev)
+    dw = torch.empty(w.shape, dtype=torch.float32, device=dev)
+    _launch(dev, load().scc_dw_backward, x.data_ptr(), kdw.data_ptr(), w.data_ptr(), dy.data_ptr(), dx.data_ptr(),
+            dk.data_ptr(), dw.data_ptr(), *shape, ws_ptr, ws_len)
+    return dx, dk, dw

@@ -1,0 +1,36 @@
+"""The backward of a DW + SCC block in one call: the results of its three stages, bit for bit, and the host's checks."""
+import ctypes
+
+import pytest
+import torch
+
+import paper_2101_00745_amd as S
+
+SHAPES = [(1, 16, 24, 4, 4, 1, 2, 0.5), (3, 32, 40, 9, 7, 2, 4, 0.25), (40, 64, 96, 10, 12, 1, 2, 0.33), (130, 64, 64, 16, 16, 2, 1, 0.5)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shape", SHAPES)
+def test_one_call_is_its_three_stages(shape, dtype):
+    N, Cin, Cout, H, W, s, cg, co = shape
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x, kdw, w, dy = (torch.randn(*d, generator=gen, device="cuda").to(dtype) for d in
+                     ((N, Cin, H, W), (Cin, 3, 3), (Cout, Cin // cg), (N, Cout, (H - 1) // s + 1, (W - 1) // s + 1)))
+    z = S.scc_depthwise3x3_forward(x, kdw, s)
+    dz, dw = S.scc_backward(z, dy, w, cg, co)
+    dx, dk = S.scc_depthwise3x3_backward(x, kdw, dz, s)
+    got = S.scc_dw_backward(x, kdw, w, dy, cg, co, s)
+    assert all(torch.equal(a, b) and a.dtype == b.dtype for a, b in zip(got, (dx, dk, dw)))
+
+
+def test_host_checks():
+    lib, p = S.load(), ctypes.c_void_p(0x1000)
+    shape = (3, 32, 40, 9, 7, 2, 4, 0.25, 0)
+    need = lib.scc_dw_backward_workspace_bytes(*shape)
+    assert need >= 2 * 3 * 32 * 5 * 4 * 4
+    assert lib.scc_dw_backward(p, p, p, p, p, p, p, *shape, 0x1000, need - 1, None) == -5
+    assert lib.scc_dw_backward(p, p, p, p, p, p, p, *shape, None, need, None) == -5
+    assert lib.scc_dw_backward(p, p, p, None, p, p, p, *shape, 0x1000, need, None) == -1
+    bad = (3, 32, 40, 9, 7, 0, 4, 0.25, 0)
+    assert lib.scc_dw_backward(p, p, p, p, p, p, p, *bad, 0x1000, need, None) == -2 and lib.scc_dw_backward_workspace_bytes(*bad) == 0
