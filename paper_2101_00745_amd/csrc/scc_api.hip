@@ -134,7 +134,6 @@ int run_weight(const void* x, const void* dy, void* dw, const Problem& p, scc_dt
     });
 }
 
-// The workspace of scc_backward: grad-weight's partial sums first, then grad-input's packed weights.
 size_t align256(size_t v) { return (v + 255) / 256 * 256; }
 
 }  // namespace
@@ -232,13 +231,16 @@ size_t scc_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int 
 {
     Problem p;
     if (make_problem(N, Cin, Cout, H, W, cg, co, &p) != SCC_OK || !dtype_ok(dtype)) return 0;
-    // the fused kernel's need, or that of the separate grad-weight pass it may fall back to, whichever is larger
-    size_t need = scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype);
-    if (dtype == SCC_F32 && scc::backward_fused_eligible(p)) {
-        const size_t fused = scc::backward_fused_workspace(p);
-        return fused > need ? fused : need;
-    }
-    return align256(need) + scc::packed_workspace<false>(p, dtype == SCC_F32 ? 4 : 2);
+    // whichever of its kernels runs (tensors that are not aligned to 16 bytes keep a layer from the fused one): the most
+    size_t need = 0;
+    auto at_least = [&](size_t v) { need = v > need ? v : need; };
+    at_least(scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype));
+    at_least(weight_workspace(p, dtype, false));
+    if (dtype == SCC_F32 && scc::backward_fused_eligible(p))
+        at_least(scc::backward_fused_workspace(p));
+    else
+        at_least(scc::backward_shared_workspace(p, dtype == SCC_F32 ? 4 : 2));
+    return need;
 }
 
 int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* dw, int N, int Cin, int Cout, int H,
@@ -259,12 +261,12 @@ int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* d
             return launch_status(scc::launch_backward_fused((const float*)x, (const float*)dy, (const float*)w,
                                                             (float*)dx, (float*)dw, (float*)workspace, p,
                                                             (hipStream_t)stream));
-    } else if (scc::packed_workspace<false>(p, dtype == SCC_F32 ? 4 : 2) > 0 || weight_shared(p, dtype)) {
-        const size_t at = align256(scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype));
-        const int r = scc_backward_input_ws(dy, w, dx, N, Cin, Cout, H, W, cg, co, dtype, (char*)workspace + at,
-                                            workspace_bytes - at, stream);
-        if (r != SCC_OK) return r;
-        return scc_backward_weight(x, dy, dw, N, Cin, Cout, H, W, cg, co, dtype, workspace, workspace_bytes, stream);
+    } else if (scc::backward_shared_workspace(p, dtype == SCC_F32 ? 4 : 2) > 0) {
+        return with_type(dtype, [&](auto t) {
+            typedef decltype(t) T;
+            return launch_status(scc::launch_backward_shared((const T*)x, (const T*)dy, (const T*)w, (T*)dx, (float*)dw,
+                                                             workspace, p, (hipStream_t)stream));
+        });
     }
     // layers both matrix-core kernels take: their two grids as one launch
     if (dtype == SCC_F32) {

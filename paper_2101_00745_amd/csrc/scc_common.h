@@ -141,6 +141,8 @@ hipError_t launch_backward_input_shared(const float* dy, const float* w, float* 
 // workspace they are packed into, 0 for layers that do not take this path; es is the storage type's size
 template <bool FWD> size_t packed_workspace(const Problem& p, int es);
 template <typename T, bool FWD>
+hipError_t pack_only(const T* w, void* workspace, const Problem& p, int ct, hipStream_t st);
+template <typename T, bool FWD>
 hipError_t launch_packed(const T* src, const T* w, T* out, void* workspace, const Problem& p, hipStream_t st);
 bool backward_weight_mfma_eligible(const Problem& p);
 size_t backward_weight_mfma_workspace(const Problem& p);  // bytes of K-split partials (0 when not split)
@@ -150,10 +152,16 @@ hipError_t launch_backward_weight_mfma(const T* x, const T* dy, float* dw, float
 
 // Grad-weight with both operands shared by four filter tiles through LDS (scc_shared_bww.hip)
 bool backward_weight_shared_preferred(const Problem& p, int es);
-size_t backward_weight_shared_workspace(const Problem& p, int es);  // bytes of partial sums (0 when not split)
+size_t backward_weight_shared_workspace(const Problem& p, int es);  // bytes of partial sums
 template <typename T>
 hipError_t launch_backward_weight_shared(const T* x, const T* dy, float* dw, float* workspace, const Problem& p,
                                          hipStream_t st);
+
+// Packed grad-input and shared grad-weight as one launch (scc_shared_merged.hip)
+size_t backward_shared_workspace(const Problem& p, int es);   // 0 for layers that do not take it
+template <typename T>
+hipError_t launch_backward_shared(const T* x, const T* dy, const T* w, T* dx, float* dw, void* workspace, const Problem& p,
+                                  hipStream_t st);
 
 // dw[e] = sum over K-splits of part[ks][e], e < count, in a fixed order (scc_mfma_bww.hip)
 hipError_t launch_weight_reduce(const float* part, float* dw, int count, int KS, hipStream_t st);

@@ -1,0 +1,307 @@
+// Grad-weight of SCC for layers in which many 32-filter tiles read the same planes: both operands go through LDS once per
+// workgroup of four filter tiles.
+//
+// dw[k,j] = sum_{n,p} dy[n,k,p] * x[n,(s_k+j) mod Cin,p]     (the derivative of the forward definition with respect to w)
+//
+// scc_mfma_bww_kernel.h gives every wavefront its own 32 filters x 32..96 positions and lets the wavefronts of a workgroup
+// split the columns: every x plane is fetched once per filter tile whose windows reach it, every dy plane once per chunk
+// of span positions (the channel-expanding layer moves 1 GB through L2 in a pass), and binary32 operands go through
+// v_mfma_f32_32x32x2_f32, at 3/8 of the rate of the bf16 instruction on the exact three-way split.  Here a workgroup owns 128
+// filters in the order of their window starts times 32*PT positions of the walk that covers their windows (the channels
+// from the first window's start to the last one's end), for one slice of the columns.  Per round of 16*KG columns its 256
+// lanes fetch 128 dy planes and 32*PT x planes, 16 bytes per lane and plane, cut each value once and park the pieces in
+// LDS in operand layout (8 columns of one plane = 16 bytes); wavefront t multiplies filter tile t with all PT position
+// tiles and skips those none of its windows reaches.  One LDS buffer and two barriers per round; the next round's loads
+// are in flight while this one is multiplied, and three (binary32) or four workgroups per CU overlap each other's phases.
+//
+// A wavefront's tiles are its own, so there is no sum inside a workgroup; the slices' partial sums go to the workspace in the
+// layout of dw and launch_weight_reduce adds them in slice order: no atomics, bitwise reproducible.
+#pragma once
+#include "scc_band.h"
+#include "scc_common.h"
+#include "scc_mfma_bww_kernel.h"
+#include "scc_mfma_bww_kernel.h"
+
+namespace scc {
+
+namespace shared_bww {
+
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+struct WeightTiling {
+    Band b;
+    int rows;       // filters in order of their starts: P*F
+    int NG;         // groups of 128 rows
+    int NSC;        // chunks of 32*PT walk positions (of the longest walk)
+    int KS8;        // slices of the columns per XCD
+    int KS;         // slices: 8 * KS8
+    int eighth;     // rounds of an XCD: it takes a contiguous eighth of the columns
+    int per_slice;  // consecutive rounds of it that a slice takes
+    int chunk;      // workgroups of an XCD: KS8 * NG * NSC
+    Groups q;       // column groups of 16 bytes
+};
+
+// walk of row group ng: first channel, channels (at most Cin: each channel once)
+__host__ __device__ inline void weight_walk(const Problem& P, const Band& b, int rows, int ng, int& first, int& len)
+{
+    const int r0 = ng * 128, r1 = r0 + 127 < rows ? r0 + 127 : rows - 1;
+    const int m0 = r0 / b.F, m1 = r1 / b.F;
+    first = b.g * m0;
+    const long long span = (long long)P.L + (long long)b.g * (m1 - m0);
+    len = span < P.Cin ? (int)span : P.Cin;
+}
+
+constexpr int weight_rows(int pt) { return 128 + 32 * pt; }
+// bytes of the operands of one K group and half-wave: 32 of padding, so that 16 lanes' 8-byte stores (2 planes x 4 such
+// blocks) cover the 128 bytes of all banks; with 128 they conflict four by four (channel-expanding layer, dw alone: f32 105 us
+// against 95, bf16 50 against 36)
+constexpr int weight_half(int pt) { return weight_rows(pt) * 16 + 32; }
+constexpr int weight_lds(int es, int pt) { return (es == 2 ? 8 : 3 * 4) * weight_half(pt); }
+
+// bid: the workgroup's index in a launch whose first workgroup is a multiple of 8 (bid % 8 names the XCD)
+template <typename T_, int PT>
+__device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* __restrict__ dy, float* __restrict__ out,
+                                            const Problem& P, const WeightTiling& T, const int bid, char* const lds_w)
+{
+    constexpr uint32_t ES = sizeof(T_);
+    constexpr int NP = ES == 2 ? 1 : 3;                 // bf16 pieces of a value
+    constexpr int KG = ES == 2 ? 4 : 2;                 // K groups of 16 columns per round
+    constexpr int CT = 16 / (int)ES;                    // columns per lane and load
+    constexpr int NL = 4 + PT;                          // loads per lane and round: planes tid/8 + 32*it
+    constexpr int kHalf = weight_half(PT);
+    constexpr int kPiece = 2 * KG * kHalf;
+    typedef T_ ldvec __attribute__((ext_vector_type(CT), aligned(sizeof(T_))));
+
+    const int xcd = bid & 7, slot = bid >> 3;
+    const int tiles = T.NG * T.NSC;
+    if (slot >= T.chunk) return;                        // the whole workgroup leaves
+    const int s8 = slot / tiles, tix = slot % tiles, ks = xcd * T.KS8 + s8;
+    const int ng = tix / T.NSC, sc = tix % T.NSC;
+    int first, len;
+    weight_walk(P, T.b, T.rows, ng, first, len);
+    const int pos0 = 32 * PT * sc;
+    if (pos0 >= len) return;                            // shorter walk than the longest: the whole workgroup leaves
+
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int lane = tid & 63, f = lane & 31, h = lane >> 5;
+    const int lr = tid >> 3, lc = tid & 7;              // loading role: planes lr + 32*it, column group lc of 8
+
+    auto filter = [&](int row) {                        // filter of a row, -1 where there is none
+        if (row >= T.rows) return -1;
+        const int m = row / T.b.F;
+        const int k = (int)(((uint32_t)m * (uint32_t)T.b.inv) % (uint32_t)T.b.P) + T.b.P * (row - m * T.b.F);
+        return k < P.Cout ? k : -1;
+    };
+    const uint32_t plane = (uint32_t)P.HW * ES;
+    uint32_t rowoff[NL];
+#pragma unroll
+    for (int it = 0; it < NL; ++it) {
+        if (it < 4) {
+            const int k = filter(128 * ng + 32 * it + lr);
+            rowoff[it] = (uint32_t)(k < 0 ? 0 : k) * plane;      // rows without a filter are fetched, never stored
+        } else {
+            const int pos = pos0 + 32 * (it - 4) + lr;
+            int c = first + (pos < len ? pos : 0);
+            c -= c >= P.Cin ? P.Cin : 0;
+            rowoff[it] = (uint32_t)c * plane;
+        }
+    }
+    // this wavefront's filters start between walk positions d0 and d0 + ..., its windows end before d1; a walk around the
+    // whole circle is entered again past its end
+    const int row0 = 128 * ng + 32 * wave;
+    const int last = row0 + 31 < T.rows ? row0 + 31 : T.rows - 1;
+    const int d0 = T.b.g * (row0 / T.b.F) - first, d1 = T.b.g * (last / T.b.F) - first + P.L;
+    uint32_t active = 0;
+#pragma unroll
+    for (int t = 0; t < PT; ++t) {
+        const int p0 = pos0 + 32 * t;
+        if (row0 < T.rows && p0 < len && ((p0 < d1 && p0 + 32 > d0) || p0 < d1 - P.Cin)) active |= 1u << t;
+    }
+
+    // this slice's rounds (8 column groups each), r0 up to r1.  (Slices that take every KS8-th round instead, so that an XCD
+    // sweeps its eighth on a narrow front, are slower: channel-expanding layer f32 95 -> 103 us, bf16 40 -> 51.)
+    const int rounds = (int)((T.q.count + 7) / 8), count = (int)T.q.count;
+    const int r0 = xcd * T.eighth + s8 * T.per_slice;
+    int r1 = (xcd + 1) * T.eighth < rounds ? (xcd + 1) * T.eighth : rounds;
+    r1 = r0 + T.per_slice < r1 ? r0 + T.per_slice : r1;
+    const int nround = r1 > r0 ? r1 - r0 : 0;           // none: the slice's sums are zeros
+
+    const uint32_t per = (uint32_t)T.q.per;
+    const uint32_t sampA = (uint32_t)P.Cout * plane, sampB = (uint32_t)P.Cin * plane;
+    uint32_t cp, offA, offB;                            // group inside the sample, byte offsets of the sample
+    {
+        const uint32_t u = (uint32_t)(8 * r0 + lc), n = u / per;
+        cp = u - n * per;
+        offA = n * sampA;
+        offB = n * sampB;
+    }
+    const uint32_t dn = 8u / per, dp = 8u % per;
+    const uint32_t dup = (uint32_t)CT * per - (uint32_t)P.HW;    // pixels the last group of a sample shares with the one before
+    int next = 8 * r0 + lc;
+    ldvec raw[NL];
+    uint32_t in = 0;                                    // one bit per column of the loaded group that counts
+    auto issue = [&]() {
+        const bool gin = next < count;
+        in = gin ? (((1u << CT) - 1u) & (0xffffffffu << (cp == per - 1u ? dup : 0u))) : 0u;
+        const uint32_t p = ((uint32_t)CT * cp < (uint32_t)T.q.last ? (uint32_t)CT * cp : (uint32_t)T.q.last) * ES;
+        const uint32_t ca = gin ? offA + p : 0u, cb = gin ? offB + p : 0u;
+#pragma unroll
+        for (int it = 0; it < NL; ++it)
+            raw[it] = *(const ldvec*)((it < 4 ? (const char*)dy + ca : (const char*)x + cb) + rowoff[it]);
+        next += 8;
+        cp += dp;
+        const bool wr = cp >= per;
+        cp -= wr ? per : 0u;
+        offA += dn * sampA + (wr ? sampA : 0u);
+        offB += dn * sampB + (wr ? sampB : 0u);
+    };
+    // lane's 16 bytes: binary32, 4 columns = half an operand of (K group lc/4, half-wave lc/2%2); bf16, a whole operand of (lc/2, lc%2)
+    char* const dst0 = lds_w + (ES == 2 ? lc * kHalf : (lc >> 1) * kHalf + 8 * (lc & 1)) + lr * 16;
+    auto commit = [&](bool full) {
+#pragma unroll
+        for (int it = 0; it < NL; ++it) {
+            ldvec v = raw[it];
+            if (!full) {
+#pragma unroll
+                for (int e = 0; e < CT; ++e) v[e] = (in >> e) & 1u ? v[e] : (T_)0;
+            }
+            char* dst = dst0 + it * 512;
+            if constexpr (ES == 2) {
+                *(u32x4*)dst = __builtin_bit_cast(u32x4, v);
+            } else {
+                uint32_t hi[2], mid[2], lo[2];
+                split3<4>([&](int e) { return v[e]; }, hi, mid, lo);
+                *(u32x2*)dst = u32x2{hi[0], hi[1]};
+                *(u32x2*)(dst + kPiece) = u32x2{mid[0], mid[1]};
+                *(u32x2*)(dst + 2 * kPiece) = u32x2{lo[0], lo[1]};
+            }
+        }
+    };
+
+    f32x16 acc[PT];
+#pragma unroll
+    for (int t = 0; t < PT; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+    auto mm = [&](const u32x4& a, const u32x4& b, f32x16& d) {
+        const uint32_t aa[4] = {a[0], a[1], a[2], a[3]}, ba[4] = {b[0], b[1], b[2], b[3]};
+        d = mfma_bf16<8>(aa, ba, d);
+    };
+    auto compute = [&]() {
+#pragma unroll
+        for (int j = 0; j < KG; ++j) {
+            const char* base = lds_w + (2 * j + h) * kHalf + f * 16;
+            u32x4 a[NP];
+#pragma unroll
+            for (int q = 0; q < NP; ++q) a[q] = *(const u32x4*)(base + q * kPiece + wave * 512);
+#pragma unroll
+            for (int t = 0; t < PT; ++t) {
+                if (!((active >> t) & 1u)) continue;
+                u32x4 b[NP];
+#pragma unroll
+                for (int q = 0; q < NP; ++q) b[q] = *(const u32x4*)(base + q * kPiece + (4 + t) * 512);
+                if constexpr (NP == 1) {
+                    mm(a[0], b[0], acc[t]);
+                } else {                                // six of the nine partial products, the smallest first
+                    mm(a[2], b[0], acc[t]);
+                    mm(a[0], b[2], acc[t]);
+                    mm(a[1], b[1], acc[t]);
+                    mm(a[1], b[0], acc[t]);
+                    mm(a[0], b[1], acc[t]);
+                    mm(a[0], b[0], acc[t]);
+                }
+            }
+        }
+    };
+
+    if (nround > 0) issue();
+    for (int r = 0; r < nround; ++r) {
+        __syncthreads();                                // nobody reads the previous round any more
+        commit(dup == 0u && 8 * (r0 + r) + 8 <= count);
+        if (r + 1 < nround) issue();
+        __syncthreads();
+        compute();
+    }
+
+    // accumulator register v holds row 8*(v/4) + 4*h + v%4 of the wavefront's tile, walk position pos0 + 32t + f
+    const int k_f = filter(row0 + f);
+    const int s_f = T.b.g * ((row0 + f) / T.b.F);
+    float* dst = out + (size_t)ks * ((size_t)P.Cout * P.L);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
+        const int fr = 8 * (v >> 2) + 4 * h + (v & 3);
+        const int k = __shfl(k_f, fr, 64), s = __shfl(s_f, fr, 64);
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            const int pos = pos0 + 32 * t + f;
+            int j = first + pos - s;                    // first <= s: j starts at first - s > -Cin
+            j += j < 0 ? P.Cin : 0;
+            j -= j >= P.Cin ? P.Cin : 0;
+            if (k >= 0 && pos < len && j < P.L) dst[(size_t)k * P.L + j] = acc[t][v];
+        }
+    }
+}
+
+// workgroups: how many to aim at, 0 for the pass on its own
+inline WeightTiling make_weight_tiling(const Problem& p, int es, int* PT, int workgroups = 0)
+{
+    WeightTiling t;
+    t.b = make_band(p);
+    t.rows = t.b.P * t.b.F;
+    t.NG = (t.rows + 127) / 128;
+    int longest = 1;
+    for (int ng = 0; ng < t.NG; ++ng) {
+        int first, len;
+        weight_walk(p, t.b, t.rows, ng, first, len);
+        longest = len > longest ? len : longest;
+    }
+    // position tiles per workgroup: the fewest planes fetched over all chunks, ties to the larger tile
+    long long best = -1;
+    for (int pt = 4; pt >= 2; --pt) {
+        const long long planes = (long long)((longest + 32 * pt - 1) / (32 * pt)) * (4 + pt);
+        if (best < 0 || planes < best) {
+            best = planes;
+            *PT = pt;
+        }
+    }
+    t.NSC = (longest + 32 * *PT - 1) / (32 * *PT);
+    t.q = column_groups(p, 16 / es);
+    const long long tiles = (long long)t.NG * t.NSC;
+    // as many slices as make `workgroups` workgroups at most, and at least four rounds per slice
+    const long long rounds = (t.q.count + 7) / 8, dw_bytes = (long long)p.Cout * p.L * 4;
+    t.eighth = (int)((rounds + 7) / 8);
+    // alone: three workgroups per CU, which hides more (752 channels: 89 us against 108 with two), or two where the slices'
+    // partial sums, written and read once each, are then a third of what the pass moves (cg = 1 at 256 channels: 42 against 46)
+    if (workgroups == 0) workgroups = 768 / tiles * dw_bytes > (20 << 20) ? 512 : 768;
+    long long ks8 = workgroups / (8 * tiles);
+    if (ks8 > t.eighth / 4) ks8 = t.eighth / 4;
+    t.KS8 = ks8 < 1 ? 1 : (int)ks8;
+    t.KS = 8 * t.KS8;
+    t.chunk = (int)(t.KS8 * tiles);
+    t.per_slice = (t.eighth + t.KS8 - 1) / t.KS8;
+    return t;
+}
+
+inline bool weight_eligible(const Problem& p, int es)
+{
+    if (!backward_weight_mfma_eligible(p) || p.HW < 16 / es) return false;
+    const Band b = make_band(p);
+    return 4ll * b.P * b.F <= 5ll * p.Cout && b.P * (long long)b.F <= (1 << 20);   // else too many empty rows
+}
+
+// planes fetched, columns included, by the per-tile kernel and by this one
+inline void weight_fetches(const Problem& p, int es, double* there, double* here)
+{
+    int pt;
+    const WeightTiling t = make_weight_tiling(p, es, &pt);
+    const bww::BwwTiling o = bww::make_tiling(p);
+    *here = (double)t.NG * t.NSC * weight_rows(pt) * p.NQ;
+    *there = (double)o.IB * o.MB * o.NSC * bww::rows_of(o.NPT) * p.NQ;
+}
+
+}  // namespace shared_bww
+
+}  // namespace scc

@@ -1,0 +1,110 @@
+// Both gradients of the layers whose tiles share their planes, in ONE launch behind the packing of the weights: the workgroups
+// of the shared grad-weight (scc_shared_bww_kernel.h) and those of the packed grad-input (scc_packed_kernel.h) are two ranges
+// of one grid.  Nothing about either computation changes (dw sums fewer slices than scc_backward_weight does).  Grad-weight
+// comes first, with one (bf16) or one and a half (binary32) workgroups per CU that stay for the whole launch; grad-input's
+// pass through what is left of the CUs, so that one range's matrix instructions run beside the other's loads and stores, and
+// both read the same eighth of the columns on an XCD, where part of dy is still on the chip for the second of them.
+// us, two launches -> one: 128 x 128 -> 512, 32x32, cg 2, co 0.33: f32 191 -> 182, bf16 79 -> 64; 128 x 256 -> 256, 16x16, cg 1: f32 74
+// -> 68, bf16 40 -> 32; 64 x 512 -> 1024, 7x7, cg 2, co 0.33 (from the per-tile kernels' merged launch): f32 58 -> 48, bf16 45 -> 33.
+#include "scc_packed_kernel.h"
+#include "scc_shared_bww_kernel.h"
+
+namespace scc {
+
+namespace {
+
+// workgroups of the grad-weight range.  256 / 384 / 512, us: the first layer above f32 184 / 182 / 184, bf16 64 / 66 / 69, the second
+// 70 / 68 / 74, 32 / 34 / 37, the third 51 / 48 / 48, 33 / 34 / 34
+constexpr int weight_workgroups(int es) { return es == 2 ? 256 : 384; }
+
+template <typename T_, int CT, int PT>
+__global__ __launch_bounds__(256, 3) void backward_shared(const T_* __restrict__ x, const T_* __restrict__ dy,
+                                                          const char* __restrict__ packed_w, T_* __restrict__ dx,
+                                                          float* __restrict__ part, Problem P, packed::Packed TI,
+                                                          shared_bww::WeightTiling TW, int nweight)
+{
+    extern __shared__ __attribute__((aligned(16))) char lds_b[];
+    const int bid = (int)blockIdx.x;
+    if (bid < nweight)
+        shared_bww::weight_body<T_, PT>(x, dy, part, P, TW, bid, lds_b);
+    else
+        packed::packed_body<T_, CT, false>(dy, packed_w, dx, P, TI, bid - nweight, lds_b);
+}
+
+template <typename T_, int CT, int PT>
+hipError_t launch_variant(const T_* x, const T_* dy, const char* packed_w, T_* dx, float* part, const Problem& p,
+                          const packed::Packed& ti, const shared_bww::WeightTiling& tw, hipStream_t st)
+{
+    constexpr int kW = shared_bww::weight_lds((int)sizeof(T_), PT), kI = packed::lds_bytes((int)sizeof(T_), CT);
+    constexpr int kMost = kI + packed::kMaxGroups * 16 * 4 > kW ? kI + packed::kMaxGroups * 16 * 4 : kW;
+    static const hipError_t allowed = hipFuncSetAttribute((const void*)backward_shared<T_, CT, PT>,
+                                                          hipFuncAttributeMaxDynamicSharedMemorySize, kMost);
+    if (allowed != hipSuccess) return allowed;
+    const int need = kI + ti.nround * 16 * ti.KG * 4, nweight = 8 * tw.chunk;
+    backward_shared<T_, CT, PT><<<dim3((unsigned)(nweight + 8 * ti.chunk)), dim3(256), need > kW ? need : kW, st>>>(
+        x, dy, packed_w, dx, part, p, ti, tw, nweight);
+    return hipGetLastError();
+}
+
+size_t partial_bytes(const Problem& p, const shared_bww::WeightTiling& t)
+{
+    return ((size_t)t.KS * p.Cout * p.L * sizeof(float) + 255) / 256 * 256;
+}
+
+}  // namespace
+
+// Taken where sharing saves enough plane fetches over the per-tile kernels of both passes (grad-weight's and grad-input's
+// together): measured on 39 layers against the merged launch of those, every one above the line gains 1.06 to 1.35 times,
+// those below 0.6 (deep layers with few columns) to 1.18; 65e6 lies between 128 x 256 -> 256 on 16x16 with cg 2 (59e6: 48 -> 51 us)
+// and 274 x 384 -> 384 on 14x14 with cg 8 (73e6, bf16: 63 -> 50).
+size_t backward_shared_workspace(const Problem& p, int es)
+{
+    const int ct = packed::tile_width<false>(p, es);
+    if (ct == 0 || !shared_bww::weight_eligible(p, es)) return 0;
+    const Band b = make_band(p);
+    double there, here, again;
+    shared_bww::weight_fetches(p, es, &there, &here);
+    double saved = there - here;
+    saved += packed::fetches_without_sharing<false>(p, b, &again);
+    for (int c0 = 0; c0 < p.Cin; c0 += 128) {
+        int first, len;
+        packed::walk_of<false>(p, b, p.Cin, c0 / 128, first, len);
+        saved -= (double)len * p.NQ;
+    }
+    if (saved < (packed::uneven(p, b) ? (es == 2 ? 30e6 : 35e6) : 65e6)) return 0;
+    int pt;
+    return partial_bytes(p, shared_bww::make_weight_tiling(p, es, &pt, weight_workgroups(es))) +
+           packed::make_packed<false>(p, es, ct).bytes;
+}
+
+template <typename T_>
+hipError_t launch_backward_shared(const T_* x, const T_* dy, const T_* w, T_* dx, float* dw, void* workspace,
+                                  const Problem& p, hipStream_t st)
+{
+    constexpr int es = (int)sizeof(T_);
+    int pt;
+    const shared_bww::WeightTiling tw = shared_bww::make_weight_tiling(p, es, &pt, weight_workgroups(es));
+    const int ct = packed::tile_width<false>(p, es);
+    if (ct == 0) return hipErrorInvalidValue;
+    const packed::Packed ti = packed::make_packed<false>(p, es, ct);
+    float* part = (float*)workspace;
+    char* packed_w = (char*)workspace + partial_bytes(p, tw);
+    hipError_t e = pack_only<T_, false>(w, packed_w, p, ct, st);
+    if (e != hipSuccess) return e;
+    auto with_ct = [&](auto c) {
+        constexpr int CT = decltype(c)::value;
+        return pt == 2   ? launch_variant<T_, CT, 2>(x, dy, packed_w, dx, part, p, ti, tw, st)
+               : pt == 3 ? launch_variant<T_, CT, 3>(x, dy, packed_w, dx, part, p, ti, tw, st)
+                         : launch_variant<T_, CT, 4>(x, dy, packed_w, dx, part, p, ti, tw, st);
+    };
+    e = ct == 4 ? with_ct(std::integral_constant<int, 4>{}) : with_ct(std::integral_constant<int, 2>{});
+    if (e != hipSuccess) return e;
+    return launch_weight_reduce(part, dw, p.Cout * p.L, tw.KS, st);
+}
+
+template hipError_t launch_backward_shared<float>(const float*, const float*, const float*, float*, float*, void*,
+                                                  const Problem&, hipStream_t);
+template hipError_t launch_backward_shared<bf16_t>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, float*, void*,
+                                                   const Problem&, hipStream_t);
+
+}  // namespace scc

@@ -42,8 +42,44 @@ def test_parity_and_repeat(dtype, shape):
     assert np.max(np.abs(got - ref)) <= 2e-5 * np.max(np.abs(ref))
     assert np.linalg.norm(got - ref) <= 4 * 2.0 ** -24 * np.sqrt(N * H * W / 16) * np.linalg.norm(ref)
     assert torch.equal(dw, S.scc_backward_weight(xd, dyd, cg, co))
-    dx, dw2 = S.scc_backward(xd, dyd, wd, cg, co)
-    assert torch.equal(dw, dw2) and torch.equal(dx, S.scc_backward_input(dyd, wd, Cin, cg, co))
     static = torch.empty_like(dw)
     S.scc_backward_weight_static(xd, dyd, cg, co, static)       # its buffer holds 8 MiB: either kernel
     assert np.max(np.abs(static.cpu().numpy() - ref)) <= 2e-5 * np.max(np.abs(ref))
+
+
+# (dtype, layer) of scc_backward with both gradients in one launch; the first two as above, then: 64-column tiles beside
+# slices of a few rounds; grad-input blocks of 16 channels in the last row group
+BOTH = [("f32", (330, 120, 500, 11, 9, 2, 0.33)), ("bf16", (100, 104, 400, 23, 22, 1, 0.3)),
+        ("f32", (64, 512, 1000, 7, 7, 2, 0.33)), ("bf16", (64, 512, 1000, 7, 7, 2, 0.33)),
+        ("f32", (40, 272, 270, 28, 29, 1, 0.5)), ("bf16", (37, 336, 330, 20, 41, 1, 0.5))]
+
+
+def backward_workspace(dtype, shape):
+    return S.load().scc_backward_workspace_bytes(*shape, 0 if dtype == "f32" else 1)
+
+
+@pytest.mark.parametrize("dtype,shape", BOTH)
+def test_layers_here_take_one_launch(dtype, shape):
+    # its workspace holds the packed weights as well: 16-position groups x 128 rows x 16 positions x (3 pieces or 1) of 2 bytes
+    Cin, Cout = shape[1], shape[2]
+    assert backward_workspace(dtype, shape) >= 8 * 4 * Cout * (Cin // shape[5]) + Cin * Cin // shape[5] * (6 if dtype == "f32" else 2)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,shape", BOTH)
+def test_both_gradients_in_one_launch(dtype, shape):
+    N, Cin, Cout, H, W, cg, co = shape
+    layer = Wk.Layer("both", 9, N=N, Cin=Cin, Cout=Cout, H=H, W=W, cg=cg, co=co)
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    xd, wd, dyd = (torch.from_numpy(a).to(td).cuda() for a in Wk.make_inputs(layer))
+    x, w, dy = (t.float().cpu().numpy() for t in (xd, wd, dyd))
+    dx, dw = S.scc_backward(xd, dyd, wd, cg, co)
+    ref_dx, ref_dw = O.backward_input(dy, w, Cin, cg, co), O.backward_weight(x, dy, cg, co)
+    assert np.max(np.abs(dx.float().cpu().numpy() - ref_dx)) <= (2e-5 if dtype == "f32" else 1e-2) * np.max(np.abs(ref_dx))
+    assert np.max(np.abs(dw.cpu().numpy() - ref_dw)) <= 2e-5 * np.max(np.abs(ref_dw))
+    dx2, dw2 = S.scc_backward(xd, dyd, wd, cg, co)
+    assert torch.equal(dx, dx2) and torch.equal(dw, dw2)
+    # the same operands one float off their 16-byte alignment: same kernels, same bits
+    shifted = [torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape).copy_(t) for t in (xd, dyd, wd)]
+    dx3, dw3 = S.scc_backward(*shifted, cg, co)
+    assert torch.equal(dx, dx3) and torch.equal(dw, dw3)
