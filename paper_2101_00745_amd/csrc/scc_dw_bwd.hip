@@ -13,6 +13,8 @@
 #include "scc_common.h"
 #include "scc_dw_strip.h"
 
+#include <type_traits>
+
 namespace scc {
 
 namespace {
@@ -54,14 +56,14 @@ __global__ __launch_bounds__(256) void depthwise3x3_backward_input_gather(const 
 //   dx[2m  ][2q  ] = k11*g[m][q]                      dx[2m  ][2q+1] = k10*g[m][q+1] + k12*g[m][q]
 //   dx[2m+1][2q  ] = k01*g[m+1][q] + k21*g[m][q]      dx[2m+1][2q+1] = k00*g[m+1][q+1] + k02*g[m+1][q] + k20*g[m][q+1] + k22*g[m][q]
 template <typename T_>
-__global__ __launch_bounds__(256) void depthwise3x3_backward_input_s2(const T_* __restrict__ dz, const T_* __restrict__ kdw,
-                                                                      T_* __restrict__ dx, int C, DwGeom G, uint32_t items)
+__device__ __forceinline__ void input_s2_body(const T_* __restrict__ dz, const T_* __restrict__ kdw, T_* __restrict__ dx, int C,
+                                              const DwGeom& G, uint32_t items, uint32_t bid, uint32_t blocks)
 {
     typedef T_ tvec __attribute__((ext_vector_type(4)));
     typedef T_ tvec2 __attribute__((ext_vector_type(2)));
     const uint32_t W2 = G.Wo / 2;
     const size_t HWi = (size_t)G.H * G.W, HWo = (size_t)G.Ho * G.Wo;
-    for (uint32_t e = blockIdx.x * 256u + threadIdx.x; e < items; e += gridDim.x * 256u) {
+    for (uint32_t e = bid * 256u + threadIdx.x; e < items; e += blocks * 256u) {
         const int q0 = (int)(e % W2) * 2;
         uint32_t t = e / W2;
         const int m = (int)(t % (uint32_t)G.Ho);
@@ -90,21 +92,31 @@ __global__ __launch_bounds__(256) void depthwise3x3_backward_input_s2(const T_* 
     }
 }
 
+template <typename T_>
+__global__ __launch_bounds__(256) void depthwise3x3_backward_input_s2(const T_* __restrict__ dz, const T_* __restrict__ kdw,
+                                                                      T_* __restrict__ dx, int C, DwGeom G, uint32_t items)
+{
+    input_s2_body<T_>(dz, kdw, dx, C, G, items, blockIdx.x, gridDim.x);
+}
+
 // ---- grad-filter ----------------------------------------------------------------------------------------------
 constexpr int kDkThreads = 256;
 
-// the workgroup's nine sums: threads -> LDS -> thread t < 9 adds them in thread order
+// the workgroup's nine sums: a tree over the lanes of each wavefront, then thread t < 9 adds the four wavefronts in order.
+// (One thread per sum adding 256 values from LDS one after the other was half of the kernel on small maps.)
 __device__ __forceinline__ void reduce_nine(const float (&s)[9], float* out9)
 {
-    __shared__ float part[9][kDkThreads];
+    __shared__ float part[kDkThreads / 64][9];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) part[t][threadIdx.x] = s[t];
-    __syncthreads();
-    if (threadIdx.x < 9) {
-        float acc = 0.f;
-        for (int u = 0; u < kDkThreads; ++u) acc += part[threadIdx.x][u];
-        out9[threadIdx.x] = acc;
+    for (int t = 0; t < 9; ++t) {
+        float v = s[t];
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][t] = v;
     }
+    __syncthreads();
+    if (threadIdx.x < 9)
+        out9[threadIdx.x] = ((part[0][threadIdx.x] + part[1][threadIdx.x]) + part[2][threadIdx.x]) + part[3][threadIdx.x];
 }
 
 // On strips (stride S = 1 or 2, output rows of whole column quads, input maps of exactly S times the output size,
@@ -112,14 +124,12 @@ __device__ __forceinline__ void reduce_nine(const float (&s)[9], float* out9)
 // S*(RB-1)+3 rows of x once (dw::strip_row) and adds their products to its nine sums.
 // Workgroup (a, slice) walks the strips of channel a in samples [slice*per, slice*per + per).
 template <typename T_, int S, int RB>
-__global__ __launch_bounds__(kDkThreads) void depthwise3x3_backward_filter_strips(const T_* __restrict__ x,
-                                                                                  const T_* __restrict__ dz,
-                                                                                  float* __restrict__ part, int N, int C,
-                                                                                  DwGeom G, int per)
+__device__ __forceinline__ void filter_strips_body(const T_* __restrict__ x, const T_* __restrict__ dz,
+                                                   float* __restrict__ part, int N, int C, const DwGeom& G, int per, int a,
+                                                   int slice)
 {
     typedef T_ tvec __attribute__((ext_vector_type(4)));
     constexpr int NR = S * (RB - 1) + 3;
-    const int a = blockIdx.x, slice = blockIdx.y;
     const int n0 = slice * per, n1 = n0 + per < N ? n0 + per : N;
     const uint32_t W4 = G.Wo / 4, SB = G.Ho / RB, spp = W4 * SB;             // strips per plane
     const uint32_t items = (uint32_t)(n1 > n0 ? n1 - n0 : 0) * spp;
@@ -164,6 +174,33 @@ __global__ __launch_bounds__(kDkThreads) void depthwise3x3_backward_filter_strip
     reduce_nine(s, part + ((size_t)slice * C + a) * 9);
 }
 
+template <typename T_, int S, int RB>
+__global__ __launch_bounds__(kDkThreads) void depthwise3x3_backward_filter_strips(const T_* __restrict__ x,
+                                                                                  const T_* __restrict__ dz,
+                                                                                  float* __restrict__ part, int N, int C,
+                                                                                  DwGeom G, int per)
+{
+    filter_strips_body<T_, S, RB>(x, dz, part, N, C, G, per, (int)blockIdx.x, (int)blockIdx.y);
+}
+
+// Both gradients in one launch where both run on strips: the filter's workgroups (channel fastest) are the first range of the
+// grid, grad-input's the second.  Neither computation changes; small maps, whose kernels take about as long as a launch, gain
+// most (13-block stack at batch 128, training step: kernels 810 -> 737 us with the sums and slices above, 11 of 13 blocks take it).
+template <typename T_, int S, int RB, int RBX>
+__global__ __launch_bounds__(256) void depthwise3x3_backward_strips(const T_* __restrict__ x, const T_* __restrict__ kdw,
+                                                                    const T_* __restrict__ dz, T_* __restrict__ dx,
+                                                                    float* __restrict__ part, int N, int C, DwGeom G, int per,
+                                                                    uint32_t nfilter, long long items)
+{
+    const uint32_t bid = blockIdx.x;
+    if (bid < nfilter)
+        filter_strips_body<T_, S, RB>(x, dz, part, N, C, G, per, (int)(bid % (uint32_t)C), (int)(bid / (uint32_t)C));
+    else if constexpr (S == 1)
+        dw::strips_body<T_, 1, RBX>(dz, kdw, dx, C, G, items, 1, bid - nfilter, gridDim.x - nfilter);
+    else
+        input_s2_body<T_>(dz, kdw, dx, C, G, (uint32_t)items, bid - nfilter, gridDim.x - nfilter);
+}
+
 // Any stride and map size: a thread takes output pixels one by one.
 template <typename T_>
 __global__ __launch_bounds__(kDkThreads) void depthwise3x3_backward_filter_generic(const T_* __restrict__ x,
@@ -205,14 +242,29 @@ __global__ __launch_bounds__(256) void depthwise3x3_filter_reduce(const float* _
     const int e = blockIdx.x * 256 + threadIdx.x;
     if (e >= count) return;
     float s = 0.f;
-    for (int sl = 0; sl < slices; ++sl) s += part[(size_t)sl * count + e];
+    int sl = 0;
+    for (; sl + 8 <= slices; sl += 8) {          // 8 loads in flight, added in order
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = part[(size_t)(sl + u) * count + e];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; sl < slices; ++sl) s += part[(size_t)sl * count + e];
     dk[e] = s;
 }
 
-// slices of the samples per channel: about 1024 workgroups in all, at least one sample per slice, at most 65535
-int filter_slices(int N, int C)
+// slices of the samples per channel: about 1024 workgroups in all, at least one sample for each and, on strips, one strip per
+// thread; at most 65535.  Maps of 4x4 at batch 128 have 128 strips per channel: with two slices three quarters of the
+// threads had none and the slices' sums took another launch (512 channels: 10.4 + 3.9 us, 9.6 with one).
+int filter_slices(int N, int C, const DwGeom& g)
 {
     int sl = (1024 + C - 1) / C;
+    if ((g.s == 1 || g.s == 2) && g.Wo % 4 == 0 && g.H == g.s * g.Ho && g.W == g.s * g.Wo) {
+        const int rb = g.Ho % 4 == 0 ? 4 : g.Ho % 2 == 0 ? 2 : 1;
+        const long long full = ((long long)N * (g.Wo / 4) * (g.Ho / rb) + kDkThreads - 1) / kDkThreads;
+        if (sl > full) sl = (int)full;
+    }
     if (sl > N) sl = N;
     if (sl > 65535) sl = 65535;
     return sl < 1 ? 1 : sl;
@@ -231,11 +283,45 @@ void launch_filter_strips(const T* x, const T* dz, float* part, int N, int C, co
         depthwise3x3_backward_filter_strips<T, S, 1><<<grid, block, 0, st>>>(x, dz, part, N, C, g, per);
 }
 
+// One launch for both gradients; false where the layer does not run on strips throughout.
+template <typename T, int S>
+bool launch_both_strips(const T* x, const T* kdw, const T* dz, T* dx, float* part, int N, int C, const DwGeom& g, int slices,
+                        int per, hipStream_t st)
+{
+    long long items, blocks;
+    int rbx = dw::strip_rows(N, C, g, &items, &blocks);
+    if (S == 2) {
+        items = (long long)N * C * g.Ho * (g.Wo / 2);
+        blocks = (items + 255) / 256;
+        if (blocks > (1ll << 20)) blocks = 1ll << 20;
+        rbx = 1;                                              // no strips on that side
+    }
+    const long long nfilter = (long long)C * slices;
+    if (items >= (1ll << 31) || nfilter + blocks >= (1ll << 31)) return false;
+    const int rb = g.Ho % 4 == 0 ? 4 : g.Ho % 2 == 0 ? 2 : 1;
+    auto go = [&](auto r, auto q) {
+        depthwise3x3_backward_strips<T, S, decltype(r)::value, decltype(q)::value>
+            <<<dim3((unsigned)(nfilter + blocks)), dim3(kDkThreads), 0, st>>>(x, kdw, dz, dx, part, N, C, g, per,
+                                                                              (uint32_t)nfilter, items);
+    };
+    auto with_rb = [&](auto r) {                              // rbx divides rb
+        constexpr int RB = decltype(r)::value;
+        if constexpr (S == 1 && RB >= 4)
+            if (rbx == 4) return go(r, std::integral_constant<int, 4>{});
+        if constexpr (S == 1 && RB >= 2)
+            if (rbx == 2) return go(r, std::integral_constant<int, 2>{});
+        go(r, std::integral_constant<int, 1>{});
+    };
+    rb == 4 ? with_rb(std::integral_constant<int, 4>{})
+    : rb == 2 ? with_rb(std::integral_constant<int, 2>{}) : with_rb(std::integral_constant<int, 1>{});
+    return true;
+}
+
 }  // namespace
 
-size_t depthwise3x3_backward_workspace(int N, int C, const DwGeom&)
+size_t depthwise3x3_backward_workspace(int N, int C, const DwGeom& g)
 {
-    const int slices = filter_slices(N, C);
+    const int slices = filter_slices(N, C, g);
     return slices > 1 ? (size_t)slices * C * 9 * sizeof(float) : 0;
 }
 
@@ -243,7 +329,17 @@ template <typename T>
 hipError_t launch_depthwise3x3_backward(const T* x, const T* kdw, const T* dz, T* dx, float* dk, float* workspace, int N,
                                         int C, const DwGeom& g, hipStream_t st)
 {
-    if (dx) {
+    const int slices = filter_slices(N, C, g);
+    const int per = (N + slices - 1) / slices;
+    float* part = slices > 1 ? workspace : dk;
+    const bool strips = (g.s == 1 || g.s == 2) && g.Wo % 4 == 0 && g.H == g.s * g.Ho && g.W == g.s * g.Wo &&
+                        (((uintptr_t)x | (uintptr_t)dz) & (4 * sizeof(T) - 1)) == 0 &&
+                        (long long)per * g.Ho * (g.Wo / 4) < (1ll << 31);
+    bool both = false;
+    if (dx && dk && strips && ((uintptr_t)dx & (4 * sizeof(T) - 1)) == 0)
+        both = g.s == 1 ? launch_both_strips<T, 1>(x, kdw, dz, dx, part, N, C, g, slices, per, st)
+                        : launch_both_strips<T, 2>(x, kdw, dz, dx, part, N, C, g, slices, per, st);
+    if (dx && !both) {
         if (g.s == 1) {
             // the stage applied to dz (an Ho x Wo = H x W map) with the filters turned by 180 degrees
             DwGeom gz = g;
@@ -268,13 +364,9 @@ hipError_t launch_depthwise3x3_backward(const T* x, const T* kdw, const T* dz, T
         }
     }
     if (dk) {
-        const int slices = filter_slices(N, C);
-        const int per = (N + slices - 1) / slices;
-        float* part = slices > 1 ? workspace : dk;
-        const bool strips = (g.s == 1 || g.s == 2) && g.Wo % 4 == 0 && g.H == g.s * g.Ho && g.W == g.s * g.Wo &&
-                            (((uintptr_t)x | (uintptr_t)dz) & (4 * sizeof(T) - 1)) == 0 &&
-                            (long long)per * g.Ho * (g.Wo / 4) < (1ll << 31);
-        if (strips && g.s == 1)
+        if (both)
+            ;                                                 // launched above
+        else if (strips && g.s == 1)
             launch_filter_strips<T, 1>(x, dz, part, N, C, g, slices, per, st);
         else if (strips)
             launch_filter_strips<T, 2>(x, dz, part, N, C, g, slices, per, st);

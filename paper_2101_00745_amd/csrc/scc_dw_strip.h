@@ -112,6 +112,62 @@ __device__ __forceinline__ uint32_t strip_rowmask(int r0, int Ho)
     return m;
 }
 
+// Stand-alone depthwise stage on strips (see scc_dw_strip.h): stride 1 or 2, input maps of exactly S times the
+// output size, RB dividing the output rows, output rows of whole quads of pixels, tensors aligned to 4 values.
+// Workgroup `bid` of `blocks`.
+template <typename T_, int S, int RB>
+__device__ __forceinline__ void strips_body(const T_* __restrict__ x, const T_* __restrict__ kdw, T_* __restrict__ z, int C,
+                                            const DwGeom& G, long long items, int flip, uint32_t bid, uint32_t blocks)
+{
+    typedef T_ tvec __attribute__((ext_vector_type(4)));
+    const size_t HWi = (size_t)G.H * G.W, HWo = (size_t)G.Ho * G.Wo;
+    const uint32_t W4 = G.Wo / 4, SB = G.Ho / RB;
+    // 32-bit index arithmetic (the launcher sends fewer than 2^31 strips here): 64-bit divisions in every lane
+    // cost more than the stencil itself.  All lanes of a wavefront run the same number of trips (the strip
+    // routine shuffles between lanes); lanes past the end compute strip 0 again and store nothing.
+    const uint32_t lane = threadIdx.x & 63;
+    for (uint32_t e0 = bid * 256u; e0 < (uint32_t)items; e0 += blocks * 256u) {
+        const uint32_t ee = e0 + threadIdx.x;
+        const bool live = ee < (uint32_t)items;
+        const uint32_t e = live ? ee : 0;
+        const int cw = (int)(e % W4) * 4;
+        uint32_t t = e / W4;
+        const int r0 = (int)(t % SB) * RB;
+        t /= SB;                          // t = n*C + a
+        const int a = (int)(t % (uint32_t)C);
+        float k[9];
+        load_taps(kdw, a, flip != 0, k);
+        const uint32_t rowmask = strip_rowmask<S, RB>(r0, G.Ho);
+        float out[RB][4];
+        // consecutive strips of a row are consecutive lanes; the first and last lane of the wavefront and the
+        // last live one have no neighbour to ask
+        dw_strip<S, RB>(x + t * HWi + (size_t)(S * r0) * G.W + S * cw, G.W, k, rowmask, cw > 0, cw + 4 < G.Wo, lane == 0,
+                        lane == 63 || ee + 1 >= (uint32_t)items, out);
+        if (!live) continue;
+        T_* zo = z + t * HWo + (size_t)r0 * G.Wo + cw;
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) {
+            tvec o;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) o[i] = from_f32<T_>(out[rr][i]);
+            __builtin_nontemporal_store(o, (tvec*)(zo + rr * G.Wo));
+        }
+    }
+}
+
+// Rows per thread of the stage on strips, its strips and workgroups: taller strips read fewer halo rows per output; small
+// problems take shorter ones to have enough threads.
+inline int strip_rows(int N, int C, const DwGeom& g, long long* items, long long* blocks)
+{
+    const long long w4 = g.Wo / 4;
+    int rb = g.Ho % 4 == 0 ? 4 : g.Ho % 2 == 0 ? 2 : 1;
+    while (rb > 1 && (long long)N * C * (g.Ho / rb) * w4 < 256 * 1024) rb /= 2;
+    *items = (long long)N * C * (g.Ho / rb) * w4;
+    *blocks = (*items + 255) / 256;
+    if (*blocks > (1ll << 20)) *blocks = 1ll << 20;   // the kernel strides over what is left
+    return rb;
+}
+
 }  // namespace dw
 
 }  // namespace scc

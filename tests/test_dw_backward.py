@@ -34,3 +34,22 @@ def test_host_checks():
     assert lib.scc_dw_backward(p, p, p, None, p, p, p, *shape, 0x1000, need, None) == -1
     bad = (3, 32, 40, 9, 7, 0, 4, 0.25, 0)
     assert lib.scc_dw_backward(p, p, p, p, p, p, p, *bad, 0x1000, need, None) == -2 and lib.scc_dw_backward_workspace_bytes(*bad) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N,C,H,W,s", [(1, 3, 4, 4, 1), (129, 5, 4, 4, 1), (70, 9, 6, 8, 1), (33, 2, 5, 12, 1), (40, 7, 32, 32, 1),
+                                       (65, 4, 8, 8, 2), (3, 6, 10, 24, 2), (257, 2, 4, 8, 2)])
+def test_depthwise_gradients_in_one_launch_are_those_of_two(N, C, H, W, s, dtype):
+    """Strips of 1, 2 and 4 rows, strips per channel below, at and above a workgroup's 256 threads, both strides."""
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x, kdw, dz = (torch.randn(*d, generator=gen, device="cuda").to(dtype) for d in
+                  ((N, C, H, W), (C, 3, 3), (N, C, (H - 1) // s + 1, (W - 1) // s + 1)))
+    dx, dk = S.scc_depthwise3x3_backward(x, kdw, dz, s)
+    assert torch.equal(dx, S.scc_depthwise3x3_backward(x, kdw, dz, s, need_dk=False)[0])
+    assert torch.equal(dk, S.scc_depthwise3x3_backward(x, kdw, dz, s, need_dx=False)[1])
+    import numpy as np
+    from oracle import scc_oracle as O
+    ref_dx, ref_dk = O.depthwise3x3_backward(*(t.float().cpu().numpy() for t in (x, kdw, dz)), s)
+    assert np.max(np.abs(dx.float().cpu().numpy() - ref_dx)) <= (2e-5 if dtype == torch.float32 else 1e-2) * np.max(np.abs(ref_dx))
+    assert np.max(np.abs(dk.cpu().numpy() - ref_dk)) <= 2e-5 * np.max(np.abs(ref_dk))
