@@ -79,7 +79,7 @@ typedef enum {
 } scc_status;
 
 /* Size of the device buffer the library itself holds, per GPU, for scc_backward_weight_static. */
-#define SCC_STATIC_SCRATCH_BYTES (8u << 20)
+#define SCC_STATIC_SCRATCH_BYTES (32u << 20)
 
 /*
  * Window arithmetic of Algorithm 1, host only (no GPU call).

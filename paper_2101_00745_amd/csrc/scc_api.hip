@@ -460,9 +460,7 @@ int scc_backward_weight_static(const void* x, const void* dy, void* dw, int N, i
     const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    // where the shared kernel's partial sums do not fit the buffer, the other kernel's do, and it runs as it always has
-    bool shared = weight_shared(p, dtype);
-    if (shared && weight_workspace(p, dtype, true) > (size_t)SCC_STATIC_SCRATCH_BYTES) shared = false;
+    const bool shared = weight_shared(p, dtype);
     const size_t need = weight_workspace(p, dtype, shared);
     if (need > (size_t)SCC_STATIC_SCRATCH_BYTES) return SCC_ERR_SCRATCH;
     void* ptr = nullptr;

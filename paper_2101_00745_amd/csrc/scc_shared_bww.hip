@@ -34,7 +34,7 @@ hipError_t launch_tile(const T_* x, const T_* dy, float* out, const Problem& p, 
 // (50e6 fetches, not taken); 882 x 256 -> 128, cg 4, co 0: 70 -> 77 (0.75 times the fetches, not taken).
 bool backward_weight_shared_preferred(const Problem& p, int es)
 {
-    if (!weight_eligible(p, es)) return false;
+    if (!weight_eligible(p, es) || backward_weight_shared_workspace(p, es) > (size_t)SCC_STATIC_SCRATCH_BYTES) return false;
     double there, here;
     weight_fetches(p, es, &there, &here);
     return there >= (es == 2 ? 105e6 : 90e6) && there >= 1.4 * here;

@@ -17,6 +17,7 @@
 // A wavefront's tiles are its own, so there is no sum inside a workgroup; the slices' partial sums go to the workspace in the
 // layout of dw and launch_weight_reduce adds them in slice order: no atomics, bitwise reproducible.
 #pragma once
+#include "scc.h"
 #include "scc_band.h"
 #include "scc_common.h"
 #include "scc_mfma_bww_kernel.h"
@@ -277,6 +278,8 @@ inline WeightTiling make_weight_tiling(const Problem& p, int es, int* PT, int wo
     // partial sums, written and read once each, are then a third of what the pass moves (cg = 1 at 256 channels: 42 against 46)
     if (workgroups == 0) workgroups = 768 / tiles * dw_bytes > (20 << 20) ? 512 : 768;
     long long ks8 = workgroups / (8 * tiles);
+    // scc_backward_weight_static runs the same kernels on the library's own buffer
+    if (ks8 * 8 * dw_bytes > (long long)SCC_STATIC_SCRATCH_BYTES) ks8 = (long long)SCC_STATIC_SCRATCH_BYTES / (8 * dw_bytes);
     if (ks8 > t.eighth / 4) ks8 = t.eighth / 4;
     t.KS8 = ks8 < 1 ? 1 : (int)ks8;
     t.KS = 8 * t.KS8;

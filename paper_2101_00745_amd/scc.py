@@ -22,7 +22,7 @@ SYMBOLS = ("scc_window_params", "scc_forward", "scc_forward_workspace_bytes", "s
            "scc_depthwise3x3_out", "scc_depthwise3x3_forward", "scc_depthwise3x3_backward_workspace_bytes",
            "scc_depthwise3x3_backward", "scc_dw_forward_workspace_bytes", "scc_dw_forward_fusable", "scc_dw_forward",
            "scc_dw_backward_workspace_bytes", "scc_dw_backward", "scc_status_string")
-STATIC_SCRATCH_BYTES = 8 << 20    # SCC_STATIC_SCRATCH_BYTES of include/scc.h
+STATIC_SCRATCH_BYTES = 32 << 20    # SCC_STATIC_SCRATCH_BYTES of include/scc.h
 
 _lib = None
 

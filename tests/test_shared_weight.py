@@ -26,7 +26,7 @@ def workspace(dtype, shape):
 @pytest.mark.parametrize("dtype,shape", CASES)
 def test_layers_here_take_the_path(dtype, shape):
     # the per-tile kernel cuts the columns into at most 256 slices of all tiles and asks for 4 MiB at most
-    assert workspace(dtype, shape) > 4 << 20
+    assert 4 << 20 < workspace(dtype, shape) <= S.scc.STATIC_SCRATCH_BYTES
 
 
 @pytest.mark.gpu
@@ -43,8 +43,8 @@ def test_parity_and_repeat(dtype, shape):
     assert np.linalg.norm(got - ref) <= 4 * 2.0 ** -24 * np.sqrt(N * H * W / 16) * np.linalg.norm(ref)
     assert torch.equal(dw, S.scc_backward_weight(xd, dyd, cg, co))
     static = torch.empty_like(dw)
-    S.scc_backward_weight_static(xd, dyd, cg, co, static)       # its buffer holds 8 MiB: either kernel
-    assert np.max(np.abs(static.cpu().numpy() - ref)) <= 2e-5 * np.max(np.abs(ref))
+    S.scc_backward_weight_static(xd, dyd, cg, co, static)       # the same kernels on the library's own buffer
+    assert torch.equal(dw, static)
 
 
 # (dtype, layer) of scc_backward with both gradients in one launch; the first two as above, then: 64-column tiles beside
