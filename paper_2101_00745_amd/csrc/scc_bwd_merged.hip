@@ -19,7 +19,7 @@ namespace scc {
 
 namespace {
 
-template <typename T_, int CT, int S, int NPT>
+template <typename T_, int CT, int S, int NPT, bool SMALL>
 __global__ __launch_bounds__(256) void backward_merged(const T_* __restrict__ x, const T_* __restrict__ dy,
                                                        const T_* __restrict__ w, T_* __restrict__ dx,
                                                        float* __restrict__ out, Problem P, bwi::BwiTiling TI,
@@ -30,12 +30,12 @@ __global__ __launch_bounds__(256) void backward_merged(const T_* __restrict__ x,
     extern __shared__ __attribute__((aligned(16))) float lds_dyn[];
     const int bid = (int)blockIdx.x;
     if (bid < nbww)
-        bww::backward_weight_body<T_, NPT, true>(x, dy, out, P, TW, bid);
+        bww::backward_weight_body<T_, NPT, true, SMALL>(x, dy, out, P, TW, bid);
     else
         bwi::backward_input_body<T_, CT, 8, S, 4, true>(dy, w, dx, P, TI, bid - nbww, lds_dyn);
 }
 
-template <typename T_, int CT, int S, int NPT>
+template <typename T_, int CT, int S, int NPT, bool SMALL = false>
 hipError_t launch_variant(const T_* x, const T_* dy, const T_* w, T_* dx, float* out, const Problem& p,
                           const bwi::BwiTiling& ti, long long nbwi, const bww::BwwTiling& tw, hipStream_t st)
 {
@@ -43,12 +43,12 @@ hipError_t launch_variant(const T_* x, const T_* dy, const T_* w, T_* dx, float*
     constexpr size_t kLds = kNeedW > kNeedI ? kNeedW : kNeedI;
     if (kLds > 48 * 1024) {
         // more than 64 KiB of LDS per workgroup has to be allowed once
-        static const hipError_t allowed = hipFuncSetAttribute((const void*)backward_merged<T_, CT, S, NPT>,
+        static const hipError_t allowed = hipFuncSetAttribute((const void*)backward_merged<T_, CT, S, NPT, SMALL>,
                                                               hipFuncAttributeMaxDynamicSharedMemorySize, (int)kLds);
         if (allowed != hipSuccess) return allowed;
     }
     const long long nbww = (long long)8 * tw.chunk;
-    backward_merged<T_, CT, S, NPT><<<dim3((unsigned)(nbww + nbwi)), dim3(256), kLds, st>>>(x, dy, w, dx, out, p, ti,
+    backward_merged<T_, CT, S, NPT, SMALL><<<dim3((unsigned)(nbww + nbwi)), dim3(256), kLds, st>>>(x, dy, w, dx, out, p, ti,
                                                                                                tw, (int)nbww);
     return hipGetLastError();
 }
@@ -78,7 +78,9 @@ hipError_t launch_backward_merged(const T_* x, const T_* dy, const T_* w, T_* dx
     bwi::select_backward_input<T_>(p, [&](auto ct, auto s, auto wpb, const bwi::BwiTiling& ti, long long nbwi) {
         constexpr int CT = decltype(ct)::value, S = decltype(s)::value, WPB = decltype(wpb)::value;
         if constexpr (WPB == 4) {
-            if (tw.NPT == 1)
+            if (sizeof(T_) == 4 && p.NQ < 256)
+                e = launch_variant<T_, CT, S, 1, true>(x, dy, w, dx, out, p, ti, nbwi, tw, st);
+            else if (tw.NPT == 1)
                 e = launch_variant<T_, CT, S, 1>(x, dy, w, dx, out, p, ti, nbwi, tw, st);
             else if (tw.NPT == 2)
                 e = launch_variant<T_, CT, S, 2>(x, dy, w, dx, out, p, ti, nbwi, tw, st);

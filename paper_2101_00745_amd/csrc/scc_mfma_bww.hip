@@ -29,12 +29,12 @@ namespace {
 
 using namespace bww;
 
-template <typename T_, int kPosTiles, bool VEC>
+template <typename T_, int kPosTiles, bool VEC, bool SMALL>
 __global__ __launch_bounds__(kWaves * 64) void backward_weight_mfma32(const T_* __restrict__ x,
                                                                       const T_* __restrict__ dy,
                                                                       float* __restrict__ out, Problem P, BwwTiling T)
 {
-    backward_weight_body<T_, kPosTiles, VEC>(x, dy, out, P, T, (int)blockIdx.x);
+    backward_weight_body<T_, kPosTiles, VEC, SMALL>(x, dy, out, P, T, (int)blockIdx.x);
 }
 
 // dw[e] = sum over K-splits of part[ks][e].  A workgroup owns 64 weights; its 4 wavefronts take the
@@ -63,19 +63,19 @@ __global__ __launch_bounds__(256) void backward_weight_reduce(const float* __res
     if (w == 0 && e < count) dw[e] = ((sums[0][el] + sums[1][el]) + sums[2][el]) + sums[3][el];
 }
 
-template <typename T_, int NPT, bool VEC>
+template <typename T_, int NPT, bool VEC, bool SMALL = false>
 hipError_t launch_tile(dim3 grid, dim3 block, hipStream_t st, const T_* x, const T_* dy, float* out, const Problem& p,
                        const BwwTiling& t)
 {
     constexpr size_t kLds = lds_bytes_of(NPT, (int)sizeof(T_));
     if (kLds > 64 * 1024) {
         // more than 64 KiB of LDS per workgroup has to be allowed once (per process: the library drives one GPU)
-        static const hipError_t allowed = hipFuncSetAttribute((const void*)backward_weight_mfma32<T_, NPT, VEC>,
+        static const hipError_t allowed = hipFuncSetAttribute((const void*)backward_weight_mfma32<T_, NPT, VEC, SMALL>,
                                                               hipFuncAttributeMaxDynamicSharedMemorySize,
                                                               (int)kLds);
         if (allowed != hipSuccess) return allowed;
     }
-    backward_weight_mfma32<T_, NPT, VEC><<<grid, block, kLds, st>>>(x, dy, out, p, t);
+    backward_weight_mfma32<T_, NPT, VEC, SMALL><<<grid, block, kLds, st>>>(x, dy, out, p, t);
     return hipGetLastError();
 }
 
@@ -87,10 +87,13 @@ hipError_t launch_weight_reduce(const float* part, float* dw, int count, int KS,
     return hipGetLastError();
 }
 
+// From 64 columns on: the any-shape kernel takes a wavefront per weight, which is as fast for 32 filters x 16 weights (one 8x8
+// image: scc_backward 8 us with it in a launch of its own, 6 in the merged launch) and far slower for large layers on few
+// columns (16 x 1024 -> 1024 on 2x2, cg 2: 304 -> 17 us; 4 x 512 -> 1024 on 7x7: 86 -> 17).
 bool backward_weight_mfma_eligible(const Problem& p)
 {
     const long long rows = p.Cin > p.Cout ? p.Cin : p.Cout;
-    return p.L >= 8 && p.NQ >= 256 && p.Cout >= 8 && p.Cin < 65536 &&
+    return p.L >= 8 && p.NQ >= 64 && p.Cout >= 8 && p.Cin < 65536 &&
            (long long)p.NQ * rows * 4 < (1ll << 32) && (long long)p.Cout * p.L * 4 < (1ll << 31);
 }
 
@@ -110,7 +113,10 @@ hipError_t launch_backward_weight_mfma(const T_* x, const T_* dy, float* dw, flo
     const dim3 grid((unsigned)blocks), block(kWaves * 64);
     hipError_t e = hipSuccess;
     const bool vec = p.HW >= 4;
-    if (t.NPT == 1)
+    if (sizeof(T_) == 4 && p.NQ < 256)
+        e = vec ? launch_tile<T_, 1, true, true>(grid, block, st, x, dy, out, p, t)
+                : launch_tile<T_, 1, false, true>(grid, block, st, x, dy, out, p, t);
+    else if (t.NPT == 1)
         e = vec ? launch_tile<T_, 1, true>(grid, block, st, x, dy, out, p, t)
                 : launch_tile<T_, 1, false>(grid, block, st, x, dy, out, p, t);
     else if (t.NPT == 2)

@@ -78,7 +78,7 @@ __device__ __forceinline__ void tile_filter(const BwwTiling& T, const Problem& P
 // VEC: planes of at least 4 pixels: a lane's 4 columns are a group of consecutive pixels of one sample
 // (column_groups in scc_common.h) and one vector load; the pixels a sample's last group shares with the one before it
 // are zeroed when they are parked.  Otherwise the columns are 4 scalar loads with their own addresses.
-template <typename T_, int kPosTiles, bool VEC>
+template <typename T_, int kPosTiles, bool VEC, bool SMALL = false>
 __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, const T_* __restrict__ dy,
                                                      float* __restrict__ out, const Problem& P, const BwwTiling& T,
                                                      const int bid)
@@ -186,11 +186,18 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
     const char* bb = (const char*)x;
     char* stage = (char*)lds + wave * (kRows * kRowB);
 
-    f32x16 acc[kPosTiles];
+    // One position tile: a chunk's matrix instructions go round independent accumulators, summed as a tree behind the K loop.
+    // On layers with a few hundred columns (SMALL: fewer than 256) one chain would round more than the lane sums of the any-shape
+    // kernel, which such layers took before: 2-norm against binary64 at 196 columns, binary32, that kernel 0.76e-7, one chain
+    // 1.3e-7, four 0.86e-7, eight 0.78e-7.
+    constexpr int NA = kPosTiles == 1 ? (ES == 2 ? 2 : SMALL ? 8 : 4) : 1;
+    f32x16 accs[NA][kPosTiles];
 #pragma unroll
-    for (int c = 0; c < kPosTiles; ++c)
+    for (int n = 0; n < NA; ++n)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
+        for (int c = 0; c < kPosTiles; ++c)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) accs[n][c][v] = 0.f;
 
     // global -> registers: 4 columns of each of this lane's rows; `rin` gets one bit per column that exists
     auto load_chunk = [&](ldvec (&r)[kRows / 8], uint32_t& rin) {
@@ -257,7 +264,7 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
 #pragma unroll
                 for (int c = 0; c < kPosTiles; ++c) {
                     const bf16x8 bv = __builtin_bit_cast(bf16x8, *(const u16x8*)(stage + (32 + 32 * c + f) * kRowB + cb));
-                    acc[c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, acc[c], 0, 0, 0);
+                    accs[s % NA][c] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, bv, accs[s % NA][c], 0, 0, 0);
                 }
             }
         } else {
@@ -272,7 +279,8 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
                 for (int e = 0; e < 4; ++e)
 #pragma unroll
                     for (int c = 0; c < kPosTiles; ++c)
-                        acc[c] = __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], bv[c][e], acc[c], 0, 0, 0);
+                        accs[(e + 4 * s) % NA][c] =
+                            __builtin_amdgcn_mfma_f32_32x32x2f32(av[e], bv[c][e], accs[(e + 4 * s) % NA][c], 0, 0, 0);
             }
         }
     };
@@ -291,6 +299,15 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
         if (ci + 1 < nchunk) load_chunk(r, in);
         mma_chunk();
     }
+#pragma unroll
+    for (int d = 1; d < NA; d *= 2)
+#pragma unroll
+        for (int n = 0; n + d < NA; n += 2 * d)
+#pragma unroll
+            for (int c = 0; c < kPosTiles; ++c)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) accs[n][c][v] += accs[n + d][c][v];
+    f32x16(&acc)[kPosTiles] = accs[0];
     __syncthreads();                           // everyone is done with the staging blocks
 
     // wavefront partials -> LDS; accumulator register v holds row 8*(v/4) + 4*h + v%4, column f
@@ -306,9 +323,10 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
     float* dst = out + (size_t)ks * ((size_t)P.Cout * P.L);
     for (int e = threadIdx.x; e < 32 * 32 * kPosTiles; e += kWaves * 64) {
         const int fr = e / (32 * kPosTiles), uc = e % (32 * kPosTiles);
-        float s = 0.f;
+        float part[kWaves];
 #pragma unroll
-        for (int wv = 0; wv < kWaves; ++wv) s += red[(wv * 32 + fr) * (32 * kPosTiles) + uc];
+        for (int wv = 0; wv < kWaves; ++wv) part[wv] = red[(wv * 32 + fr) * (32 * kPosTiles) + uc];
+        const float s = (part[0] + part[1]) + (part[2] + part[3]);
         const int kr = row_k[fr];
         const int j = sc * (32 * kPosTiles) + uc - row_off[fr];
         if (kr >= 0 && j >= 0 && j < P.L) dst[(size_t)kr * P.L + j] = s;
@@ -351,7 +369,7 @@ inline BwwTiling make_tiling(const Problem& p, bool side_by_side = false)
     // workgroups per K-split (so fewer splits to reduce) and a third less LDS per workgroup, which lets more of
     // them, and of the grad-input workgroups that share their grid in scc_backward, be resident (measured on
     // the 2x2 to 8x8 layers of the stack: 1-3 us per pass, except for spans of 512 channels)
-    if (p.NQ <= 8192 && t.U <= 256) t.NPT = 1;
+    if (p.NQ < 256 || (p.NQ <= 8192 && t.U <= 256)) t.NPT = 1;
     t.NSC = (t.U + 32 * t.NPT - 1) / (32 * t.NPT);
     t.q = column_groups(p, 4);
     t.NQ4 = p.HW >= 4 ? (int)t.q.count : (int)((p.NQ + 3) / 4);   // HW < 4: the last group may be partial
