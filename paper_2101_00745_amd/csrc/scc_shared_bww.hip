@@ -18,7 +18,7 @@ __global__ __launch_bounds__(256, 3) void weight_product(const T_* __restrict__ 
 template <typename T_, int PT>
 hipError_t launch_tile(const T_* x, const T_* dy, float* out, const Problem& p, const WeightTiling& t, hipStream_t st)
 {
-    constexpr int kLds = weight_lds((int)sizeof(T_), PT);
+    constexpr int kLds = weight_lds(PT);
     static const hipError_t allowed = hipFuncSetAttribute((const void*)weight_product<T_, PT>,
                                                           hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
     if (allowed != hipSuccess) return allowed;
@@ -28,16 +28,16 @@ hipError_t launch_tile(const T_* x, const T_* dy, float* out, const Problem& p, 
 
 }  // namespace
 
-// Used where the per-tile kernel fetches at least 1.4 times the planes this one does, and enough of them.  The pass alone, us,
-// per-tile kernel against this one: 128 x 128 -> 512 on 32x32, cg 2, co 0.33: f32 155 -> 96, bf16 66 -> 40; 128 x 256 -> 256 on
-// 16x16, cg 1: f32 51 -> 43, bf16 22 -> 23 (not taken); 30 x 640 -> 640 on 32x32, cg 4, co 0: 138 -> 72; 128 x 256 -> 256, cg 2: 31 -> 32
-// (50e6 fetches, not taken); 882 x 256 -> 128, cg 4, co 0: 70 -> 77 (0.75 times the fetches, not taken).
+// Used where the per-tile kernel fetches at least 1.4 times the planes this one does, and enough of them, and, binary32, where
+// this one's matrix time is not longer.  The pass alone, us, per-tile kernel against this one: 128 x 128 -> 512 on 32x32, cg 2,
+// co 0.33: f32 160 -> 130, bf16 66 -> 40; 40 x 272 -> 270 on 28x29, cg 1: f32 114 -> 74, bf16 56 -> 29; 253 x 112 -> 56 on 28x28, cg 1, co 0.75:
+// f32 84 -> 74.  Not taken: 150 x 288 -> 429 on 16x16, cg 2: f32 89 -> 100 (1.33 times the matrix time); 128 x 256 -> 256 on 16x16, cg 1
+// (101e6 fetches): f32 53 -> 54, bf16 23 -> 23; 882 x 256 -> 128, cg 4, co 0 (0.75 times the fetches): f32 70 -> 81, bf16 43 -> 43.
 bool backward_weight_shared_preferred(const Problem& p, int es)
 {
     if (!weight_eligible(p, es) || backward_weight_shared_workspace(p, es) > (size_t)SCC_STATIC_SCRATCH_BYTES) return false;
-    double there, here;
-    weight_fetches(p, es, &there, &here);
-    return there >= (es == 2 ? 105e6 : 90e6) && there >= 1.4 * here;
+    const WeightCost c = weight_cost(p, es);
+    return c.there >= 105e6 && c.there >= 1.4 * c.here && (es == 2 || c.matrix <= 1.15);
 }
 
 size_t backward_weight_shared_workspace(const Problem& p, int es)

@@ -5,14 +5,19 @@
 //
 // scc_mfma_bww_kernel.h gives every wavefront its own 32 filters x 32..96 positions and lets the wavefronts of a workgroup
 // split the columns: every x plane is fetched once per filter tile whose windows reach it, every dy plane once per chunk
-// of span positions (the channel-expanding layer moves 1 GB through L2 in a pass), and binary32 operands go through
-// v_mfma_f32_32x32x2_f32, at 3/8 of the rate of the bf16 instruction on the exact three-way split.  Here a workgroup owns 128
+// of span positions (the channel-expanding layer moves 1 GB through L2 in a pass).  Here a workgroup owns 128
 // filters in the order of their window starts times 32*PT positions of the walk that covers their windows (the channels
-// from the first window's start to the last one's end), for one slice of the columns.  Per round of 16*KG columns its 256
-// lanes fetch 128 dy planes and 32*PT x planes, 16 bytes per lane and plane, cut each value once and park the pieces in
-// LDS in operand layout (8 columns of one plane = 16 bytes); wavefront t multiplies filter tile t with all PT position
-// tiles and skips those none of its windows reaches.  One LDS buffer and two barriers per round; the next round's loads
-// are in flight while this one is multiplied, and three (binary32) or four workgroups per CU overlap each other's phases.
+// from the first window's start to the last one's end), for one slice of the columns.  Per round its 256 lanes fetch 16
+// bytes of 128 dy planes and 32*PT x planes each (32 columns of binary32, 64 of bf16) and park them in LDS as they are:
+// 16 bytes of one plane are a lane's operand of one bf16 instruction, or of four binary32 ones; wavefront t multiplies
+// filter tile t with all PT position tiles and skips those none of its windows reaches.  One LDS buffer and two barriers
+// per round; the next round's loads are in flight while this one is multiplied, and three workgroups per CU overlap each
+// other's phases.
+//
+// Products are those of the per-tile kernel: exact (bf16 tensors), binary32 through v_mfma_f32_32x32x2_f32 (fp32 tensors).
+// What bounds it: binary32, the matrix pipe (channel-expanding layer: 82 of 130 us at its peak rate, the idle share of
+// tiles that windows fill only in part included); bf16, fetching.  (binary32 through six bf16 products of a three-way cut
+// takes 101 us there, but drops the smallest partial products and loses operands near the end of the exponent range.)
 //
 // A wavefront's tiles are its own, so there is no sum inside a workgroup; the slices' partial sums go to the workspace in the
 // layout of dw and launch_weight_reduce adds them in slice order: no atomics, bitwise reproducible.
@@ -21,14 +26,12 @@
 #include "scc_band.h"
 #include "scc_common.h"
 #include "scc_mfma_bww_kernel.h"
-#include "scc_mfma_bww_kernel.h"
 
 namespace scc {
 
 namespace shared_bww {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 struct WeightTiling {
@@ -55,11 +58,12 @@ __host__ __device__ inline void weight_walk(const Problem& P, const Band& b, int
 }
 
 constexpr int weight_rows(int pt) { return 128 + 32 * pt; }
-// bytes of the operands of one K group and half-wave: 32 of padding, so that 16 lanes' 8-byte stores (2 planes x 4 such
-// blocks) cover the 128 bytes of all banks; with 128 they conflict four by four (channel-expanding layer, dw alone: f32 105 us
-// against 95, bf16 50 against 36)
-constexpr int weight_half(int pt) { return weight_rows(pt) * 16 + 32; }
-constexpr int weight_lds(int es, int pt) { return (es == 2 ? 8 : 3 * 4) * weight_half(pt); }
+// bytes of one lane group's operands: 16 of padding, so that the 16-byte stores of eight lanes (one plane, eight such blocks)
+// cover the 128 bytes of all banks; with 32 they conflict two by two, without any eight by eight (dw alone, binary32:
+// channel-expanding layer 130 against 138 us with 32, 120 -> 500 channels on 11x9 55 against 59; bf16 the same with 32 and 16,
+// 50 against 36 us for four-way conflicts on the first layer)
+constexpr int weight_half(int pt) { return weight_rows(pt) * 16 + 16; }
+constexpr int weight_lds(int pt) { return 8 * weight_half(pt); }
 
 // bid: the workgroup's index in a launch whose first workgroup is a multiple of 8 (bid % 8 names the XCD)
 template <typename T_, int PT>
@@ -67,12 +71,9 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
                                             const Problem& P, const WeightTiling& T, const int bid, char* const lds_w)
 {
     constexpr uint32_t ES = sizeof(T_);
-    constexpr int NP = ES == 2 ? 1 : 3;                 // bf16 pieces of a value
-    constexpr int KG = ES == 2 ? 4 : 2;                 // K groups of 16 columns per round
     constexpr int CT = 16 / (int)ES;                    // columns per lane and load
     constexpr int NL = 4 + PT;                          // loads per lane and round: planes tid/8 + 32*it
     constexpr int kHalf = weight_half(PT);
-    constexpr int kPiece = 2 * KG * kHalf;
     typedef T_ ldvec __attribute__((ext_vector_type(CT), aligned(sizeof(T_))));
 
     const int xcd = bid & 7, slot = bid >> 3;
@@ -159,8 +160,8 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
         offA += dn * sampA + (wr ? sampA : 0u);
         offB += dn * sampB + (wr ? sampB : 0u);
     };
-    // lane's 16 bytes: binary32, 4 columns = half an operand of (K group lc/4, half-wave lc/2%2); bf16, a whole operand of (lc/2, lc%2)
-    char* const dst0 = lds_w + (ES == 2 ? lc * kHalf : (lc >> 1) * kHalf + 8 * (lc & 1)) + lr * 16;
+    // operand layout: [column group lc][plane], 16 bytes each; half-wave h reads group 2*j + h in step j
+    char* const dst0 = lds_w + lc * kHalf + lr * 16;
     auto commit = [&](bool full) {
 #pragma unroll
         for (int it = 0; it < NL; ++it) {
@@ -169,16 +170,7 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
 #pragma unroll
                 for (int e = 0; e < CT; ++e) v[e] = (in >> e) & 1u ? v[e] : (T_)0;
             }
-            char* dst = dst0 + it * 512;
-            if constexpr (ES == 2) {
-                *(u32x4*)dst = __builtin_bit_cast(u32x4, v);
-            } else {
-                uint32_t hi[2], mid[2], lo[2];
-                split3<4>([&](int e) { return v[e]; }, hi, mid, lo);
-                *(u32x2*)dst = u32x2{hi[0], hi[1]};
-                *(u32x2*)(dst + kPiece) = u32x2{mid[0], mid[1]};
-                *(u32x2*)(dst + 2 * kPiece) = u32x2{lo[0], lo[1]};
-            }
+            *(u32x4*)(dst0 + it * 512) = __builtin_bit_cast(u32x4, v);
         }
     };
 
@@ -187,32 +179,23 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
     for (int t = 0; t < PT; ++t)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
-    auto mm = [&](const u32x4& a, const u32x4& b, f32x16& d) {
-        const uint32_t aa[4] = {a[0], a[1], a[2], a[3]}, ba[4] = {b[0], b[1], b[2], b[3]};
-        d = mfma_bf16<8>(aa, ba, d);
-    };
     auto compute = [&]() {
 #pragma unroll
-        for (int j = 0; j < KG; ++j) {
+        for (int j = 0; j < 4; ++j) {
             const char* base = lds_w + (2 * j + h) * kHalf + f * 16;
-            u32x4 a[NP];
-#pragma unroll
-            for (int q = 0; q < NP; ++q) a[q] = *(const u32x4*)(base + q * kPiece + wave * 512);
+            const u32x4 a = *(const u32x4*)(base + wave * 512);
 #pragma unroll
             for (int t = 0; t < PT; ++t) {
                 if (!((active >> t) & 1u)) continue;
-                u32x4 b[NP];
+                const u32x4 b = *(const u32x4*)(base + (4 + t) * 512);
+                if constexpr (ES == 2) {                // 8 columns of the half-wave's
+                    const uint32_t aa[4] = {a[0], a[1], a[2], a[3]}, ba[4] = {b[0], b[1], b[2], b[3]};
+                    acc[t] = mfma_bf16<8>(aa, ba, acc[t]);
+                } else {                                // column e of the half-wave's 4
 #pragma unroll
-                for (int q = 0; q < NP; ++q) b[q] = *(const u32x4*)(base + q * kPiece + (4 + t) * 512);
-                if constexpr (NP == 1) {
-                    mm(a[0], b[0], acc[t]);
-                } else {                                // six of the nine partial products, the smallest first
-                    mm(a[2], b[0], acc[t]);
-                    mm(a[0], b[2], acc[t]);
-                    mm(a[1], b[1], acc[t]);
-                    mm(a[1], b[0], acc[t]);
-                    mm(a[0], b[1], acc[t]);
-                    mm(a[0], b[0], acc[t]);
+                    for (int e = 0; e < 4; ++e)
+                        acc[t] = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(a[e]), __uint_as_float(b[e]), acc[t],
+                                                                      0, 0, 0);
                 }
             }
         }
@@ -295,14 +278,25 @@ inline bool weight_eligible(const Problem& p, int es)
     return 4ll * b.P * b.F <= 5ll * p.Cout && b.P * (long long)b.F <= (1 << 20);   // else too many empty rows
 }
 
-// planes fetched, columns included, by the per-tile kernel and by this one
-inline void weight_fetches(const Problem& p, int es, double* there, double* here)
+struct WeightCost {
+    double there, here;   // planes fetched, columns included, by the per-tile kernel and by this one
+    double matrix;        // matrix time of this one over that of the per-tile kernel
+};
+
+// The matrix time counts every tile of 32 x 32 in which a wavefront may wait for another one's (windows that reach a part of a
+// walk only leave matrix pipes idle: 227 x 400 -> 200 on 20x20, cg 2: twice the tiles, 203 against 146 us), and on the other side the
+// per-tile kernel's last generation of workgroups, one per CU (40 x 272 -> 270, cg 1: 270 of them on 256 CUs, 114 against 77 us).
+inline WeightCost weight_cost(const Problem& p, int es)
 {
     int pt;
     const WeightTiling t = make_weight_tiling(p, es, &pt);
     const bww::BwwTiling o = bww::make_tiling(p);
-    *here = (double)t.NG * t.NSC * weight_rows(pt) * p.NQ;
-    *there = (double)o.IB * o.MB * o.NSC * bww::rows_of(o.NPT) * p.NQ;
+    const long long tiles = (long long)o.IB * o.MB * o.NSC, groups = tiles * o.KS;
+    WeightCost c;
+    c.here = (double)t.NG * t.NSC * weight_rows(pt) * p.NQ;
+    c.there = (double)tiles * bww::rows_of(o.NPT) * p.NQ;
+    c.matrix = 4.0 * pt * t.NG * t.NSC / ((double)tiles * o.NPT) * (double)groups / (256.0 * ((groups + 255) / 256));
+    return c;
 }
 
 }  // namespace shared_bww

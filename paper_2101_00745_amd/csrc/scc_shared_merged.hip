@@ -13,9 +13,9 @@ namespace scc {
 
 namespace {
 
-// workgroups of the grad-weight range.  256 / 384 / 512, us: the first layer above f32 184 / 182 / 184, bf16 64 / 66 / 69, the second
-// 70 / 68 / 74, 32 / 34 / 37, the third 51 / 48 / 48, 33 / 34 / 34
-constexpr int weight_workgroups(int es) { return es == 2 ? 256 : 384; }
+// workgroups of the grad-weight range: 256 / 512, us: the first layer above f32 219 / 209, bf16 64 / 70, the second 78 / 82, 31 / 36,
+// the third 56 / 55, 33 / 35; 37 x 336 -> 330 on 20x41, cg 1: f32 132 / 122
+constexpr int weight_workgroups(int es) { return es == 2 ? 256 : 512; }
 
 template <typename T_, int CT, int PT>
 __global__ __launch_bounds__(256, 3) void backward_shared(const T_* __restrict__ x, const T_* __restrict__ dy,
@@ -35,7 +35,7 @@ template <typename T_, int CT, int PT>
 hipError_t launch_variant(const T_* x, const T_* dy, const char* packed_w, T_* dx, float* part, const Problem& p,
                           const packed::Packed& ti, const shared_bww::WeightTiling& tw, hipStream_t st)
 {
-    constexpr int kW = shared_bww::weight_lds((int)sizeof(T_), PT), kI = packed::lds_bytes((int)sizeof(T_), CT);
+    constexpr int kW = shared_bww::weight_lds(PT), kI = packed::lds_bytes((int)sizeof(T_), CT);
     constexpr int kMost = kI + packed::kMaxGroups * 16 * 4 > kW ? kI + packed::kMaxGroups * 16 * 4 : kW;
     static const hipError_t allowed = hipFuncSetAttribute((const void*)backward_shared<T_, CT, PT>,
                                                           hipFuncAttributeMaxDynamicSharedMemorySize, kMost);
@@ -62,9 +62,10 @@ size_t backward_shared_workspace(const Problem& p, int es)
     const int ct = packed::tile_width<false>(p, es);
     if (ct == 0 || !shared_bww::weight_eligible(p, es)) return 0;
     const Band b = make_band(p);
-    double there, here, again;
-    shared_bww::weight_fetches(p, es, &there, &here);
-    double saved = there - here;
+    double again;
+    const shared_bww::WeightCost c = shared_bww::weight_cost(p, es);
+    if (es == 4 && c.matrix > 1.4) return 0;
+    double saved = c.there - c.here;
     saved += packed::fetches_without_sharing<false>(p, b, &again);
     for (int c0 = 0; c0 < p.Cin; c0 += 128) {
         int first, len;

@@ -83,3 +83,36 @@ def test_both_gradients_in_one_launch(dtype, shape):
     shifted = [torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")[1:].view(t.shape).copy_(t) for t in (xd, dyd, wd)]
     dx3, dw3 = S.scc_backward(*shifted, cg, co)
     assert torch.equal(dx, dx3) and torch.equal(dw, dw3)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which", ["backward_weight", "backward"])
+@pytest.mark.parametrize("shape", [s for d, s in CASES if d == "f32"])
+def test_products_are_binary32_to_the_end_of_the_exponent_range(shape, which):
+    """dy of magnitude 2**-124 to 2**-123: normal numbers whose low halves no bf16 holds.  A product of cut pieces is off by up to
+    2**-10 there; binary32 products keep the bar of test_parity_and_repeat."""
+    N, Cin, Cout, H, W, cg, co = shape
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    x = torch.randn(N, Cin, H, W, generator=gen, device="cuda") * 2.0 ** 60
+    dy = torch.rand(N, Cout, H, W, generator=gen, device="cuda") + 1
+    dy = dy * (torch.randint(0, 2, dy.shape, generator=gen, device="cuda") * 2 - 1) * 2.0 ** -62 * 2.0 ** -62
+    ref = O.backward_weight(x.cpu().numpy(), dy.cpu().numpy(), cg, co)
+    if which == "backward":
+        dw = S.scc_backward(x, dy, torch.randn(Cout, Cin // cg, generator=gen, device="cuda"), cg, co)[1]
+    else:
+        dw = S.scc_backward_weight(x, dy, cg, co)
+    got = dw.cpu().numpy().astype(np.float64)
+    assert np.linalg.norm(got - ref) <= 4 * 2.0 ** -24 * np.sqrt(N * H * W / 16) * np.linalg.norm(ref)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,shape", CASES)
+def test_an_infinite_gradient_stays_infinite(dtype, shape):
+    N, Cin, Cout, H, W, cg, co = shape
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(4)
+    x = (torch.rand(N, Cin, H, W, generator=gen, device="cuda") + 1).to(td)
+    dy = torch.randn(N, Cout, H, W, generator=gen, device="cuda").to(td)
+    dy[N // 2, Cout // 3, H - 1, W - 1] = float("inf")
+    dw = S.scc_backward_weight(x, dy, cg, co)
+    assert bool((dw[Cout // 3] == float("inf")).all())
