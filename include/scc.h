@@ -71,7 +71,7 @@ typedef enum {
     SCC_ERR_SHAPE = -2,     /* a dimension <= 0, cg < 1, Cin % cg != 0, or a tensor too large to index */
     SCC_ERR_OVERLAP = -3,   /* co is not finite or lies outside [0, 1] */
     SCC_ERR_DTYPE = -4,     /* dtype is neither SCC_F32 nor SCC_BF16 */
-    SCC_ERR_WORKSPACE = -5, /* workspace missing, misaligned or smaller than the query says */
+    SCC_ERR_WORKSPACE = -5, /* workspace missing, misaligned or smaller than the call needs */
     SCC_ERR_LAUNCH = -6,    /* the HIP runtime refused a launch (hipGetLastError != hipSuccess) */
     SCC_ERR_SCRATCH = -7    /* scc_backward_weight_static: the problem needs more than SCC_STATIC_SCRATCH_BYTES */
 } scc_status;
@@ -141,8 +141,11 @@ size_t scc_backward_weight_workspace_bytes(int N, int Cin, int Cout, int H, int 
  * x: in, N*Cin*H*W.  dy: in, N*Cout*H*W.  dw: out, Cout*L binary32 values (both dtypes).
  * workspace: device scratch of at least scc_backward_weight_workspace_bytes(...) bytes,
  * 256-byte aligned, owned by the caller, contents undefined before and after; may be NULL
- * when the query returns 0.  The reduction order is fixed: two calls on the same inputs
- * give bitwise identical results.
+ * when the query returns 0.  On layers whose filters share many channels the query asks for more
+ * than the layer cannot do without: a smaller workspace (or NULL) then runs the kernel of every
+ * other layer, as long as it holds that kernel's partial sums (at most 6 MiB), and is refused
+ * otherwise.  The reduction order is fixed: two calls on the same inputs with workspaces of the
+ * same size give bitwise identical results.
  */
 int scc_backward_weight(const void* x, const void* dy, void* dw,
                         int N, int Cin, int Cout, int H, int W, int cg, double co,
@@ -167,8 +170,9 @@ size_t scc_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int 
  * x: in, N*Cin*H*W.  dy: in, N*Cout*H*W.  w: in, Cout*L.  dx: out, N*Cin*H*W.
  * dw: out, Cout*L binary32 values (both dtypes).  workspace: device scratch of at least
  * scc_backward_workspace_bytes(...) bytes, 256-byte aligned, owned by the caller, contents
- * undefined before and after; may be NULL when the query returns 0.  Two calls on the same inputs
- * give bitwise identical results.
+ * undefined before and after; may be NULL when the query returns 0.  A workspace smaller than the
+ * query is treated as scc_backward_weight treats it.  Two calls on the same inputs with workspaces
+ * of the same size give bitwise identical results.
  */
 int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* dw,
                  int N, int Cin, int Cout, int H, int W, int cg, double co,

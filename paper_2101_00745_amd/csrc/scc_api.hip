@@ -3,6 +3,7 @@
 #include "scc.h"
 #include "scc_common.h"
 
+#include <algorithm>
 #include <cmath>
 #include <limits>
 #include <mutex>
@@ -107,17 +108,26 @@ int run_product(const T* src, const T* w, T* out, const Problem& p, void* worksp
     }
 }
 
-// Grad-weight: the kernel that shares its operands between filter tiles on the layers that gain from it (`shared`), else
-// the one with a tile per wavefront, else the one for any shape.  `workspace`: weight_workspace bytes.
-bool weight_shared(const Problem& p, scc_dtype dtype)
+int size_of(scc_dtype dtype) { return dtype == SCC_F32 ? 4 : 2; }
+
+// Whether a call may use `need` bytes of its workspace.
+bool holds(size_t need, const void* workspace, size_t workspace_bytes)
 {
-    return scc::backward_weight_shared_preferred(p, dtype == SCC_F32 ? 4 : 2);
+    return need == 0 || (workspace && workspace_bytes >= need && ((uintptr_t)workspace & 255u) == 0);
 }
 
-size_t weight_workspace(const Problem& p, scc_dtype dtype, bool shared)
+// Grad-weight: the kernel that shares its operands between filter tiles on the layers that gain from it (`shared`) where
+// the workspace holds its partial sums, else the one with a tile per wavefront, else the one for any shape.  A workspace of
+// weight_least bytes is what a call cannot do without.
+size_t weight_least(const Problem& p)
 {
-    if (shared) return scc::backward_weight_shared_workspace(p, dtype == SCC_F32 ? 4 : 2);
     return scc::backward_weight_mfma_eligible(p) ? scc::backward_weight_mfma_workspace(p) : 0;
+}
+
+size_t weight_shared_need(const Problem& p, scc_dtype dtype)   // 0: not a layer for that kernel
+{
+    const int es = size_of(dtype);
+    return scc::backward_weight_shared_preferred(p, es) ? scc::backward_weight_shared_workspace(p, es) : 0;
 }
 
 int run_weight(const void* x, const void* dy, void* dw, const Problem& p, scc_dtype dtype, bool shared, void* workspace,
@@ -209,7 +219,7 @@ size_t scc_backward_weight_workspace_bytes(int N, int Cin, int Cout, int H, int 
 {
     Problem p;
     if (make_problem(N, Cin, Cout, H, W, cg, co, &p) != SCC_OK || !dtype_ok(dtype)) return 0;
-    return weight_workspace(p, dtype, weight_shared(p, dtype));
+    return std::max(weight_least(p), weight_shared_need(p, dtype));
 }
 
 int scc_backward_weight(const void* x, const void* dy, void* dw, int N, int Cin, int Cout, int H, int W, int cg,
@@ -220,27 +230,31 @@ int scc_backward_weight(const void* x, const void* dy, void* dw, int N, int Cin,
     const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    const bool shared = weight_shared(p, dtype);
-    const size_t need = weight_workspace(p, dtype, shared);
-    if (need > 0 && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0))
-        return SCC_ERR_WORKSPACE;
-    return run_weight(x, dy, dw, p, dtype, shared, workspace, (hipStream_t)stream);
+    if (!holds(weight_least(p), workspace, workspace_bytes)) return SCC_ERR_WORKSPACE;
+    const size_t need = weight_shared_need(p, dtype);
+    return run_weight(x, dy, dw, p, dtype, need > 0 && holds(need, workspace, workspace_bytes), workspace, (hipStream_t)stream);
+}
+
+// scc_backward: what a call cannot do without, whichever of the kernels that follow runs (tensors that are not aligned to
+// 16 bytes keep a layer from the fused one), and what the launch of both shared kernels takes (0: not a layer for it).
+static size_t backward_least(const Problem& p, scc_dtype dtype)
+{
+    const size_t least = weight_least(p);
+    return dtype == SCC_F32 && scc::backward_fused_eligible(p) ? std::max(least, scc::backward_fused_workspace(p)) : least;
+}
+
+static size_t backward_shared_need(const Problem& p, scc_dtype dtype)
+{
+    if (dtype == SCC_F32 && scc::backward_fused_eligible(p)) return 0;
+    return scc::backward_shared_workspace(p, size_of(dtype));
 }
 
 size_t scc_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype)
 {
     Problem p;
     if (make_problem(N, Cin, Cout, H, W, cg, co, &p) != SCC_OK || !dtype_ok(dtype)) return 0;
-    // whichever of its kernels runs (tensors that are not aligned to 16 bytes keep a layer from the fused one): the most
-    size_t need = 0;
-    auto at_least = [&](size_t v) { need = v > need ? v : need; };
-    at_least(scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype));
-    at_least(weight_workspace(p, dtype, false));
-    if (dtype == SCC_F32 && scc::backward_fused_eligible(p))
-        at_least(scc::backward_fused_workspace(p));
-    else
-        at_least(scc::backward_shared_workspace(p, dtype == SCC_F32 ? 4 : 2));
-    return need;
+    const size_t least = std::max(backward_least(p, dtype), scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype));
+    return std::max(least, backward_shared_need(p, dtype));
 }
 
 int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* dw, int N, int Cin, int Cout, int H,
@@ -251,17 +265,14 @@ int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* d
     const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    const size_t need = scc_backward_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype);
-    if (need > 0 && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0))
-        return SCC_ERR_WORKSPACE;
+    if (!holds(backward_least(p, dtype), workspace, workspace_bytes)) return SCC_ERR_WORKSPACE;
     drop_stale_error();
-    if (dtype == SCC_F32 && scc::backward_fused_eligible(p)) {
-        const bool aligned = (((uintptr_t)x | (uintptr_t)dy | (uintptr_t)dx) & 15u) == 0;
-        if (aligned)
-            return launch_status(scc::launch_backward_fused((const float*)x, (const float*)dy, (const float*)w,
-                                                            (float*)dx, (float*)dw, (float*)workspace, p,
-                                                            (hipStream_t)stream));
-    } else if (scc::backward_shared_workspace(p, dtype == SCC_F32 ? 4 : 2) > 0) {
+    const bool aligned = (((uintptr_t)x | (uintptr_t)dy | (uintptr_t)dx) & 15u) == 0;
+    if (dtype == SCC_F32 && aligned && scc::backward_fused_eligible(p))
+        return launch_status(scc::launch_backward_fused((const float*)x, (const float*)dy, (const float*)w, (float*)dx,
+                                                        (float*)dw, (float*)workspace, p, (hipStream_t)stream));
+    const size_t shared = backward_shared_need(p, dtype);
+    if (shared > 0 && holds(shared, workspace, workspace_bytes)) {
         return with_type(dtype, [&](auto t) {
             typedef decltype(t) T;
             return launch_status(scc::launch_backward_shared((const T*)x, (const T*)dy, (const T*)w, (T*)dx, (float*)dw,
@@ -460,15 +471,14 @@ int scc_backward_weight_static(const void* x, const void* dy, void* dw, int N, i
     const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    const bool shared = weight_shared(p, dtype);
-    const size_t need = weight_workspace(p, dtype, shared);
+    const size_t shared = weight_shared_need(p, dtype), need = std::max(weight_least(p), shared);
     if (need > (size_t)SCC_STATIC_SCRATCH_BYTES) return SCC_ERR_SCRATCH;
     void* ptr = nullptr;
     if (need > 0) {
         const int sc = scratch_of_current_device(&ptr);
         if (sc != SCC_OK) return sc;
     }
-    return run_weight(x, dy, dw, p, dtype, shared, ptr, (hipStream_t)stream);
+    return run_weight(x, dy, dw, p, dtype, shared > 0, ptr, (hipStream_t)stream);
 }
 
 const char* scc_status_string(int status)

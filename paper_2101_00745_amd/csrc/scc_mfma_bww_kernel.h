@@ -376,7 +376,8 @@ inline BwwTiling make_tiling(const Problem& p, bool side_by_side = false)
     // about one workgroup per CU (one wavefront per SIMD, deep prefetch), at least 32 column groups per wavefront
     const long long tiles = (long long)t.IB * t.MB * t.NSC;
     long long ks = (256 + tiles - 1) / tiles;
-    const long long ks_max = t.NQ4 / (32 * kWaves);
+    // (counted in columns: the groups of planes that are not a multiple of 4 pixels share some)
+    const long long ks_max = (p.NQ + 3) / 4 / (32 * kWaves);
     if (ks > ks_max) ks = ks_max;
     if (ks < 1) ks = 1;
     if (side_by_side && ks <= 2) ks = 1;
