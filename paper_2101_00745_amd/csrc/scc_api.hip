@@ -253,8 +253,11 @@ size_t scc_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int 
 {
     Problem p;
     if (make_problem(N, Cin, Cout, H, W, cg, co, &p) != SCC_OK || !dtype_ok(dtype)) return 0;
-    const size_t least = std::max(backward_least(p, dtype), scc_backward_weight_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype));
-    return std::max(least, backward_shared_need(p, dtype));
+    size_t most = backward_shared_need(p, dtype);
+    const bool two_passes = most == 0 && !(dtype == SCC_F32 && scc::backward_fused_eligible(p)) &&
+                            !with_type(dtype, [&](auto t) { return (int)scc::backward_merged_applicable<decltype(t)>(p); });
+    if (two_passes) most = weight_shared_need(p, dtype);
+    return std::max(backward_least(p, dtype), most);
 }
 
 int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* dw, int N, int Cin, int Cout, int H,

@@ -46,3 +46,10 @@ def test_the_least_is_enough(shape, least):
     assert lib.scc_backward(x.data_ptr(), dy.data_ptr(), w.data_ptr(), dx.data_ptr(), dw.data_ptr(), *shape, ws_ptr, least, st) == 0
     for got, ref, bar in ((dw, ref_dw, 2e-5), (dw1, ref_dw, 2e-5), (dx, ref_dx, 1e-2 if code else 2e-5)):
         assert np.max(np.abs(got.float().cpu().numpy() - ref)) <= bar * np.max(np.abs(ref))
+
+
+@pytest.mark.parametrize("shape,need", [((190, 800, 69, 16, 16, 8, 0.0, 1), 13 * 69 * 100 * 4), ((117, 416, 65, 28, 28, 8, 0.0, 1), 16 * 65 * 52 * 4)])
+def test_scc_backward_asks_for_what_runs(shape, need):
+    """Layers whose two passes share one grid never run scc_backward_weight's kernel, which alone would take more."""
+    lib = S.load()
+    assert lib.scc_backward_workspace_bytes(*shape) == need < lib.scc_backward_weight_workspace_bytes(*shape)
