@@ -50,6 +50,9 @@ constexpr size_t region_bytes_of(int npt, int esz)
 }
 constexpr size_t lds_bytes_of(int npt, int esz) { return region_bytes_of(npt, esz) + 2 * 32 * 4; }
 
+// independent accumulators per tile of a wavefront (see backward_weight_body)
+constexpr int accumulators_of(int npt, int es, bool few) { return npt == 1 ? (es == 2 ? 2 : few ? 8 : 4) : 1; }
+
 struct BwwTiling {
     Band b;
     int TI, TM;   // tile = TM starts x TI filters per start
@@ -190,7 +193,7 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
     // On layers with a few hundred columns (SMALL: fewer than 256) one chain would round more than the lane sums of the any-shape
     // kernel, which such layers took before: 2-norm against binary64 at 196 columns, binary32, that kernel 0.76e-7, one chain
     // 1.3e-7, four 0.86e-7, eight 0.78e-7.
-    constexpr int NA = kPosTiles == 1 ? (ES == 2 ? 2 : SMALL ? 8 : 4) : 1;
+    constexpr int NA = accumulators_of(kPosTiles, (int)ES, SMALL);
     f32x16 accs[NA][kPosTiles];
 #pragma unroll
     for (int n = 0; n < NA; ++n)

@@ -29,15 +29,18 @@ hipError_t launch_tile(const T_* x, const T_* dy, float* out, const Problem& p, 
 }  // namespace
 
 // Used where the per-tile kernel fetches at least 1.4 times the planes this one does, and enough of them, and, binary32, where
-// this one's matrix time is not longer.  The pass alone, us, per-tile kernel against this one: 128 x 128 -> 512 on 32x32, cg 2,
-// co 0.33: f32 160 -> 130, bf16 66 -> 40; 40 x 272 -> 270 on 28x29, cg 1: f32 114 -> 74, bf16 56 -> 29; 253 x 112 -> 56 on 28x28, cg 1, co 0.75:
-// f32 84 -> 74.  Not taken: 150 x 288 -> 429 on 16x16, cg 2: f32 89 -> 100 (1.33 times the matrix time); 128 x 256 -> 256 on 16x16, cg 1
-// (101e6 fetches): f32 53 -> 54, bf16 23 -> 23; 882 x 256 -> 128, cg 4, co 0 (0.75 times the fetches): f32 70 -> 81, bf16 43 -> 43.
+// this one's matrix time is at most 1.1 times the other's.  The pass alone, us, per-tile kernel against this one: 128 x 128 -> 512 on
+// 32x32, cg 2, co 0.33: f32 148 -> 134, bf16 66 -> 45; 37 x 336 -> 330 on 20x41, cg 1: f32 150 -> 97, bf16 74 -> 34; 64 x 2048 -> 2048 on 7x7, cg 2: f32
+// 153 -> 140, bf16 78 -> 54; 22 fp32 layers below 1.1 gain 1.04 to 2.4 times, nine from 1.27 on lose 1.1 to 1.5 times (150 x 288 -> 429 on
+// 16x16, cg 2: 89 -> 106).  Too few fetches: 128 x 256 -> 256 on 16x16, cg 1 (101e6): f32 53 -> 54, bf16 23 -> 23.
 bool backward_weight_shared_preferred(const Problem& p, int es)
 {
-    if (!weight_eligible(p, es) || backward_weight_shared_workspace(p, es) > (size_t)SCC_STATIC_SCRATCH_BYTES) return false;
-    const WeightCost c = weight_cost(p, es);
-    return c.there >= 105e6 && c.there >= 1.4 * c.here && (es == 2 || c.matrix <= 1.15);
+    if (!weight_eligible(p, es)) return false;
+    int pt;
+    const WeightTiling t = make_weight_tiling(p, es, &pt);
+    if (t.KS == 0) return false;
+    const WeightCost c = weight_cost(p, es, t, pt, false);
+    return c.there >= 105e6 && c.there >= 1.4 * c.here && (es == 2 || c.matrix <= 1.1);
 }
 
 size_t backward_weight_shared_workspace(const Problem& p, int es)
@@ -53,6 +56,7 @@ hipError_t launch_backward_weight_shared(const T_* x, const T_* dy, float* dw, f
 {
     int pt;
     const WeightTiling t = make_weight_tiling(p, (int)sizeof(T_), &pt);
+    if (t.KS == 0) return hipErrorInvalidValue;
     const hipError_t e = pt == 2   ? launch_tile<T_, 2>(x, dy, workspace, p, t, st)
                          : pt == 3 ? launch_tile<T_, 3>(x, dy, workspace, p, t, st)
                                    : launch_tile<T_, 4>(x, dy, workspace, p, t, st);

@@ -39,11 +39,10 @@ struct WeightTiling {
     int rows;       // filters in order of their starts: P*F
     int NG;         // groups of 128 rows
     int NSC;        // chunks of 32*PT walk positions (of the longest walk)
-    int KS8;        // slices of the columns per XCD
-    int KS;         // slices: 8 * KS8
-    int eighth;     // rounds of an XCD: it takes a contiguous eighth of the columns
-    int per_slice;  // consecutive rounds of it that a slice takes
-    int chunk;      // workgroups of an XCD: KS8 * NG * NSC
+    int KS;         // slices of the columns, 0 where the layer's partial sums would cost more than the kernel saves
+    int per_slice;  // consecutive rounds a slice takes; the last slice may have fewer, none is empty
+    int total;      // workgroups with work: KS * NG * NSC, slice slowest
+    int chunk;      // consecutive workgroups of that order given to one XCD
     Groups q;       // column groups of 16 bytes
 };
 
@@ -77,9 +76,9 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
     typedef T_ ldvec __attribute__((ext_vector_type(CT), aligned(sizeof(T_))));
 
     const int xcd = bid & 7, slot = bid >> 3;
-    const int tiles = T.NG * T.NSC;
-    if (slot >= T.chunk) return;                        // the whole workgroup leaves
-    const int s8 = slot / tiles, tix = slot % tiles, ks = xcd * T.KS8 + s8;
+    const int tiles = T.NG * T.NSC, logical = xcd * T.chunk + slot;
+    if (slot >= T.chunk || logical >= T.total) return;  // the whole workgroup leaves
+    const int ks = logical / tiles, tix = logical % tiles;
     const int ng = tix / T.NSC, sc = tix % T.NSC;
     int first, len;
     weight_walk(P, T.b, T.rows, ng, first, len);
@@ -123,13 +122,11 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
         if (row0 < T.rows && p0 < len && ((p0 < d1 && p0 + 32 > d0) || p0 < d1 - P.Cin)) active |= 1u << t;
     }
 
-    // this slice's rounds (8 column groups each), r0 up to r1.  (Slices that take every KS8-th round instead, so that an XCD
-    // sweeps its eighth on a narrow front, are slower: channel-expanding layer f32 95 -> 103 us, bf16 40 -> 51.)
+    // this slice's rounds (8 column groups each) from r0 on.  (Slices of an XCD that take every n-th round of its columns
+    // instead, so that it sweeps them on a narrow front, are slower: channel-expanding layer, bf16 40 -> 51 us.)
     const int rounds = (int)((T.q.count + 7) / 8), count = (int)T.q.count;
-    const int r0 = xcd * T.eighth + s8 * T.per_slice;
-    int r1 = (xcd + 1) * T.eighth < rounds ? (xcd + 1) * T.eighth : rounds;
-    r1 = r0 + T.per_slice < r1 ? r0 + T.per_slice : r1;
-    const int nround = r1 > r0 ? r1 - r0 : 0;           // none: the slice's sums are zeros
+    const int r0 = ks * T.per_slice;
+    const int nround = (r0 + T.per_slice < rounds ? r0 + T.per_slice : rounds) - r0;   // at least one
 
     const uint32_t per = (uint32_t)T.q.per;
     const uint32_t sampA = (uint32_t)P.Cout * plane, sampB = (uint32_t)P.Cin * plane;
@@ -201,7 +198,7 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
         }
     };
 
-    if (nround > 0) issue();
+    issue();
     for (int r = 0; r < nround; ++r) {
         __syncthreads();                                // nobody reads the previous round any more
         commit(dup == 0u && 8 * (r0 + r) + 8 <= count);
@@ -229,10 +226,10 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
     }
 }
 
-// workgroups: how many to aim at, 0 for the pass on its own
-inline WeightTiling make_weight_tiling(const Problem& p, int es, int* PT, int workgroups = 0)
+// beside: for the launch that carries grad-input as well (scc_shared_merged.hip)
+inline WeightTiling make_weight_tiling(const Problem& p, int es, int* PT, bool beside = false)
 {
-    WeightTiling t;
+    WeightTiling t = {};
     t.b = make_band(p);
     t.rows = t.b.P * t.b.F;
     t.NG = (t.rows + 127) / 128;
@@ -254,20 +251,38 @@ inline WeightTiling make_weight_tiling(const Problem& p, int es, int* PT, int wo
     t.NSC = (longest + 32 * *PT - 1) / (32 * *PT);
     t.q = column_groups(p, 16 / es);
     const long long tiles = (long long)t.NG * t.NSC;
-    // as many slices as make `workgroups` workgroups at most, and at least four rounds per slice
-    const long long rounds = (t.q.count + 7) / 8, dw_bytes = (long long)p.Cout * p.L * 4;
-    t.eighth = (int)((rounds + 7) / 8);
-    // alone: three workgroups per CU, which hides more (752 channels: 89 us against 108 with two), or two where the slices'
-    // partial sums, written and read once each, are then a third of what the pass moves (cg = 1 at 256 channels: 42 against 46)
-    if (workgroups == 0) workgroups = 768 / tiles * dw_bytes > (20 << 20) ? 512 : 768;
-    long long ks8 = workgroups / (8 * tiles);
-    // scc_backward_weight_static runs the same kernels on the library's own buffer
-    if (ks8 * 8 * dw_bytes > (long long)SCC_STATIC_SCRATCH_BYTES) ks8 = (long long)SCC_STATIC_SCRATCH_BYTES / (8 * dw_bytes);
-    if (ks8 > t.eighth / 4) ks8 = t.eighth / 4;
-    t.KS8 = ks8 < 1 ? 1 : (int)ks8;
-    t.KS = 8 * t.KS8;
-    t.chunk = (int)(t.KS8 * tiles);
-    t.per_slice = (t.eighth + t.KS8 - 1) / t.KS8;
+    const int rounds = (int)((t.q.count + 7) / 8);
+    // No sum is longer (by 2 %, a hundredth of the error) than the per-tile kernel's, of which each wavefront and accumulator adds
+    // a share of the columns: the rounding error against binary64 is then no larger (30 x 640 -> 640 on 32x32, cg 4, co 0, bf16:
+    // 2.0e-7 there, 2.6e-7 with 17 slices, 2.0e-7 with the 29 this asks for, and 50 against 53 us).
+    const bww::BwwTiling o = bww::make_tiling(p, beside);
+    const long long its = (long long)o.per_ks * 4 / (bww::kWaves * bww::accumulators_of(o.NPT, es, p.NQ < 256));   // columns
+    const long long longest_slice = its * 51 / (50 * 8 * (16 / es));
+    if (longest_slice == 0) return t;
+    // Workgroups to aim at, per CU: alone three, which hides most (752 channels, bf16: 89 us against 108 with two), beside
+    // grad-input one (bf16) or two (binary32): channel-expanding layer f32 219 us with one, 209 with two, bf16 64 and 70; 256 -> 256, 16x16,
+    // cg 1: 78 and 82, 31 and 36; 512 -> 1024, 7x7, cg 2, co 0.33: 56 and 55, 33 and 35; 37 x 336 -> 330, 20x41, cg 1: f32 132 and 122.
+    // A slice's partial sums are written and read once each: with more than a quarter of the values x and dy hold they cost
+    // more than the slices hide (256 -> 256, 16x16, cg 1, f32: 78 us at a quarter, 82 at a half).
+    const long long dw = (long long)p.Cout * p.L, values = (long long)(p.Cin + p.Cout) * p.NQ, quarter = values / (4 * dw);
+    long long best_time = -1;
+    for (int per_cu = !beside ? 3 : es == 2 ? 1 : 2; per_cu > 0; --per_cu) {
+        long long ks = 256 * per_cu / tiles;
+        ks = ks < quarter ? ks : quarter;
+        long long len = ks > 0 ? (rounds + ks - 1) / ks : rounds;
+        len = len < longest_slice ? len : longest_slice;
+        const long long slices = (rounds + len - 1) / len, time = (slices * tiles + 255) / 256 * len;   // of the busiest CU
+        if (best_time >= 0 && 100 * time >= 95 * best_time) continue;
+        best_time = time;
+        t.per_slice = (int)len;
+        t.KS = (int)slices;
+        if (es == 2) break;                             // not bound by the matrix pipe
+    }
+    // Layers with few columns and many weights (16 x 768 -> 1533 on 7x7, cg 1: f32 60 us per tile, 71 here) would mostly move
+    // partial sums; alone they also have to fit the buffer of scc_backward_weight_static, which runs the same kernels.
+    if (t.KS * dw > 2 * values || (!beside && t.KS * dw * 4 > (long long)SCC_STATIC_SCRATCH_BYTES)) t.KS = 0;
+    t.total = (int)(t.KS * tiles);
+    t.chunk = (t.total + 7) / 8;
     return t;
 }
 
@@ -280,22 +295,21 @@ inline bool weight_eligible(const Problem& p, int es)
 
 struct WeightCost {
     double there, here;   // planes fetched, columns included, by the per-tile kernel and by this one
-    double matrix;        // matrix time of this one over that of the per-tile kernel
+    double matrix;        // matrix time of the busiest CU with this one over that with the per-tile kernel
 };
 
-// The matrix time counts every tile of 32 x 32 in which a wavefront may wait for another one's (windows that reach a part of a
-// walk only leave matrix pipes idle: 227 x 400 -> 200 on 20x20, cg 2: twice the tiles, 203 against 146 us), and on the other side the
-// per-tile kernel's last generation of workgroups, one per CU (40 x 272 -> 270, cg 1: 270 of them on 256 CUs, 114 against 77 us).
-inline WeightCost weight_cost(const Problem& p, int es)
+// Both sides' matrix time counts every tile of 32 x 32 that some wavefront of a workgroup may wait for (windows that reach a part
+// of a walk only leave matrix pipes idle: 227 x 400 -> 200 on 20x20, cg 2: twice the tiles, f32 203 against 146 us) and the last
+// generation of workgroups (per-tile kernel on 40 x 272 -> 270, cg 1: 270 of them on 256 CUs, 114 us against 77 here).
+inline WeightCost weight_cost(const Problem& p, int es, const WeightTiling& t, int pt, bool beside)
 {
-    int pt;
-    const WeightTiling t = make_weight_tiling(p, es, &pt);
-    const bww::BwwTiling o = bww::make_tiling(p);
-    const long long tiles = (long long)o.IB * o.MB * o.NSC, groups = tiles * o.KS;
+    const bww::BwwTiling o = bww::make_tiling(p, beside);
+    const long long tiles = (long long)o.IB * o.MB * o.NSC, mine = (long long)t.NG * t.NSC;
     WeightCost c;
-    c.here = (double)t.NG * t.NSC * weight_rows(pt) * p.NQ;
+    c.here = (double)mine * weight_rows(pt) * p.NQ;
     c.there = (double)tiles * bww::rows_of(o.NPT) * p.NQ;
-    c.matrix = 4.0 * pt * t.NG * t.NSC / ((double)tiles * o.NPT) * (double)groups / (256.0 * ((groups + 255) / 256));
+    c.matrix = (double)((t.total + 255) / 256) * t.per_slice * (8 * 16 / es) * 4 * pt /
+               ((double)((tiles * o.KS + 255) / 256) * o.per_ks * 4 * o.NPT);
     return c;
 }
 

@@ -1,21 +1,18 @@
 // Both gradients of the layers whose tiles share their planes, in ONE launch behind the packing of the weights: the workgroups
 // of the shared grad-weight (scc_shared_bww_kernel.h) and those of the packed grad-input (scc_packed_kernel.h) are two ranges
-// of one grid.  Nothing about either computation changes (dw sums fewer slices than scc_backward_weight does).  Grad-weight
-// comes first, with one (bf16) or one and a half (binary32) workgroups per CU that stay for the whole launch; grad-input's
-// pass through what is left of the CUs, so that one range's matrix instructions run beside the other's loads and stores, and
-// both read the same eighth of the columns on an XCD, where part of dy is still on the chip for the second of them.
-// us, two launches -> one: 128 x 128 -> 512, 32x32, cg 2, co 0.33: f32 191 -> 182, bf16 79 -> 64; 128 x 256 -> 256, 16x16, cg 1: f32 74
-// -> 68, bf16 40 -> 32; 64 x 512 -> 1024, 7x7, cg 2, co 0.33 (from the per-tile kernels' merged launch): f32 58 -> 48, bf16 45 -> 33.
+// of one grid.  Nothing about either computation changes (dw sums other slices than scc_backward_weight does).  Grad-weight
+// comes first, with one (bf16) or two (binary32) workgroups per CU that stay for the whole launch; grad-input's pass through
+// what is left of the CUs, so that one range's matrix instructions run beside the other's loads and stores, and both read the
+// same eighth of the columns on an XCD, where part of dy is still on the chip for the second of them.
+// us, the per-tile kernels' merged launch -> this one: 128 x 128 -> 512, 32x32, cg 2, co 0.33: f32 261 -> 213, bf16 118 -> 62; 128 x 256 -> 256,
+// 16x16, cg 1: f32 80 -> 76, bf16 36 -> 31; 64 x 512 -> 1024, 7x7, cg 2, co 0.33: bf16 42 -> 34; 37 x 336 -> 330, 20x41, cg 1: f32 179 -> 130,
+// bf16 89 -> 46.
 #include "scc_packed_kernel.h"
 #include "scc_shared_bww_kernel.h"
 
 namespace scc {
 
 namespace {
-
-// workgroups of the grad-weight range: 256 / 512, us: the first layer above f32 219 / 209, bf16 64 / 70, the second 78 / 82, 31 / 36,
-// the third 56 / 55, 33 / 35; 37 x 336 -> 330 on 20x41, cg 1: f32 132 / 122
-constexpr int weight_workgroups(int es) { return es == 2 ? 256 : 512; }
 
 template <typename T_, int CT, int PT>
 __global__ __launch_bounds__(256, 3) void backward_shared(const T_* __restrict__ x, const T_* __restrict__ dy,
@@ -54,17 +51,22 @@ size_t partial_bytes(const Problem& p, const shared_bww::WeightTiling& t)
 }  // namespace
 
 // Taken where sharing saves enough plane fetches over the per-tile kernels of both passes (grad-weight's and grad-input's
-// together): measured on 39 layers against the merged launch of those, every one above the line gains 1.06 to 1.35 times,
-// those below 0.6 (deep layers with few columns) to 1.18; 65e6 lies between 128 x 256 -> 256 on 16x16 with cg 2 (59e6: 48 -> 51 us)
-// and 274 x 384 -> 384 on 14x14 with cg 8 (73e6, bf16: 63 -> 50).
+// together) and, binary32, where grad-weight's matrix time is at most 1.1 times theirs.  Measured against their merged launch.
+// bf16, 114 layers: above the lines 0.92 to 3 times as fast, median 1.4, those below 0.7 to 1.05; uneven layers, on which the per-tile
+// kernels lose more, from 37e6 on (28 x 416 -> 1664 on 9x6, 36.6e6: 0.78).  fp32, 107 layers: above the lines 0.97 to 1.7 times, median 1.2
+// (but 53 x 960 -> 1437 on 9x6, cg 8: 0.78); longer matrix times lose down to 0.8, and so do fewer fetches, uneven layers among them
+// (116 x 312 -> 156 on 9x9, 36e6: 0.78; 64 x 512 -> 1024 on 7x7, 39e6: 57 -> 56 us).
 size_t backward_shared_workspace(const Problem& p, int es)
 {
     const int ct = packed::tile_width<false>(p, es);
     if (ct == 0 || !shared_bww::weight_eligible(p, es)) return 0;
     const Band b = make_band(p);
+    int pt;
+    const shared_bww::WeightTiling t = shared_bww::make_weight_tiling(p, es, &pt, true);
+    if (t.KS == 0) return 0;
     double again;
-    const shared_bww::WeightCost c = shared_bww::weight_cost(p, es);
-    if (es == 4 && c.matrix > 1.4) return 0;
+    const shared_bww::WeightCost c = shared_bww::weight_cost(p, es, t, pt, true);
+    if (es == 4 && c.matrix > 1.1) return 0;
     double saved = c.there - c.here;
     saved += packed::fetches_without_sharing<false>(p, b, &again);
     for (int c0 = 0; c0 < p.Cin; c0 += 128) {
@@ -72,10 +74,8 @@ size_t backward_shared_workspace(const Problem& p, int es)
         packed::walk_of<false>(p, b, p.Cin, c0 / 128, first, len);
         saved -= (double)len * p.NQ;
     }
-    if (saved < (packed::uneven(p, b) ? (es == 2 ? 30e6 : 35e6) : 65e6)) return 0;
-    int pt;
-    return partial_bytes(p, shared_bww::make_weight_tiling(p, es, &pt, weight_workgroups(es))) +
-           packed::make_packed<false>(p, es, ct).bytes;
+    if (saved < (es == 2 && packed::uneven(p, b) ? 37e6 : 65e6)) return 0;
+    return partial_bytes(p, t) + packed::make_packed<false>(p, es, ct).bytes;
 }
 
 template <typename T_>
@@ -84,9 +84,9 @@ hipError_t launch_backward_shared(const T_* x, const T_* dy, const T_* w, T_* dx
 {
     constexpr int es = (int)sizeof(T_);
     int pt;
-    const shared_bww::WeightTiling tw = shared_bww::make_weight_tiling(p, es, &pt, weight_workgroups(es));
+    const shared_bww::WeightTiling tw = shared_bww::make_weight_tiling(p, es, &pt, true);
     const int ct = packed::tile_width<false>(p, es);
-    if (ct == 0) return hipErrorInvalidValue;
+    if (ct == 0 || tw.KS == 0) return hipErrorInvalidValue;
     const packed::Packed ti = packed::make_packed<false>(p, es, ct);
     float* part = (float*)workspace;
     char* packed_w = (char*)workspace + partial_bytes(p, tw);
