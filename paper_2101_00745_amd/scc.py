@@ -152,16 +152,24 @@ def _workspace_need(query, *shape):
     return int(getattr(load(), query)(*shape))
 
 
-def _scratch(need, dev):
+def _scratch(need, dev, workspace=None):
     """(tensor to keep alive until the call has been enqueued, its address, its size); nothing where nothing is needed."""
-    if need == 0:
-        return None, None, 0
-    t = torch.empty(need, dtype=torch.uint8, device=dev)
-    return t, t.data_ptr(), need
+    if workspace is None:
+        if need == 0:
+            return None, None, 0
+        workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+    return workspace, workspace.data_ptr(), workspace.numel() * workspace.element_size()
 
 
-def scc_forward(x, w, cg, co, out=None):
-    """y = SCC(x; w): x [N,Cin,H,W], w [Cout,Cin//cg] -> y [N,Cout,H,W] (same dtype)."""
+def scc_forward_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype=torch.float32):
+    code = SCC_F32 if dtype == torch.float32 else SCC_BF16
+    return int(load().scc_forward_workspace_bytes(N, Cin, Cout, H, W, cg, float(co), code))
+
+
+def scc_forward(x, w, cg, co, out=None, workspace=None):
+    """y = SCC(x; w): x [N,Cin,H,W], w [Cout,Cin//cg] -> y [N,Cout,H,W] (same dtype).  Layers that pack their weights take a
+    workspace for it; without one it is allocated, unless `out` is given: such a call allocates nothing and runs the
+    kernels that need none."""
     dev = _dev(x, w)
     N, Cin, H, W = x.shape
     Cout = w.shape[0]
@@ -172,13 +180,19 @@ def scc_forward(x, w, cg, co, out=None):
         _dev(out)
         assert out.shape == (N, Cout, H, W) and out.dtype == x.dtype
     shape = (N, Cin, Cout, H, W, cg, float(co), _dtype_code(x))
-    ws, ws_ptr, ws_len = _scratch(_workspace_need("scc_forward_workspace_bytes", *shape), dev)
+    need = _workspace_need("scc_forward_workspace_bytes", *shape) if workspace is None and out is None else 0
+    ws, ws_ptr, ws_len = _scratch(need, dev, workspace)
     _launch(dev, load().scc_forward_ws, x.data_ptr(), w.data_ptr(), y.data_ptr(), *shape, ws_ptr, ws_len)
     return y
 
 
-def scc_backward_input(dy, w, Cin, cg, co, out=None):
-    """dx from dy [N,Cout,H,W] and w [Cout,Cin//cg] -> dx [N,Cin,H,W]."""
+def scc_backward_input_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype=torch.float32):
+    code = SCC_F32 if dtype == torch.float32 else SCC_BF16
+    return int(load().scc_backward_input_workspace_bytes(N, Cin, Cout, H, W, cg, float(co), code))
+
+
+def scc_backward_input(dy, w, Cin, cg, co, out=None, workspace=None):
+    """dx from dy [N,Cout,H,W] and w [Cout,Cin//cg] -> dx [N,Cin,H,W].  out, workspace: as for scc_forward."""
     dev = _dev(dy, w)
     N, Cout, H, W = dy.shape
     if w.dtype != dy.dtype or w.dim() != 2 or w.shape[0] != Cout or \
@@ -189,7 +203,8 @@ def scc_backward_input(dy, w, Cin, cg, co, out=None):
         _dev(out)
         assert out.shape == (N, Cin, H, W) and out.dtype == dy.dtype
     shape = (N, Cin, Cout, H, W, cg, float(co), _dtype_code(dy))
-    ws, ws_ptr, ws_len = _scratch(_workspace_need("scc_backward_input_workspace_bytes", *shape), dev)
+    need = _workspace_need("scc_backward_input_workspace_bytes", *shape) if workspace is None and out is None else 0
+    ws, ws_ptr, ws_len = _scratch(need, dev, workspace)
     _launch(dev, load().scc_backward_input_ws, dy.data_ptr(), w.data_ptr(), dx.data_ptr(), *shape, ws_ptr, ws_len)
     return dx
 

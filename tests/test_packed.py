@@ -67,3 +67,33 @@ def test_queries_of_bad_arguments_are_zero():
     for bad in ((0, 8, 8, 4, 4, 2, 0.5, 0), (1, 9, 8, 4, 4, 2, 0.5, 0), (1, 8, 8, 4, 4, 2, 1.5, 0), (1, 8, 8, 4, 4, 2, 0.5, 7)):
         assert B.load().scc_forward_workspace_bytes(*bad) == 0
         assert B.load().scc_backward_input_workspace_bytes(*bad) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which,dtype,shape", [CASES[0], CASES[7], CASES[10], CASES[15]])
+def test_calls_with_out_allocate_nothing_and_a_workspace_can_be_handed_over(which, dtype, shape):
+    N, Cin, Cout, H, W, cg, co = shape
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    src, dst = (Cin, Cout) if which == "forward" else (Cout, Cin)
+    x = torch.randn(N, src, H, W, generator=gen, device="cuda").to(td)
+    w = torch.randn(Cout, Cin // cg, generator=gen, device="cuda").to(td)
+    out = torch.empty(N, dst, H, W, dtype=td, device="cuda")
+
+    def call(**kw):
+        return S.scc_forward(x, w, cg, co, **kw) if which == "forward" else S.scc_backward_input(x, w, Cin, cg, co, **kw)
+
+    plain = call()
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    assert call(out=out) is out
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+    bar = 2e-5 if dtype == "f32" else 1e-2
+    assert float((out.float() - plain.float()).abs().max()) <= bar * float(plain.float().abs().max())
+    query = S.scc_forward_workspace_bytes if which == "forward" else S.scc_backward_input_workspace_bytes
+    ws = torch.empty(query(*shape, td), dtype=torch.uint8, device="cuda")
+    before = torch.cuda.memory_stats()["allocation.all.allocated"]
+    call(out=out, workspace=ws)
+    assert torch.cuda.memory_stats()["allocation.all.allocated"] == before
+    assert torch.equal(out, plain)
+    with pytest.raises(S.SccError):
+        call(out=out, workspace=ws[:-1])
