@@ -375,7 +375,8 @@ def scc_dw_forward(x, kdw, w, cg, co, dw_stride=1, out=None, workspace=None, fus
     Ho, Wo = _out(H, dw_stride), _out(W, dw_stride)
     if fused is False:
         z = scc_depthwise3x3_forward(x, kdw, dw_stride)
-        return scc_forward(z, w, cg, co, out=out)
+        # an out tensor: no packing of the weights, as in the library's own two stages
+        return scc_forward(z, w, cg, co, out=x.new_empty((N, Cout, Ho, Wo)) if out is None else out)
     shape = (N, Cin, Cout, H, W, dw_stride, cg, float(co), _dtype_code(x))
     need = _workspace_need("scc_dw_forward_workspace_bytes", *shape)
     if fused:

@@ -310,3 +310,17 @@ def test_block_module_trains(S):
         opt.step()
         losses.append(float(loss.detach()))
     assert losses[-1] < 0.5 * losses[0], losses[::10]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_two_stages_are_the_librarys_own(S, dtype):
+    """fused=False and a block the library runs in two stages: the same kernels, bit for bit, also on a layer whose stand-alone
+    forward packs its weights."""
+    layer = layer_of(130, 120, 500, 11, 9, 2, 0.33)          # 120 channels: not a layer for the fused kernel
+    assert S.scc_forward_workspace_bytes(layer.N, layer.Cin, layer.Cout, layer.H, layer.W, layer.cg, layer.co, dtype) > 0
+    xin, kdw, w = Wk.make_block_inputs(layer, 1)
+    xd, kd, wd = (to_dev(a, dtype) for a in (xin, kdw, w))
+    own = S.scc_dw_forward(xd, kd, wd, layer.cg, layer.co, 1)
+    out = torch.empty_like(own)
+    S.scc_dw_forward(xd, kd, wd, layer.cg, layer.co, 1, out=out, fused=False)
+    assert torch.equal(own, S.scc_dw_forward(xd, kd, wd, layer.cg, layer.co, 1, fused=False)) and torch.equal(own, out)
