@@ -129,7 +129,12 @@ def _dev(*tensors):
     return dev
 
 
-_raw_stream = torch._C._cuda_getCurrentRawStream    # the address alone: torch.cuda.current_stream builds a Stream object around it
+def _stream_address(index):
+    return torch.cuda.current_stream(index).cuda_stream
+
+
+# the address alone, without a Stream object around it; a torch that lacks this function still has the other way
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", _stream_address)
 
 
 def _launch(dev, call, *args):

@@ -196,3 +196,23 @@ def test_binding_refuses_cpu_tensors():
         S.scc_backward_input(x, w, 4, 2, 0.5)
     with pytest.raises(ValueError):
         S.scc_backward_weight(x, x, 2, 0.5)
+
+
+def test_package_imports_on_a_torch_without_the_raw_stream_function():
+    """The function is not part of torch's public interface; host-only calls need no stream at all."""
+    import subprocess
+    import sys
+    code = ("import torch\n"
+            "if hasattr(torch._C, '_cuda_getCurrentRawStream'): del torch._C._cuda_getCurrentRawStream\n"
+            "import paper_2101_00745_amd as S\n"
+            "assert S.scc_window_params(4, 4, 2, 0.5) == (2, 1, 4) and S.scc._raw_stream is S.scc._stream_address\n")
+    subprocess.run([sys.executable, "-c", code], cwd=ROOT, check=True, timeout=300)
+
+
+@pytest.mark.gpu
+def test_both_ways_to_the_stream_agree():
+    import torch
+    for stream in (torch.cuda.default_stream(), torch.cuda.Stream()):
+        with torch.cuda.stream(stream):
+            index = torch.cuda.current_device()
+            assert B._raw_stream(index) == B._stream_address(index) == stream.cuda_stream
