@@ -19,11 +19,24 @@ namespace scc {
 
 namespace {
 
+// Wavefronts per SIMD that a variant's registers have to leave room for.  Unbounded, the compiler keeps accumulators apart from
+// the other registers and copies between the two: with the four accumulators of grad-weight's narrow tiles (NPT 1) a SIMD then
+// holds two wavefronts instead of three (11 x 320 -> 1280 on 16x16, cg 2, f32: 42 us, with this bound 37.5), with three position
+// tiles as well, and with a contraction shared by four wavefronts (S 4) one instead of two (64 x 512 -> 1024 on 7x7, cg 2,
+// co 0.33, f32: 57 -> 47; 128 x 512 -> 512 on 4x4, cg 2, bf16: 17.6 -> 12.5).  1: as it is; no more would fit, or nothing is gained
+// (882 x 256 -> 128 on 16x16, cg 4, f32: 133 us, 136 with a bound of two).
 template <typename T_, int CT, int S, int NPT, bool SMALL>
-__global__ __launch_bounds__(256) void backward_merged(const T_* __restrict__ x, const T_* __restrict__ dy,
-                                                       const T_* __restrict__ w, T_* __restrict__ dx,
-                                                       float* __restrict__ out, Problem P, bwi::BwiTiling TI,
-                                                       bww::BwwTiling TW, int nbww)
+constexpr int least_waves()
+{
+    if (SMALL) return 1;
+    if (CT == 4) return S == 4 ? 2 : sizeof(T_) == 2 ? 3 : 1;
+    return NPT == 2 ? 1 : 3;
+}
+
+template <typename T_, int CT, int S, int NPT, bool SMALL>
+__global__ __launch_bounds__(256, (least_waves<T_, CT, S, NPT, SMALL>())) void backward_merged(
+    const T_* __restrict__ x, const T_* __restrict__ dy, const T_* __restrict__ w, T_* __restrict__ dx, float* __restrict__ out,
+    Problem P, bwi::BwiTiling TI, bww::BwwTiling TW, int nbww)
 {
     // the dynamic LDS is the grad-weight range's staging area; the grad-input range, which a workgroup never is at
     // the same time, adds its shared tiles' partial sums in it

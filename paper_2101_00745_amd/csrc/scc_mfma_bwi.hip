@@ -18,8 +18,10 @@ namespace scc {
 
 namespace {
 
+// The bound as in scc_mfma_fwd.hip: 320 registers without it (16 x 960 -> 960 on 14x7, cg 4, bf16: 20 -> 14 us; 64 x 512 -> 1024 on 7x7,
+// cg 2, co 0.33, f32 30 -> 25, bf16 26 -> 18).
 template <typename T_, int CT, int KC, int S, int WPB>
-__global__ __launch_bounds__(WPB * 64) void backward_input_mfma32(const T_* __restrict__ dy, const T_* __restrict__ w,
+__global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void backward_input_mfma32(const T_* __restrict__ dy, const T_* __restrict__ w,
                                                              T_* __restrict__ dx, Problem P, bwi::BwiTiling T)
 {
     bwi::backward_input_body<T_, CT, KC, S, WPB>(dy, w, dx, P, T, (int)blockIdx.x);

@@ -53,8 +53,11 @@ struct FwdTiling {
 //      resident at once, and without the stagger all of them load, then all multiply, then all store; with
 //      it one half's stores and arithmetic overlap the other half's loads (17 against 19-21 us at the metric
 //      layer; used only where it wins, see launch_chunk).
+// Four columns per lane and a contraction shared by four wavefronts: unbounded, the compiler takes 320 registers, which leaves
+// one wavefront per SIMD. Bounded to two (256, a few dwords spilled outside the loops), us: 64 x 512 -> 1024 on 7x7, cg 2, co 0.33,
+// f32 47 -> 34, bf16 37 -> 23; 15 x 608 -> 2432 on 7x9, cg 2, bf16 30 -> 21.
 template <typename T_, int CT, int KC, bool AL4, int S, int WPB>
-__global__ __launch_bounds__(WPB * 64) void forward_mfma32(const T_* __restrict__ x, const T_* __restrict__ w,
+__global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void forward_mfma32(const T_* __restrict__ x, const T_* __restrict__ w,
                                                       T_* __restrict__ y, Problem P, FwdTiling T)
 {
     typedef T_ bvec __attribute__((ext_vector_type(CT), aligned(sizeof(T_))));   // CT consecutive columns of one plane
