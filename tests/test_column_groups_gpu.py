@@ -32,3 +32,21 @@ def test_every_remainder(shape, dtype, tol):
     for got, ref, bar in ((y, O.forward(x, w, cg, co), tol), (dx, rdx, tol), (dx2, rdx, tol), (dw, rdw, 2e-5), (dw2, rdw, 2e-5)):
         err = np.max(np.abs(got.float().cpu().numpy() - ref)) / np.max(np.abs(ref))
         assert err <= bar, (shape, dtype, err)
+
+
+# planes that are no multiple of 4 pixels whose wide tiles would be shared by four wavefronts: pairs of columns, one, two and four
+# wavefronts per tile; the last has too few pairs and keeps the wide tiles
+THIN = [(64, 512, 1024, 7, 7, 2, 0.33), (9, 360, 1440, 14, 7, 1, 0.0), (38, 384, 576, 7, 7, 1, 0.5), (5, 512, 448, 5, 5, 1, 0.5)]
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float32, 2e-5), (torch.bfloat16, 1e-2)])
+@pytest.mark.parametrize("shape", THIN)
+def test_forward_of_thin_layers_without_workspace(shape, dtype, tol):
+    import paper_2101_00745_amd as S
+    N, Cin, Cout, H, W, cg, co = shape
+    layer = Wk.Layer("thin", 9, N=N, Cin=Cin, Cout=Cout, H=H, W=W, cg=cg, co=co)
+    xd, wd, _ = (torch.from_numpy(a).to(dtype).cuda() for a in Wk.make_inputs(layer))
+    out = torch.full((N, Cout, H, W), float("nan"), dtype=dtype, device="cuda")
+    S.scc_forward(xd, wd, cg, co, out=out)
+    ref = O.forward(xd.float().cpu().numpy(), wd.float().cpu().numpy(), cg, co)
+    assert np.max(np.abs(out.float().cpu().numpy() - ref)) <= tol * np.max(np.abs(ref))
