@@ -179,6 +179,27 @@ int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* d
                  scc_dtype dtype, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * Which kernels scc_backward_weight and scc_backward run a layer on, given a workspace of that many bytes (256-byte aligned)
+ * and tensors aligned to 16 bytes: the decision the calls themselves take.  Host only; a negative scc_status where the
+ * call would be refused.
+ */
+typedef enum {
+    SCC_WEIGHT_ANY = 0,     /* the kernel for any shape */
+    SCC_WEIGHT_TILE = 1,    /* a filter tile per wavefront */
+    SCC_WEIGHT_SHARED = 2   /* both operands shared by four filter tiles */
+} scc_weight_path;
+typedef enum {
+    SCC_BACKWARD_TWO_PASSES = 0,   /* scc_backward_input, then scc_backward_weight */
+    SCC_BACKWARD_MERGED = 1,       /* the per-tile kernels of both as one launch */
+    SCC_BACKWARD_SHARED = 2,       /* grad-input with packed weights and shared grad-weight as one launch */
+    SCC_BACKWARD_FUSED = 3         /* dy and x read once for both gradients */
+} scc_backward_paths;
+int scc_backward_weight_path(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype,
+                             size_t workspace_bytes);
+int scc_backward_path(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype,
+                      size_t workspace_bytes);
+
+/*
  * Depthwise 3x3 stage of a DW + SCC block (Eq. 2 of the paper):
  *     z[n,a,m,q] = sum_{i,j in 0..2} kdw[a,i,j] * x[n,a, s*m + i - 1, s*q + j - 1],   s = dw_stride,
  * pixels outside the H x W map counting as zero (the filter is centred on input pixel (s*m, s*q), no

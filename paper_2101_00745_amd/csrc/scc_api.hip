@@ -130,15 +130,24 @@ size_t weight_shared_need(const Problem& p, scc_dtype dtype)   // 0: not a layer
     return scc::backward_weight_shared_preferred(p, es) ? scc::backward_weight_shared_workspace(p, es) : 0;
 }
 
-int run_weight(const void* x, const void* dy, void* dw, const Problem& p, scc_dtype dtype, bool shared, void* workspace,
+// SCC_WEIGHT_*, or SCC_ERR_WORKSPACE.
+int weight_path(const Problem& p, scc_dtype dtype, const void* workspace, size_t workspace_bytes)
+{
+    if (!holds(weight_least(p), workspace, workspace_bytes)) return SCC_ERR_WORKSPACE;
+    const size_t need = weight_shared_need(p, dtype);
+    if (need > 0 && holds(need, workspace, workspace_bytes)) return SCC_WEIGHT_SHARED;
+    return scc::backward_weight_mfma_eligible(p) ? SCC_WEIGHT_TILE : SCC_WEIGHT_ANY;
+}
+
+int run_weight(const void* x, const void* dy, void* dw, const Problem& p, scc_dtype dtype, int path, void* workspace,
                hipStream_t st)
 {
     drop_stale_error();
     return with_type(dtype, [&](auto t) {
         typedef const decltype(t)* In;
-        if (shared)
+        if (path == SCC_WEIGHT_SHARED)
             return launch_status(scc::launch_backward_weight_shared((In)x, (In)dy, (float*)dw, (float*)workspace, p, st));
-        if (scc::backward_weight_mfma_eligible(p))
+        if (path == SCC_WEIGHT_TILE)
             return launch_status(scc::launch_backward_weight_mfma((In)x, (In)dy, (float*)dw, (float*)workspace, p, st));
         return launch_status(scc::launch_backward_weight_generic((In)x, (In)dy, (float*)dw, p, st));
     });
@@ -230,9 +239,9 @@ int scc_backward_weight(const void* x, const void* dy, void* dw, int N, int Cin,
     const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    if (!holds(weight_least(p), workspace, workspace_bytes)) return SCC_ERR_WORKSPACE;
-    const size_t need = weight_shared_need(p, dtype);
-    return run_weight(x, dy, dw, p, dtype, need > 0 && holds(need, workspace, workspace_bytes), workspace, (hipStream_t)stream);
+    const int path = weight_path(p, dtype, workspace, workspace_bytes);
+    if (path < 0) return path;
+    return run_weight(x, dy, dw, p, dtype, path, workspace, (hipStream_t)stream);
 }
 
 // scc_backward: what a call cannot do without, whichever of the kernels that follow runs (tensors that are not aligned to
@@ -247,6 +256,36 @@ static size_t backward_shared_need(const Problem& p, scc_dtype dtype)
 {
     if (dtype == SCC_F32 && scc::backward_fused_eligible(p)) return 0;
     return scc::backward_shared_workspace(p, size_of(dtype));
+}
+
+// SCC_BACKWARD_*, or SCC_ERR_WORKSPACE.
+static int backward_path(const Problem& p, scc_dtype dtype, bool aligned, const void* workspace, size_t workspace_bytes)
+{
+    if (!holds(backward_least(p, dtype), workspace, workspace_bytes)) return SCC_ERR_WORKSPACE;
+    if (dtype == SCC_F32 && aligned && scc::backward_fused_eligible(p)) return SCC_BACKWARD_FUSED;
+    const size_t shared = backward_shared_need(p, dtype);
+    if (shared > 0 && holds(shared, workspace, workspace_bytes)) return SCC_BACKWARD_SHARED;
+    // layers both per-tile kernels take: their two grids as one launch
+    const bool merged = with_type(dtype, [&](auto t) { return (int)scc::backward_merged_applicable<decltype(t)>(p); });
+    return merged ? SCC_BACKWARD_MERGED : SCC_BACKWARD_TWO_PASSES;
+}
+
+int scc_backward_weight_path(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype, size_t workspace_bytes)
+{
+    Problem p;
+    const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
+    if (rc != SCC_OK) return rc;
+    if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
+    return weight_path(p, dtype, workspace_bytes ? (const void*)256 : nullptr, workspace_bytes);   // any aligned address
+}
+
+int scc_backward_path(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype, size_t workspace_bytes)
+{
+    Problem p;
+    const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
+    if (rc != SCC_OK) return rc;
+    if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
+    return backward_path(p, dtype, true, workspace_bytes ? (const void*)256 : nullptr, workspace_bytes);
 }
 
 size_t scc_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype)
@@ -268,31 +307,23 @@ int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* d
     const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    if (!holds(backward_least(p, dtype), workspace, workspace_bytes)) return SCC_ERR_WORKSPACE;
-    drop_stale_error();
     const bool aligned = (((uintptr_t)x | (uintptr_t)dy | (uintptr_t)dx) & 15u) == 0;
-    if (dtype == SCC_F32 && aligned && scc::backward_fused_eligible(p))
+    const int path = backward_path(p, dtype, aligned, workspace, workspace_bytes);
+    if (path < 0) return path;
+    drop_stale_error();
+    const hipStream_t st = (hipStream_t)stream;
+    if (path == SCC_BACKWARD_FUSED)
         return launch_status(scc::launch_backward_fused((const float*)x, (const float*)dy, (const float*)w, (float*)dx,
-                                                        (float*)dw, (float*)workspace, p, (hipStream_t)stream));
-    const size_t shared = backward_shared_need(p, dtype);
-    if (shared > 0 && holds(shared, workspace, workspace_bytes)) {
+                                                        (float*)dw, (float*)workspace, p, st));
+    if (path == SCC_BACKWARD_SHARED || path == SCC_BACKWARD_MERGED)
         return with_type(dtype, [&](auto t) {
             typedef decltype(t) T;
-            return launch_status(scc::launch_backward_shared((const T*)x, (const T*)dy, (const T*)w, (T*)dx, (float*)dw,
-                                                             workspace, p, (hipStream_t)stream));
+            return launch_status(path == SCC_BACKWARD_SHARED
+                                     ? scc::launch_backward_shared((const T*)x, (const T*)dy, (const T*)w, (T*)dx, (float*)dw,
+                                                                   workspace, p, st)
+                                     : scc::launch_backward_merged((const T*)x, (const T*)dy, (const T*)w, (T*)dx, (float*)dw,
+                                                                   (float*)workspace, p, st));
         });
-    }
-    // layers both matrix-core kernels take: their two grids as one launch
-    if (dtype == SCC_F32) {
-        if (scc::backward_merged_applicable<float>(p))
-            return launch_status(scc::launch_backward_merged((const float*)x, (const float*)dy, (const float*)w,
-                                                             (float*)dx, (float*)dw, (float*)workspace, p,
-                                                             (hipStream_t)stream));
-    } else if (scc::backward_merged_applicable<scc::bf16_t>(p)) {
-        return launch_status(scc::launch_backward_merged((const scc::bf16_t*)x, (const scc::bf16_t*)dy,
-                                                         (const scc::bf16_t*)w, (scc::bf16_t*)dx, (float*)dw,
-                                                         (float*)workspace, p, (hipStream_t)stream));
-    }
     // every other layer: the two passes one after the other
     const int r1 = scc_backward_input(dy, w, dx, N, Cin, Cout, H, W, cg, co, dtype, stream);
     if (r1 != SCC_OK) return r1;
@@ -474,14 +505,14 @@ int scc_backward_weight_static(const void* x, const void* dy, void* dw, int N, i
     const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    const size_t shared = weight_shared_need(p, dtype), need = std::max(weight_least(p), shared);
+    const size_t need = std::max(weight_least(p), weight_shared_need(p, dtype));
     if (need > (size_t)SCC_STATIC_SCRATCH_BYTES) return SCC_ERR_SCRATCH;
     void* ptr = nullptr;
     if (need > 0) {
         const int sc = scratch_of_current_device(&ptr);
         if (sc != SCC_OK) return sc;
     }
-    return run_weight(x, dy, dw, p, dtype, shared > 0, ptr, (hipStream_t)stream);
+    return run_weight(x, dy, dw, p, dtype, weight_path(p, dtype, ptr, need), ptr, (hipStream_t)stream);
 }
 
 const char* scc_status_string(int status)

@@ -1,8 +1,9 @@
 """Grad-weight with both operands shared by four filter tiles, on layers that take this path, against the fp64 oracle: row
 groups and position chunks that are full, ragged and wrap, 2, 3 and 4 position tiles per workgroup, slices whose last round
 is partial, planes of any remainder.  Bar: the suite's 2e-5 of the largest value (dw is binary32 in both data types); and the
-error's 2-norm, which grows with the square root of the number of columns, 2**-24 * sqrt(N*H*W / 16) for one rounding per K group
-of 16 columns, with a factor of 4 for the six products of a group."""
+error's 2-norm, 2**-24 * sqrt(N*H*W / 64): these layers are cut into at least 28 slices, a slice of n columns rounds its growing sum
+n / 2 times (binary32, two columns a time) or n / 16 (bf16) by 2**-24 at most, which leaves 2**-24 * sqrt(n / 4) of the result
+where partial sums grow as their square root, and sqrt(N*H*W / 112) of it for n = N*H*W / 28; the rest is for the sum over the slices."""
 import numpy as np
 import pytest
 import torch
@@ -23,10 +24,38 @@ def workspace(dtype, shape):
     return S.load().scc_backward_weight_workspace_bytes(*shape, 0 if dtype == "f32" else 1)
 
 
+ANY, TILE, SHARED = 0, 1, 2                       # scc_weight_path of include/scc.h
+TWO_PASSES, MERGED, BOTH_SHARED, FUSED = 0, 1, 2, 3   # scc_backward_paths
+
+
+def path(which, dtype, shape, size):
+    return getattr(S.load(), "scc_%s_path" % which)(*shape, 0 if dtype == "f32" else 1, size)
+
+
 @pytest.mark.parametrize("dtype,shape", CASES)
 def test_layers_here_take_the_path(dtype, shape):
-    # the per-tile kernel cuts the columns into at most 256 slices of all tiles and asks for 4 MiB at most
-    assert 4 << 20 < workspace(dtype, shape) <= S.scc.STATIC_SCRATCH_BYTES
+    need = workspace(dtype, shape)
+    assert need <= S.scc.STATIC_SCRATCH_BYTES
+    # 6 MiB: the per-tile kernel's up to 510 tiles of 12 KiB
+    assert [path("backward_weight", dtype, shape, size) for size in (need, need - 1, 6 << 20)] == [SHARED, TILE, TILE]
+
+
+@pytest.mark.parametrize("shape,want", [((128, 256, 256, 16, 16, 4, 0.5, 0), (TILE, FUSED)), ((128, 256, 256, 16, 16, 4, 0.5, 1), (TILE, MERGED)),
+                                        ((2, 8, 6, 3, 3, 2, 0.5, 0), (ANY, TWO_PASSES)), ((300, 32, 40, 1, 1, 2, 0.5, 0), (TILE, TWO_PASSES)),
+                                        ((64, 1440, 510, 6, 6, 1, 0.5, 0), (TILE, MERGED)), ((64, 2048, 2048, 7, 7, 2, 0.5, 0), (SHARED, BOTH_SHARED)),
+                                        ((190, 800, 69, 16, 16, 8, 0.0, 1), (SHARED, MERGED))])
+def test_paths_of_other_layers(shape, want):
+    lib = S.load()
+    sizes = lib.scc_backward_weight_workspace_bytes(*shape), lib.scc_backward_workspace_bytes(*shape)
+    assert (lib.scc_backward_weight_path(*shape, sizes[0]), lib.scc_backward_path(*shape, sizes[1])) == want
+
+
+def test_paths_of_calls_that_are_refused():
+    lib = S.load()
+    for name in ("scc_backward_weight_path", "scc_backward_path"):
+        call = getattr(lib, name)
+        assert call(0, 8, 8, 4, 4, 2, 0.5, 0, 0) == -2 and call(1, 8, 8, 4, 4, 2, 1.5, 0, 0) == -3 and call(1, 8, 8, 4, 4, 2, 0.5, 7, 0) == -4
+        assert call(128, 256, 256, 16, 16, 4, 0.5, 0, 1024) == -5
 
 
 @pytest.mark.gpu
@@ -40,7 +69,7 @@ def test_parity_and_repeat(dtype, shape):
     dw = S.scc_backward_weight(xd, dyd, cg, co)
     got = dw.cpu().numpy().astype(np.float64)
     assert np.max(np.abs(got - ref)) <= 2e-5 * np.max(np.abs(ref))
-    assert np.linalg.norm(got - ref) <= 4 * 2.0 ** -24 * np.sqrt(N * H * W / 16) * np.linalg.norm(ref)
+    assert np.linalg.norm(got - ref) <= 2.0 ** -24 * np.sqrt(N * H * W / 64) * np.linalg.norm(ref)
     assert torch.equal(dw, S.scc_backward_weight(xd, dyd, cg, co))
     static = torch.empty_like(dw)
     S.scc_backward_weight_static(xd, dyd, cg, co, static)       # the same kernels on the library's own buffer
@@ -59,11 +88,11 @@ def backward_workspace(dtype, shape):
     return S.load().scc_backward_workspace_bytes(*shape, 0 if dtype == "f32" else 1)
 
 
-@pytest.mark.parametrize("dtype,shape", [c for c in BOTH if c != BELOW])
+@pytest.mark.parametrize("dtype,shape", BOTH)
 def test_layers_here_take_one_launch(dtype, shape):
-    # its workspace holds the packed weights as well: 16-position groups x 128 rows x 16 positions x (3 pieces or 1) of 2 bytes
-    Cin, Cout = shape[1], shape[2]
-    assert backward_workspace(dtype, shape) >= 8 * 4 * Cout * (Cin // shape[5]) + Cin * Cin // shape[5] * (6 if dtype == "f32" else 2)
+    need, least = backward_workspace(dtype, shape), 6 << 20
+    assert path("backward", dtype, shape, need) == (MERGED if (dtype, shape) == BELOW else BOTH_SHARED)
+    assert path("backward", dtype, shape, least) == MERGED
 
 
 @pytest.mark.gpu
@@ -103,7 +132,7 @@ def test_products_are_binary32_to_the_end_of_the_exponent_range(shape, which):
     else:
         dw = S.scc_backward_weight(x, dy, cg, co)
     got = dw.cpu().numpy().astype(np.float64)
-    assert np.linalg.norm(got - ref) <= 4 * 2.0 ** -24 * np.sqrt(N * H * W / 16) * np.linalg.norm(ref)
+    assert np.linalg.norm(got - ref) <= 2.0 ** -24 * np.sqrt(N * H * W / 64) * np.linalg.norm(ref)
 
 
 @pytest.mark.gpu
@@ -150,3 +179,36 @@ def test_sums_are_no_longer_than_the_per_tile_kernels(dtype, shape):
                                          ("f32", (4, 2048, 2048, 7, 7, 1, 0.5))])
 def test_few_columns_and_many_weights_are_not_cut_into_copies_of_dw(dtype, shape):
     assert backward_workspace(dtype, shape) == 0
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype,shape", [BOTH[0], BOTH[1], BOTH[3], BOTH[6]])
+def test_both_gradients_in_a_graph(dtype, shape):
+    """Every replay against the eager result, with other work and new inputs in between."""
+    N, Cin, Cout, H, W, cg, co = shape
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    x, dy = (torch.randn(N, c, H, W, generator=gen, device="cuda").to(td) for c in (Cin, Cout))
+    w = torch.randn(Cout, Cin // cg, generator=gen, device="cuda").to(td)
+    dx, dw, alone = torch.empty_like(x), torch.empty(w.shape, device="cuda"), torch.empty(w.shape, device="cuda")
+    ws = torch.empty(backward_workspace(dtype, shape), dtype=torch.uint8, device="cuda")
+
+    def call():
+        S.scc_backward(x, dy, w, cg, co, out_dx=dx, out_dw=dw, workspace=ws)
+        S.scc_backward_weight_static(x, dy, cg, co, alone)
+
+    call()                                               # code objects are loaded before the capture
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call()
+    for _ in range(3):
+        for t in (x, dy, w):
+            t.copy_(torch.randn(t.shape, generator=gen, device="cuda"))
+        for t in (dx, dw, alone):
+            t.fill_(float("nan"))
+        ws.fill_(255)
+        graph.replay()
+        torch.cuda.synchronize()
+        want = S.scc_backward(x, dy, w, cg, co)
+        assert torch.equal(dx, want[0]) and torch.equal(dw, want[1]) and torch.equal(alone, S.scc_backward_weight(x, dy, cg, co))
