@@ -91,9 +91,12 @@ hipError_t launch_backward_merged(const T_* x, const T_* dy, const T_* w, T_* dx
     bwi::select_backward_input<T_>(p, [&](auto ct, auto s, auto wpb, const bwi::BwiTiling& ti, long long nbwi) {
         constexpr int CT = decltype(ct)::value, S = decltype(s)::value, WPB = decltype(wpb)::value;
         if constexpr (WPB == 4) {
-            if (sizeof(T_) == 4 && p.NQ < 256)
-                e = launch_variant<T_, CT, S, 1, true>(x, dy, w, dx, out, p, ti, nbwi, tw, st);
-            else if (tw.NPT == 1)
+            if constexpr (sizeof(T_) == 4)
+                if (p.NQ < 256) {
+                    e = launch_variant<T_, CT, S, 1, true>(x, dy, w, dx, out, p, ti, nbwi, tw, st);
+                    return;
+                }
+            if (tw.NPT == 1)
                 e = launch_variant<T_, CT, S, 1>(x, dy, w, dx, out, p, ti, nbwi, tw, st);
             else if (tw.NPT == 2)
                 e = launch_variant<T_, CT, S, 2>(x, dy, w, dx, out, p, ti, nbwi, tw, st);

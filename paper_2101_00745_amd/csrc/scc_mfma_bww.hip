@@ -126,9 +126,9 @@ hipError_t launch_backward_weight_mfma(const T_* x, const T_* dy, float* dw, flo
     const dim3 grid((unsigned)blocks), block(kWaves * 64);
     hipError_t e = hipSuccess;
     const bool vec = p.HW >= 4;
-    if (sizeof(T_) == 4 && p.NQ < 256)
-        e = vec ? launch_tile<T_, 1, true, true>(grid, block, st, x, dy, out, p, t)
-                : launch_tile<T_, 1, false, true>(grid, block, st, x, dy, out, p, t);
+    if (constexpr bool binary32 = sizeof(T_) == 4; binary32 && p.NQ < 256)
+        e = vec ? launch_tile<T_, 1, true, binary32>(grid, block, st, x, dy, out, p, t)
+                : launch_tile<T_, 1, false, binary32>(grid, block, st, x, dy, out, p, t);
     else if (t.NPT == 1)
         e = vec ? launch_tile<T_, 1, true>(grid, block, st, x, dy, out, p, t)
                 : launch_tile<T_, 1, false>(grid, block, st, x, dy, out, p, t);
