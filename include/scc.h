@@ -27,8 +27,9 @@
  *   - dtype SCC_F32: all tensors are IEEE binary32 and all sums are binary32.
  *     Products are binary32 products, or (forward, grad-input and the fused
  *     backward on the matrix cores) six of the nine partial products of an
- *     exact three-way bfloat16 split of both factors, which differ from the
- *     binary32 product by less than 2^-23 of it.
+ *     exact three-way bfloat16 split of both factors (by truncation), which
+ *     fall short of the product by less than 2^-21 of it (normal factors: by
+ *     0.7 x 2^-24 on average).
  *     Finite inputs: a filter never sees a channel outside its window, and
  *     all-zero weights give exact zeros.  Non-finite inputs: an Inf or NaN
  *     element gives NaN where binary32 arithmetic would give Inf, and in the
@@ -38,9 +39,9 @@
  *     grad-weight, which sums over all samples and pixels, it may reach any
  *     weight gradient.
  *     Operands below about 2^-110 in magnitude lose the low pieces of the
- *     split to underflow: the error is then bounded by a fraction of the
- *     smallest normal number instead of 2^-23 of the product (scc_backward_weight
- *     multiplies in binary32 and is not affected).
+ *     split to underflow: such an operand is then off by up to 2^-126, and its
+ *     products by that much of the other factor (scc_backward_weight multiplies
+ *     in binary32 and is not affected).
  *     dtype SCC_BF16: x, w, y, dy, dx are bfloat16 (upper half of a binary32,
  *     results rounded to nearest even), products accumulated in binary32;
  *     dw is written as binary32 in BOTH dtypes.
@@ -162,11 +163,15 @@ size_t scc_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int 
  * Both gradients of one layer in one call (Section 4.2, backward pass: the gradients with respect
  * to the input feature map and to the trainable weights are the two results of a layer's backward
  * step):
- *     dx as scc_backward_input computes it, dw as scc_backward_weight computes it.
+ *     dx as scc_backward_input computes it, dw as scc_backward_weight computes it,
+ * up to the order of the binary32 sums (and, in the first of the kernels below, dw's products).
  * For fp32 layers whose windows start on multiples of 32 channels and are 64 channels long, with
  * at most 32 filters per window, H*W a multiple of 4 and 16-byte aligned tensors, one kernel reads
  * dy and x from memory once and produces both (a third less memory traffic than the two passes;
- * all products are binary32 products).  Every other layer runs the two passes one after the other.
+ * products of split factors for both gradients).  Layers whose filters share many channels run
+ * grad-input with packed weights and the grad-weight that shares its operands as one launch, most
+ * others the kernels of the two passes as one launch, the rest one pass after the other
+ * (scc_backward_path).
  * x: in, N*Cin*H*W.  dy: in, N*Cout*H*W.  w: in, Cout*L.  dx: out, N*Cin*H*W.
  * dw: out, Cout*L binary32 values (both dtypes).  workspace: device scratch of at least
  * scc_backward_workspace_bytes(...) bytes, 256-byte aligned, owned by the caller, contents

@@ -112,7 +112,7 @@ __device__ __forceinline__ uint32_t strip_rowmask(int r0, int Ho)
     return m;
 }
 
-// Stand-alone depthwise stage on strips (see scc_dw_strip.h): stride 1 or 2, input maps of exactly S times the
+// Stand-alone depthwise stage on strips (see above): stride 1 or 2, input maps of exactly S times the
 // output size, RB dividing the output rows, output rows of whole quads of pixels, tensors aligned to 4 values.
 // Workgroup `bid` of `blocks`.
 template <typename T_, int S, int RB>

@@ -17,7 +17,8 @@
 // zeros outside the filter's window, parked in a wavefront-private LDS block.  Two B buffers and two register
 // sets: the loads of rounds r+1 and r+2 are in flight while round r is multiplied, one barrier per round.
 //
-// fp32 tensors and planes of at least 4 pixels only (a lane owns a group of 4 consecutive columns); the products are the six-of-nine bf16 partial products of scc_common.h, sums binary32.
+// fp32 tensors and planes of at least 4 pixels only (a lane owns a group of 4 consecutive columns); the products are the
+// six-of-nine bf16 partial products of scc_common.h, sums binary32.
 #include <type_traits>
 
 #include "scc_band.h"
@@ -129,7 +130,7 @@ __global__ __launch_bounds__(kWavesS * 64, 2) void forward_shared32(const float*
                 for (int q = 0; q < 4; ++q) m4 |= (j0 + q >= 0 && j0 + q < P.L) ? (1u << q) : 0u;
                 const int e0 = srw[it] + j0;
                 if (m4 == 0u || (e0 >= 0 && e0 + 4 <= P.Cout * P.L)) {
-                        ga[set][it] = *(const f32x4u*)(w + (m4 ? e0 : 0));
+                    ga[set][it] = *(const f32x4u*)(w + (m4 ? e0 : 0));
                 } else {
 #pragma unroll
                     for (int q = 0; q < 4; ++q) ga[set][it][q] = w[(m4 >> q) & 1u ? e0 + q : 0];

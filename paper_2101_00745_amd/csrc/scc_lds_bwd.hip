@@ -31,7 +31,7 @@
 //   dw tile  [32 filters of window b] x [64 positions] += dy rows(32 x 32 cols) * x rows(64 x 32 cols)^T
 // Both run on the bf16 matrix instruction with every binary32 operand cut EXACTLY into three bf16 pieces
 // (v = hi + mid + lo) and six of the nine partial products taken (the dropped mid*lo, lo*mid, lo*lo are below
-// 2^-23 of the product, the size of one binary32 rounding; sums are binary32): 6 x 32 cycles per 16 K values
+// 2^-21 of the product, 0.7 x 2^-24 on average, always toward zero; sums are binary32): 6 x 32 cycles per 16 K values
 // against 8 x 64 for v_mfma_f32_32x32x2_f32, paid for with about 5.5 vector instructions per value cut.
 // Measured, a SIMD's matrix instructions, vector instructions and incoming loads overlap only in part, and
 // this kernel is bound by their sum, not by memory: fp32 matrix instructions for both tiles measured 4 us

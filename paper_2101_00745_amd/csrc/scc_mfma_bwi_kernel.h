@@ -153,7 +153,7 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
             }
         } else {
             // fp32 storage: exact three-way bf16 split of every operand, six of the nine partial products
-            // (the dropped ones are below 2^-23 of the product), fp32 accumulation
+            // (the dropped ones are below 2^-21 of the product), fp32 accumulation
             uint32_t ah[KC / 2], amd[KC / 2], al[KC / 2];
             split3<KC>([&](int e) { return (am >> e) & 1u ? as[e] : 0.f; }, ah, amd, al);
 #pragma unroll

@@ -1,6 +1,6 @@
 // Forward SCC on the gfx950 matrix cores.  bf16 tensors go through the bf16 matrix instruction directly
 // (exact products, fp32 sums); fp32 tensors are split exactly into three bf16 pieces per value and take six
-// bf16 matrix instructions per K group (error below 2^-23 of each product, fp32 sums), which costs 3/8 of
+// bf16 matrix instructions per K group (error below 2^-21 of each product, fp32 sums), which costs 3/8 of
 // the matrix time of v_mfma_f32_32x32x2_f32 and measures the same error against an fp64 reference.
 //
 // y[n,k,p] = sum_j w[k,j] * x[n,(s_k+j) mod Cin,p]   (Section 4.2, output-centric forward)
@@ -230,7 +230,7 @@ __global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void forward_m
     // pieces (a half-wave's KC values side by side in its lanes' registers; which K-slot a value takes does
     // not matter as long as A and B agree).  bf16 tensors: one instruction, exact products.  fp32 tensors:
     // B is cut into its three bf16 pieces here, and six of the nine partial products are taken (the dropped
-    // mid*lo, lo*mid, lo*lo are below 2^-23 of the product).  Sums are fp32 either way.
+    // mid*lo, lo*mid, lo*lo are below 2^-21 of the product).  Sums are fp32 either way.
     auto mma = [&](int tl, const bvec (&bs)[KC]) {   // tl: first K-step of the chunk inside the staged block
         uint32_t ap[kParts][KC / 2];
 #pragma unroll

@@ -20,9 +20,11 @@
 // instruction and piece, without any vector work.  Two LDS buffers, one barrier per round; B is in flight for a round, A
 // for KG-1 K groups.
 //
-// What bounds it: a wavefront of 32*RT rows x 32*CT columns takes 6*RT*CT matrix instructions per K group (binary32) for
-// 3*CT 16-byte LDS reads and 3*RT global loads.  RT = 2 halves the LDS reads and the cuts per matrix instruction (with
-// RT = 1 the LDS pipe, shared by four SIMDs, is busy for 0.6 of the matrix time).
+// What bounds it: a wavefront of 32 rows x 32*CT columns takes 6*CT matrix instructions per K group (binary32; bf16: CT) for
+// 3*CT 16-byte LDS reads and 3 global loads of A. With tiles of 128 columns matrix and LDS pipe (shared by four SIMDs, busy
+// for 0.6 of the matrix time) and the cuts' vector work add up; tiles of 64 columns read A through L1 as often for half the
+// arithmetic and are bound by that. Two tiles of 32 rows per wavefront would halve the LDS reads and the cuts per matrix
+// instruction and were slower (228 registers, two workgroups per CU: channel-expanding layer, forward, f32 98 us against 88).
 #pragma once
 #include "scc_band.h"
 #include "scc_common.h"
@@ -212,7 +214,8 @@ __device__ __forceinline__ void packed_body(const T_* __restrict__ src, const ch
     // the other K groups.  A is requested KG-1 groups ahead, so the wait for an A that was requested after round r+2's
     // planes comes a round later.  The last two rounds are written out: no load is conditional inside the loop (a wait
     // behind a branch that may have issued loads has to assume it did not).  Requesting B two rounds and A three K groups
-    // further ahead costs the registers of the third workgroup per CU and is slower (86 against 94 us, see above).
+    // further ahead costs the registers of the third workgroup per CU and is slower (channel-expanding layer, forward, f32 94 us
+    // against 86, bf16 64 against 46).
     auto body = [&](int r, auto ISSUE, auto COMMIT) {
         const int buf = r & 1;
         auto step = [&](auto J) {
@@ -296,7 +299,7 @@ inline Packed make_packed(const Problem& p, int es, int CT)
     t.act_at = (uint32_t)at;
     at = (at + t.NG * kTiles * kMaxGroups + 1023) / 1024 * 1024;
     t.a_at = (uint32_t)at;
-    at += (t.NG * nkg + t.KG) * kTiles * np * 1024;   // slack of one round: A is requested ahead of its use: A is requested ahead of its use
+    at += (t.NG * nkg + t.KG) * kTiles * np * 1024;   // slack of one round: A is requested ahead of its use
     t.bytes = (size_t)at;
     return t;
 }

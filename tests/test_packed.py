@@ -97,3 +97,96 @@ def test_calls_with_out_allocate_nothing_and_a_workspace_can_be_handed_over(whic
     assert torch.equal(out, plain)
     with pytest.raises(S.SccError):
         call(out=out, workspace=ws[:-1])
+
+
+# ---- the products of binary32 operands: six of the nine partial products of two three-way cuts ------------------------------
+def cut(v):
+    """The cut of split3 (scc_common.h): upper halves taken off one after the other."""
+    top = lambda a: (a.view(np.uint32) & np.uint32(0xffff0000)).view(np.float32)
+    hi = top(v)
+    mid = top(v - hi)
+    return [p.astype(np.float64) for p in (hi, mid, top((v - hi) - mid))]
+
+
+def test_dropped_products_are_below_the_stated_bound():
+    """include/scc.h: less than 2**-21 of the product, always toward zero; and not less than 2**-23."""
+    rng = np.random.default_rng(3)
+    a, b = (np.concatenate([rng.standard_normal(1 << 18), [1 + 2.0 ** -7 - 2.0 ** -23]]).astype(np.float32) for _ in range(2))
+    (ah, am, al), (bh, bm, bl) = cut(a), cut(b)
+    exact = a.astype(np.float64) * b
+    assert np.array_equal((ah + am) + al, a) and np.array_equal((bh + bm) + bl, b)
+    loss = (exact - (ah * bh + (ah * bm + am * bh) + (am * bm + ah * bl + al * bh))) / exact
+    assert loss.min() >= 0 and 2.0 ** -23 < loss.max() < 2.0 ** -21 and loss[-1] > 0.97 * 2.0 ** -21
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which,shape", [("forward", BANDED), ("forward", ROUND), ("backward_input", CIRCLE), ("backward_input", GAPS)])
+def test_weights_near_the_end_of_the_exponent_range(which, shape):
+    """include/scc.h: a weight of 2**-120 keeps an absolute error of up to 2**-126, which the other factor multiplies.  Every
+    output within that, 2**-21 of its products' magnitudes and 2**-24 of them per rounding of at most 64 partial sums."""
+    N, Cin, Cout, H, W, cg, co = shape
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.randn(N, Cin if which == "forward" else Cout, H, W, generator=gen, device="cuda") * 2.0 ** 40
+    w = torch.randn(Cout, Cin // cg, generator=gen, device="cuda") * 2.0 ** -60 * 2.0 ** -60
+    hx, hw = x.cpu().numpy(), w.cpu().numpy()
+    run = (lambda a, b: O.forward(a, b, cg, co)) if which == "forward" else (lambda a, b: O.backward_input(a, b, Cin, cg, co))
+    got = (S.scc_forward(x, w, cg, co) if which == "forward" else S.scc_backward_input(x, w, Cin, cg, co)).cpu().numpy()
+    bound = run(np.abs(hx), (np.abs(hw) * (2.0 ** -21 + 64 * 2.0 ** -24) + 2.0 ** -126).astype(np.float32))
+    assert np.all(np.abs(got - run(hx, hw)) <= bound)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which,dtype,shape", [CASES[0], CASES[6], CASES[10], CASES[15]])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_non_finite_values_stay_in_their_column(which, dtype, shape, value):
+    N, Cin, Cout, H, W, cg, co = shape
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(10)
+    src = Cin if which == "forward" else Cout
+    x = torch.randn(N, src, H, W, generator=gen, device="cuda").to(td)
+    w = torch.randn(Cout, Cin // cg, generator=gen, device="cuda").to(td)
+    call = (lambda: S.scc_forward(x, w, cg, co)) if which == "forward" else (lambda: S.scc_backward_input(x, w, Cin, cg, co))
+    clean = call()
+    x[N // 2, src // 2, H - 1, W - 1] = value            # the last pixel: where groups of columns overlap
+    got = call()
+    column = torch.zeros_like(got, dtype=torch.bool)
+    column[N // 2, :, H - 1, W - 1] = True
+    assert torch.equal(got[~column], clean[~column])
+    hit = got[N // 2, :, H - 1, W - 1]
+    if which == "forward":                               # every filter whose window has the channel
+        L, step, _ = S.scc_window_params(Cin, Cout, cg, co)
+        reads = (src // 2 - torch.arange(Cout, device="cuda") * step) % Cin < L
+        assert not bool(torch.isfinite(hit[reads]).any())
+    else:
+        assert not bool(torch.isfinite(hit).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("which,dtype,shape", [CASES[0], CASES[7], CASES[10], CASES[15]])
+def test_calls_with_a_workspace_in_a_graph(which, dtype, shape):
+    """Every replay against the eager result, with other work and new inputs in between."""
+    N, Cin, Cout, H, W, cg, co = shape
+    td = torch.float32 if dtype == "f32" else torch.bfloat16
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    src, dst = (Cin, Cout) if which == "forward" else (Cout, Cin)
+    query = S.scc_forward_workspace_bytes if which == "forward" else S.scc_backward_input_workspace_bytes
+    x = torch.randn(N, src, H, W, generator=gen, device="cuda").to(td)
+    w = torch.randn(Cout, Cin // cg, generator=gen, device="cuda").to(td)
+    out, ws = torch.empty(N, dst, H, W, dtype=td, device="cuda"), torch.empty(query(*shape, td), dtype=torch.uint8, device="cuda")
+
+    def call(**kw):
+        return S.scc_forward(x, w, cg, co, **kw) if which == "forward" else S.scc_backward_input(x, w, Cin, cg, co, **kw)
+
+    call(out=out, workspace=ws)                          # code objects are loaded before the capture
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        call(out=out, workspace=ws)
+    for _ in range(3):
+        x.copy_(torch.randn(x.shape, generator=gen, device="cuda"))
+        w.copy_(torch.randn(w.shape, generator=gen, device="cuda"))
+        out.fill_(float("nan"))
+        ws.fill_(255)
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, call())
