@@ -4,9 +4,9 @@
 // comes first, with one (bf16) or two (binary32) workgroups per CU that stay for the whole launch; grad-input's pass through
 // what is left of the CUs, so that one range's matrix instructions run beside the other's loads and stores, and both read the
 // same eighth of the columns on an XCD, where part of dy is still on the chip for the second of them.
-// us, the per-tile kernels' merged launch -> this one: 128 x 128 -> 512, 32x32, cg 2, co 0.33: f32 261 -> 213, bf16 118 -> 62; 128 x 256 -> 256,
-// 16x16, cg 1: f32 80 -> 76, bf16 36 -> 31; 64 x 512 -> 1024, 7x7, cg 2, co 0.33: bf16 42 -> 34; 37 x 336 -> 330, 20x41, cg 1: f32 179 -> 130,
-// bf16 89 -> 46.
+// us, the per-tile kernels' merged launch -> this one: 128 x 128 -> 512, 32x32, cg 2, co 0.33: f32 251 -> 214, bf16 118 -> 63; 128 x 256 -> 256,
+// 16x16, cg 1: f32 78 -> 75, bf16 35 -> 31; 37 x 336 -> 330, 20x41, cg 1: f32 179 -> 130, bf16 88 -> 47; 64 x 2048 -> 2048, 7x7, cg 2: f32 262 -> 213,
+// bf16 132 -> 95.
 #include "scc_packed_kernel.h"
 #include "scc_shared_bww_kernel.h"
 
@@ -51,11 +51,10 @@ size_t partial_bytes(const Problem& p, const shared_bww::WeightTiling& t)
 }  // namespace
 
 // Taken where sharing saves enough plane fetches over the per-tile kernels of both passes (grad-weight's and grad-input's
-// together) and, binary32, where grad-weight's matrix time is at most 1.1 times theirs.  Measured against their merged launch.
-// bf16, 114 layers: above the lines 0.92 to 3 times as fast, median 1.4, those below 0.7 to 1.05; uneven layers, on which the per-tile
-// kernels lose more, from 37e6 on (28 x 416 -> 1664 on 9x6, 36.6e6: 0.78).  fp32, 107 layers: above the lines 0.97 to 1.7 times, median 1.2
-// (but 53 x 960 -> 1437 on 9x6, cg 8: 0.78); longer matrix times lose down to 0.8, and so do fewer fetches, uneven layers among them
-// (116 x 312 -> 156 on 9x9, 36e6: 0.78; 64 x 512 -> 1024 on 7x7, 39e6: 57 -> 56 us).
+// together) and, binary32, where grad-weight's matrix time is at most 1.1 times theirs.  Against their merged launch: bf16, of 110
+// layers the 99 above the lines run 0.88 to 2.9 times as fast, median 1.3, the 11 below 0.76 to 1.36, median 1.0 (uneven layers, on which
+// the per-tile kernels lose more, have a line of their own); fp32, 34 above 0.98 to 1.7, median 1.16, nine below 0.76 (53 x 960 ->
+// 1437 on 9x6, cg 8: 48 -> 64 us) to 1.19, median 1.0, and with longer matrix times down to 0.8 (186 x 416 -> 208 on 14x14, cg 2: 101 -> 116).
 size_t backward_shared_workspace(const Problem& p, int es)
 {
     const int ct = packed::tile_width<false>(p, es);
@@ -74,7 +73,7 @@ size_t backward_shared_workspace(const Problem& p, int es)
         packed::walk_of<false>(p, b, p.Cin, c0 / 128, first, len);
         saved -= (double)len * p.NQ;
     }
-    if (saved < (es == 2 && packed::uneven(p, b) ? 37e6 : 65e6)) return 0;
+    if (saved < (es == 4 ? 80e6 : packed::uneven(p, b) ? 45e6 : 65e6)) return 0;
     return partial_bytes(p, t) + packed::make_packed<false>(p, es, ct).bytes;
 }
 
