@@ -349,7 +349,7 @@ inline int tile_width(const Problem& p, int es)
 // The packing launch costs 4 to 5 us, so the path is for layers whose tiles fetch the same planes many times.  Measured
 // against the kernels that need no workspace, forward / grad-input, us (30 drawn layers besides):
 //   128 x 128 -> 512, 32x32, cg 2, co 0.33   f32 118 -> 86 / 116 -> 93     bf16 100 -> 46 / 63 -> 38
-//   64 x 512 -> 1024, 7x7, cg 2, co 0.33     f32 46 -> 23 / 30 -> 30       bf16 36 -> 16 / 26 -> 19
+//   64 x 512 -> 1024, 7x7, cg 2, co 0.33     f32 31 -> 23 / 25 -> 30       bf16 19 -> 16 / 18 -> 19
 //   128 x 256 -> 256, 16x16, cg 1            f32 31 -> 31 / 35 -> 32       bf16 20 -> 17 / 22 -> 17
 //   the same, cg 2                           f32 22 -> 24 / 23 -> 25       bf16 13 -> 15 / 14 -> 15
 //   225 x 320 -> 160, 28x28, cg 4, co 0      f32 88 -> 124 (every plane fetched twice only) / 88 -> 73
@@ -360,6 +360,9 @@ inline int choose(const Problem& p, int es)
     const int ct = tile_width<FWD>(p, es);
     if (!ct) return 0;
     const Band b = make_band(p);
+    // weights packed once per call: with more bytes than half of x and y hold (few columns, many weights) they are what the pass
+    // moves (4 x 2048 -> 2048 on 7x7, cg 1: forward f32 36 -> 65, bf16 22 -> 43, grad-input bf16 29 -> 45; 16 x 768 -> 1533 on 7x7: 30 -> 31, 18 -> 22)
+    if (2 * (long long)make_packed<FWD>(p, es, ct).bytes > (long long)(p.Cin + p.Cout) * p.NQ * es) return 0;
     double again;
     const double fetches = fetches_without_sharing<FWD>(p, b, &again);
     const bool odd = uneven(p, b), banded = FWD && b.F < 32 && b.P > 1;

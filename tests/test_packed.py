@@ -190,3 +190,8 @@ def test_calls_with_a_workspace_in_a_graph(which, dtype, shape):
         graph.replay()
         torch.cuda.synchronize()
         assert torch.equal(out, call())
+
+
+@pytest.mark.parametrize("shape", [(4, 2048, 2048, 7, 7, 1, 0.5), (16, 768, 1533, 7, 7, 1, 0.5), (9, 880, 3520, 9, 9, 2, 0.5)])
+def test_weights_that_outweigh_the_planes_are_not_packed(shape):
+    assert [need(which, dtype, shape) for which in ("forward", "backward_input") for dtype in ("f32", "bf16")] == [0] * 4
