@@ -281,9 +281,10 @@ int scc_dw_backward(const void* x, const void* kdw, const void* w, const void* d
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments, kernels, arithmetic and summation order as scc_backward_weight (results are bitwise
  * equal), but the scratch is a buffer of SCC_STATIC_SCRATCH_BYTES that the library holds in
- * device memory on every GPU it runs on, from load until the process ends.  The call allocates
- * and frees nothing; its first use on a device looks the buffer's address up once (do that
- * before starting a capture), later calls only enqueue kernels.
+ * device memory until the process ends, on every GPU on which a call has needed it.  The call
+ * itself allocates and frees nothing; its first use on a device looks the buffer's address up
+ * once, which is when the runtime loads it (do that before starting a capture), later calls only
+ * enqueue kernels.
  * Errors: those of scc_backward_weight, and SCC_ERR_SCRATCH when the problem needs more scratch
  * than the buffer holds (then scc_backward_weight_workspace_bytes(...) > SCC_STATIC_SCRATCH_BYTES;
  * decided on the host, nothing is launched).
