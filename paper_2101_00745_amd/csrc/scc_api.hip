@@ -288,15 +288,20 @@ int scc_backward_path(int N, int Cin, int Cout, int H, int W, int cg, double co,
     return backward_path(p, dtype, true, workspace_bytes ? (const void*)256 : nullptr, workspace_bytes);
 }
 
-size_t scc_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype)
+static size_t backward_need(const Problem& p, scc_dtype dtype)
 {
-    Problem p;
-    if (make_problem(N, Cin, Cout, H, W, cg, co, &p) != SCC_OK || !dtype_ok(dtype)) return 0;
     size_t most = backward_shared_need(p, dtype);
     const bool two_passes = most == 0 && !(dtype == SCC_F32 && scc::backward_fused_eligible(p)) &&
                             !with_type(dtype, [&](auto t) { return (int)scc::backward_merged_applicable<decltype(t)>(p); });
     if (two_passes) most = weight_shared_need(p, dtype);
     return std::max(backward_least(p, dtype), most);
+}
+
+size_t scc_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype)
+{
+    Problem p;
+    if (make_problem(N, Cin, Cout, H, W, cg, co, &p) != SCC_OK || !dtype_ok(dtype)) return 0;
+    return backward_need(p, dtype);
 }
 
 int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* dw, int N, int Cin, int Cout, int H,
@@ -461,15 +466,30 @@ static size_t dw_backward_plane_bytes(const Problem& p, scc_dtype dtype)
     return align256((size_t)p.NQ * p.Cin * (dtype == SCC_F32 ? 4 : 2));
 }
 
+// What its three stages one after the other cannot do without.
+static size_t dw_backward_least(const Problem& p, const scc::DwGeom& g, scc_dtype dtype)
+{
+    return 2 * dw_backward_plane_bytes(p, dtype) +
+           std::max(backward_need(p, dtype), scc::depthwise3x3_backward_workspace(p.N, p.Cin, g));
+}
+
+// What the stages side by side take (they keep the partial sums of dw and dk at once); 0: not a layer for that.
+static size_t dw_backward_paired_need(const Problem& p, const scc::DwGeom& g, scc_dtype dtype)
+{
+    const bool fused = dtype == SCC_F32 && scc::backward_fused_eligible(p);
+    if (fused || backward_shared_need(p, dtype) > 0 ||
+        !with_type(dtype, [&](auto t) { return (int)scc::block_backward_applicable<decltype(t)>(p, g); }))
+        return 0;
+    return 2 * dw_backward_plane_bytes(p, dtype) + scc::block_backward_workspace(p, g);
+}
+
 size_t scc_dw_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co,
                                        scc_dtype dtype)
 {
     Problem p;
     scc::DwGeom g;
     if (make_dw_problem(N, Cin, Cout, H, W, dw_stride, cg, co, &p, &g) != SCC_OK || !dtype_ok(dtype)) return 0;
-    const size_t a = scc_backward_workspace_bytes(N, Cin, Cout, g.Ho, g.Wo, cg, co, dtype);
-    const size_t b = scc_depthwise3x3_backward_workspace_bytes(N, Cin, H, W, dw_stride, dtype);
-    return 2 * dw_backward_plane_bytes(p, dtype) + (a > b ? a : b);
+    return std::max(dw_backward_least(p, g, dtype), dw_backward_paired_need(p, g, dtype));
 }
 
 int scc_dw_backward(const void* x, const void* kdw, const void* w, const void* dy, void* dx, void* dkdw, void* dw, int N,
@@ -482,13 +502,21 @@ int scc_dw_backward(const void* x, const void* kdw, const void* w, const void* d
     const int rc = make_dw_problem(N, Cin, Cout, H, W, dw_stride, cg, co, &p, &g);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    if (!workspace || workspace_bytes < scc_dw_backward_workspace_bytes(N, Cin, Cout, H, W, dw_stride, cg, co, dtype) ||
-        ((uintptr_t)workspace & 255u) != 0)
-        return SCC_ERR_WORKSPACE;
+    if (!workspace || !holds(dw_backward_least(p, g, dtype), workspace, workspace_bytes)) return SCC_ERR_WORKSPACE;
     const size_t plane = dw_backward_plane_bytes(p, dtype);
     char* z = (char*)workspace;
     char* dz = z + plane;
     char* rest = dz + plane;
+    const size_t paired = dw_backward_paired_need(p, g, dtype);
+    if (paired > 0 && holds(paired, workspace, workspace_bytes)) {
+        drop_stale_error();
+        return with_type(dtype, [&](auto t) {
+            typedef decltype(t) T;
+            return launch_status(scc::launch_block_backward((const T*)x, (const T*)kdw, (const T*)w, (const T*)dy, (T*)dx,
+                                                            (float*)dkdw, (float*)dw, (T*)z, (T*)dz, rest, p, g,
+                                                            (hipStream_t)stream));
+        });
+    }
     int r = scc_depthwise3x3_forward(x, kdw, z, N, Cin, H, W, dw_stride, dtype, stream);
     if (r != SCC_OK) return r;
     r = scc_backward(z, dy, w, dz, dw, N, Cin, Cout, g.Ho, g.Wo, cg, co, dtype, rest, workspace_bytes - 2 * plane, stream);

@@ -191,6 +191,13 @@ size_t depthwise3x3_backward_workspace(int N, int C, const DwGeom& g);
 template <typename T>
 hipError_t launch_depthwise3x3_backward(const T* x, const T* kdw, const T* dz, T* dx, float* dk, float* workspace, int N,
                                         int C, const DwGeom& g, hipStream_t st);
+
+// A block's backward in two launches and a sum (scc_block_bwd.hip); z, dz: planes of the depthwise output and its gradient
+template <typename T> bool block_backward_applicable(const Problem& p, const DwGeom& g);
+size_t block_backward_workspace(const Problem& p, const DwGeom& g);   // bytes behind those planes
+template <typename T>
+hipError_t launch_block_backward(const T* x, const T* kdw, const T* w, const T* dy, T* dx, float* dk, float* dw, T* z, T* dz,
+                                 void* workspace, const Problem& p, const DwGeom& g, hipStream_t st);
 bool dw_forward_fused_eligible(const Problem& p);    // the fused kernel can run the layer
 bool dw_forward_fused_preferred(const Problem& p);   // ... and is the faster path for it
 hipError_t launch_dw_forward_fused(const float* x, const float* kdw, const float* w, float* y, const Problem& p,

@@ -1,0 +1,298 @@
+// Bodies of the depthwise stage's gradients (formulas in scc_dw_bwd.hip), for its own kernels and for the ranges of a block's
+// backward (scc_block_bwd.hip).
+#pragma once
+#include "scc_common.h"
+#include "scc_dw_strip.h"
+
+namespace scc {
+
+namespace dw {
+
+// ---- grad-input, any stride: one thread per input pixel pulls from the outputs whose taps reach it ---------------
+template <typename T_>
+__device__ __forceinline__ void input_gather_body(const T_* __restrict__ dz, const T_* __restrict__ kdw, T_* __restrict__ dx, int C,
+                                                  const DwGeom& G, long long items, uint32_t bid, uint32_t blocks)
+{
+    const long long HWo = (long long)G.Ho * G.Wo;
+    for (long long e = (long long)bid * 256 + threadIdx.x; e < items; e += (long long)blocks * 256) {
+        const int c = (int)(e % G.W);
+        long long t = e / G.W;
+        const int r = (int)(t % G.H);
+        t /= G.H;                                  // t = n*C + a
+        const int a = (int)(t % C);
+        const T_* go = dz + t * HWo;
+        float out = 0.f;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int rr = r + 1 - i;              // = s*m
+            if (rr < 0 || rr % G.s != 0 || rr / G.s >= G.Ho) continue;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const int cc = c + 1 - j;          // = s*q
+                if (cc < 0 || cc % G.s != 0 || cc / G.s >= G.Wo) continue;
+                out += to_f32(kdw[a * 9 + i * 3 + j]) * to_f32(go[(long long)(rr / G.s) * G.Wo + cc / G.s]);
+            }
+        }
+        dx[e] = from_f32<T_>(out);
+    }
+}
+
+// ---- grad-input at stride 2 on even maps (H = 2*Ho, W = 2*Wo, Wo even, tensors aligned to 4 values): the taps
+// that reach input pixel (r, c) are fixed by the parities of r and c, so a thread writes the 2 x 4 input pixels
+// under two neighbouring outputs (m, q0), (m, q0+1) from the 2 x 3 outputs around them:
+//   dx[2m  ][2q  ] = k11*g[m][q]                      dx[2m  ][2q+1] = k10*g[m][q+1] + k12*g[m][q]
+//   dx[2m+1][2q  ] = k01*g[m+1][q] + k21*g[m][q]      dx[2m+1][2q+1] = k00*g[m+1][q+1] + k02*g[m+1][q] + k20*g[m][q+1] + k22*g[m][q]
+template <typename T_>
+__device__ __forceinline__ void input_s2_body(const T_* __restrict__ dz, const T_* __restrict__ kdw, T_* __restrict__ dx, int C,
+                                              const DwGeom& G, uint32_t items, uint32_t bid, uint32_t blocks)
+{
+    typedef T_ tvec __attribute__((ext_vector_type(4)));
+    typedef T_ tvec2 __attribute__((ext_vector_type(2)));
+    const uint32_t W2 = G.Wo / 2;
+    const size_t HWi = (size_t)G.H * G.W, HWo = (size_t)G.Ho * G.Wo;
+    for (uint32_t e = bid * 256u + threadIdx.x; e < items; e += blocks * 256u) {
+        const int q0 = (int)(e % W2) * 2;
+        uint32_t t = e / W2;
+        const int m = (int)(t % (uint32_t)G.Ho);
+        t /= (uint32_t)G.Ho;                        // t = n*C + a
+        const int a = (int)(t % (uint32_t)C);
+        float k[9];
+        load_taps(kdw, a, false, k);
+        const T_* g0 = dz + t * HWo + (size_t)m * G.Wo + q0;
+        const bool down = m + 1 < G.Ho, right = q0 + 2 < G.Wo;
+        const T_* g1 = down ? g0 + G.Wo : g0;
+        const tvec2 a01 = *(const tvec2*)g0, b01 = *(const tvec2*)g1;
+        const float a2 = right ? to_f32(g0[2]) : 0.f, b2raw = to_f32(g1[right ? 2 : 0]);
+        const float ga[3] = {to_f32(a01[0]), to_f32(a01[1]), a2};
+        const float gb[3] = {down ? to_f32(b01[0]) : 0.f, down ? to_f32(b01[1]) : 0.f, (down && right) ? b2raw : 0.f};
+        tvec r0, r1;
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            r0[2 * j] = from_f32<T_>(k[4] * ga[j]);
+            r0[2 * j + 1] = from_f32<T_>(k[3] * ga[j + 1] + k[5] * ga[j]);
+            r1[2 * j] = from_f32<T_>(k[1] * gb[j] + k[7] * ga[j]);
+            r1[2 * j + 1] = from_f32<T_>(k[0] * gb[j + 1] + k[2] * gb[j] + k[6] * ga[j + 1] + k[8] * ga[j]);
+        }
+        T_* o = dx + t * HWi + (size_t)(2 * m) * G.W + 2 * q0;
+        __builtin_nontemporal_store(r0, (tvec*)o);
+        __builtin_nontemporal_store(r1, (tvec*)(o + G.W));
+    }
+}
+
+// ---- grad-filter ----------------------------------------------------------------------------------------------
+constexpr int kDkThreads = 256;
+
+// the workgroup's nine sums: a tree over the lanes of each wavefront, then thread t < 9 adds the four wavefronts in order.
+// (One thread per sum adding 256 values from LDS one after the other was half of the kernel on small maps.)
+__device__ __forceinline__ void reduce_nine(const float (&s)[9], float* out9)
+{
+    __shared__ float part[kDkThreads / 64][9];
+#pragma unroll
+    for (int t = 0; t < 9; ++t) {
+        float v = s[t];
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+        if ((threadIdx.x & 63) == 0) part[threadIdx.x >> 6][t] = v;
+    }
+    __syncthreads();
+    if (threadIdx.x < 9)
+        out9[threadIdx.x] = ((part[0][threadIdx.x] + part[1][threadIdx.x]) + part[2][threadIdx.x]) + part[3][threadIdx.x];
+}
+
+// On strips (stride S = 1 or 2, output rows of whole column quads, input maps of exactly S times the output size,
+// RB dividing the output rows, tensors aligned to 4 values): a thread reads the strip's RB rows of dz and its
+// S*(RB-1)+3 rows of x once (strip_row) and adds their products to its nine sums.
+// Workgroup (a, slice) walks the strips of channel a in samples [slice*per, slice*per + per).
+template <typename T_, int S, int RB>
+__device__ __forceinline__ void filter_strips_body(const T_* __restrict__ x, const T_* __restrict__ dz,
+                                                   float* __restrict__ part, int N, int C, const DwGeom& G, int per, int a,
+                                                   int slice)
+{
+    typedef T_ tvec __attribute__((ext_vector_type(4)));
+    constexpr int NR = S * (RB - 1) + 3;
+    const int n0 = slice * per, n1 = n0 + per < N ? n0 + per : N;
+    const uint32_t W4 = G.Wo / 4, SB = G.Ho / RB, spp = W4 * SB;             // strips per plane
+    const uint32_t items = (uint32_t)(n1 > n0 ? n1 - n0 : 0) * spp;
+    const size_t HWi = (size_t)G.H * G.W, HWo = (size_t)G.Ho * G.Wo;
+    const uint32_t lane = threadIdx.x & 63;
+    float s[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // all lanes of a wavefront run the same number of trips (strip_row shuffles between lanes); lanes past the end
+    // read strip 0 again and add nothing
+    for (uint32_t e0 = 0; e0 < items; e0 += kDkThreads) {
+        const uint32_t ee = e0 + threadIdx.x;
+        const bool live = ee < items;
+        const uint32_t e = live ? ee : 0;
+        const int cw = (int)(e % W4) * 4;
+        uint32_t t = e / W4;
+        const int r0 = (int)(t % SB) * RB;
+        const size_t plane = (size_t)(n0 + t / SB) * C + a;
+        const T_* xc = x + plane * HWi + (size_t)(S * r0) * G.W + S * cw;
+        const T_* gz = dz + plane * HWo + (size_t)r0 * G.Wo + cw;
+        float g[RB][4];
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) {
+            const tvec m = *(const tvec*)(gz + rr * G.Wo);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) g[rr][i] = live ? to_f32(m[i]) : 0.f;
+        }
+        const uint32_t rowmask = strip_rowmask<S, RB>(r0, G.Ho);
+#pragma unroll
+        for (int tr = 0; tr < NR; ++tr) {
+            float v[4 * S + 2];
+            strip_row<S>(xc, G.W, tr, rowmask, cw > 0, cw + 4 < G.Wo, lane == 0, lane == 63 || ee + 1 >= items, v);
+#pragma unroll
+            for (int rr = 0; rr < RB; ++rr) {
+                const int di = tr - S * rr;      // tap row that pairs this input row with output row rr
+                if (di < 0 || di > 2) continue;
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+#pragma unroll
+                    for (int j = 0; j < 3; ++j) s[di * 3 + j] += g[rr][i] * v[S * i + j];
+            }
+        }
+    }
+    reduce_nine(s, part + ((size_t)slice * C + a) * 9);
+}
+
+// On columns (stride 1, rows of any length, RB dividing the rows): a thread owns one column of RB rows of dz, consecutive lanes
+// consecutive pixels, and the pixels left and right of its own x are its neighbours' (lane shuffle), as in columns_body: 2 + 2/RB
+// loads per output where the body below takes ten (both gradients of 64 x 256 on 14x14, f32: see scc_dw_bwd.hip).
+template <typename T_, int RB>
+__device__ __forceinline__ void filter_columns_body(const T_* __restrict__ x, const T_* __restrict__ dz, float* __restrict__ part,
+                                                    int N, int C, const DwGeom& G, int per, int a, int slice)
+{
+    const int n0 = slice * per, n1 = n0 + per < N ? n0 + per : N;
+    const uint32_t W = (uint32_t)G.W, SB = (uint32_t)G.H / RB;
+    const uint32_t items = (uint32_t)(n1 > n0 ? n1 - n0 : 0) * (W * SB);
+    const size_t HW = (size_t)G.H * G.W;
+    const uint32_t lane = threadIdx.x & 63;
+    float s[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    // all lanes of a wavefront run the same number of trips (they shuffle); lanes past the end redo item 0 and add nothing
+    for (uint32_t e0 = 0; e0 < items; e0 += kDkThreads) {
+        const uint32_t ee = e0 + threadIdx.x;
+        const bool live = ee < items;
+        const uint32_t e = live ? ee : 0;
+        uint32_t t = e / W;
+        const int c = (int)(e - t * W);
+        const uint32_t n = t / SB;
+        const int r0 = (int)(t - n * SB) * RB;
+        const size_t at = ((size_t)(n0 + n) * C + a) * HW + (size_t)r0 * W + c;
+        const T_ *xc = x + at, *gz = dz + at;
+        float g[RB];
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) {
+            const float v = to_f32(gz[rr * (int)W]);
+            g[rr] = live ? v : 0.f;
+        }
+        const bool left = c > 0, right = c + 1 < (int)W;
+        const bool lo = lane == 0, hi = lane == 63 || ee + 1 >= items;
+#pragma unroll
+        for (int tr = 0; tr < RB + 2; ++tr) {
+            const int r = r0 - 1 + tr;
+            const bool ok = r >= 0 && r < G.H;
+            const T_* row = ok ? xc + (tr - 1) * (int)W : xc;
+            const float mid = to_f32(row[0]);
+            float lv = __shfl_up(mid, 1, 64), rv = __shfl_down(mid, 1, 64);
+            if (lo && left) lv = to_f32(row[-1]);
+            if (hi && right) rv = to_f32(row[1]);
+            const float v[3] = {(ok && left) ? lv : 0.f, ok ? mid : 0.f, (ok && right) ? rv : 0.f};
+#pragma unroll
+            for (int rr = 0; rr < RB; ++rr) {
+                const int di = tr - rr;              // tap row that pairs this row of x with row rr of dz
+                if (di < 0 || di > 2) continue;
+#pragma unroll
+                for (int j = 0; j < 3; ++j) s[di * 3 + j] += g[rr] * v[j];
+            }
+        }
+    }
+    reduce_nine(s, part + ((size_t)slice * C + a) * 9);
+}
+
+// Any stride and map size: a thread takes output pixels one by one.  The batch's pixels fit 32 bits (64-bit divisions in every
+// lane cost more than the nine products).
+template <typename T_>
+__device__ __forceinline__ void filter_pixels_body(const T_* __restrict__ x, const T_* __restrict__ dz, float* __restrict__ part,
+                                                   int N, int C, const DwGeom& G, int per, int a, int slice)
+{
+    const int n0 = slice * per, n1 = n0 + per < N ? n0 + per : N;
+    const uint32_t HWo = (uint32_t)G.Ho * (uint32_t)G.Wo, Wo = (uint32_t)G.Wo;
+    const size_t HWi = (size_t)G.H * G.W;
+    const uint32_t items = (uint32_t)(n1 > n0 ? n1 - n0 : 0) * HWo;
+    float s[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    for (uint32_t e = threadIdx.x; e < items; e += kDkThreads) {
+        const uint32_t n = e / HWo, px = e - n * HWo;
+        const int m = (int)(px / Wo), q = (int)(px - (uint32_t)m * Wo);
+        const size_t plane = (size_t)(n0 + n) * C + a;
+        const float g = to_f32(dz[plane * HWo + px]);
+        const T_* xc = x + plane * HWi;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int rr = G.s * m + i - 1;
+            if (rr < 0 || rr >= G.H) continue;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const int cc = G.s * q + j - 1;
+                if (cc < 0 || cc >= G.W) continue;
+                s[i * 3 + j] += g * to_f32(xc[(size_t)rr * G.W + cc]);
+            }
+        }
+    }
+    reduce_nine(s, part + ((size_t)slice * C + a) * 9);
+}
+
+// dk[e] = sum over slices of part[slice][e], in slice order
+__device__ __forceinline__ void filter_reduce_body(const float* __restrict__ part, float* __restrict__ dk, int count, int slices,
+                                                   uint32_t bid)
+{
+    const int e = (int)bid * 256 + (int)threadIdx.x;
+    if (e >= count) return;
+    float s = 0.f;
+    int sl = 0;
+    for (; sl + 8 <= slices; sl += 8) {          // 8 loads in flight, added in order
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = part[(size_t)(sl + u) * count + e];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) s += v[u];
+    }
+    for (; sl < slices; ++sl) s += part[(size_t)sl * count + e];
+    dk[e] = s;
+}
+
+// slices of the samples per channel: about 1024 workgroups in all, at least one sample for each and, on strips, one strip per
+// thread; at most 65535.  Maps of 4x4 at batch 128 have 128 strips per channel: with two slices three quarters of the
+// threads had none and the slices' sums took another launch (512 channels: 10.4 + 3.9 us, 9.6 with one).
+inline int filter_slices(int N, int C, const DwGeom& g)
+{
+    int sl = (1024 + C - 1) / C;
+    if ((g.s == 1 || g.s == 2) && g.Wo % 4 == 0 && g.H == g.s * g.Ho && g.W == g.s * g.Wo) {
+        const int rb = g.Ho % 4 == 0 ? 4 : g.Ho % 2 == 0 ? 2 : 1;
+        const long long full = ((long long)N * (g.Wo / 4) * (g.Ho / rb) + kDkThreads - 1) / kDkThreads;
+        if (sl > full) sl = (int)full;
+    }
+    if (sl > N) sl = N;
+    if (sl > 65535) sl = 65535;
+    return sl < 1 ? 1 : sl;
+}
+
+// Whether the filter gradient runs on strips (rows of a strip: strip_rows_of), `per` samples to a slice.
+template <typename T_>
+inline bool filter_on_strips(const T_* x, const T_* dz, const DwGeom& g, int per)
+{
+    return (g.s == 1 || g.s == 2) && g.Wo % 4 == 0 && g.H == g.s * g.Ho && g.W == g.s * g.Wo &&
+           (((uintptr_t)x | (uintptr_t)dz) & (4 * sizeof(T_) - 1)) == 0 && (long long)per * g.Ho * (g.Wo / 4) < (1ll << 31);
+}
+
+inline int strip_rows_of(const DwGeom& g) { return g.Ho % 4 == 0 ? 4 : g.Ho % 2 == 0 ? 2 : 1; }
+
+// Whether grad-input at stride 2 runs on input_s2_body.
+template <typename T_>
+inline bool input_on_s2(const T_* dz, const T_* dx, int N, int C, const DwGeom& g)
+{
+    return g.s == 2 && g.H == 2 * g.Ho && g.W == 2 * g.Wo && g.Wo % 2 == 0 &&
+           (((uintptr_t)dz | (uintptr_t)dx) & (4 * sizeof(T_) - 1)) == 0 && (long long)N * C * g.Ho * (g.Wo / 2) < (1ll << 31);
+}
+
+}  // namespace dw
+
+}  // namespace scc

@@ -13,6 +13,8 @@
 #include "scc_common.h"
 #include "scc_dw_strip.h"
 
+#include <type_traits>
+
 namespace scc {
 
 namespace {
@@ -49,89 +51,20 @@ __global__ __launch_bounds__(256) void depthwise3x3_strips(const T_* __restrict_
     dw::strips_body<T_, S, RB>(x, kdw, z, C, G, items, flip, blockIdx.x, gridDim.x);
 }
 
-// Stand-alone depthwise stage at stride 1 for rows of any length: a thread owns ONE column of RB consecutive output
-// rows, consecutive lanes own consecutive pixels of the row-major map, so every load instruction reads consecutive
-// values; the pixels left and right of a lane's column are what its neighbouring lanes loaded (lane shuffle), and
-// each input row is loaded once per strip.  1 + 2/RB loads per output instead of the nine of the kernel below.
 template <typename T_, int RB>
 __global__ __launch_bounds__(256) void depthwise3x3_columns(const T_* __restrict__ x, const T_* __restrict__ kdw,
                                                             T_* __restrict__ z, int C, DwGeom G, long long items,
                                                             int flip)
 {
-    const size_t HW = (size_t)G.H * G.W;
-    const uint32_t W = (uint32_t)G.W, SB = (uint32_t)G.H / RB;
-    const uint32_t lane = threadIdx.x & 63;
-    // all lanes of a wavefront run the same number of trips (they shuffle); lanes past the end redo item 0 and store nothing
-    for (uint32_t e0 = blockIdx.x * 256u; e0 < (uint32_t)items; e0 += gridDim.x * 256u) {
-        const uint32_t ee = e0 + threadIdx.x;
-        const bool live = ee < (uint32_t)items;
-        const uint32_t e = live ? ee : 0;
-        const int c = (int)(e % W);
-        uint32_t t = e / W;
-        const int r0 = (int)(t % SB) * RB;
-        t /= SB;                          // t = n*C + a
-        float k[9];
-        dw::load_taps(kdw, (int)(t % (uint32_t)C), flip != 0, k);
-        const T_* xc = x + t * HW + (size_t)r0 * W + c;      // input pixel (r0, c)
-        const bool left = c > 0, right = c + 1 < (int)W;
-        const bool lo = lane == 0, hi = lane == 63 || ee + 1 >= (uint32_t)items;
-        float out[RB];
-#pragma unroll
-        for (int rr = 0; rr < RB; ++rr) out[rr] = 0.f;
-#pragma unroll
-        for (int tr = 0; tr < RB + 2; ++tr) {
-            const int r = r0 - 1 + tr;
-            const bool ok = r >= 0 && r < G.H;
-            const T_* row = ok ? xc + (tr - 1) * (int)W : xc;
-            const float mid = to_f32(row[0]);
-            float lv = __shfl_up(mid, 1, 64), rv = __shfl_down(mid, 1, 64);
-            if (lo && left) lv = to_f32(row[-1]);
-            if (hi && right) rv = to_f32(row[1]);
-            const float v0 = (ok && left) ? lv : 0.f, v1 = ok ? mid : 0.f, v2 = (ok && right) ? rv : 0.f;
-#pragma unroll
-            for (int rr = 0; rr < RB; ++rr) {
-                const int di = tr - rr;
-                if (di < 0 || di > 2) continue;
-                out[rr] += k[di * 3] * v0 + k[di * 3 + 1] * v1 + k[di * 3 + 2] * v2;
-            }
-        }
-        if (!live) continue;
-        T_* zo = z + t * HW + (size_t)r0 * W + c;
-#pragma unroll
-        for (int rr = 0; rr < RB; ++rr) __builtin_nontemporal_store(from_f32<T_>(out[rr]), zo + rr * (int)W);
-    }
+    dw::columns_body<T_, RB>(x, kdw, z, C, G, items, flip, blockIdx.x, gridDim.x);
 }
 
-// Stand-alone depthwise stage, any stride and map size: one thread per output value, taps in row-major order.
-// IDX is the type of the flat output index: 32 bits whenever the tensor allows it (64-bit divisions in every lane
-// cost several times the stencil).
 template <typename T_, typename IDX>
 __global__ __launch_bounds__(256) void depthwise3x3_kernel(const T_* __restrict__ x, const T_* __restrict__ kdw,
                                                            T_* __restrict__ z, int C, DwGeom G, long long items,
                                                            int flip)
 {
-    const size_t HWi = (size_t)G.H * G.W;
-    for (IDX e = (IDX)blockIdx.x * 256 + threadIdx.x; e < (IDX)items; e += (IDX)gridDim.x * 256) {
-        const int q = (int)(e % (IDX)G.Wo);
-        IDX t = e / (IDX)G.Wo;
-        const int m = (int)(t % (IDX)G.Ho);
-        t /= (IDX)G.Ho;
-        const int a = (int)(t % (IDX)C);
-        const T_* xc = x + (size_t)t * HWi;
-        float out = 0.f;
-#pragma unroll
-        for (int i = 0; i < 3; ++i) {
-            const int rr = G.s * m + i - 1;
-            if (rr < 0 || rr >= G.H) continue;
-#pragma unroll
-            for (int j = 0; j < 3; ++j) {
-                const int cc = G.s * q + j - 1;
-                if (cc < 0 || cc >= G.W) continue;
-                out += to_f32(kdw[a * 9 + (flip ? 8 - (i * 3 + j) : i * 3 + j)]) * to_f32(xc[(size_t)rr * G.W + cc]);
-            }
-        }
-        z[e] = from_f32<T_>(out);
-    }
+    dw::pixels_body<T_, IDX>(x, kdw, z, C, G, items, flip, blockIdx.x, gridDim.x);
 }
 
 // ---------------------------------------------------------------------------------------------------------
@@ -448,52 +381,27 @@ hipError_t launch_fused_cp(const float* x, const float* kdw, const float* w, flo
     return rb == 4 ? launch_fused<CP, 2, 4>(x, kdw, w, y, p, g, st) : launch_fused<CP, 2, 2>(x, kdw, w, y, p, g, st);
 }
 
-template <typename T, int S>
-hipError_t launch_strips(const T* x, const T* kdw, T* z, int N, int C, const DwGeom& g, hipStream_t st, int flip)
-{
-    long long items, blocks;
-    const int rb = dw::strip_rows(N, C, g, &items, &blocks);
-    const dim3 grid((unsigned)blocks), block(256);
-    if (rb == 4)
-        depthwise3x3_strips<T, S, 4><<<grid, block, 0, st>>>(x, kdw, z, C, g, items, flip);
-    else if (rb == 2)
-        depthwise3x3_strips<T, S, 2><<<grid, block, 0, st>>>(x, kdw, z, C, g, items, flip);
-    else
-        depthwise3x3_strips<T, S, 1><<<grid, block, 0, st>>>(x, kdw, z, C, g, items, flip);
-    return hipGetLastError();
-}
-
 }  // namespace
 
 template <typename T>
 hipError_t launch_depthwise3x3(const T* x, const T* kdw, T* z, int N, int C, const DwGeom& g, hipStream_t st, bool flip)
 {
-    const bool sized = (g.s == 1 || g.s == 2) && g.H == g.s * g.Ho && g.W == g.s * g.Wo &&
-                       (long long)N * C * g.Ho * ((g.Wo + 3) / 4) < (1ll << 31);
-    const bool vec = g.Wo % 4 == 0 && (((uintptr_t)x | (uintptr_t)z) & (4 * sizeof(T) - 1)) == 0;
-    if (sized && vec)
-        return g.s == 1 ? launch_strips<T, 1>(x, kdw, z, N, C, g, st, flip) : launch_strips<T, 2>(x, kdw, z, N, C, g, st, flip);
-    if (g.s == 1 && (long long)N * C * g.H * g.W < (1ll << 31)) {       // rows of any length
-        const int rb = g.H % 4 == 0 ? 4 : g.H % 2 == 0 ? 2 : 1;
-        const long long items = (long long)N * C * (g.H / rb) * g.W;
-        long long blocks = (items + 255) / 256;
-        if (blocks > (1ll << 20)) blocks = 1ll << 20;   // the kernel strides over what is left
-        const dim3 grid((unsigned)blocks), block(256);
-        if (rb == 4)
-            depthwise3x3_columns<T, 4><<<grid, block, 0, st>>>(x, kdw, z, C, g, items, flip);
-        else if (rb == 2)
-            depthwise3x3_columns<T, 2><<<grid, block, 0, st>>>(x, kdw, z, C, g, items, flip);
-        else
-            depthwise3x3_columns<T, 1><<<grid, block, 0, st>>>(x, kdw, z, C, g, items, flip);
-        return hipGetLastError();
-    }
-    const long long items = (long long)N * C * g.Ho * g.Wo;
-    long long blocks = (items + 255) / 256;
-    if (blocks > (1ll << 20)) blocks = 1ll << 20;
-    if (items + (1ll << 28) < (1ll << 32))      // the index plus one grid stride still fits 32 bits
-        depthwise3x3_kernel<T, uint32_t><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(x, kdw, z, C, g, items, flip);
+    const dw::Stage s = dw::plan_stage(x, z, N, C, g, flip);
+    const dim3 grid(s.blocks), block(256);
+    auto rows = [&](auto launch) {
+        s.rb == 4 ? launch(std::integral_constant<int, 4>{})
+        : s.rb == 2 ? launch(std::integral_constant<int, 2>{}) : launch(std::integral_constant<int, 1>{});
+    };
+    if (s.kind == dw::kStrips1)
+        rows([&](auto rb) { depthwise3x3_strips<T, 1, decltype(rb)::value><<<grid, block, 0, st>>>(x, kdw, z, C, g, s.items, flip); });
+    else if (s.kind == dw::kStrips2)
+        rows([&](auto rb) { depthwise3x3_strips<T, 2, decltype(rb)::value><<<grid, block, 0, st>>>(x, kdw, z, C, g, s.items, flip); });
+    else if (s.kind == dw::kColumns)
+        rows([&](auto rb) { depthwise3x3_columns<T, decltype(rb)::value><<<grid, block, 0, st>>>(x, kdw, z, C, g, s.items, flip); });
+    else if (s.kind == dw::kPixels)
+        depthwise3x3_kernel<T, uint32_t><<<grid, block, 0, st>>>(x, kdw, z, C, g, s.items, flip);
     else
-        depthwise3x3_kernel<T, unsigned long long><<<dim3((unsigned)blocks), dim3(256), 0, st>>>(x, kdw, z, C, g, items, flip);
+        depthwise3x3_kernel<T, unsigned long long><<<grid, block, 0, st>>>(x, kdw, z, C, g, s.items, flip);
     return hipGetLastError();
 }
 

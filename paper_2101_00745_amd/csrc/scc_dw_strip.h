@@ -168,6 +168,147 @@ inline int strip_rows(int N, int C, const DwGeom& g, long long* items, long long
     return rb;
 }
 
+// Stand-alone depthwise stage at stride 1 for rows of any length: a thread owns ONE column of RB consecutive output
+// rows, consecutive lanes own consecutive pixels of the row-major map, so every load instruction reads consecutive
+// values; the pixels left and right of a lane's column are what its neighbouring lanes loaded (lane shuffle), and
+// each input row is loaded once per strip.  1 + 2/RB loads per output instead of the nine of the kernel below.
+template <typename T_, int RB>
+__device__ __forceinline__ void columns_body(const T_* __restrict__ x, const T_* __restrict__ kdw, T_* __restrict__ z, int C,
+                                             const DwGeom& G, long long items, int flip, uint32_t bid, uint32_t blocks)
+{
+    const size_t HW = (size_t)G.H * G.W;
+    const uint32_t W = (uint32_t)G.W, SB = (uint32_t)G.H / RB;
+    const uint32_t lane = threadIdx.x & 63;
+    // all lanes of a wavefront run the same number of trips (they shuffle); lanes past the end redo item 0 and store nothing
+    for (uint32_t e0 = bid * 256u; e0 < (uint32_t)items; e0 += blocks * 256u) {
+        const uint32_t ee = e0 + threadIdx.x;
+        const bool live = ee < (uint32_t)items;
+        const uint32_t e = live ? ee : 0;
+        const int c = (int)(e % W);
+        uint32_t t = e / W;
+        const int r0 = (int)(t % SB) * RB;
+        t /= SB;                          // t = n*C + a
+        float k[9];
+        load_taps(kdw, (int)(t % (uint32_t)C), flip != 0, k);
+        const T_* xc = x + t * HW + (size_t)r0 * W + c;      // input pixel (r0, c)
+        const bool left = c > 0, right = c + 1 < (int)W;
+        const bool lo = lane == 0, hi = lane == 63 || ee + 1 >= (uint32_t)items;
+        float out[RB];
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) out[rr] = 0.f;
+#pragma unroll
+        for (int tr = 0; tr < RB + 2; ++tr) {
+            const int r = r0 - 1 + tr;
+            const bool ok = r >= 0 && r < G.H;
+            const T_* row = ok ? xc + (tr - 1) * (int)W : xc;
+            const float mid = to_f32(row[0]);
+            float lv = __shfl_up(mid, 1, 64), rv = __shfl_down(mid, 1, 64);
+            if (lo && left) lv = to_f32(row[-1]);
+            if (hi && right) rv = to_f32(row[1]);
+            const float v0 = (ok && left) ? lv : 0.f, v1 = ok ? mid : 0.f, v2 = (ok && right) ? rv : 0.f;
+#pragma unroll
+            for (int rr = 0; rr < RB; ++rr) {
+                const int di = tr - rr;
+                if (di < 0 || di > 2) continue;
+                // the order of the strips' sums, spelled out: which product of a sum of three is contracted is the compiler's
+                // choice, and was another one in another kernel
+                out[rr] = __builtin_fmaf(k[di * 3], v0, out[rr]);
+                out[rr] = __builtin_fmaf(k[di * 3 + 1], v1, out[rr]);
+                out[rr] = __builtin_fmaf(k[di * 3 + 2], v2, out[rr]);
+            }
+        }
+        if (!live) continue;
+        T_* zo = z + t * HW + (size_t)r0 * W + c;
+#pragma unroll
+        for (int rr = 0; rr < RB; ++rr) __builtin_nontemporal_store(from_f32<T_>(out[rr]), zo + rr * (int)W);
+    }
+}
+
+// Stand-alone depthwise stage, any stride and map size: one thread per output value, taps in row-major order.
+// IDX is the type of the flat output index: 32 bits whenever the tensor allows it (64-bit divisions in every lane
+// cost several times the stencil).
+template <typename T_, typename IDX>
+__device__ __forceinline__ void pixels_body(const T_* __restrict__ x, const T_* __restrict__ kdw, T_* __restrict__ z, int C,
+                                            const DwGeom& G, long long items, int flip, uint32_t bid, uint32_t blocks)
+{
+    const size_t HWi = (size_t)G.H * G.W;
+    for (IDX e = (IDX)bid * 256 + threadIdx.x; e < (IDX)items; e += (IDX)blocks * 256) {
+        const int q = (int)(e % (IDX)G.Wo);
+        IDX t = e / (IDX)G.Wo;
+        const int m = (int)(t % (IDX)G.Ho);
+        t /= (IDX)G.Ho;
+        const int a = (int)(t % (IDX)C);
+        const T_* xc = x + (size_t)t * HWi;
+        float out = 0.f;
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+            const int rr = G.s * m + i - 1;
+            if (rr < 0 || rr >= G.H) continue;
+#pragma unroll
+            for (int j = 0; j < 3; ++j) {
+                const int cc = G.s * q + j - 1;
+                if (cc < 0 || cc >= G.W) continue;
+                out += to_f32(kdw[a * 9 + (flip ? 8 - (i * 3 + j) : i * 3 + j)]) * to_f32(xc[(size_t)rr * G.W + cc]);
+            }
+        }
+        z[e] = from_f32<T_>(out);
+    }
+}
+
+// How the stage runs on a layer: which of the bodies above, its work items and its workgroups of 256 threads.
+enum { kStrips1, kStrips2, kColumns, kPixels, kPixels64 };
+
+struct Stage {
+    int kind, rb, flip;
+    uint32_t blocks;
+    long long items;
+};
+
+template <typename T_>
+inline Stage plan_stage(const T_* x, const T_* z, int N, int C, const DwGeom& g, bool flip)
+{
+    Stage s;
+    s.flip = flip;
+    s.rb = 1;
+    long long blocks;
+    const bool sized = (g.s == 1 || g.s == 2) && g.H == g.s * g.Ho && g.W == g.s * g.Wo &&
+                       (long long)N * C * g.Ho * ((g.Wo + 3) / 4) < (1ll << 31);
+    const bool vec = g.Wo % 4 == 0 && (((uintptr_t)x | (uintptr_t)z) & (4 * sizeof(T_) - 1)) == 0;
+    if (sized && vec) {
+        s.kind = g.s == 1 ? kStrips1 : kStrips2;
+        s.rb = strip_rows(N, C, g, &s.items, &blocks);
+    } else {
+        const bool columns = g.s == 1 && (long long)N * C * g.H * g.W < (1ll << 31);   // rows of any length
+        if (columns) s.rb = g.H % 4 == 0 ? 4 : g.H % 2 == 0 ? 2 : 1;
+        s.items = (long long)N * C * (g.Ho / s.rb) * g.Wo;
+        // the index plus one grid stride still fits 32 bits
+        s.kind = columns ? kColumns : s.items + (1ll << 28) < (1ll << 32) ? kPixels : kPixels64;
+        blocks = (s.items + 255) / 256;
+        if (blocks > (1ll << 20)) blocks = 1ll << 20;   // the kernel strides over what is left
+    }
+    s.blocks = (uint32_t)blocks;
+    return s;
+}
+
+// The stage as a range of a grid that other work shares: the variant is chosen when the workgroup runs (any kind but kPixels64).
+template <typename T_>
+__device__ __forceinline__ void stage_body(const T_* __restrict__ x, const T_* __restrict__ kdw, T_* __restrict__ z, int C,
+                                           const DwGeom& G, const Stage& s, uint32_t bid)
+{
+    switch (s.kind * 8 + s.rb) {
+        case kStrips1 * 8 + 1: return strips_body<T_, 1, 1>(x, kdw, z, C, G, s.items, s.flip, bid, s.blocks);
+        case kStrips1 * 8 + 2: return strips_body<T_, 1, 2>(x, kdw, z, C, G, s.items, s.flip, bid, s.blocks);
+        case kStrips1 * 8 + 4: return strips_body<T_, 1, 4>(x, kdw, z, C, G, s.items, s.flip, bid, s.blocks);
+        case kStrips2 * 8 + 1: return strips_body<T_, 2, 1>(x, kdw, z, C, G, s.items, s.flip, bid, s.blocks);
+        case kStrips2 * 8 + 2: return strips_body<T_, 2, 2>(x, kdw, z, C, G, s.items, s.flip, bid, s.blocks);
+        case kStrips2 * 8 + 4: return strips_body<T_, 2, 4>(x, kdw, z, C, G, s.items, s.flip, bid, s.blocks);
+        case kColumns * 8 + 1: return columns_body<T_, 1>(x, kdw, z, C, G, s.items, s.flip, bid, s.blocks);
+        case kColumns * 8 + 2: return columns_body<T_, 2>(x, kdw, z, C, G, s.items, s.flip, bid, s.blocks);
+        case kColumns * 8 + 4: return columns_body<T_, 4>(x, kdw, z, C, G, s.items, s.flip, bid, s.blocks);
+        default: return pixels_body<T_, uint32_t>(x, kdw, z, C, G, s.items, s.flip, bid, s.blocks);
+    }
+}
+
 }  // namespace dw
 
 }  // namespace scc

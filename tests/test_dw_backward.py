@@ -24,6 +24,47 @@ def test_one_call_is_its_three_stages(shape, dtype):
     assert all(torch.equal(a, b) and a.dtype == b.dtype for a, b in zip(got, (dx, dk, dw)))
 
 
+# Maps of strips of 1, 2 and 4 rows, of columns (2x2, 7x7, 6x10) and of single pixels (stride 2 on odd maps, stride 3), one and several
+# slices of either filter, fewer than 256 columns, and layers on both sides of the line at 2^23 (columns: 2^22) values of x and z.
+PAIRED = [(16, 512, 512, 4, 4, 1, 2, 0.5), (16, 1024, 256, 2, 2, 1, 2, 0.5), (5, 48, 40, 7, 7, 1, 4, 0.33), (9, 64, 61, 6, 10, 1, 2, 0.75),
+          (20, 64, 96, 13, 9, 2, 2, 0.5), (30, 32, 24, 10, 10, 3, 1, 0.0), (30, 64, 128, 32, 32, 2, 2, 0.5), (128, 32, 64, 32, 32, 1, 2, 0.5),
+          (129, 32, 64, 32, 32, 1, 2, 0.5), (167, 256, 256, 7, 7, 1, 4, 0.5), (168, 256, 256, 7, 7, 1, 4, 0.5), (64, 256, 512, 8, 8, 2, 2, 0.5)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shape", PAIRED)
+def test_stages_side_by_side(shape, dtype):
+    """The two launches of a block's backward are its three stages, bit for bit, also on the workspace that only the stages
+    one after the other run on; and the depthwise filter's gradient is the oracle's."""
+    test_one_call_is_its_three_stages(shape, dtype)
+    N, Cin, Cout, H, W, s, cg, co = shape
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    Ho, Wo = (H - 1) // s + 1, (W - 1) // s + 1
+    x, kdw, w, dy = (torch.randn(*d, generator=gen, device="cuda").to(dtype) for d in
+                     ((N, Cin, H, W), (Cin, 3, 3), (Cout, Cin // cg), (N, Cout, Ho, Wo)))
+    dx, dk, dw = S.scc_dw_backward(x, kdw, w, dy, cg, co, s)
+    lib, code, es = S.load(), 0 if dtype == torch.float32 else 1, x.element_size()
+    shape_c = (N, Cin, Cout, H, W, s, cg, co, code)
+    plane = (N * Cin * Ho * Wo * es + 255) // 256 * 256
+    least = 2 * plane + max(int(lib.scc_backward_workspace_bytes(N, Cin, Cout, Ho, Wo, cg, co, code)),
+                            int(lib.scc_depthwise3x3_backward_workspace_bytes(N, Cin, H, W, s, code)))
+    assert least <= lib.scc_dw_backward_workspace_bytes(*shape_c)
+    ws = torch.empty(least, dtype=torch.uint8, device="cuda")
+    dx2, dk2, dw2 = torch.empty_like(dx), torch.empty_like(dk), torch.empty_like(dw)
+    args = [t.data_ptr() for t in (x, kdw, w, dy, dx2, dk2, dw2)]
+    stream = torch.cuda.current_stream().cuda_stream
+    assert lib.scc_dw_backward(*args, *shape_c, ws.data_ptr(), least, stream) == 0
+    assert torch.equal(dx, dx2) and torch.equal(dk, dk2) and torch.equal(dw, dw2)
+    if x.numel() <= 1 << 20:
+        import numpy as np
+        from oracle import scc_oracle as O
+        z = S.scc_depthwise3x3_forward(x, kdw, s)
+        dz = S.scc_backward(z, dy, w, cg, co)[0]
+        ref = O.depthwise3x3_backward(*(t.float().cpu().numpy() for t in (x, kdw, dz)), s)[1]
+        assert np.max(np.abs(dk.cpu().numpy() - ref)) <= 2e-5 * np.max(np.abs(ref))     # binary32 sums in both types
+
+
 def test_host_checks():
     lib, p = S.load(), ctypes.c_void_p(0x1000)
     shape = (3, 32, 40, 9, 7, 2, 4, 0.25, 0)
