@@ -245,7 +245,9 @@ int scc_depthwise3x3_backward(const void* x, const void* kdw, const void* dz, vo
  * depthwise output of a tile of pixels for all channels on chip and feeds the SCC from there; x is read
  * once, y written once, the intermediate never reaches memory (and is not rounded to the storage type).
  * Two stages (every layer): scc_depthwise3x3_forward into `workspace`, then scc_forward on it; `workspace`
- * then holds the depthwise output (N*Cin*Ho*Wo values of the dtype).
+ * then holds the depthwise output (N*Cin*Ho*Wo values of the dtype); or, on layers with few output pixels on maps of 4 x n
+ * or 2 x 2, one kernel that computes it again for every group of filters (rounded to the storage type as the two stages round
+ * it) and leaves the workspace alone.
  * scc_dw_forward_workspace_bytes(...) returns 0 for the layers the library runs fused by its own choice
  * (fusable and at least 16384 output pixels over the batch, where fusing is the faster path) and the size
  * of the depthwise output for all others.  A call with a workspace of at least that size (256-byte aligned,

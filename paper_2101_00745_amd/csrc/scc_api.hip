@@ -449,6 +449,14 @@ int scc_dw_forward(const void* x, const void* kdw, const void* w, void* y, int N
     const bool fused = dtype == SCC_F32 && (need == 0 || (!workspace && scc::dw_forward_fused_eligible(p)));
     if (!fused && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0))
         return SCC_ERR_WORKSPACE;
+    if (scc::dw_forward_few_preferred(p, g)) {      // one kernel as well; the workspace it could do without stays as it is
+        drop_stale_error();
+        return with_type(dtype, [&](auto t) {
+            typedef decltype(t) T;
+            return launch_status(scc::launch_dw_forward_few((const T*)x, (const T*)kdw, (const T*)w, (T*)y, p, g,
+                                                            (hipStream_t)stream));
+        });
+    }
     if (fused) {
         drop_stale_error();
         return launch_status(scc::launch_dw_forward_fused((const float*)x, (const float*)kdw, (const float*)w, (float*)y,

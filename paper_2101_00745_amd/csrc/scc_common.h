@@ -187,6 +187,11 @@ size_t depthwise3x3_backward_workspace(int N, int C, const DwGeom& g);
 template <typename T>
 hipError_t launch_depthwise3x3_backward(const T* x, const T* kdw, const T* dz, T* dx, float* dk, float* workspace, int N,
                                         int C, const DwGeom& g, hipStream_t st);
+// ... and the one for layers with few columns (scc_dw_few.hip), fp32 and bf16
+bool dw_forward_few_eligible(const Problem& p, const DwGeom& g);
+bool dw_forward_few_preferred(const Problem& p, const DwGeom& g);   // ... and faster
+template <typename T>
+hipError_t launch_dw_forward_few(const T* x, const T* kdw, const T* w, T* y, const Problem& p, const DwGeom& g, hipStream_t st);
 
 // A block's backward in two launches and a sum (scc_block_bwd.hip); z, dz: planes of the depthwise output and its gradient
 template <typename T> bool block_backward_applicable(const Problem& p, const DwGeom& g);
