@@ -1,4 +1,4 @@
-"""Compile the HIP sources in csrc/ into libscc_hip.so (gfx950 only), in-tree."""
+"""Compile the HIP sources in csrc/ into libscc_hip.so (gfx950 only) and the Python binding's native part, in-tree."""
 import glob
 import os
 import subprocess
@@ -9,6 +9,9 @@ INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libscc_hip.so")
 MEMBW_SRC = os.path.join(CSRC, "membw", "membw.hip")
 MEMBW_LIB = os.path.join(HERE, "libscc_membw.so")   # streaming kernels of the benchmark's copy ceiling; not the SCC ABI
+
+BINDING_SRC = os.path.join(CSRC, "binding", "scc_binding.cpp")
+BINDING_LIB = os.path.join(HERE, "_binding.so")     # the Python binding's plain calls (host code, against torch's C++ API)
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMPILE_FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
@@ -23,10 +26,10 @@ def sources():
 
 
 def stale():
-    if not os.path.exists(LIB):
+    if not os.path.exists(LIB) or not os.path.exists(BINDING_LIB):
         return True
-    t = os.path.getmtime(LIB)
-    deps = sources() + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(INCLUDE, "*.h"))
+    t = min(os.path.getmtime(LIB), os.path.getmtime(BINDING_LIB))
+    deps = sources() + [BINDING_SRC] + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(INCLUDE, "*.h"))
     return any(os.path.getmtime(f) > t for f in deps)
 
 
@@ -65,7 +68,26 @@ def build(force=True, verbose=False):
         os.replace(tmp, LIB)
     finally:
         shutil.rmtree(work, ignore_errors=True)
+    build_binding(verbose)
     return LIB
+
+
+def build_binding(verbose=False):
+    """Build _binding.so, which calls libscc_hip.so beside it."""
+    import sysconfig
+
+    import torch
+    root = os.path.dirname(torch.__file__)
+    rocm = os.path.dirname(os.path.dirname(HIPCC))
+    includes = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
+                os.path.join(rocm, "include"), sysconfig.get_paths()["include"], INCLUDE]
+    tmp = BINDING_LIB + ".tmp.%d" % os.getpid()
+    _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI] + ["-I" + i for i in includes] +
+         [BINDING_SRC, "-o", tmp, "-L" + os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
+          "-L" + HERE, "-lscc_hip", "-Wl,-rpath,$ORIGIN"], verbose)
+    os.replace(tmp, BINDING_LIB)
+    return BINDING_LIB
 
 
 def build_membw(force=True, verbose=False):

@@ -1,4 +1,5 @@
-"""Thin Python binding of the SCC C ABI (include/scc.h): argument marshalling only.
+"""Thin Python binding of the SCC C ABI (include/scc.h): argument marshalling only, the everyday calls in native code
+(csrc/binding/scc_binding.cpp), all others here through ctypes.
 
 Every step of the computation runs in the HIP kernels of libscc_hip.so.  PyTorch supplies
 device memory (``torch.empty``), raw pointers (``data_ptr``) and the current HIP stream,
@@ -25,6 +26,7 @@ SYMBOLS = ("scc_window_params", "scc_forward", "scc_forward_workspace_bytes", "s
 STATIC_SCRATCH_BYTES = 32 << 20    # SCC_STATIC_SCRATCH_BYTES of include/scc.h
 
 _lib = None
+_native = None      # the module of the plain calls
 
 
 class SccError(RuntimeError):
@@ -90,6 +92,19 @@ def load():
     lib.scc_status_string.restype = ctypes.c_char_p
     _lib = lib
     return lib
+
+
+def _load_native():
+    """The plain calls: each answers None where a call is not plain (or fails), and the general way below it then goes on."""
+    global _native
+    load()
+    try:
+        from . import _binding
+    except ImportError as e:
+        raise ImportError("_binding.so is not built for this torch (%s): run `python -m paper_2101_00745_amd.build` "
+                          "(or __graft_entry__.build()) first; there is no fallback path" % e) from e
+    _native = _binding
+    return _binding
 
 
 def scc_status_string(status):
@@ -177,6 +192,10 @@ def scc_forward(x, w, cg, co, out=None, workspace=None):
     """y = SCC(x; w): x [N,Cin,H,W], w [Cout,Cin//cg] -> y [N,Cout,H,W] (same dtype).  Layers that pack their weights take a
     workspace for it; without one it is allocated, unless `out` is given: such a call allocates nothing and runs the
     kernels that need none."""
+    if out is None and workspace is None:
+        y = (_native or _load_native()).forward(x, w, cg, co)
+        if y is not None:
+            return y
     dev = _dev(x, w)
     N, Cin, H, W = x.shape
     Cout = w.shape[0]
@@ -266,6 +285,10 @@ def scc_backward_workspace_bytes(N, Cin, Cout, H, W, cg, co, dtype=torch.float32
 
 def scc_backward(x, dy, w, cg, co, out_dx=None, out_dw=None, workspace=None):
     """(dx, dw) of one layer in one call: x [N,Cin,H,W], dy [N,Cout,H,W], w [Cout,Cin//cg]."""
+    if out_dx is None and out_dw is None and workspace is None:
+        both = (_native or _load_native()).backward(x, dy, w, cg, co)
+        if both is not None:
+            return both
     dev = _dev(x, dy, w)
     N, Cin, H, W = x.shape
     Cout = dy.shape[1]
@@ -371,6 +394,10 @@ def scc_dw_forward(x, kdw, w, cg, co, dw_stride=1, out=None, workspace=None, fus
     -> y [N,Cout,Ho,Wo].  fused=None: the path the library prefers (a workspace is allocated when it asks for
     one); fused=True: no workspace is passed, so the fused kernel runs or the call is refused; fused=False: the
     two stages through a workspace, also where the library would fuse."""
+    if fused is None and out is None and workspace is None:
+        y = (_native or _load_native()).dw_forward(x, kdw, w, cg, co, dw_stride)
+        if y is not None:
+            return y
     dev = _dev(x, kdw, w)
     N, Cin, H, W = x.shape
     Cout = w.shape[0]
@@ -403,6 +430,9 @@ def scc_dw_forward(x, kdw, w, cg, co, dw_stride=1, out=None, workspace=None, fus
 def scc_dw_backward(x, kdw, w, dy, cg, co, dw_stride=1):
     """(dx, dkdw, dw), all gradients of a DW + SCC block in one call: x [N,Cin,H,W], kdw [Cin,3,3], w [Cout,Cin//cg],
     dy [N,Cout,Ho,Wo]; dkdw and dw are float32."""
+    grads = (_native or _load_native()).dw_backward(x, kdw, w, dy, cg, co, dw_stride)
+    if grads is not None:
+        return grads
     dev = _dev(x, kdw, w, dy)
     N, Cin, H, W = x.shape
     Cout = w.shape[0]

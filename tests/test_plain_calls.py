@@ -1,0 +1,90 @@
+"""The plain calls of the binding in native code: the results of the general way, and its errors for whatever is not plain."""
+import pytest
+import torch
+
+import paper_2101_00745_amd as S
+from paper_2101_00745_amd import scc as B
+
+
+def calls(x, k, w, dy, cg, co, s=1):
+    return (lambda: S.scc_forward(x, w, cg, co), lambda: S.scc_backward(x, dy, w, cg, co), lambda: S.scc_dw_forward(x, k, w, cg, co, s),
+            lambda: S.scc_dw_backward(x, k, w, dy, cg, co, s))
+
+
+def inputs(dtype, N=3, Cin=32, Cout=24, H=6, W=4, cg=2):
+    gen = torch.Generator(device="cuda").manual_seed(2)
+    return [torch.randn(*d, generator=gen, device="cuda").to(dtype) for d in ((N, Cin, H, W), (Cin, 3, 3), (Cout, Cin // cg), (N, Cout, H, W))]
+
+
+class General:
+    """A native module that finds no call plain."""
+    def __getattr__(self, name):
+        return lambda *a: None
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_plain_is_general(dtype, monkeypatch):
+    for shape in (dict(), dict(N=128, Cin=128, Cout=512, H=32, W=32), dict(N=1, H=4, W=4), dict(N=16, Cin=512, Cout=512, H=4, W=4)):
+        args = inputs(dtype, **shape)
+        with torch.no_grad():
+            B._load_native()
+            plain = [c() for c in calls(*args, 2, 0.33)]
+            native = (B._native.forward(args[0], args[2], 2, 0.33), B._native.backward(args[0], args[3], args[2], 2, 0.33),
+                      B._native.dw_forward(*args[:3], 2, 0.33, 1), B._native.dw_backward(*args, 2, 0.33, 1))
+            assert all(n is not None for n in native)                     # the calls above took the native way
+            with monkeypatch.context() as m:
+                m.setattr(B, "_native", General())
+                general = [c() for c in calls(*args, 2, 0.33)]
+        for p, g in zip(plain, general):
+            for a, b in zip(p if isinstance(p, tuple) else (p,), g if isinstance(g, tuple) else (g,)):
+                assert torch.equal(a, b) and a.dtype == b.dtype and a.stride() == b.stride() and not a.requires_grad
+
+
+@pytest.mark.gpu
+def test_not_plain_goes_the_general_way():
+    x, k, w, dy = inputs(torch.float32)
+    n = B._load_native()
+    assert n.forward(x, w, 2, 0.5) is not None
+    for a in ((x.cpu(), w, 2, 0.5), (x, w.bfloat16(), 2, 0.5), (x.transpose(2, 3), w, 2, 0.5), (x, w[:, :8].contiguous(), 2, 0.5), (x, w, 2, 0),
+              (x, w, 0, 0.5), (x, w, 5, 0.5), (x, w, 2.0, 0.5), (x, w, True, 0.5), (x, w, 1 << 40, 0.5), (x, w, 2, 1.5), (x[:0], w, 2, 0.5), (x[0], w, 2, 0.5),
+              (x.as_subclass(type("T", (torch.Tensor,), {})), w, 2, 0.5), (x, w, 2), ("x", w, 2, 0.5), (None, w, 2, 0.5)):
+        assert n.forward(*a) is None
+    assert n.backward(x, dy[:1], w, 2, 0.5) is None and n.dw_forward(x, k[:8], w, 2, 0.5, 1) is None
+    assert n.dw_forward(x, k, w, 2, 0.5, 0) is None and n.dw_forward(x, k, w, 2, 0.5, 1.0) is None
+    assert n.dw_backward(x, k, w, dy, 2, 0.5, 2) is None
+    assert torch.equal(S.scc_forward(x, w, 2, 0), S.scc_forward(x, w, 2, 0.0))
+    with pytest.raises(S.SccError) as e:
+        S.scc_forward(x, w, 2, 1.5)
+    assert e.value.status == -3
+    with pytest.raises(RuntimeError):
+        torch.func.vmap(lambda t: S.scc_forward(t, w, 2, 0.5))(x[None])
+
+
+@pytest.mark.gpu
+def test_streams_and_graphs():
+    args = inputs(torch.float32, N=16, Cin=256, Cout=256, H=8, W=8)
+    with torch.no_grad():
+        want = [c() for c in calls(*args, 2, 0.5)]
+        side = torch.cuda.Stream()
+        side.wait_stream(torch.cuda.current_stream())
+        with torch.cuda.stream(side):
+            got = [c() for c in calls(*args, 2, 0.5)]
+        torch.cuda.current_stream().wait_stream(side)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g):
+            rec = [c() for c in calls(*args, 2, 0.5)]
+        for replay in range(3):
+            g.replay()
+            got += [tuple(t.clone() for t in r) if isinstance(r, tuple) else r.clone() for r in rec]
+            torch.cuda.synchronize()
+    for i, r in enumerate(got):
+        for a, b in zip(r if isinstance(r, tuple) else (r,), want[i % 4] if isinstance(r, tuple) else (want[i % 4],)):
+            assert torch.equal(a, b)
+
+
+def test_errors_without_a_gpu():
+    x, w = torch.zeros(1, 8, 8, 8), torch.zeros(8, 4)
+    for c in calls(x, torch.zeros(8, 3, 3), w, x, 2, 0.5):
+        with pytest.raises(ValueError, match="must live on the GPU"):
+            c()
