@@ -30,6 +30,7 @@ struct BwiTiling {
     int FG;     // workgroups per column tile = ceil(CB / 4)
     int total;  // workgroups with work: column tiles * FG, channel-block group fastest
     int chunk;  // consecutive workgroups of that order given to one XCD: ceil(total / 8)
+    int even;   // every window start has F filters and F is a multiple of a chunk: see the walk below
     Groups q;   // column groups of CT pixels
 };
 
@@ -77,11 +78,6 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
     // unwrapped window index range: g*m in [c0-L+1, c0+31]
     const int mlo = -floor_div(P.L - 1 - c0, T.b.g);   // ceil((c0-L+1)/g)
     const int M = floor_div(c0 + 31, T.b.g) - mlo + 1;  // window starts this block can see (>= 1)
-    // K-steps: each half-wave walks Uh (window, filter) slots; an even number of chunks
-    const int Uh = ((M * T.b.F + 1) / 2 + 2 * KC - 1) / (2 * KC) * (2 * KC);
-    const int Us = ((Uh + S - 1) / S + 2 * KC - 1) / (2 * KC) * (2 * KC);   // K-steps of one slice
-    const int t0 = split * Us < Uh ? split * Us : Uh;                         // this wavefront's K-steps [t0, t1)
-    const int t1 = !tvalid ? t0 : (t0 + Us < Uh ? t0 + Us : Uh);
     const char* wb = (const char*)w;
     const char* gb = (const char*)dy;
 
@@ -95,13 +91,6 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
         dcol = n * (uint32_t)P.Cin * (uint32_t)P.HW + p;
     }
 
-    // K-slot state of this half-wave: slot u = h*Uh + t  <->  (mm, i) = (u / F, u % F)
-    const int u0 = h * Uh + t0;
-    int mm = u0 / T.b.F, i = u0 % T.b.F;
-    int mw = (mlo + mm) % T.b.P;                 // window index on the circle
-    if (mw < 0) mw += T.b.P;
-    int r = (int)(((uint32_t)mw * (uint32_t)T.b.inv) % (uint32_t)T.b.P);   // residue class owning window mw
-    int ju = c - T.b.g * (mlo + mm);             // position of channel c inside that window (unwrapped)
     const uint32_t plane = (uint32_t)P.HW * ES;
 
     f32x16 acc[CT];
@@ -110,28 +99,6 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[cc][v] = 0.f;
 
-    auto load_chunk = [&](T_ (&ad)[KC], uint32_t& am, bvec (&bd)[KC]) {
-        am = 0;
-#pragma unroll
-        for (int s = 0; s < KC; ++s) {
-            const int k = r + T.b.P * i;
-            const bool kvalid = (mm < M) && (k < P.Cout);
-            const bool in = kvalid && cvalid && ju >= 0 && ju < P.L;
-            ad[s] = *(const T_*)(wb + (uint32_t)(in ? (k * P.L + ju) : 0) * ES);
-            am |= in ? (1u << s) : 0u;
-            const uint32_t rowofs = (uint32_t)(kvalid ? k : 0) * plane;
-            bd[s] = *(const bvec*)(gb + (uint32_t)(gcol + rowofs));
-            // next slot: next filter of this window, or the first filter of the next window
-            ++i;
-            const bool nextw = (i == T.b.F);
-            i = nextw ? 0 : i;
-            mm += nextw ? 1 : 0;
-            ju -= nextw ? T.b.g : 0;
-            int rn = r + T.b.inv;                // r(m+1) = r(m) + inv (mod P)
-            rn = (rn >= T.b.P) ? rn - T.b.P : rn;
-            r = nextw ? rn : r;
-        }
-    };
     auto mma_chunk = [&](const T_ (&as)[KC], uint32_t am, const bvec (&bs)[KC]) {
         if constexpr (ES == 2) {
             // bf16 storage: the KC slots of a chunk are the K values of ONE bf16 matrix instruction per column
@@ -139,9 +106,14 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
             uint32_t ap[KC / 2];
 #pragma unroll
             for (int e = 0; e < KC / 2; ++e) {
-                const uint32_t lo = (am >> (2 * e)) & 1u ? (uint32_t)as[2 * e] : 0u;
-                const uint32_t hi = (am >> (2 * e + 1)) & 1u ? (uint32_t)as[2 * e + 1] : 0u;
-                ap[e] = lo | (hi << 16);
+                // am holds one bit per slot; with all of them equal (chunks of one window) a pair is kept or dropped as one
+                if (T.even) {
+                    ap[e] = am ? (uint32_t)as[2 * e] | ((uint32_t)as[2 * e + 1] << 16) : 0u;
+                } else {
+                    const uint32_t lo = (am >> (2 * e)) & 1u ? (uint32_t)as[2 * e] : 0u;
+                    const uint32_t hi = (am >> (2 * e + 1)) & 1u ? (uint32_t)as[2 * e + 1] : 0u;
+                    ap[e] = lo | (hi << 16);
+                }
             }
 #pragma unroll
             for (int cc = 0; cc < CT; ++cc) {
@@ -155,7 +127,7 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
             // fp32 storage: exact three-way bf16 split of every operand, six of the nine partial products
             // (the dropped ones are below 2^-21 of the product), fp32 accumulation
             uint32_t ah[KC / 2], amd[KC / 2], al[KC / 2];
-            split3<KC>([&](int e) { return (am >> e) & 1u ? as[e] : 0.f; }, ah, amd, al);
+            split3<KC>([&](int e) { return (T.even ? am : (am >> e) & 1u) ? as[e] : 0.f; }, ah, amd, al);
 #pragma unroll
             for (int cc = 0; cc < CT; ++cc) {
                 uint32_t bh[KC / 2], bm[KC / 2], bl[KC / 2];
@@ -170,22 +142,81 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
         }
     };
 
-    // software pipelined over an even number of chunks (Uh is a multiple of 2*KC)
-    T_ a0[KC], a1[KC];
-    bvec b0[KC], b1[KC];
-    uint32_t m0, m1;
-    const int nch = (t1 - t0) / KC;
-    if (nch > 0) {
-        load_chunk(a0, m0, b0);
-        for (int cix = 0; cix + 2 < nch; cix += 2) {
-            load_chunk(a1, m1, b1);
+    // Software pipelined over an even number n of chunks, which load(a, in, b) requests one after the other.
+    auto pipeline = [&](int n, auto&& load) __attribute__((always_inline)) {
+        T_ a0[KC], a1[KC];
+        bvec b0[KC], b1[KC];
+        uint32_t m0, m1;
+        if (n <= 0) return;
+        load(a0, m0, b0);
+        for (int cix = 0; cix + 2 < n; cix += 2) {
+            load(a1, m1, b1);
             mma_chunk(a0, m0, b0);
-            load_chunk(a0, m0, b0);
+            load(a0, m0, b0);
             mma_chunk(a1, m1, b1);
         }
-        load_chunk(a1, m1, b1);
+        load(a1, m1, b1);
         mma_chunk(a0, m0, b0);
         mma_chunk(a1, m1, b1);
+    };
+    // K-steps: each half-wave walks Uh (window, filter) slots; an even number of chunks
+    const int Uh = ((M * T.b.F + 1) / 2 + 2 * KC - 1) / (2 * KC) * (2 * KC);
+    const int Us = ((Uh + S - 1) / S + 2 * KC - 1) / (2 * KC) * (2 * KC);   // K-steps of one slice
+    const int t0 = split * Us < Uh ? split * Us : Uh;                         // this wavefront's K-steps [t0, t1)
+    const int t1 = !tvalid ? t0 : (t0 + Us < Uh ? t0 + Us : Uh);
+    // K-slot state of this half-wave: slot u = h*Uh + t  <->  (mm, i) = (u / F, u % F)
+    const int u0 = h * Uh + t0;
+    int mm = u0 / T.b.F, i = u0 % T.b.F;
+    int mw = (mlo + mm) % T.b.P;                 // window index on the circle
+    if (mw < 0) mw += T.b.P;
+    int r = (int)(((uint32_t)mw * (uint32_t)T.b.inv) % (uint32_t)T.b.P);   // residue class owning window mw
+    int ju = c - T.b.g * (mlo + mm);             // position of channel c inside that window (unwrapped)
+    // `step` filters further in the walk
+    auto advance = [&](int step) {
+        i += step;
+        const bool nextw = (i == T.b.F);
+        i = nextw ? 0 : i;
+        mm += nextw ? 1 : 0;
+        ju -= nextw ? T.b.g : 0;
+        int rn = r + T.b.inv;                    // r(m+1) = r(m) + inv (mod P)
+        rn = (rn >= T.b.P) ? rn - T.b.P : rn;
+        r = nextw ? rn : r;
+    };
+    if (T.even) {
+        // A chunk is KC filters of ONE window, P apart: one offset per lane and operand for all of them, and scalar bases that do
+        // not change from chunk to chunk.  Taking every slot for itself (below) costs 25 vector instructions per slot, most of
+        // what a bf16 tile executes: 226 per chunk of 4 matrix instructions (fp32: 345 of 24), 45 (fp32: 160) here; same
+        // operands in the same order.
+        const uint32_t wstep = (uint32_t)T.b.P * (uint32_t)P.L * ES, gstep = (uint32_t)T.b.P * plane;
+        pipeline((t1 - t0) / KC, [&](T_(&ad)[KC], uint32_t& am, bvec(&bd)[KC]) __attribute__((always_inline)) {
+            const int k = mm < M ? r + T.b.P * i : 0;
+            const bool in = (mm < M) & cvalid & (ju >= 0) & (ju < P.L);
+            am = in ? 0xffffffffu : 0u;
+            const uint32_t wofs = (uint32_t)(k * P.L + (in ? ju : 0)) * ES, gofs = gcol + (uint32_t)k * plane;
+#pragma unroll
+            for (int s = 0; s < KC; ++s) {
+                ad[s] = *(const T_*)(wb + (size_t)(s * wstep) + wofs);
+                bd[s] = *(const bvec*)(gb + (size_t)(s * gstep) + gofs);
+            }
+            advance(KC);
+        });
+    } else {
+        pipeline((t1 - t0) / KC, [&](T_(&ad)[KC], uint32_t& am, bvec(&bd)[KC]) {
+            am = 0;
+#pragma unroll
+            for (int s = 0; s < KC; ++s) {
+                const int k = r + T.b.P * i;
+                // bitwise: short-circuit forms became branches with a load behind each
+                const bool kvalid = (mm < M) & (k < P.Cout);
+                const bool in = kvalid & cvalid & (ju >= 0) & (ju < P.L);
+                const int at = k * P.L + ju;
+                ad[s] = *(const T_*)(wb + (uint32_t)(in ? at : 0) * ES);
+                am |= in ? (1u << s) : 0u;
+                const uint32_t rowofs = (uint32_t)(kvalid ? k : 0) * plane;
+                bd[s] = *(const bvec*)(gb + (uint32_t)(gcol + rowofs));
+                advance(1);                      // next filter of this window, or the first filter of the next window
+            }
+        });
     }
 
     if constexpr (S > 1) {   // add the slices of each tile, in slice order, into the wavefront that took slice 0
@@ -216,15 +247,20 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
     }
 
     // accumulator register v holds tile row 8*(v/4) + 4*h + v%4 (= channel c0 + that), column f
+    const uint32_t dofs = (dcol + (uint32_t)(c0 + 4 * h) * (uint32_t)P.HW) * ES;
+    auto store_row = [&](int v) {
+        bvec o;
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int cr = c0 + 8 * (v >> 2) + 4 * h + (v & 3);
-        if (cr < P.Cin && live) {
-            bvec o;
+        for (int cc = 0; cc < CT; ++cc) o[cc] = from_f32<T_>(acc[cc][v]);
+        __builtin_nontemporal_store(o, (bvec*)((char*)dx + (size_t)((uint32_t)(8 * (v >> 2) + (v & 3)) * plane) + dofs));  // written once, not re-read here
+    };
+    if (c0 + 32 <= P.Cin && __all((int)live)) {      // a whole tile: no row and no column is asked for
 #pragma unroll
-            for (int cc = 0; cc < CT; ++cc) o[cc] = from_f32<T_>(acc[cc][v]);
-            __builtin_nontemporal_store(o, (bvec*)(dx + (size_t)dcol + (size_t)cr * P.HW));  // written once, not re-read here
-        }
+        for (int v = 0; v < 16; ++v) store_row(v);
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (c0 + 8 * (v >> 2) + 4 * h + (v & 3) < P.Cin && live) store_row(v);
     }
 }
 
@@ -237,6 +273,7 @@ inline BwiTiling make_tiling(const Problem& p, long long* blocks)
     BwiTiling t;
     t.b = make_band(p);
     t.CB = (p.Cin + 31) / 32;
+    t.even = t.b.F % 8 == 0 && p.Cout == t.b.P * t.b.F;
     t.q = column_groups(p, CT);
     const long long nct = (t.q.count + 31) / 32;
     t.FG = (t.CB * S + WPB - 1) / WPB;

@@ -17,6 +17,8 @@
 #include "scc_band.h"
 #include "scc_common.h"
 
+#include <type_traits>
+
 namespace scc {
 
 namespace {
@@ -41,6 +43,9 @@ struct FwdTiling {
 // CT   column groups of 32 per wavefront (the tile is 32 filters x 32*CT columns)
 // KC   K-steps per pipelined chunk of B loads
 // AL4  g and L are multiples of 4: groups of four weights are wholly inside or outside a window
+// CH8  Cin and the tiles' first channels are multiples of KC: the KC planes of a chunk follow one another in memory, only a chunk's
+//      start wraps.  Their addresses are then one vector offset per chunk and KC scalar bases for the whole kernel, instead of
+//      four vector instructions per plane.
 //      A lane owns one group of CT CONSECUTIVE columns of a sample (column_groups in scc_common.h: one load per
 //      plane, one store per output row, whatever the size of the plane)
 // T    storage type of x, w, y (float or bf16_t); sums are binary32 either way, products go through the
@@ -56,7 +61,11 @@ struct FwdTiling {
 // Four columns per lane and a contraction shared by four wavefronts: unbounded, the compiler takes 320 registers, which leaves
 // one wavefront per SIMD. Bounded to two (256, a few dwords spilled outside the loops), us: 64 x 512 -> 1024 on 7x7, cg 2, co 0.33,
 // f32 47 -> 34, bf16 37 -> 23; 15 x 608 -> 2432 on 7x9, cg 2, bf16 30 -> 21.
-template <typename T_, int CT, int KC, bool AL4, int S, int WPB>
+//
+// What a wavefront executes once, before its first and behind its last matrix instruction, counts as much as the loop in grids of
+// one or two wavefronts per SIMD (a wavefront alone on a SIMD issues an instruction every five cycles): lane exchanges are requested together and not
+// one per row behind a wait each, the two lengths of a block of weights are separate straight code.
+template <typename T_, int CT, int KC, bool AL4, bool CH8, int S, int WPB>
 __global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void forward_mfma32(const T_* __restrict__ x, const T_* __restrict__ w,
                                                       T_* __restrict__ y, Problem P, FwdTiling T)
 {
@@ -120,70 +129,90 @@ __global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void forward_m
     char* A = a_lds + wave * kBlockB;
     const int offv = fvalid ? off : (1 << 30);       // rows without a filter: every position is outside
     avec ga[kG];                                     // raw loaded weights; zeroed per mask bit when committed
-    uint32_t gam = 0;                                // bit 4*it + q: weight q of group `it` is inside the window
-    // position of group `it` of a block of nb steps in the (row, group) grid: full blocks take rows f and
-    // 32+f together (kG lanes per row, 64/kG rows per trip), short ones walk the rows in order
-    auto group_pos = [&](int it, int nb, uint32_t& row, uint32_t& c) {
-        if (nb == kAB) {
+    typedef uint32_t g2vec __attribute__((ext_vector_type(2), aligned(2)));
+    g2vec g2[ES == 2 && AL4 ? kG : 1];               // the same, bf16 in groups of four
+    uint32_t gam = 0;                                // bit 4*it + q (AL4: 4*it): weight q of group `it` is inside the window
+    // position of group `it` in the (row, group) grid of a block: full blocks take rows f and 32+f together (kG lanes per
+    // row, 64/kG rows per trip), blocks of one round (half as many trips) walk the rows in order
+    auto group_pos = [&](int it, auto full, uint32_t& row, uint32_t& c) {
+        if constexpr (decltype(full)::value) {
             row = (uint32_t)((it % (kG / 2)) * (64 / kG) + lane / kG + 32 * (it / (kG / 2)));
             c = (uint32_t)(lane % kG);
         } else {
-            const uint32_t e = (uint32_t)nb >> 2, idx = (uint32_t)(it * 64 + lane);
-            row = idx / e;
-            c = idx - row * e;
+            row = (uint32_t)(it * (128 / kG) + lane / (kG / 2));
+            c = (uint32_t)(lane % (kG / 2));
         }
     };
-    // global -> registers: the weights of K-steps [tb, tb+nb) of both half-waves (nb a multiple of KA, <= kAB)
-    auto stage_issue = [&](int tb, int nb) {
+    // global -> registers: the weights of K-steps [tb, tb + KA) or, full, [tb, tb + kAB) of both half-waves
+    auto issue = [&](int tb, auto full) __attribute__((always_inline)) {
+        constexpr int kTrips = decltype(full)::value ? kG : kG / 2;
+        int ro[kTrips], rw[kTrips];                  // offset and first weight of each group's filter
+#pragma unroll
+        for (int it = 0; it < kTrips; ++it) {
+            uint32_t row, c;
+            group_pos(it, full, row, c);
+            if (decltype(full)::value && it >= kG / 2) {      // rows 32+f: the filters of rows f
+                ro[it] = ro[it % (kG / 2)];
+                rw[it] = rw[it % (kG / 2)];
+            } else {
+                ro[it] = __shfl(offv, (int)(row & 31u), 64);
+                rw[it] = __shfl(wrow, (int)(row & 31u), 64);
+            }
+        }
         gam = 0;
 #pragma unroll
-        for (int it = 0; it < kG; ++it) {
+        for (int it = 0; it < kTrips; ++it) {
             uint32_t row, c;
-            group_pos(it, nb, row, c);
-            const bool act = row < 64u;              // short blocks have fewer groups than lanes * kG
-            const int fr = (int)(row & 31u);
-            const int ro = __shfl(offv, fr, 64), rw = __shfl(wrow, fr, 64);
-            const int j0 = (int)((row >> 5) & 1u) * T.Uh + tb + 4 * (int)c - ro;
+            group_pos(it, full, row, c);
+            const int j0 = (int)(row >> 5) * T.Uh + tb + 4 * (int)c - ro[it];
             if (AL4) {
-                const bool in = act && j0 >= 0 && j0 < P.L;
-                ga[it] = *(const avec*)(wb + (uint32_t)(in ? rw + j0 : 0) * ES);
-                gam |= in ? (0xfu << (4 * it)) : 0u;
+                const bool in = j0 >= 0 && j0 < P.L;
+                const char* at = wb + (uint32_t)(in ? rw[it] + j0 : 0) * ES;
+                if constexpr (ES == 2)
+                    g2[it] = *(const g2vec*)at;
+                else
+                    ga[it] = *(const avec*)at;
+                gam |= in ? (1u << (4 * it)) : 0u;
             } else {
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {
                     const int j = j0 + q;
-                    const bool in = act && j >= 0 && j < P.L;
-                    ga[it][q] = *(const T_*)(wb + (uint32_t)(in ? rw + j : 0) * ES);
+                    const bool in = j >= 0 && j < P.L;
+                    ga[it][q] = *(const T_*)(wb + (uint32_t)(in ? rw[it] + j : 0) * ES);
                     gam |= in ? (1u << (4 * it + q)) : 0u;
                 }
             }
         }
     };
     // registers -> LDS
-    auto stage_commit = [&](int nb) {
+    auto commit = [&](auto full) __attribute__((always_inline)) {
+        constexpr int kTrips = decltype(full)::value ? kG : kG / 2;
 #pragma unroll
-        for (int it = 0; it < kG; ++it) {
+        for (int it = 0; it < kTrips; ++it) {
             uint32_t row, c;
-            group_pos(it, nb, row, c);
-            if (row < 64u) {
-                char* dst = A + row * kRowB + 8 * c;
-                const uint32_t m4 = gam >> (4 * it);
-                if constexpr (ES == 2) {
-                    const uint32_t v0 = (m4 & 1u ? (uint32_t)ga[it][0] : 0u) | ((m4 & 2u ? (uint32_t)ga[it][1] : 0u) << 16);
-                    const uint32_t v1 = (m4 & 4u ? (uint32_t)ga[it][2] : 0u) | ((m4 & 8u ? (uint32_t)ga[it][3] : 0u) << 16);
-                    *(u32x2*)dst = u32x2{v0, v1};
-                } else {
-                    const float v[4] = {m4 & 1u ? ga[it][0] : 0.f, m4 & 2u ? ga[it][1] : 0.f, m4 & 4u ? ga[it][2] : 0.f,
-                                        m4 & 8u ? ga[it][3] : 0.f};
-                    uint32_t hi[2], mid[2], lo3[2];
-                    split3<4>([&](int e) { return v[e]; }, hi, mid, lo3);
-                    *(u32x2*)dst = u32x2{hi[0], hi[1]};
-                    *(u32x2*)(dst + kPartB) = u32x2{mid[0], mid[1]};
-                    *(u32x2*)(dst + 2 * kPartB) = u32x2{lo3[0], lo3[1]};
-                }
+            group_pos(it, full, row, c);
+            char* dst = A + row * kRowB + 8 * c;
+            auto in = [&](int q) { return ((gam >> (AL4 ? 4 * it : 4 * it + q)) & 1u) != 0; };
+            if constexpr (ES == 2 && AL4) {
+                *(u32x2*)dst = u32x2{in(0) ? g2[it][0] : 0u, in(0) ? g2[it][1] : 0u};
+            } else if constexpr (ES == 2) {
+                const uint32_t v0 = (in(0) ? (uint32_t)ga[it][0] : 0u) | ((in(1) ? (uint32_t)ga[it][1] : 0u) << 16);
+                const uint32_t v1 = (in(2) ? (uint32_t)ga[it][2] : 0u) | ((in(3) ? (uint32_t)ga[it][3] : 0u) << 16);
+                *(u32x2*)dst = u32x2{v0, v1};
+            } else {
+                const float v[4] = {in(0) ? ga[it][0] : 0.f, in(1) ? ga[it][1] : 0.f, in(2) ? ga[it][2] : 0.f,
+                                    in(3) ? ga[it][3] : 0.f};
+                uint32_t hi[2], mid[2], lo3[2];
+                split3<4>([&](int e) { return v[e]; }, hi, mid, lo3);
+                *(u32x2*)dst = u32x2{hi[0], hi[1]};
+                *(u32x2*)(dst + kPartB) = u32x2{mid[0], mid[1]};
+                *(u32x2*)(dst + 2 * kPartB) = u32x2{lo3[0], lo3[1]};
             }
         }
     };
+    // nb: kAB, or KA for the last round of an odd number
+    auto stage_issue = [&](int tb, int nb) __attribute__((always_inline)) { nb == kAB ? issue(tb, std::true_type()) : issue(tb, std::false_type()); };
+    auto stage_commit = [&](int nb) __attribute__((always_inline)) { nb == kAB ? commit(std::true_type()) : commit(std::false_type()); };
 
     // The second half of the workgroup holds its first request back.  The clock runs on, so the wait ends; the
     // poll count bounds it anyway (64 polls of 256+ cycles each are well beyond the delay).
@@ -206,7 +235,7 @@ __global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void forward_m
         uint32_t n, p;
         column_of_group(live ? u : 0u, T.q, n, p);
         xcol = (n * (uint32_t)P.Cin * (uint32_t)P.HW + p) * ES;
-        ycol = n * (uint32_t)P.Cout * (uint32_t)P.HW + p;
+        ycol = (n * (uint32_t)P.Cout * (uint32_t)P.HW + p) * ES;
     }
     const uint32_t plane = (uint32_t)P.HW * ES;                  // bytes between channel planes
     const uint32_t wrap = (uint32_t)P.Cin * plane;               // bytes of one sample's channels
@@ -219,11 +248,19 @@ __global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void forward_m
         for (int v = 0; v < 16; ++v) acc[c][v] = 0.f;
 
     auto load_b = [&](bvec (&bd)[KC]) {
+        if constexpr (CH8) {
+            const uint32_t at = xcol + rowofs;
 #pragma unroll
-        for (int s = 0; s < KC; ++s) {
-            bd[s] = *(const bvec*)(xb + (uint32_t)(xcol + rowofs));
-            rowofs += plane;
-            rowofs = (rowofs == wrap) ? 0u : rowofs;             // cyclic wrap past channel Cin-1
+            for (int s = 0; s < KC; ++s) bd[s] = *(const bvec*)(xb + (size_t)s * plane + at);
+            rowofs += (uint32_t)KC * plane;
+            rowofs = (rowofs == wrap) ? 0u : rowofs;
+        } else {
+#pragma unroll
+            for (int s = 0; s < KC; ++s) {
+                bd[s] = *(const bvec*)(xb + (uint32_t)(xcol + rowofs));
+                rowofs += plane;
+                rowofs = (rowofs == wrap) ? 0u : rowofs;             // cyclic wrap past channel Cin-1
+            }
         }
     };
     // The KC steps of a chunk are the K values of one bf16 matrix instruction per column group and pair of
@@ -319,18 +356,25 @@ __global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void forward_m
         }
     }
 
-    // ---- store: register v of the accumulator holds tile row 8*(v/4) + 4*h + v%4, column f ----
+    // ---- store: register v of the accumulator holds tile row 8*(v/4) + 4*h + v%4, column f; that row's filter lives in the
+    // registers of the lane of its number ----
+    const int kv = fvalid ? k : -1;
+    int krow[16];
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int fr = 8 * (v >> 2) + 4 * h + (v & 3);
-        const int kr = __shfl(k, fr, 64);            // filter of tile row fr lives in lane fr's registers
-        const bool rvalid = __shfl((int)fvalid, fr, 64) != 0;
-        if (rvalid && live) {
-            bvec o;
+    for (int v = 0; v < 16; ++v) krow[v] = __shfl(kv, 8 * (v >> 2) + 4 * h + (v & 3), 64);
+    auto store_row = [&](int v) {
+        bvec o;
 #pragma unroll
-            for (int c = 0; c < CT; ++c) o[c] = from_f32<T_>(acc[c][v]);
-            __builtin_nontemporal_store(o, (bvec*)(y + (size_t)ycol + (size_t)kr * P.HW));  // written once, not re-read here
-        }
+        for (int c = 0; c < CT; ++c) o[c] = from_f32<T_>(acc[c][v]);
+        __builtin_nontemporal_store(o, (bvec*)((char*)y + (ycol + (uint32_t)krow[v] * plane)));  // written once, not re-read here
+    };
+    if (__all((int)(live && fvalid))) {              // a whole tile: no row and no column is asked for
+#pragma unroll
+        for (int v = 0; v < 16; ++v) store_row(v);
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (krow[v] >= 0 && live) store_row(v);
     }
 }
 
@@ -382,10 +426,14 @@ void launch_wpb(const T_* x, const T_* w, T_* y, const Problem& p, hipStream_t s
     t.chunk = (t.total + 7) / 8;
     const long long blocks = (long long)8 * t.chunk;
     const bool al4 = (t.b.g % 4 == 0) && (p.L % 4 == 0);
-    if (al4)
-        forward_mfma32<T_, CT, KC, true, S, WPB><<<dim3((unsigned)blocks), dim3(WPB * 64), 0, st>>>(x, w, y, p, t);
+    const bool ch8 = al4 && p.Cin % KC == 0 && (t.b.g * t.TM % KC == 0 || t.MB == 1);
+    const dim3 grid((unsigned)blocks), block(WPB * 64);
+    if (ch8)
+        forward_mfma32<T_, CT, KC, true, true, S, WPB><<<grid, block, 0, st>>>(x, w, y, p, t);
+    else if (al4)
+        forward_mfma32<T_, CT, KC, true, false, S, WPB><<<grid, block, 0, st>>>(x, w, y, p, t);
     else
-        forward_mfma32<T_, CT, KC, false, S, WPB><<<dim3((unsigned)blocks), dim3(WPB * 64), 0, st>>>(x, w, y, p, t);
+        forward_mfma32<T_, CT, KC, false, false, S, WPB><<<grid, block, 0, st>>>(x, w, y, p, t);
 }
 
 template <typename T_, int CT, int S, int KC>
