@@ -134,19 +134,17 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
     const int ksafe = valid_f ? k_f : 0;       // rows of filters that do not exist are loaded but never stored
     const int cbase = (lo + sc * (32 * kPosTiles)) % P.Cin;
 #pragma unroll
-    for (int it = 0; it < kRows / 8; ++it) {
-        const int row = 8 * it + lr;
-        if (it < 4) {
-            rowoff[it] = (uint32_t)__shfl(ksafe, row, 64) * plane;
-        } else {
-            int c = cbase + (row - 32);
-            if (P.Cin >= 32 * kPosTiles) {     // at most one wrap
-                c -= (c >= P.Cin) ? P.Cin : 0;
-            } else {
-                c %= P.Cin;
-            }
-            rowoff[it] = (uint32_t)c * plane;
-        }
+    for (int it = 0; it < 4; ++it) rowoff[it] = (uint32_t)__shfl(ksafe, 8 * it + lr, 64) * plane;
+    const bool once = P.Cin >= 32 * kPosTiles;   // at most one wrap
+#pragma unroll
+    for (int it = 4; it < kRows / 8; ++it) {
+        int c = cbase + (8 * it + lr - 32);
+        c -= (c >= P.Cin) ? P.Cin : 0;
+        rowoff[it] = (uint32_t)c * plane;
+    }
+    if (!once) {
+#pragma unroll
+        for (int it = 4; it < kRows / 8; ++it) rowoff[it] = (uint32_t)((cbase + (8 * it + lr - 32)) % P.Cin) * plane;
     }
 
     // column groups [qb, qe) of this wavefront: the K-split's share, split again over the waves
@@ -366,9 +364,15 @@ __device__ __forceinline__ void weight_reduce_body(const float* __restrict__ par
         };
         while (ks + 60 < KS) trip(std::integral_constant<int, 16>());
         while (ks + 28 < KS) trip(std::integral_constant<int, 8>());
-        float rest = 0.f;
-        for (; ks < KS; ks += 4) rest += part[(size_t)ks * count + e];
-        s += rest;
+        if (ks < KS) {                        // up to 7 more, in flight together as well: one after the other each takes a memory latency
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = part[(size_t)(ks + 4 * u < KS ? ks + 4 * u : ks) * count + e];
+            float rest = v[0];
+#pragma unroll
+            for (int u = 1; u < 8; ++u) rest += ks + 4 * u < KS ? v[u] : 0.f;
+            s += rest;
+        }
     }
     sums[w][el] = s;
     __syncthreads();

@@ -25,28 +25,51 @@ __global__ __launch_bounds__(256) void pack_weights(const T_* __restrict__ w, ch
         k_row = filter_of(T.b, row / T.b.F, row % T.b.F, P.Cout);
         s_row = T.b.g * (row / T.b.F);
     }
+    // Indexes first, then 8 loads without a condition, then the masks: a load behind a condition each is a branch and a wait each.
+    // Grad-input walks on from the lane's first position instead of dividing for every one.
     float v[8];
     bool any = false;
+    uint32_t at[8], in8 = 0;
+    const int pos0 = 16 * kg + 8 * h;
+    int mm = FWD ? 0 : pos0 / T.b.F, i = FWD ? 0 : pos0 - mm * T.b.F, m = 0, r = 0;
+    if (!FWD) {
+        m = (first + mm) % T.b.P;
+        m += m < 0 ? T.b.P : 0;
+        r = (int)(((uint32_t)m * (uint32_t)T.b.inv) % (uint32_t)T.b.P);
+    }
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        const int pos = 16 * kg + 8 * h + e;
+        const int pos = pos0 + e;
         int k = k_row, s = s_row, c = row;
         if (FWD) {
             c = first + pos;                       // first < Cin and pos < Cin where it counts
             c -= c >= P.Cin ? P.Cin : 0;
         } else {
-            const int mm = pos / T.b.F;
-            int m = (first + mm) % T.b.P;
-            m += m < 0 ? T.b.P : 0;
-            k = filter_of(T.b, m, pos - mm * T.b.F, P.Cout);
+            k = r + T.b.P * i;
+            k = k < P.Cout ? k : -1;
             s = T.b.g * m;
+            ++i;                                   // the next filter of window m, or the first of the next window
+            const bool next = i == T.b.F;
+            i = next ? 0 : i;
+            int rn = r + T.b.inv, mn = m + 1;
+            rn -= rn >= T.b.P ? T.b.P : 0;
+            mn -= mn >= T.b.P ? T.b.P : 0;
+            r = next ? rn : r;
+            m = next ? mn : m;
         }
         int j = c - s;
         j += j < 0 ? P.Cin : 0;
-        const bool in = pos < len && row < T.rows && k >= 0 && j < P.L;
-        v[e] = to_f32(in ? w[(size_t)k * P.L + j] : (T_)0);
-        any |= in;
+        const bool in = (pos < len) & (row < T.rows) & (k >= 0) & (j < P.L);
+        const uint32_t idx = (uint32_t)k * (uint32_t)P.L + (uint32_t)j;
+        at[e] = in ? idx : 0u;
+        in8 |= in ? 1u << e : 0u;
     }
+    T_ raw[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) raw[e] = w[at[e]];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = (in8 >> e) & 1u ? to_f32(raw[e]) : 0.f;
+    any = in8 != 0;
     constexpr int NP = sizeof(T_) == 2 ? 1 : 3;
     char* dst = ws + T.a_at + ((size_t)((ng * nkg + kg) * kTiles + tile) * NP) * 1024 + lane * 16;
     if constexpr (NP == 3) {

@@ -257,19 +257,26 @@ __device__ __forceinline__ void packed_body(const T_* __restrict__ src, const ch
     const bool live = u < (uint32_t)T.q.count;
     uint32_t n, p;
     column_of_group(live ? u : 0u, T.q, n, p);
-    T_* ob = out + (size_t)n * drows * P.HW + p;
+    const uint32_t step = (uint32_t)P.HW * ES, ob = (n * (uint32_t)drows * (uint32_t)P.HW + p) * ES;
     const int row0 = (ng * kTiles + wave) * 32;
     int plane = row0 + f < T.rows ? row0 + f : -1;      // output plane of tile row f
     if (FWD && plane >= 0) plane = filter_of(T.b, plane / T.b.F, plane % T.b.F, P.Cout);
+    int prow[16];                                       // requested together: one by one each would wait for its exchange
 #pragma unroll
-    for (int v = 0; v < 16; ++v) {
-        const int pr = __shfl(plane, 8 * (v >> 2) + 4 * h + (v & 3), 64);
-        if (pr >= 0 && live) {
-            bvec o;
+    for (int v = 0; v < 16; ++v) prow[v] = __shfl(plane, 8 * (v >> 2) + 4 * h + (v & 3), 64);
+    auto store_row = [&](int v) {
+        bvec o;
 #pragma unroll
-            for (int c = 0; c < CT; ++c) o[c] = from_f32<T_>(acc[c][v]);
-            __builtin_nontemporal_store(o, (bvec*)(ob + (size_t)pr * P.HW));   // written once, never re-read here
-        }
+        for (int c = 0; c < CT; ++c) o[c] = from_f32<T_>(acc[c][v]);
+        __builtin_nontemporal_store(o, (bvec*)((char*)out + (ob + (uint32_t)prow[v] * step)));   // written once, never re-read here
+    };
+    if (__all((int)(live && plane >= 0))) {             // a whole tile: no row and no column is asked for
+#pragma unroll
+        for (int v = 0; v < 16; ++v) store_row(v);
+    } else {
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+            if (prow[v] >= 0 && live) store_row(v);
     }
 }
 

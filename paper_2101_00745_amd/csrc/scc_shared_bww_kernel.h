@@ -210,18 +210,23 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
     // accumulator register v holds row 8*(v/4) + 4*h + v%4 of the wavefront's tile, walk position pos0 + 32t + f
     const int k_f = filter(row0 + f);
     const int s_f = T.b.g * ((row0 + f) / T.b.F);
-    float* dst = out + (size_t)ks * ((size_t)P.Cout * P.L);
+    char* dst = (char*)(out + (size_t)ks * ((size_t)P.Cout * P.L));
+    int kr[16], sr[16];                                 // requested together: one by one each would wait for its exchange
 #pragma unroll
     for (int v = 0; v < 16; ++v) {
         const int fr = 8 * (v >> 2) + 4 * h + (v & 3);
-        const int k = __shfl(k_f, fr, 64), s = __shfl(s_f, fr, 64);
+        kr[v] = __shfl(k_f, fr, 64);
+        sr[v] = __shfl(s_f, fr, 64);
+    }
+#pragma unroll
+    for (int v = 0; v < 16; ++v) {
 #pragma unroll
         for (int t = 0; t < PT; ++t) {
             const int pos = pos0 + 32 * t + f;
-            int j = first + pos - s;                    // first <= s: j starts at first - s > -Cin
+            int j = first + pos - sr[v];                // first <= s: j starts at first - s > -Cin
             j += j < 0 ? P.Cin : 0;
             j -= j >= P.Cin ? P.Cin : 0;
-            if (k >= 0 && pos < len && j < P.L) dst[(size_t)k * P.L + j] = acc[t][v];
+            if ((kr[v] >= 0) & (pos < len) & (j < P.L)) *(float*)(dst + (uint32_t)(kr[v] * P.L + j) * 4u) = acc[t][v];
         }
     }
 }
