@@ -373,11 +373,25 @@ inline int choose(const Problem& p, int es)
     double again;
     const double fetches = fetches_without_sharing<FWD>(p, b, &again);
     const bool odd = uneven(p, b), banded = FWD && b.F < 32 && b.P > 1;
-    if (es == 2) return again >= 3.0 && fetches >= (odd ? 20e6 : 55e6) ? ct : 0;
-    if (FWD) {
-        if (!odd && !banded && p.L < 300) return 0;         // forward_shared32 is as fast there
-        return again >= 3.0 && fetches >= (odd || banded ? 25e6 : 60e6) ? ct : 0;
+    // Layers of whole groups of 4 pixels and weights and one window per tile, forward: the kernels without a workspace lose least
+    // there (fp32 has forward_shared32), so it counts how much longer the row groups' walks are than their windows.  Of 220
+    // fp32 layers from 5 fetches on, null / packed: below 1.2 from 60e6 fetches 1.06 to 1.19 by class of fetches, above 1.2 from 120e6 1.09 (60e6
+    // to 120e6 0.97 to 1.1, single layers 0.7); 120 bf16 layers: from 7 fetches 1.01 to 1.18 from 80e6 on (below 0.72 to 1.0), walks
+    // no longer than the windows 1.11 from 60e6 on.
+    if (FWD && !odd && !banded && (es == 2 || p.L < 300)) {
+        double walks = 0;
+        const int rows = b.P * b.F;
+        for (int ng = 0; 128 * ng < rows; ++ng) {
+            int first, len;
+            walk_of<true>(p, b, rows, ng, first, len);
+            walks += len;
+        }
+        const double longer = walks * 128 / ((double)rows * p.L);
+        if (es == 2) return again >= 7.0 && fetches >= (longer < 1.05 ? 60e6 : 80e6) ? ct : 0;
+        return (again >= 5.0 && longer < 1.2 && fetches >= 60e6) || (again >= 7.0 && fetches >= 120e6) ? ct : 0;
     }
+    if (es == 2) return again >= 3.0 && fetches >= (odd ? 20e6 : 55e6) ? ct : 0;
+    if (FWD) return again >= 3.0 && fetches >= (odd || banded ? 25e6 : 60e6) ? ct : 0;
     return fetches >= (odd ? 80e6 : 110e6) && (again >= 5.0 || fetches >= 150e6) ? ct : 0;
 }
 
