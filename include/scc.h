@@ -279,6 +279,19 @@ int scc_dw_backward(const void* x, const void* kdw, const void* w, const void* d
                     void* workspace, size_t workspace_bytes, void* stream);
 
 /*
+ * The same with the two filter gradients in the type `grad`: SCC_F32 as above, SCC_BF16 rounded to nearest even from the same
+ * binary32 sums (what a training step that keeps its weights in bf16 accumulates).  With a workspace of
+ * scc_dw_backward_as_workspace_bytes(...) bytes the call runs the stages of smaller layers side by side and adds the partial sums
+ * of both gradients in one launch, and so does scc_dw_backward given that much for SCC_F32; SCC_F32 also runs on
+ * scc_dw_backward_workspace_bytes(...), one stage after the other, with the same results bit for bit.
+ */
+size_t scc_dw_backward_as_workspace_bytes(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co,
+                                          scc_dtype dtype, scc_dtype grad);
+int scc_dw_backward_as(const void* x, const void* kdw, const void* w, const void* dy, void* dx, void* dkdw, void* dw,
+                       int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype,
+                       scc_dtype grad, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
  * scc_backward_weight for callers that cannot allocate device memory or hand over a workspace:
  * code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same
  * arguments, kernels, arithmetic and summation order as scc_backward_weight (results are bitwise

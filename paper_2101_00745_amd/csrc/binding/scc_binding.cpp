@@ -198,16 +198,18 @@ PyObject* dw_backward(PyObject*, PyObject* const* args, Py_ssize_t n)
     HANDLE_TH_ERRORS
     Args a;
     Layer l;
-    if (!parse(args, n, 4, true, &a) || !layer(a, *a.t[0], *a.t[2], &l)) Py_RETURN_NONE;
+    if (n != 8 || !PyBool_Check(args[7]) || !parse(args, 7, 4, true, &a) || !layer(a, *a.t[0], *a.t[2], &l)) Py_RETURN_NONE;
     const at::Tensor &x = *a.t[0], &k = *a.t[1], &w = *a.t[2], &dy = *a.t[3];
     if (!taps(k, x, l) || !outputs(dy, x, l)) Py_RETURN_NONE;
-    const at::TensorOptions f32 = x.options().dtype(at::kFloat);
-    at::Tensor dx = at::empty_like(x), dk = at::empty(k.sizes(), f32), dw = at::empty(w.sizes(), f32);
-    const size_t need = scc_dw_backward_workspace_bytes(l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg, a.co, l.dtype);
+    const scc_dtype grad = args[7] == Py_True ? l.dtype : SCC_F32;
+    const at::TensorOptions of = x.options().dtype(grad == SCC_F32 ? at::kFloat : at::kBFloat16);
+    at::Tensor dx = at::empty_like(x), dk = at::empty(k.sizes(), of), dw = at::empty(w.sizes(), of);
+    const size_t need = scc_dw_backward_as_workspace_bytes(l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg, a.co, l.dtype, grad);
     const at::Tensor ws = scratch(need, x);
     const int rc = launch(x, [&](void* st) {
-        return scc_dw_backward(x.data_ptr(), k.data_ptr(), w.data_ptr(), dy.data_ptr(), dx.data_ptr(), dk.data_ptr(), dw.data_ptr(),
-                               l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg, a.co, l.dtype, address(ws), need, st);
+        return scc_dw_backward_as(x.data_ptr(), k.data_ptr(), w.data_ptr(), dy.data_ptr(), dx.data_ptr(), dk.data_ptr(),
+                                  dw.data_ptr(), l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg, a.co, l.dtype, grad, address(ws), need,
+                                  st);
     });
     if (rc != SCC_OK) Py_RETURN_NONE;
     return tuple_of({dx, dk, dw});
@@ -217,7 +219,7 @@ PyObject* dw_backward(PyObject*, PyObject* const* args, Py_ssize_t n)
 #define METHOD(name, doc) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, doc}
 PyMethodDef methods[] = {METHOD(forward, "(x, w, cg, co) -> y or None"), METHOD(backward, "(x, dy, w, cg, co) -> (dx, dw) or None"),
                          METHOD(dw_forward, "(x, kdw, w, cg, co, stride) -> y or None"),
-                         METHOD(dw_backward, "(x, kdw, w, dy, cg, co, stride) -> (dx, dkdw, dw) or None"),
+                         METHOD(dw_backward, "(x, kdw, w, dy, cg, co, stride, stored) -> (dx, dkdw, dw) or None"),
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};
 

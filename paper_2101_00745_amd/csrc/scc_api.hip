@@ -474,21 +474,29 @@ static size_t dw_backward_plane_bytes(const Problem& p, scc_dtype dtype)
     return align256((size_t)p.NQ * p.Cin * (dtype == SCC_F32 ? 4 : 2));
 }
 
-// What its three stages one after the other cannot do without.
+// What a call that adds each gradient's slices right behind its stage cannot do without.
 static size_t dw_backward_least(const Problem& p, const scc::DwGeom& g, scc_dtype dtype)
 {
     return 2 * dw_backward_plane_bytes(p, dtype) +
            std::max(backward_need(p, dtype), scc::depthwise3x3_backward_workspace(p.N, p.Cin, g));
 }
 
-// What the stages side by side take (they keep the partial sums of dw and dk at once); 0: not a layer for that.
-static size_t dw_backward_paired_need(const Problem& p, const scc::DwGeom& g, scc_dtype dtype)
+// What one that adds them together at the end takes: the scratch of both at once and, where the gradients leave rounded, both in
+// binary32.
+static size_t dw_backward_whole(const Problem& p, const scc::DwGeom& g, scc_dtype dtype, scc_dtype grad)
 {
-    const bool fused = dtype == SCC_F32 && scc::backward_fused_eligible(p);
-    if (fused || backward_shared_need(p, dtype) > 0 ||
-        !with_type(dtype, [&](auto t) { return (int)scc::block_backward_applicable<decltype(t)>(p, g); }))
-        return 0;
-    return 2 * dw_backward_plane_bytes(p, dtype) + scc::block_backward_workspace(p, g);
+    const size_t wide = grad == SCC_BF16 ? align256((size_t)p.Cout * p.L * 4) + align256((size_t)p.Cin * 9 * 4) : 0;
+    return 2 * dw_backward_plane_bytes(p, dtype) + align256(backward_need(p, dtype)) +
+           align256(scc::depthwise3x3_backward_workspace(p.N, p.Cin, g)) + wide;
+}
+
+size_t scc_dw_backward_as_workspace_bytes(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co,
+                                          scc_dtype dtype, scc_dtype grad)
+{
+    Problem p;
+    scc::DwGeom g;
+    if (make_dw_problem(N, Cin, Cout, H, W, dw_stride, cg, co, &p, &g) != SCC_OK || !dtype_ok(dtype) || !dtype_ok(grad)) return 0;
+    return dw_backward_whole(p, g, dtype, grad);
 }
 
 size_t scc_dw_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co,
@@ -497,40 +505,80 @@ size_t scc_dw_backward_workspace_bytes(int N, int Cin, int Cout, int H, int W, i
     Problem p;
     scc::DwGeom g;
     if (make_dw_problem(N, Cin, Cout, H, W, dw_stride, cg, co, &p, &g) != SCC_OK || !dtype_ok(dtype)) return 0;
-    return std::max(dw_backward_least(p, g, dtype), dw_backward_paired_need(p, g, dtype));
+    return dw_backward_least(p, g, dtype);
 }
 
-int scc_dw_backward(const void* x, const void* kdw, const void* w, const void* dy, void* dx, void* dkdw, void* dw, int N,
-                    int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype, void* workspace,
-                    size_t workspace_bytes, void* stream)
+int scc_dw_backward_as(const void* x, const void* kdw, const void* w, const void* dy, void* dx, void* dkdw, void* dw, int N,
+                       int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype, scc_dtype grad,
+                       void* workspace, size_t workspace_bytes, void* stream)
 {
     if (!x || !kdw || !w || !dy || !dx || !dkdw || !dw) return SCC_ERR_NULL;
     Problem p;
     scc::DwGeom g;
     const int rc = make_dw_problem(N, Cin, Cout, H, W, dw_stride, cg, co, &p, &g);
     if (rc != SCC_OK) return rc;
-    if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    if (!workspace || !holds(dw_backward_least(p, g, dtype), workspace, workspace_bytes)) return SCC_ERR_WORKSPACE;
+    if (!dtype_ok(dtype) || !dtype_ok(grad)) return SCC_ERR_DTYPE;
+    const size_t whole = dw_backward_whole(p, g, dtype, grad);
+    const bool together = workspace && holds(whole, workspace, workspace_bytes);
+    if (!together && (grad != SCC_F32 || !workspace || !holds(dw_backward_least(p, g, dtype), workspace, workspace_bytes)))
+        return SCC_ERR_WORKSPACE;
     const size_t plane = dw_backward_plane_bytes(p, dtype);
     char* z = (char*)workspace;
     char* dz = z + plane;
     char* rest = dz + plane;
-    const size_t paired = dw_backward_paired_need(p, g, dtype);
-    if (paired > 0 && holds(paired, workspace, workspace_bytes)) {
-        drop_stale_error();
-        return with_type(dtype, [&](auto t) {
-            typedef decltype(t) T;
-            return launch_status(scc::launch_block_backward((const T*)x, (const T*)kdw, (const T*)w, (const T*)dy, (T*)dx,
-                                                            (float*)dkdw, (float*)dw, (T*)z, (T*)dz, rest, p, g,
-                                                            (hipStream_t)stream));
-        });
+    int r;
+    if (!together) {
+        r = scc_depthwise3x3_forward(x, kdw, z, N, Cin, H, W, dw_stride, dtype, stream);
+        if (r != SCC_OK) return r;
+        r = scc_backward(z, dy, w, dz, dw, N, Cin, Cout, g.Ho, g.Wo, cg, co, dtype, rest, workspace_bytes - 2 * plane, stream);
+        if (r != SCC_OK) return r;
+        return scc_depthwise3x3_backward(x, kdw, dz, dx, dkdw, N, Cin, H, W, dw_stride, dtype, rest, workspace_bytes - 2 * plane,
+                                         stream);
     }
-    int r = scc_depthwise3x3_forward(x, kdw, z, N, Cin, H, W, dw_stride, dtype, stream);
+    const hipStream_t st = (hipStream_t)stream;
+    const size_t need = backward_need(p, dtype);
+    char* part_k = rest + align256(need);
+    char* wide = part_k + align256(scc::depthwise3x3_backward_workspace(N, Cin, g));
+    // where the kernels put a gradient of one slice
+    float* to_w = grad == SCC_F32 ? (float*)dw : (float*)wide;
+    float* to_k = grad == SCC_F32 ? (float*)dkdw : (float*)(wide + align256((size_t)Cout * p.L * 4));
+    scc::SliceSum sum_w = {to_w, Cout * p.L, 1}, sum_k = {to_k, Cin * 9, 1};
+    const bool aligned = ((uintptr_t)dy & 15u) == 0;                       // z and dz are
+    const int path = backward_path(p, dtype, aligned, rest, need);
+    if (path < 0) return path;
+    drop_stale_error();
+    r = with_type(dtype, [&](auto t) {
+        typedef decltype(t) T;
+        const T *tx = (const T*)x, *tk = (const T*)kdw, *tw = (const T*)w, *ty = (const T*)dy;
+        if (path == SCC_BACKWARD_MERGED && scc::block_backward_applicable<T>(p, g))
+            return launch_status(scc::launch_block_backward(tx, tk, tw, ty, (T*)dx, to_k, to_w, (T*)z, (T*)dz, (float*)rest,
+                                                            (float*)part_k, &sum_w, &sum_k, p, g, st));
+        int e = scc_depthwise3x3_forward(x, kdw, z, N, Cin, H, W, dw_stride, dtype, stream);
+        if (e != SCC_OK) return e;
+        if (path == SCC_BACKWARD_FUSED)
+            e = launch_status(scc::launch_backward_fused((const float*)z, (const float*)dy, (const float*)w, (float*)dz, to_w,
+                                                         (float*)rest, p, st, &sum_w));
+        else if (path == SCC_BACKWARD_SHARED)
+            e = launch_status(scc::launch_backward_shared((const T*)z, ty, tw, (T*)dz, to_w, rest, p, st, &sum_w));
+        else if (path == SCC_BACKWARD_MERGED)
+            e = launch_status(scc::launch_backward_merged((const T*)z, ty, tw, (T*)dz, to_w, (float*)rest, p, st, &sum_w));
+        else
+            e = scc_backward(z, dy, w, dz, to_w, N, Cin, Cout, g.Ho, g.Wo, cg, co, dtype, rest, need, stream);
+        if (e != SCC_OK) return e;
+        return launch_status(scc::launch_depthwise3x3_backward(tx, tk, (const T*)dz, (T*)dx, to_k, (float*)part_k, N, Cin, g, st,
+                                                               &sum_k));
+    });
     if (r != SCC_OK) return r;
-    r = scc_backward(z, dy, w, dz, dw, N, Cin, Cout, g.Ho, g.Wo, cg, co, dtype, rest, workspace_bytes - 2 * plane, stream);
-    if (r != SCC_OK) return r;
-    return scc_depthwise3x3_backward(x, kdw, dz, dx, dkdw, N, Cin, H, W, dw_stride, dtype, rest,
-                                     workspace_bytes - 2 * plane, stream);
+    if (grad == SCC_F32) return launch_status(scc::launch_gradient_sums(sum_w, (float*)dw, sum_k, (float*)dkdw, st));
+    return launch_status(scc::launch_gradient_sums(sum_w, (scc::bf16_t*)dw, sum_k, (scc::bf16_t*)dkdw, st));
+}
+
+int scc_dw_backward(const void* x, const void* kdw, const void* w, const void* dy, void* dx, void* dkdw, void* dw, int N,
+                    int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype, void* workspace,
+                    size_t workspace_bytes, void* stream)
+{
+    return scc_dw_backward_as(x, kdw, w, dy, dx, dkdw, dw, N, Cin, Cout, H, W, dw_stride, cg, co, dtype, SCC_F32, workspace,
+                              workspace_bytes, stream);
 }
 
 int scc_backward_weight_static(const void* x, const void* dy, void* dw, int N, int Cin, int Cout, int H, int W, int cg,

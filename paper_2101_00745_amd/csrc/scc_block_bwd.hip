@@ -106,9 +106,10 @@ __global__ __launch_bounds__(256, SMALL ? 2 : NPT == 2 && sizeof(T_) == 4 ? 1 : 
         gradients_body<T_>(x, kdw, dz, dx, part_k, P.N, P.Cin, G, D, (uint32_t)(bid - nbww));
 }
 
-__global__ __launch_bounds__(256) void block_backward_sum(const float* __restrict__ part_w, float* __restrict__ dw, int count_w,
+template <typename T_>
+__global__ __launch_bounds__(256) void block_backward_sum(const float* __restrict__ part_w, T_* __restrict__ dw, int count_w,
                                                           int slices_w, int nw, const float* __restrict__ part_k,
-                                                          float* __restrict__ dk, int count_k, int slices_k)
+                                                          T_* __restrict__ dk, int count_k, int slices_k)
 {
     const int bid = (int)blockIdx.x;
     if (bid < nw)
@@ -135,11 +136,6 @@ hipError_t launch_second(const T_* x, const T_* kdw, const T_* dy, const T_* z, 
     return hipGetLastError();
 }
 
-size_t weight_part_bytes(const Problem& p, const bww::BwwTiling& tw)
-{
-    return tw.KS > 1 ? ((size_t)tw.KS * p.Cout * p.L * sizeof(float) + 255) / 256 * 256 : 0;
-}
-
 }  // namespace
 
 // Layers that gain: those small enough that launches and latencies count.  The depthwise ranges share the matrix kernels'
@@ -155,15 +151,10 @@ bool block_backward_applicable(const Problem& p, const DwGeom& g)
     return values <= (g.Wo % 4 == 0 ? 1ll << 23 : 1ll << 22) && backward_merged_applicable<T_>(p);
 }
 
-// Bytes behind z and dz.
-size_t block_backward_workspace(const Problem& p, const DwGeom& g)
-{
-    return weight_part_bytes(p, bww::make_tiling(p, true)) + depthwise3x3_backward_workspace(p.N, p.Cin, g);
-}
-
 template <typename T_>
 hipError_t launch_block_backward(const T_* x, const T_* kdw, const T_* w, const T_* dy, T_* dx, float* dk, float* dw, T_* z,
-                                 T_* dz, void* workspace, const Problem& p, const DwGeom& g, hipStream_t st)
+                                 T_* dz, float* part_w, float* part_k, SliceSum* later_w, SliceSum* later_k, const Problem& p,
+                                 const DwGeom& g, hipStream_t st)
 {
     hipError_t e = hipErrorInvalidValue;
     const dw::Stage stage = dw::plan_stage(x, (const T_*)z, p.N, p.Cin, g, false);
@@ -177,8 +168,10 @@ hipError_t launch_block_backward(const T_* x, const T_* kdw, const T_* w, const 
     if (e != hipSuccess) return e;
     const bww::BwwTiling tw = bww::make_tiling(p, true);
     const DwGrads d = plan_gradients(x, (const T_*)dz, (const T_*)dx, p.N, p.Cin, g);
-    float* part_w = tw.KS > 1 ? (float*)workspace : dw;
-    float* part_k = d.slices > 1 ? (float*)((char*)workspace + weight_part_bytes(p, tw)) : dk;
+    if (tw.KS == 1) part_w = dw;
+    if (d.slices == 1) part_k = dk;
+    *later_w = {part_w, p.Cout * p.L, tw.KS};
+    *later_k = {part_k, p.Cin * 9, d.slices};
     if (sizeof(T_) == 4 && p.NQ < 256)
         e = launch_second<T_, 1, sizeof(T_) == 4>(x, kdw, dy, z, dz, dx, part_k, part_w, p, tw, g, d, st);
     else if (tw.NPT == 1)
@@ -187,18 +180,29 @@ hipError_t launch_block_backward(const T_* x, const T_* kdw, const T_* w, const 
         e = launch_second<T_, 2>(x, kdw, dy, z, dz, dx, part_k, part_w, p, tw, g, d, st);
     else
         e = launch_second<T_, 3>(x, kdw, dy, z, dz, dx, part_k, part_w, p, tw, g, d, st);
-    if (e != hipSuccess || (tw.KS == 1 && d.slices == 1)) return e;
-    const int nw = tw.KS > 1 ? (p.Cout * p.L + 63) / 64 : 0, nk = d.slices > 1 ? (p.Cin * 9 + 255) / 256 : 0;
-    block_backward_sum<<<dim3((unsigned)(nw + nk)), dim3(256), 0, st>>>(part_w, dw, p.Cout * p.L, tw.KS, nw, part_k, dk,
-                                                                        p.Cin * 9, d.slices);
+    return e;
+}
+
+template <typename T_>
+hipError_t launch_gradient_sums(const SliceSum& w, T_* dw, const SliceSum& k, T_* dk, hipStream_t st)
+{
+    const bool done_w = w.slices == 1 && (const void*)w.part == (const void*)dw, done_k = k.slices == 1 && (const void*)k.part == (const void*)dk;
+    const int nw = done_w ? 0 : (w.count + 63) / 64, nk = done_k ? 0 : (k.count + 255) / 256;
+    if (nw + nk == 0) return hipSuccess;
+    block_backward_sum<T_><<<dim3((unsigned)(nw + nk)), dim3(256), 0, st>>>(w.part, dw, w.count, w.slices, nw, k.part, dk, k.count,
+                                                                          k.slices);
     return hipGetLastError();
 }
 
 template bool block_backward_applicable<float>(const Problem&, const DwGeom&);
 template bool block_backward_applicable<bf16_t>(const Problem&, const DwGeom&);
 template hipError_t launch_block_backward<float>(const float*, const float*, const float*, const float*, float*, float*, float*,
-                                                 float*, float*, void*, const Problem&, const DwGeom&, hipStream_t);
+                                                 float*, float*, float*, float*, SliceSum*, SliceSum*, const Problem&, const DwGeom&,
+                                                 hipStream_t);
 template hipError_t launch_block_backward<bf16_t>(const bf16_t*, const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, float*,
-                                                  float*, bf16_t*, bf16_t*, void*, const Problem&, const DwGeom&, hipStream_t);
+                                                  float*, bf16_t*, bf16_t*, float*, float*, SliceSum*, SliceSum*, const Problem&,
+                                                  const DwGeom&, hipStream_t);
+template hipError_t launch_gradient_sums<float>(const SliceSum&, float*, const SliceSum&, float*, hipStream_t);
+template hipError_t launch_gradient_sums<bf16_t>(const SliceSum&, bf16_t*, const SliceSum&, bf16_t*, hipStream_t);
 
 }  // namespace scc

@@ -83,7 +83,7 @@ bool backward_merged_applicable(const Problem& p)
 
 template <typename T_>
 hipError_t launch_backward_merged(const T_* x, const T_* dy, const T_* w, T_* dx, float* dw, float* workspace,
-                                  const Problem& p, hipStream_t st)
+                                  const Problem& p, hipStream_t st, SliceSum* later)
 {
     const bww::BwwTiling tw = bww::make_tiling(p, true);
     float* out = tw.KS > 1 ? workspace : dw;
@@ -104,15 +104,16 @@ hipError_t launch_backward_merged(const T_* x, const T_* dy, const T_* w, T_* dx
                 e = launch_variant<T_, CT, S, 3>(x, dy, w, dx, out, p, ti, nbwi, tw, st);
         }
     });
-    if (e != hipSuccess || tw.KS == 1) return e;
+    if (later) *later = {out, p.Cout * p.L, tw.KS};
+    if (e != hipSuccess || tw.KS == 1 || later) return e;
     return launch_weight_reduce(workspace, dw, p.Cout * p.L, tw.KS, st);
 }
 
 template bool backward_merged_applicable<float>(const Problem&);
 template bool backward_merged_applicable<bf16_t>(const Problem&);
 template hipError_t launch_backward_merged<float>(const float*, const float*, const float*, float*, float*, float*,
-                                                  const Problem&, hipStream_t);
+                                                  const Problem&, hipStream_t, SliceSum*);
 template hipError_t launch_backward_merged<bf16_t>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, float*, float*,
-                                                   const Problem&, hipStream_t);
+                                                   const Problem&, hipStream_t, SliceSum*);
 
 }  // namespace scc

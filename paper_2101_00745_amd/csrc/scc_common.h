@@ -153,11 +153,18 @@ template <typename T>
 hipError_t launch_backward_weight_shared(const T* x, const T* dy, float* dw, float* workspace, const Problem& p,
                                          hipStream_t st);
 
+// A filter gradient whose partial sums over `slices` of the batch are not added yet; one slice: it is complete where the
+// kernel was told to write it.  The launchers below that take one leave their sum to launch_gradient_sums.
+struct SliceSum {
+    const float* part;
+    int count, slices;
+};
+
 // Packed grad-input and shared grad-weight as one launch (scc_shared_merged.hip)
 size_t backward_shared_workspace(const Problem& p, int es);   // 0 for layers that do not take it
 template <typename T>
 hipError_t launch_backward_shared(const T* x, const T* dy, const T* w, T* dx, float* dw, void* workspace, const Problem& p,
-                                  hipStream_t st);
+                                  hipStream_t st, SliceSum* later = nullptr);
 
 // dw[e] = sum over K-splits of part[ks][e], e < count, in a fixed order (scc_mfma_bww.hip)
 hipError_t launch_weight_reduce(const float* part, float* dw, int count, int KS, hipStream_t st);
@@ -166,14 +173,14 @@ hipError_t launch_weight_reduce(const float* part, float* dw, int count, int KS,
 bool backward_fused_eligible(const Problem& p);
 size_t backward_fused_workspace(const Problem& p);  // bytes of K-split partials (0 when not split)
 hipError_t launch_backward_fused(const float* x, const float* dy, const float* w, float* dx, float* dw,
-                                 float* workspace, const Problem& p, hipStream_t st);
+                                 float* workspace, const Problem& p, hipStream_t st, SliceSum* later = nullptr);
 
 // Both gradients in one launch, the two matrix-core kernels side by side in one grid (scc_bwd_merged.hip);
 // needs the workspace of the grad-weight pass
 template <typename T> bool backward_merged_applicable(const Problem& p);
 template <typename T>
 hipError_t launch_backward_merged(const T* x, const T* dy, const T* w, T* dx, float* dw, float* workspace,
-                                  const Problem& p, hipStream_t st);
+                                  const Problem& p, hipStream_t st, SliceSum* later = nullptr);
 
 // Depthwise 3x3 stage and the fused DW + SCC forward (scc_dw_fwd.hip); `p` describes the SCC on the Ho x Wo map
 // flip: the filters turned by 180 degrees (tap (i, j) takes the weight of tap (2-i, 2-j)): at stride 1 that is the
@@ -186,19 +193,23 @@ hipError_t launch_depthwise3x3(const T* x, const T* kdw, T* z, int N, int C, con
 size_t depthwise3x3_backward_workspace(int N, int C, const DwGeom& g);
 template <typename T>
 hipError_t launch_depthwise3x3_backward(const T* x, const T* kdw, const T* dz, T* dx, float* dk, float* workspace, int N,
-                                        int C, const DwGeom& g, hipStream_t st);
+                                        int C, const DwGeom& g, hipStream_t st, SliceSum* later = nullptr);
 // ... and the one for layers with few columns (scc_dw_few.hip), fp32 and bf16
 bool dw_forward_few_eligible(const Problem& p, const DwGeom& g);
 bool dw_forward_few_preferred(const Problem& p, const DwGeom& g);   // ... and faster
 template <typename T>
 hipError_t launch_dw_forward_few(const T* x, const T* kdw, const T* w, T* y, const Problem& p, const DwGeom& g, hipStream_t st);
 
-// A block's backward in two launches and a sum (scc_block_bwd.hip); z, dz: planes of the depthwise output and its gradient
+// A block's backward in two launches (scc_block_bwd.hip), both sums left; z, dz: planes of the depthwise output and its gradient,
+// part_w, part_k: the scratch of launch_backward_merged and launch_depthwise3x3_backward
 template <typename T> bool block_backward_applicable(const Problem& p, const DwGeom& g);
-size_t block_backward_workspace(const Problem& p, const DwGeom& g);   // bytes behind those planes
 template <typename T>
 hipError_t launch_block_backward(const T* x, const T* kdw, const T* w, const T* dy, T* dx, float* dk, float* dw, T* z, T* dz,
-                                 void* workspace, const Problem& p, const DwGeom& g, hipStream_t st);
+                                 float* part_w, float* part_k, SliceSum* later_w, SliceSum* later_k, const Problem& p,
+                                 const DwGeom& g, hipStream_t st);
+// dw and dk (binary32, or rounded to bf16) from what their launchers left; one launch, none where both are complete in place
+template <typename T>
+hipError_t launch_gradient_sums(const SliceSum& w, T* dw, const SliceSum& k, T* dk, hipStream_t st);
 bool dw_forward_fused_eligible(const Problem& p);    // the fused kernel can run the layer
 bool dw_forward_fused_preferred(const Problem& p);   // ... and is the faster path for it
 hipError_t launch_dw_forward_fused(const float* x, const float* kdw, const float* w, float* y, const Problem& p,

@@ -159,7 +159,7 @@ size_t depthwise3x3_backward_workspace(int N, int C, const DwGeom& g)
 
 template <typename T>
 hipError_t launch_depthwise3x3_backward(const T* x, const T* kdw, const T* dz, T* dx, float* dk, float* workspace, int N,
-                                        int C, const DwGeom& g, hipStream_t st)
+                                        int C, const DwGeom& g, hipStream_t st, SliceSum* later)
 {
     const int slices = dw::filter_slices(N, C, g);
     const int per = (N + slices - 1) / slices;
@@ -205,7 +205,8 @@ hipError_t launch_depthwise3x3_backward(const T* x, const T* kdw, const T* dz, T
                 x, dz, part, N, C, g, per);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
-        if (slices > 1) {
+        if (later) *later = {part, C * 9, slices};
+        if (slices > 1 && !later) {
             depthwise3x3_filter_reduce<<<dim3((unsigned)((C * 9 + 255) / 256)), dim3(256), 0, st>>>(part, dk, C * 9, slices);
             e = hipGetLastError();
             if (e != hipSuccess) return e;
@@ -215,8 +216,8 @@ hipError_t launch_depthwise3x3_backward(const T* x, const T* kdw, const T* dz, T
 }
 
 template hipError_t launch_depthwise3x3_backward<float>(const float*, const float*, const float*, float*, float*, float*,
-                                                        int, int, const DwGeom&, hipStream_t);
+                                                        int, int, const DwGeom&, hipStream_t, SliceSum*);
 template hipError_t launch_depthwise3x3_backward<bf16_t>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, float*,
-                                                         float*, int, int, const DwGeom&, hipStream_t);
+                                                         float*, int, int, const DwGeom&, hipStream_t, SliceSum*);
 
 }  // namespace scc

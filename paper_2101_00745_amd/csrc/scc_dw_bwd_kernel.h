@@ -241,7 +241,8 @@ __device__ __forceinline__ void filter_pixels_body(const T_* __restrict__ x, con
 }
 
 // dk[e] = sum over slices of part[slice][e], in slice order
-__device__ __forceinline__ void filter_reduce_body(const float* __restrict__ part, float* __restrict__ dk, int count, int slices,
+template <typename T_>
+__device__ __forceinline__ void filter_reduce_body(const float* __restrict__ part, T_* __restrict__ dk, int count, int slices,
                                                    uint32_t bid)
 {
     const int e = (int)bid * 256 + (int)threadIdx.x;
@@ -256,7 +257,7 @@ __device__ __forceinline__ void filter_reduce_body(const float* __restrict__ par
         for (int u = 0; u < 8; ++u) s += v[u];
     }
     for (; sl < slices; ++sl) s += part[(size_t)sl * count + e];
-    dk[e] = s;
+    dk[e] = from_f32<T_>(s);
 }
 
 // slices of the samples per channel: about 1024 workgroups in all, at least one sample for each and, on strips, one strip per

@@ -394,7 +394,7 @@ size_t backward_fused_workspace(const Problem& p)
 }
 
 hipError_t launch_backward_fused(const float* x, const float* dy, const float* w, float* dx, float* dw,
-                                 float* workspace, const Problem& p, hipStream_t st)
+                                 float* workspace, const Problem& p, hipStream_t st, SliceSum* later)
 {
     const FusedTiling t = make_fused_tiling(p);
     static const hipError_t allowed = hipFuncSetAttribute((const void*)backward_fused_lds32,
@@ -403,7 +403,8 @@ hipError_t launch_backward_fused(const float* x, const float* dy, const float* w
     float* out = t.KS > 1 ? workspace : dw;
     backward_fused_lds32<<<dim3((unsigned)(8 * t.chunk)), dim3(kWaves * 64), kLdsBytes, st>>>(x, dy, w, dx, out, p, t);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess || t.KS == 1) return e;
+    if (later) *later = {out, p.Cout * p.L, t.KS};
+    if (e != hipSuccess || t.KS == 1 || later) return e;
     return launch_weight_reduce(workspace, dw, p.Cout * p.L, t.KS, st);
 }
 

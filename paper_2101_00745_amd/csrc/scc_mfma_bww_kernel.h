@@ -341,7 +341,8 @@ __device__ __forceinline__ void backward_weight_body(const T_* __restrict__ x, c
 // four sums are added in wavefront order: the summation tree is fixed, so results are reproducible.  The values of a
 // trip are added as a tree: one chain over the 60 values of a wavefront rounds more than the products' sums in the slices
 // (431 x 112 -> 112 on 32x6, cg 2, bf16, 259 slices: 2-norm against binary64 1.8e-7 with it, 1.3e-7 on the 64 of the per-tile kernel).
-__device__ __forceinline__ void weight_reduce_body(const float* __restrict__ part, float* __restrict__ dw, int count, int KS,
+template <typename T_>
+__device__ __forceinline__ void weight_reduce_body(const float* __restrict__ part, T_* __restrict__ dw, int count, int KS,
                                                    int bid)
 {
     __shared__ float sums[4][64];
@@ -376,7 +377,7 @@ __device__ __forceinline__ void weight_reduce_body(const float* __restrict__ par
     }
     sums[w][el] = s;
     __syncthreads();
-    if (w == 0 && e < count) dw[e] = ((sums[0][el] + sums[1][el]) + sums[2][el]) + sums[3][el];
+    if (w == 0 && e < count) dw[e] = from_f32<T_>(((sums[0][el] + sums[1][el]) + sums[2][el]) + sums[3][el]);
 }
 
 // ---- host side: tiling of a layer -------------------------------------------------------------------------

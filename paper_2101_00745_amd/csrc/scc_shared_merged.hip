@@ -79,7 +79,7 @@ size_t backward_shared_workspace(const Problem& p, int es)
 
 template <typename T_>
 hipError_t launch_backward_shared(const T_* x, const T_* dy, const T_* w, T_* dx, float* dw, void* workspace,
-                                  const Problem& p, hipStream_t st)
+                                  const Problem& p, hipStream_t st, SliceSum* later)
 {
     constexpr int es = (int)sizeof(T_);
     int pt;
@@ -98,13 +98,14 @@ hipError_t launch_backward_shared(const T_* x, const T_* dy, const T_* w, T_* dx
                          : launch_variant<T_, CT, 4>(x, dy, packed_w, dx, part, p, ti, tw, st);
     };
     e = ct == 4 ? with_ct(std::integral_constant<int, 4>{}) : with_ct(std::integral_constant<int, 2>{});
-    if (e != hipSuccess) return e;
+    if (later) *later = {part, p.Cout * p.L, tw.KS > 1 ? tw.KS : 1};
+    if (e != hipSuccess || later) return e;
     return launch_weight_reduce(part, dw, p.Cout * p.L, tw.KS, st);
 }
 
 template hipError_t launch_backward_shared<float>(const float*, const float*, const float*, float*, float*, void*,
-                                                  const Problem&, hipStream_t);
+                                                  const Problem&, hipStream_t, SliceSum*);
 template hipError_t launch_backward_shared<bf16_t>(const bf16_t*, const bf16_t*, const bf16_t*, bf16_t*, float*, void*,
-                                                   const Problem&, hipStream_t);
+                                                   const Problem&, hipStream_t, SliceSum*);
 
 }  // namespace scc

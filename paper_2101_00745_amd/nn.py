@@ -95,8 +95,8 @@ class DWSCCFunction(torch.autograd.Function):
         dy = dy.contiguous()
         need_x, need_k, need_w = ctx.needs_input_grad[:3]
         if need_x and need_k and need_w:                                    # the training step: the three stages in one call
-            dx, dk, dw = _scc.scc_dw_backward(x, kdw, weight, dy, ctx.cg, ctx.co, ctx.s)
-            return dx, dk.to(kdw.dtype), dw.to(weight.dtype), None, None, None
+            dx, dk, dw = _scc._dw_backward(x, kdw, weight, dy, ctx.cg, ctx.co, ctx.s, True)   # the gradients in the weights' type
+            return dx, dk, dw, None, None, None
         z = _scc.scc_depthwise3x3_forward(x, kdw, ctx.s)
         dz = dw = None
         if (need_x or need_k) and need_w:

@@ -22,7 +22,8 @@ SYMBOLS = ("scc_window_params", "scc_forward", "scc_forward_workspace_bytes", "s
            "scc_backward_workspace_bytes", "scc_backward", "scc_backward_weight_path", "scc_backward_path",
            "scc_depthwise3x3_out", "scc_depthwise3x3_forward", "scc_depthwise3x3_backward_workspace_bytes",
            "scc_depthwise3x3_backward", "scc_dw_forward_workspace_bytes", "scc_dw_forward_fusable", "scc_dw_forward",
-           "scc_dw_backward_workspace_bytes", "scc_dw_backward", "scc_status_string")
+           "scc_dw_backward_workspace_bytes", "scc_dw_backward", "scc_dw_backward_as_workspace_bytes", "scc_dw_backward_as",
+           "scc_status_string")
 STATIC_SCRATCH_BYTES = 32 << 20    # SCC_STATIC_SCRATCH_BYTES of include/scc.h
 
 _lib = None
@@ -88,6 +89,10 @@ def load():
     lib.scc_dw_backward_workspace_bytes.restype = c_sz
     lib.scc_dw_backward.argtypes = [c_vp] * 7 + dw_shape + [c_vp, c_sz, c_vp]
     lib.scc_dw_backward.restype = c_int
+    lib.scc_dw_backward_as_workspace_bytes.argtypes = dw_shape + [c_int]
+    lib.scc_dw_backward_as_workspace_bytes.restype = c_sz
+    lib.scc_dw_backward_as.argtypes = [c_vp] * 7 + dw_shape + [c_int, c_vp, c_sz, c_vp]
+    lib.scc_dw_backward_as.restype = c_int
     lib.scc_status_string.argtypes = [c_int]
     lib.scc_status_string.restype = ctypes.c_char_p
     _lib = lib
@@ -430,7 +435,12 @@ def scc_dw_forward(x, kdw, w, cg, co, dw_stride=1, out=None, workspace=None, fus
 def scc_dw_backward(x, kdw, w, dy, cg, co, dw_stride=1):
     """(dx, dkdw, dw), all gradients of a DW + SCC block in one call: x [N,Cin,H,W], kdw [Cin,3,3], w [Cout,Cin//cg],
     dy [N,Cout,Ho,Wo]; dkdw and dw are float32."""
-    grads = (_native or _load_native()).dw_backward(x, kdw, w, dy, cg, co, dw_stride)
+    return _dw_backward(x, kdw, w, dy, cg, co, dw_stride, False)
+
+
+def _dw_backward(x, kdw, w, dy, cg, co, dw_stride, stored):
+    """scc_dw_backward; stored: dkdw and dw in the type of x, rounded from the same sums."""
+    grads = (_native or _load_native()).dw_backward(x, kdw, w, dy, cg, co, dw_stride, stored)
     if grads is not None:
         return grads
     dev = _dev(x, kdw, w, dy)
@@ -444,10 +454,12 @@ def scc_dw_backward(x, kdw, w, dy, cg, co, dw_stride=1):
     if dy.dtype != x.dtype or tuple(dy.shape) != (N, Cout, _out(H, dw_stride), _out(W, dw_stride)):
         raise ValueError("dy must be [N, Cout, Ho, Wo] with the dtype of x")
     shape = (N, Cin, Cout, H, W, dw_stride, cg, float(co), _dtype_code(x))
-    ws, ws_ptr, ws_len = _scratch(_workspace_need("scc_dw_backward_workspace_bytes", *shape), dev)
+    grad = x.dtype if stored else torch.float32
+    shape += (_CODES[grad],)
+    ws, ws_ptr, ws_len = _scratch(_workspace_need("scc_dw_backward_as_workspace_bytes", *shape), dev)
     dx = torch.empty_like(x)
-    dk = torch.empty((Cin, 3, 3), dtype=torch.float32, device=dev)
-    dw = torch.empty(w.shape, dtype=torch.float32, device=dev)
-    _launch(dev, load().scc_dw_backward, x.data_ptr(), kdw.data_ptr(), w.data_ptr(), dy.data_ptr(), dx.data_ptr(),
+    dk = torch.empty((Cin, 3, 3), dtype=grad, device=dev)
+    dw = torch.empty(w.shape, dtype=grad, device=dev)
+    _launch(dev, load().scc_dw_backward_as, x.data_ptr(), kdw.data_ptr(), w.data_ptr(), dy.data_ptr(), dx.data_ptr(),
             dk.data_ptr(), dw.data_ptr(), *shape, ws_ptr, ws_len)
     return dx, dk, dw

@@ -26,7 +26,8 @@ def test_one_call_is_its_three_stages(shape, dtype):
 
 # Maps of strips of 1, 2 and 4 rows, of columns (2x2, 7x7, 6x10) and of single pixels (stride 2 on odd maps, stride 3), one and several
 # slices of either filter, fewer than 256 columns, and layers on both sides of the line at 2^23 (columns: 2^22) values of x and z.
-PAIRED = [(16, 512, 512, 4, 4, 1, 2, 0.5), (16, 1024, 256, 2, 2, 1, 2, 0.5), (5, 48, 40, 7, 7, 1, 4, 0.33), (9, 64, 61, 6, 10, 1, 2, 0.75),
+# the fused, the shared and the two-pass gradients of the SCC behind them
+PAIRED = [(40, 128, 128, 16, 16, 1, 2, 0.5), (128, 128, 512, 32, 32, 1, 2, 0.33), (3, 16, 24, 2, 2, 1, 4, 0.5), (16, 512, 512, 4, 4, 1, 2, 0.5), (16, 1024, 256, 2, 2, 1, 2, 0.5), (5, 48, 40, 7, 7, 1, 4, 0.33), (9, 64, 61, 6, 10, 1, 2, 0.75),
           (20, 64, 96, 13, 9, 2, 2, 0.5), (30, 32, 24, 10, 10, 3, 1, 0.0), (30, 64, 128, 32, 32, 2, 2, 0.5), (128, 32, 64, 32, 32, 1, 2, 0.5),
           (129, 32, 64, 32, 32, 1, 2, 0.5), (167, 256, 256, 7, 7, 1, 4, 0.5), (168, 256, 256, 7, 7, 1, 4, 0.5), (64, 256, 512, 8, 8, 2, 2, 0.5)]
 
@@ -44,18 +45,18 @@ def test_stages_side_by_side(shape, dtype):
     x, kdw, w, dy = (torch.randn(*d, generator=gen, device="cuda").to(dtype) for d in
                      ((N, Cin, H, W), (Cin, 3, 3), (Cout, Cin // cg), (N, Cout, Ho, Wo)))
     dx, dk, dw = S.scc_dw_backward(x, kdw, w, dy, cg, co, s)
-    lib, code, es = S.load(), 0 if dtype == torch.float32 else 1, x.element_size()
+    lib, code = S.load(), 0 if dtype == torch.float32 else 1
     shape_c = (N, Cin, Cout, H, W, s, cg, co, code)
-    plane = (N * Cin * Ho * Wo * es + 255) // 256 * 256
-    least = 2 * plane + max(int(lib.scc_backward_workspace_bytes(N, Cin, Cout, Ho, Wo, cg, co, code)),
-                            int(lib.scc_depthwise3x3_backward_workspace_bytes(N, Cin, H, W, s, code)))
-    assert least <= lib.scc_dw_backward_workspace_bytes(*shape_c)
+    least = int(lib.scc_dw_backward_workspace_bytes(*shape_c))
+    assert least <= lib.scc_dw_backward_as_workspace_bytes(*shape_c, 0) <= lib.scc_dw_backward_as_workspace_bytes(*shape_c, 1)
     ws = torch.empty(least, dtype=torch.uint8, device="cuda")
     dx2, dk2, dw2 = torch.empty_like(dx), torch.empty_like(dk), torch.empty_like(dw)
     args = [t.data_ptr() for t in (x, kdw, w, dy, dx2, dk2, dw2)]
     stream = torch.cuda.current_stream().cuda_stream
     assert lib.scc_dw_backward(*args, *shape_c, ws.data_ptr(), least, stream) == 0
     assert torch.equal(dx, dx2) and torch.equal(dk, dk2) and torch.equal(dw, dw2)
+    dx3, dk3, dw3 = S.scc._dw_backward(x, kdw, w, dy, cg, co, s, True)       # the same sums, rounded to the weights' type
+    assert torch.equal(dx, dx3) and torch.equal(dk.to(dtype), dk3) and torch.equal(dw.to(dtype), dw3)
     if x.numel() <= 1 << 20:
         import numpy as np
         from oracle import scc_oracle as O
@@ -63,6 +64,17 @@ def test_stages_side_by_side(shape, dtype):
         dz = S.scc_backward(z, dy, w, cg, co)[0]
         ref = O.depthwise3x3_backward(*(t.float().cpu().numpy() for t in (x, kdw, dz)), s)[1]
         assert np.max(np.abs(dk.cpu().numpy() - ref)) <= 2e-5 * np.max(np.abs(ref))     # binary32 sums in both types
+
+
+def test_narrow_gradients_host_checks():
+    lib, p = S.load(), ctypes.c_void_p(0x1000)
+    shape = (3, 32, 40, 9, 7, 2, 4, 0.25, 1)
+    need = lib.scc_dw_backward_as_workspace_bytes(*shape, 1)
+    assert need > lib.scc_dw_backward_workspace_bytes(*shape) > 0
+    args = [p] * 7
+    assert lib.scc_dw_backward_as(*args, *shape, 1, 0x1000, need - 1, None) == -5 and lib.scc_dw_backward_as(*args, *shape, 1, None, need, None) == -5
+    assert lib.scc_dw_backward_as(*args, *shape, 7, 0x1000, need, None) == -4 and lib.scc_dw_backward_as_workspace_bytes(*shape, 7) == 0
+    assert lib.scc_dw_backward_as(*args[:-1], None, *shape, 1, 0x1000, need, None) == -1
 
 
 def test_host_checks():

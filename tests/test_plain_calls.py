@@ -31,7 +31,7 @@ def test_plain_is_general(dtype, monkeypatch):
             B._load_native()
             plain = [c() for c in calls(*args, 2, 0.33)]
             native = (B._native.forward(args[0], args[2], 2, 0.33), B._native.backward(args[0], args[3], args[2], 2, 0.33),
-                      B._native.dw_forward(*args[:3], 2, 0.33, 1), B._native.dw_backward(*args, 2, 0.33, 1))
+                      B._native.dw_forward(*args[:3], 2, 0.33, 1), B._native.dw_backward(*args, 2, 0.33, 1, False))
             assert all(n is not None for n in native)                     # the calls above took the native way
             with monkeypatch.context() as m:
                 m.setattr(B, "_native", General())
@@ -52,7 +52,7 @@ def test_not_plain_goes_the_general_way():
         assert n.forward(*a) is None
     assert n.backward(x, dy[:1], w, 2, 0.5) is None and n.dw_forward(x, k[:8], w, 2, 0.5, 1) is None
     assert n.dw_forward(x, k, w, 2, 0.5, 0) is None and n.dw_forward(x, k, w, 2, 0.5, 1.0) is None
-    assert n.dw_backward(x, k, w, dy, 2, 0.5, 2) is None
+    assert n.dw_backward(x, k, w, dy, 2, 0.5, 2, False) is None and n.dw_backward(x, k, w, dy, 2, 0.5, 1) is None
     assert torch.equal(S.scc_forward(x, w, 2, 0), S.scc_forward(x, w, 2, 0.0))
     with pytest.raises(S.SccError) as e:
         S.scc_forward(x, w, 2, 1.5)
