@@ -15,7 +15,7 @@
 // other's phases.
 //
 // Products are those of the per-tile kernel: exact (bf16 tensors), binary32 through v_mfma_f32_32x32x2_f32 (fp32 tensors).
-// What bounds it: binary32, the matrix pipe (channel-expanding layer: 82 of 130 us at its peak rate, the idle share of
+// What bounds it: binary32, the matrix pipe (channel-expanding layer: 68 of 117 us at its peak rate, the idle share of
 // tiles that windows fill only in part included); bf16, fetching.  (binary32 through six bf16 products of a three-way cut
 // takes 101 us there, but drops the smallest partial products and loses operands near the end of the exponent range.)
 //
@@ -32,6 +32,7 @@ namespace scc {
 namespace shared_bww {
 
 typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 struct WeightTiling {
@@ -121,6 +122,22 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
         const int p0 = pos0 + 32 * t;
         if (row0 < T.rows && p0 < len && ((p0 < d1 && p0 + 32 > d0) || p0 < d1 - P.Cin)) active |= 1u << t;
     }
+    // Binary32, which the matrix pipe bounds: of a position tile that this wavefront's windows reach one half of 16 only (one such
+    // tile), that half takes v_mfma_f32_16x16x4_f32 for half the matrix time.  (Windows of 64 on 8 neighbouring starts span 71
+    // positions: 80 of three tiles instead of 96; 128 x 128 -> 512 on 32x32, cg 2, co 0.33: alone 131 -> 117 us, beside grad-input, which the
+    // memory bounds, 202 -> 200.)
+    int half_at = -1;                                   // first position of that half in the workgroup's chunk
+    if constexpr (ES == 4) {
+#pragma unroll
+        for (int t = 0; t < PT; ++t) {
+            auto reached = [&](int p0) { return p0 < len && ((p0 < d1 && p0 + 16 > d0) || p0 < d1 - P.Cin); };
+            const bool lo = reached(pos0 + 32 * t), hi = reached(pos0 + 32 * t + 16);
+            if (((active >> t) & 1u) && lo != hi && half_at < 0) {
+                half_at = 32 * t + (hi ? 16 : 0);
+                active &= ~(1u << t);
+            }
+        }
+    }
 
     // this slice's rounds (8 column groups each) from r0 on.  (Slices of an XCD that take every n-th round of its columns
     // instead, so that it sweeps them on a narrow front, are slower: channel-expanding layer, bf16 40 -> 51 us.)
@@ -176,6 +193,21 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
     for (int t = 0; t < PT; ++t)
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[t][v] = 0.f;
+    f32x4 part[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};   // the half tile: rows 16q .. 16q+15 of the wavefront's
+    const int f4 = lane & 15, h4 = lane >> 4;
+    auto compute_half = [&]() {
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {                   // 16 columns: quarter-wave h4 reads group 4*j + h4
+            const char* base = lds_w + (4 * j + h4) * kHalf + f4 * 16;
+            const u32x4 b = *(const u32x4*)(base + (128 + half_at) * 16);
+            const u32x4 a0 = *(const u32x4*)(base + wave * 512), a1 = *(const u32x4*)(base + wave * 512 + 256);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                part[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a0[e]), __uint_as_float(b[e]), part[0], 0, 0, 0);
+                part[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(a1[e]), __uint_as_float(b[e]), part[1], 0, 0, 0);
+            }
+        }
+    };
     auto compute = [&]() {
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -205,6 +237,8 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
         if (r + 1 < nround) issue();
         __syncthreads();
         compute();
+        if constexpr (ES == 4)
+            if (half_at >= 0) compute_half();
     }
 
     // accumulator register v holds row 8*(v/4) + 4*h + v%4 of the wavefront's tile, walk position pos0 + 32t + f
@@ -226,8 +260,24 @@ __device__ __forceinline__ void weight_body(const T_* __restrict__ x, const T_* 
             int j = first + pos - sr[v];                // first <= s: j starts at first - s > -Cin
             j += j < 0 ? P.Cin : 0;
             j -= j >= P.Cin ? P.Cin : 0;
-            if ((kr[v] >= 0) & (pos < len) & (j < P.L)) *(float*)(dst + (uint32_t)(kr[v] * P.L + j) * 4u) = acc[t][v];
+            const bool here = ES == 2 || half_at < 0 || t != half_at >> 5;
+            if ((kr[v] >= 0) & (pos < len) & (j < P.L) & here) *(float*)(dst + (uint32_t)(kr[v] * P.L + j) * 4u) = acc[t][v];
         }
+    }
+    if constexpr (ES == 4) {
+        if (half_at < 0) return;
+        // register v of part[q] holds row 16q + 4*h4 + v, position half_at + f4 of the chunk (of the tile's other half no row stores)
+        const int pos = pos0 + half_at + f4;
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int k = __shfl(k_f, 16 * q + 4 * h4 + v, 64);
+                int j = first + pos - __shfl(s_f, 16 * q + 4 * h4 + v, 64);
+                j += j < 0 ? P.Cin : 0;
+                j -= j >= P.Cin ? P.Cin : 0;
+                if ((k >= 0) & (pos < len) & (j < P.L)) *(float*)(dst + (uint32_t)(k * P.L + j) * 4u) = part[q][v];
+            }
     }
 }
 
