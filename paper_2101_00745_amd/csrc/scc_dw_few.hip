@@ -11,10 +11,10 @@
 // the instructions of one wavefront from end to end (about 1300: a wavefront alone on a SIMD issues one in five cycles), so
 // the maps are those whose stencils need no neighbouring lanes, and the windows those read in whole groups of four.
 //
-// The four wavefronts split the contraction: each walks its quarter of the span in rounds of 16*KR channels (KR*CP = 4), for
+// The wavefronts (four, or eight: see the launcher) split the contraction: each walks its share of the span in rounds of 16*KR channels (KR*CP = 4), for
 // which a lane computes 8 channels of 4 consecutive pixels (a round is exactly 64 such items), cuts them into bf16 pieces (fp32) or
 // rounds them to bf16 (bf16, as the two stages do) and parks them in the wavefront's own LDS in the matrix instruction's operand
-// layout; no barrier.  The four partial tiles are added through LDS in wavefront order, a quarter of the rows by each wavefront.
+// layout; no barrier.  The partial tiles are added through LDS in wavefront order, an equal share of the rows by each.
 //
 // MFMA column f of column group c is slot 32*c + f of the tile, and slot i*(8*CP) + g holds pixel i of group g: phase 1's lanes then
 // write 16 consecutive bytes each, and the matrix instruction's lanes read them the same way.
@@ -42,10 +42,18 @@ struct FewTiling {
     int chunk;      // consecutive workgroups of that order given to one XCD: ceil(total / 8)
 };
 
+// LDS of a wavefront: a round's pieces and taps (binary32), then its partial tiles in their place.
+constexpr int few_block_bytes(int cp, int tf, int parts)
+{
+    const int kr = 4 / cp, round = parts * 2 * kr * 32 * cp * 16 + 16 * kr * 9 * 4, sum = tf * cp * 16 * 64 * 4;
+    return round > sum ? round : sum;
+}
+
 enum { kMap2, kMap4 };   // output maps of 2 x 2, rows of 4: a lane's 4 pixels have no neighbours beside them
 
-template <typename T_, int S, int MAP, int CP, int TF>
-__global__ __launch_bounds__(256, 2) void dw_scc_forward_few(const T_* __restrict__ x, const T_* __restrict__ kdw,
+// WV: wavefronts of a workgroup, 4 or 8
+template <typename T_, int S, int MAP, int CP, int TF, int WV>
+__global__ __launch_bounds__(64 * WV, 2) void dw_scc_forward_few(const T_* __restrict__ x, const T_* __restrict__ kdw,
                                                           const T_* __restrict__ w, T_* __restrict__ y, Problem P, DwGeom G,
                                                           FewTiling T)
 {
@@ -53,11 +61,8 @@ __global__ __launch_bounds__(256, 2) void dw_scc_forward_few(const T_* __restric
     constexpr int kParts = sizeof(T_) == 4 ? 3 : 1;
     constexpr int TP = 32 * CP;                 // columns
     constexpr int kPartB = 2 * KR * TP * 16;    // one piece of a round: [8 channels][slot][8 values]
-    constexpr int kTapB = 16 * KR * 9 * 4;      // taps of a round's channels, binary32
-    constexpr int kWaveB = kParts * kPartB + kTapB;
-    constexpr int kSumB = TF * CP * 16 * 64 * 4;   // a wavefront's partial tiles, in place of the above
-    constexpr int kBlockB = kWaveB > kSumB ? kWaveB : kSumB;
-    __shared__ __attribute__((aligned(16))) char lds[4 * kBlockB];
+    constexpr int kBlockB = few_block_bytes(CP, TF, kParts);   // a wavefront's
+    extern __shared__ __attribute__((aligned(16))) char lds[];     // WV * kBlockB
     typedef T_ w4 __attribute__((ext_vector_type(4), aligned(sizeof(T_))));
 
     const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
@@ -72,7 +77,7 @@ __global__ __launch_bounds__(256, 2) void dw_scc_forward_few(const T_* __restric
 
     // the span, on the unwrapped channel axis, in groups of 16; this wavefront's are [k0, k1)
     const int c0 = T.b.g * mb * T.TM, cb = c0 & ~15;
-    const int KG = (c0 + T.U - cb + 15) >> 4, KGs = (KG + 3) >> 2;
+    const int KG = (c0 + T.U - cb + 15) >> 4, KGs = (KG + WV - 1) / WV;
     const int k0 = wave * KGs, k1 = k0 + KGs < KG ? k0 + KGs : KG;
 
     // ---- A side: this lane's filters ----
@@ -290,8 +295,9 @@ __global__ __launch_bounds__(256, 2) void dw_scc_forward_few(const T_* __restric
         }
     }
 
-    // ---- the wavefronts' partial tiles, added in wavefront order; wavefront v takes accumulator registers 4v..4v+3, tile rows
-    // 8v + 4h + 0..3 ----
+    // ---- the wavefronts' partial tiles, added in wavefront order; wavefront v takes RW accumulator registers from RW*v on (tile row
+    // 8*(r/4) + 4h + r%4 for register r) ----
+    constexpr int RW = 16 / WV;
     float* part = (float*)mine + lane;
 #pragma unroll
     for (int t = 0; t < TF; ++t)
@@ -304,17 +310,20 @@ __global__ __launch_bounds__(256, 2) void dw_scc_forward_few(const T_* __restric
     constexpr int kStep = kBlockB / 4;
 #pragma unroll
     for (int t = 0; t < TF; ++t) {
-        float o[CP][4];
+        float o[CP][RW];
 #pragma unroll
         for (int c = 0; c < CP; ++c)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const float* s = sum + ((t * CP + c) * 16 + 4 * wave + v) * 64;
-                o[c][v] = ((s[0] + s[kStep]) + s[2 * kStep]) + s[3 * kStep];
+            for (int v = 0; v < RW; ++v) {
+                const float* s = sum + ((t * CP + c) * 16 + RW * wave + v) * 64;
+                o[c][v] = s[0];
+#pragma unroll
+                for (int u = 1; u < WV; ++u) o[c][v] += s[u * kStep];
             }
 #pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int k = __shfl(kf[t], 8 * wave + 4 * h + v, 64);
+        for (int v = 0; v < RW; ++v) {
+            const int reg = RW * wave + v;
+            const int k = __shfl(kf[t], 8 * (reg >> 2) + 4 * h + (reg & 3), 64);
 #pragma unroll
             for (int c = 0; c < CP; ++c) {
                 const int sl = 32 * c + f, gq = sl % (8 * CP), i = sl / (8 * CP);
@@ -388,16 +397,33 @@ hipError_t launch_dw_forward_few(const T_* x, const T_* kdw, const T_* w, T_* y,
     // two tiles per workgroup once one would make two generations of workgroups: 128 x 512 -> 512 on 4x4 15.5 -> 12.1, 64 of them
     // 8.8 -> 9.1; four tiles gain nothing more (12.8)
     const bool two = cp <= 2 && few_units(p) > 768;
-    auto go = [&](auto s, auto map, auto c, auto f) {
-        constexpr int S = decltype(s)::value, MAP = decltype(map)::value, CP = decltype(c)::value, TF = decltype(f)::value;
-        const FewTiling t = few_tiling(p, CP, TF);
-        dw_scc_forward_few<T_, S, MAP, CP, TF><<<dim3(8u * (unsigned)t.chunk), dim3(256), 0, st>>>(x, kdw, w, y, p, g, t);
-    };
+    // eight wavefronts where four would walk their quarter of the span in more than one round and the chip holds all workgroups at
+    // once (one per CU): 16 x 1024 -> 1024 on 2x2, cg 2, 9.6 -> 8.3 us, bf16 9.4 -> 7.9; 16 x 512 -> 512 on 4x4, cg 1, 9.7 -> 7.8
     using std::integral_constant;
+    hipError_t e = hipSuccess;
+    auto go = [&](auto s, auto map, auto c, auto f, auto wv) {
+        constexpr int S = decltype(s)::value, MAP = decltype(map)::value, CP = decltype(c)::value, TF = decltype(f)::value;
+        constexpr int WV = decltype(wv)::value, kLds = WV * few_block_bytes(CP, TF, sizeof(T_) == 4 ? 3 : 1);
+        if constexpr (kLds > 64 * 1024) {
+            // more than 64 KiB of LDS per workgroup has to be allowed once
+            static const hipError_t allowed = hipFuncSetAttribute((const void*)dw_scc_forward_few<T_, S, MAP, CP, TF, WV>,
+                                                                  hipFuncAttributeMaxDynamicSharedMemorySize, kLds);
+            e = allowed;
+            if (e != hipSuccess) return;
+        }
+        const FewTiling t = few_tiling(p, CP, TF);
+        dw_scc_forward_few<T_, S, MAP, CP, TF, WV><<<dim3(8u * (unsigned)t.chunk), dim3(64 * WV), kLds, st>>>(x, kdw, w, y, p, g, t);
+        e = hipGetLastError();
+    };
+    const integral_constant<int, 4> four;
     auto with_tf = [&](auto s, auto map, auto c) {
         if constexpr (decltype(c)::value <= 2)
-            if (two) return go(s, map, c, integral_constant<int, 2>{});
-        go(s, map, c, integral_constant<int, 1>{});
+            if (two) return go(s, map, c, integral_constant<int, 2>{}, four);
+        if constexpr (decltype(c)::value == 1) {
+            const FewTiling t = few_tiling(p, 1, 1);
+            if (t.U > 256 && t.total <= 256) return go(s, map, c, integral_constant<int, 1>{}, integral_constant<int, 8>{});
+        }
+        go(s, map, c, integral_constant<int, 1>{}, four);
     };
     auto with_cp = [&](auto s, auto map) {
         cp == 1 ? with_tf(s, map, integral_constant<int, 1>{})
@@ -407,7 +433,7 @@ hipError_t launch_dw_forward_few(const T_* x, const T_* kdw, const T_* w, T_* y,
         g.Wo == 2 ? with_cp(s, integral_constant<int, kMap2>{}) : with_cp(s, integral_constant<int, kMap4>{});
     };
     g.s == 1 ? with_map(integral_constant<int, 1>{}) : with_map(integral_constant<int, 2>{});
-    return hipGetLastError();
+    return e;
 }
 
 template hipError_t launch_dw_forward_few<float>(const float*, const float*, const float*, float*, const Problem&, const DwGeom&,
