@@ -20,7 +20,7 @@ namespace {
 enum { kInputStage, kInputS2, kInputGather };
 
 struct DwGrads {
-    int filter;        // strips: 8 * stride + rows of a strip; columns: rows of a column; 0: pixel by pixel
+    int filter;        // strips: 8 * stride + rows of a strip; columns: rows of a column; planes: 32 + stride; 0: pixel by pixel
     int slices, per;   // slices of the samples, samples of a slice
     uint32_t nfilter;  // workgroups of the first range
     int input;         // kInput*
@@ -36,7 +36,12 @@ DwGrads plan_gradients(const T_* x, const T_* dz, const T_* dx, int N, int C, co
     d.slices = dw::filter_slices(N, C, g);
     d.per = (N + d.slices - 1) / d.slices;
     d.filter = dw::filter_on_strips(x, dz, g, d.per) ? 8 * g.s + dw::strip_rows_of(g) : g.s == 1 ? dw::strip_rows_of(g) : 0;
-    d.nfilter = (uint32_t)C * (uint32_t)d.slices;
+    uint32_t channels = (uint32_t)C;                  // or groups of them
+    if (dw::filter_on_planes(g)) {
+        d.filter = 32 + g.s;
+        channels = (channels + dw::kPlaneChannels - 1) / dw::kPlaneChannels;
+    }
+    d.nfilter = channels * (uint32_t)d.slices;
     d.stage = dw::plan_stage(dz, dx, N, C, g, true);
     d.items = 0;
     if (g.s == 1) {
@@ -54,9 +59,15 @@ DwGrads plan_gradients(const T_* x, const T_* dz, const T_* dx, int N, int C, co
 template <typename T_>
 __device__ __forceinline__ void gradients_body(const T_* __restrict__ x, const T_* __restrict__ kdw, const T_* __restrict__ dz,
                                                T_* __restrict__ dx, float* __restrict__ part, int N, int C, const DwGeom& G,
-                                               const DwGrads& D, uint32_t bid)
+                                               const DwGrads& D, uint32_t bid, float* lds)
 {
     if (bid < D.nfilter) {
+        if (D.filter > 32) {
+            const uint32_t groups = (uint32_t)(C + dw::kPlaneChannels - 1) / dw::kPlaneChannels;
+            const int group = (int)(bid % groups), part_of = (int)(bid / groups);
+            if (D.filter == 32 + 1) return dw::filter_planes_body<T_, 1>(x, dz, part, N, C, D.per, group, part_of, lds);
+            return dw::filter_planes_body<T_, 2>(x, dz, part, N, C, D.per, group, part_of, lds);
+        }
         const int a = (int)(bid % (uint32_t)C), slice = (int)(bid / (uint32_t)C);
         switch (D.filter) {
             case 8 + 1: return dw::filter_strips_body<T_, 1, 1>(x, dz, part, N, C, G, D.per, a, slice);
@@ -99,11 +110,13 @@ __global__ __launch_bounds__(256, SMALL ? 2 : NPT == 2 && sizeof(T_) == 4 ? 1 : 
     const T_* __restrict__ dz, T_* __restrict__ dx, float* __restrict__ part_k, float* __restrict__ part_w, Problem P,
     bww::BwwTiling TW, int nbww, DwGeom G, DwGrads D)
 {
+    extern __shared__ __attribute__((aligned(16))) float lds_dyn[];    // grad-weight's staging area, or the filter gradient's sums
+    static_assert(bww::lds_bytes_of(NPT, (int)sizeof(T_)) >= dw::kPlanesLds, "the first range's LDS holds the second's");
     const int bid = (int)blockIdx.x;
     if (bid < nbww)
         bww::backward_weight_body<T_, NPT, true, SMALL>(z, dy, part_w, P, TW, bid);
     else
-        gradients_body<T_>(x, kdw, dz, dx, part_k, P.N, P.Cin, G, D, (uint32_t)(bid - nbww));
+        gradients_body<T_>(x, kdw, dz, dx, part_k, P.N, P.Cin, G, D, (uint32_t)(bid - nbww), lds_dyn);
 }
 
 template <typename T_>

@@ -82,6 +82,15 @@ __global__ __launch_bounds__(kDkThreads) void depthwise3x3_backward_filter_colum
     dw::filter_columns_body<T_, RB>(x, dz, part, N, C, G, per, (int)blockIdx.x, (int)blockIdx.y);
 }
 
+template <typename T_, int S>
+__global__ __launch_bounds__(kDkThreads) void depthwise3x3_backward_filter_planes(const T_* __restrict__ x,
+                                                                                  const T_* __restrict__ dz,
+                                                                                  float* __restrict__ part, int N, int C, int per)
+{
+    __shared__ float red[dw::kPlanesLds / sizeof(float)];
+    dw::filter_planes_body<T_, S>(x, dz, part, N, C, per, (int)blockIdx.x, (int)blockIdx.y, red);
+}
+
 __global__ __launch_bounds__(256) void depthwise3x3_filter_reduce(const float* __restrict__ part, float* __restrict__ dk,
                                                                   int count, int slices)
 {
@@ -198,7 +207,13 @@ hipError_t launch_depthwise3x3_backward(const T* x, const T* kdw, const T* dz, T
             launch_filter_strips<T, 1>(x, dz, part, N, C, g, slices, per, st);
         else if (strips)
             launch_filter_strips<T, 2>(x, dz, part, N, C, g, slices, per, st);
-        else if (g.s == 1)
+        else if (dw::filter_on_planes(g)) {
+            const dim3 grid((unsigned)((C + dw::kPlaneChannels - 1) / dw::kPlaneChannels), (unsigned)slices);
+            if (g.s == 1)
+                depthwise3x3_backward_filter_planes<T, 1><<<grid, dim3(kDkThreads), 0, st>>>(x, dz, part, N, C, per);
+            else
+                depthwise3x3_backward_filter_planes<T, 2><<<grid, dim3(kDkThreads), 0, st>>>(x, dz, part, N, C, per);
+        } else if (g.s == 1)
             launch_filter_columns<T>(x, dz, part, N, C, g, slices, per, st);
         else
             depthwise3x3_backward_filter_generic<T><<<dim3((unsigned)C, (unsigned)slices), dim3(kDkThreads), 0, st>>>(

@@ -91,6 +91,24 @@ def test_host_checks():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N,C,s", [(1, 1, 1), (3, 64, 1), (31, 65, 1), (32, 63, 2), (33, 130, 1), (130, 64, 2), (67, 200, 2), (128, 1024, 1), (5, 2000, 2)])
+def test_filter_gradient_of_2x2_maps(N, C, s, dtype):
+    """A lane per channel: groups of 64 channels whole and partial, samples that fill no, one and several batches of the four
+    wavefronts, one and more slices; alone and in a block's backward."""
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    x, kdw, dz = (torch.randn(*d, generator=gen, device="cuda").to(dtype) for d in ((N, C, 2 * s, 2 * s), (C, 3, 3), (N, C, 2, 2)))
+    import numpy as np
+    from oracle import scc_oracle as O
+    ref_dx, ref_dk = O.depthwise3x3_backward(*(t.float().cpu().numpy() for t in (x, kdw, dz)), s)
+    dx, dk = S.scc_depthwise3x3_backward(x, kdw, dz, s)
+    assert np.max(np.abs(dk.cpu().numpy() - ref_dk)) <= 2e-6 * np.max(np.abs(ref_dk))     # binary32 sums of 4 N products, as trees
+    assert torch.equal(dk, S.scc_depthwise3x3_backward(x, kdw, dz, s, need_dx=False)[1])
+    if C % 16 == 0 and N >= 16:
+        test_one_call_is_its_three_stages((N, C, 24, 2 * s, 2 * s, s, 2, 0.5), dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("N,C,H,W,s", [(1, 3, 4, 4, 1), (129, 5, 4, 4, 1), (70, 9, 6, 8, 1), (33, 2, 5, 12, 1), (40, 7, 32, 32, 1),
                                        (65, 4, 8, 8, 2), (3, 6, 10, 24, 2), (257, 2, 4, 8, 2)])
 def test_depthwise_gradients_in_one_launch_are_those_of_two(N, C, H, W, s, dtype):
