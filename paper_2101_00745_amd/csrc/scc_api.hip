@@ -449,7 +449,7 @@ int scc_dw_forward(const void* x, const void* kdw, const void* w, void* y, int N
     const bool fused = dtype == SCC_F32 && (need == 0 || (!workspace && scc::dw_forward_fused_eligible(p)));
     if (!fused && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0))
         return SCC_ERR_WORKSPACE;
-    if (scc::dw_forward_few_preferred(p, g)) {      // one kernel as well; the workspace it could do without stays as it is
+    if (scc::dw_forward_few_preferred(p, g, dtype == SCC_F32 ? 4 : 2, fused)) {      // one kernel as well; the workspace it could do without stays as it is
         drop_stale_error();
         return with_type(dtype, [&](auto t) {
             typedef decltype(t) T;

@@ -196,7 +196,7 @@ hipError_t launch_depthwise3x3_backward(const T* x, const T* kdw, const T* dz, T
                                         int C, const DwGeom& g, hipStream_t st, SliceSum* later = nullptr);
 // ... and the one for layers with few columns (scc_dw_few.hip), fp32 and bf16
 bool dw_forward_few_eligible(const Problem& p, const DwGeom& g);
-bool dw_forward_few_preferred(const Problem& p, const DwGeom& g);   // ... and faster
+bool dw_forward_few_preferred(const Problem& p, const DwGeom& g, int es, bool against_fused);   // ... and faster than what would run
 template <typename T>
 hipError_t launch_dw_forward_few(const T* x, const T* kdw, const T* w, T* y, const Problem& p, const DwGeom& g, hipStream_t st);
 

@@ -374,35 +374,63 @@ bool dw_forward_few_eligible(const Problem& p, const DwGeom& g)
            (long long)p.NQ * rows < (1ll << 30) && (long long)p.Cout * p.L < (1ll << 30);
 }
 
-// Tiles of 32 filters x 32 columns of a layer: what its workgroups' number and its arithmetic go with.
-static long long few_units(const Problem& p)
+// How a layer is cut.  Two filter tiles per workgroup once one would make more than 768 workgroups of one column group: 128 x 512 -> 512 on
+// 4x4 15.5 -> 12.1 us, 64 of them 8.8 -> 9.1; four tiles gain nothing more (12.8).  Eight wavefronts where four would walk their quarter of
+// the span in more than one round and the chip holds all workgroups at once (one per CU): 16 x 1024 -> 1024 on 2x2, cg 2, 9.6 -> 8.3 us,
+// bf16 9.4 -> 7.9; 16 x 512 -> 512 on 4x4, cg 1, 9.7 -> 7.8.
+struct FewPlan {
+    FewTiling t;
+    int units;         // tiles of 32 filters x 32 columns
+    int cp, tf, wv;    // column groups, filter tiles, wavefronts of a workgroup
+    int rounds;        // of channels, of one wavefront
+};
+
+static FewPlan few_plan(const Problem& p)
 {
-    return few_tiling(p, 1, 1).FG * ((p.NQ + 31) / 32);
+    FewPlan f;
+    f.t = few_tiling(p, 1, 1);
+    f.units = f.t.total;
+    f.cp = few_cp(f.t);
+    f.tf = f.cp <= 2 && f.units > 768 ? 2 : 1;
+    f.t = few_tiling(p, f.cp, f.tf);
+    f.wv = f.cp == 1 && f.tf == 1 && f.t.U > 256 && f.t.total <= 256 ? 8 : 4;
+    f.rounds = ((f.t.U + 64 / f.cp - 1) / (64 / f.cp) + f.wv - 1) / f.wv;
+    return f;
 }
 
-// Against the two stages (us, fp32 / bf16, N x Cin -> Cout on the output map): 16 x 512 -> 512 on 4x4 (128 tiles) 9.3 -> 6.6 / 8.3 -> 5.9,
-// 128 of them (1024 tiles) 15.4 -> 12.1 / 11.7 -> 10.6, 300 (2400) 28.8 -> 23.9 / 19.6 -> 19.5; 128 x 256 -> 512 from 8x8 (1024) 12.0 -> 11.1 /
-// 9.6 -> 8.8, 300 (2400) 20.1 -> 23.5 / 13.3 -> 16.8; 128 x 1024 -> 1024 on 2x2 (512) 17.7 -> 13.6 / 17.3 -> 11.7; 60 x 1536 -> 1536 on 4x4 (1440)
-// 25.8 -> 25.3 / 16.8 -> 19.5; one image of 512 -> 512 on 4x4, which the stand-alone forward has too few columns for, 96 -> 6.4.
-bool dw_forward_few_preferred(const Problem& p, const DwGeom& g)
+// Against the two stages, of which the second reaches its tiled kernels from 64 columns up; below, this kernel is at least 1.37 times as
+// fast over 706 layers (one image of 512 -> 512 on 4x4 96 -> 6.4 us).  From 64 up its time goes with the rounds that a CU walks one after
+// another: rounds of a wavefront x generations of 256 workgroups, wider workgroups somewhat longer ones (3 + column groups x filter tiles
+// quarters of the narrowest's).  Over 4324 layers of up to 1100 tiles, warm and cold buffers, two stages / this kernel, geometric mean
+// and extremes of those it takes, mean of those it leaves: stride 1, rows of 4, fp32 1.20 (0.85 .. 1.67), 0.92, bf16 1.11 (0.72 .. 1.59),
+// 0.78; 2x2 maps, whose depthwise stage alone is slow, fp32 1.20, 0.96, bf16 1.17, 1.25 (few); stride 2, where every tile recomputes from four
+// times the input, fp32 1.12 (0.79 .. 1.74), 0.83, bf16 1.11 (0.79 .. 1.79), 0.81.  Without the rule 2.5 times slower at worst (18 x 1984 -> 5948 on
+// 4x4, cg 1: 46 -> 118).  us at the lines: 128 x 512 -> 512 on 4x4 13.2 -> 12.1, 128 x 1024 -> 1024 on 2x2 15.5 -> 14.9, left: 128 x 512 -> 1024
+// from 4x4 14.0 (16.0 here), 128 x 256 -> 512 from 8x8 11.8 (12.5).
+// Against the kernel that computes all channels once per tile of 64 columns, which a call without workspace would take (fp32, 2507 layers):
+// median 2.5 times as fast, as few columns leave that one most of the chip idle; from 4096 columns up it can lose (291 x 64 -> 96 from 8x8 9.1 to 10.8).
+bool dw_forward_few_preferred(const Problem& p, const DwGeom& g, int es, bool against_fused)
 {
-    return dw_forward_few_eligible(p, g) && few_units(p) <= 1100;
+    if (!dw_forward_few_eligible(p, g)) return false;
+    if (p.NQ < 64) return true;
+    const FewPlan f = few_plan(p);
+    if (f.units > 1100) return false;                                           // not measured above
+    if (against_fused) return p.NQ < 4096;
+    if (g.s == 2 && es == 4 && f.wv == 8) return false;
+    const long long width = f.cp == 1 ? 4 : 3 + f.cp * f.tf;
+    const long long walked = width * f.rounds * (f.t.total < 256 ? 256 : f.t.total);
+    return walked <= (g.s == 2 ? (es == 4 ? 1280 : 2048) : g.Wo == 2 && f.cp == 1 ? 4096 : 2048);
 }
 
 template <typename T_>
 hipError_t launch_dw_forward_few(const T_* x, const T_* kdw, const T_* w, T_* y, const Problem& p, const DwGeom& g,
                                  hipStream_t st)
 {
-    const int cp = few_cp(few_tiling(p, 1, 1));
-    // two tiles per workgroup once one would make two generations of workgroups: 128 x 512 -> 512 on 4x4 15.5 -> 12.1, 64 of them
-    // 8.8 -> 9.1; four tiles gain nothing more (12.8)
-    const bool two = cp <= 2 && few_units(p) > 768;
-    // eight wavefronts where four would walk their quarter of the span in more than one round and the chip holds all workgroups at
-    // once (one per CU): 16 x 1024 -> 1024 on 2x2, cg 2, 9.6 -> 8.3 us, bf16 9.4 -> 7.9; 16 x 512 -> 512 on 4x4, cg 1, 9.7 -> 7.8
+    const FewPlan f = few_plan(p);
     using std::integral_constant;
     hipError_t e = hipSuccess;
-    auto go = [&](auto s, auto map, auto c, auto f, auto wv) {
-        constexpr int S = decltype(s)::value, MAP = decltype(map)::value, CP = decltype(c)::value, TF = decltype(f)::value;
+    auto go = [&](auto s, auto map, auto c, auto tf, auto wv) {
+        constexpr int S = decltype(s)::value, MAP = decltype(map)::value, CP = decltype(c)::value, TF = decltype(tf)::value;
         constexpr int WV = decltype(wv)::value, kLds = WV * few_block_bytes(CP, TF, sizeof(T_) == 4 ? 3 : 1);
         if constexpr (kLds > 64 * 1024) {
             // more than 64 KiB of LDS per workgroup has to be allowed once
@@ -411,23 +439,20 @@ hipError_t launch_dw_forward_few(const T_* x, const T_* kdw, const T_* w, T_* y,
             e = allowed;
             if (e != hipSuccess) return;
         }
-        const FewTiling t = few_tiling(p, CP, TF);
-        dw_scc_forward_few<T_, S, MAP, CP, TF, WV><<<dim3(8u * (unsigned)t.chunk), dim3(64 * WV), kLds, st>>>(x, kdw, w, y, p, g, t);
+        dw_scc_forward_few<T_, S, MAP, CP, TF, WV><<<dim3(8u * (unsigned)f.t.chunk), dim3(64 * WV), kLds, st>>>(x, kdw, w, y, p, g, f.t);
         e = hipGetLastError();
     };
     const integral_constant<int, 4> four;
     auto with_tf = [&](auto s, auto map, auto c) {
         if constexpr (decltype(c)::value <= 2)
-            if (two) return go(s, map, c, integral_constant<int, 2>{}, four);
-        if constexpr (decltype(c)::value == 1) {
-            const FewTiling t = few_tiling(p, 1, 1);
-            if (t.U > 256 && t.total <= 256) return go(s, map, c, integral_constant<int, 1>{}, integral_constant<int, 8>{});
-        }
+            if (f.tf == 2) return go(s, map, c, integral_constant<int, 2>{}, four);
+        if constexpr (decltype(c)::value == 1)
+            if (f.wv == 8) return go(s, map, c, integral_constant<int, 1>{}, integral_constant<int, 8>{});
         go(s, map, c, integral_constant<int, 1>{}, four);
     };
     auto with_cp = [&](auto s, auto map) {
-        cp == 1 ? with_tf(s, map, integral_constant<int, 1>{})
-        : cp == 2 ? with_tf(s, map, integral_constant<int, 2>{}) : with_tf(s, map, integral_constant<int, 4>{});
+        f.cp == 1 ? with_tf(s, map, integral_constant<int, 1>{})
+        : f.cp == 2 ? with_tf(s, map, integral_constant<int, 2>{}) : with_tf(s, map, integral_constant<int, 4>{});
     };
     auto with_map = [&](auto s) {
         g.Wo == 2 ? with_cp(s, integral_constant<int, kMap2>{}) : with_cp(s, integral_constant<int, kMap4>{});

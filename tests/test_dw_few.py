@@ -14,7 +14,10 @@ CASES = [(1, 64, 40, 4, 4, 1, 2, 0.5), (1, 512, 512, 4, 4, 1, 2, 0.5), (1, 512, 
          (12, 240, 130, 3, 4, 2, 4, 0.4), (33, 64, 128, 2, 2, 1, 1, 0.5), (128, 512, 512, 4, 4, 1, 2, 0.5), (110, 512, 500, 4, 4, 1, 2, 0.5),
          (70, 256, 768, 4, 4, 2, 2, 0.5), (6, 1600, 64, 4, 4, 1, 2, 0.5), (40, 128, 128, 2, 2, 2, 8, 0.5), (8, 96, 24, 4, 4, 1, 3, 1.0),
          # eight wavefronts: spans of 272 to 1024 channels, the last wavefronts with little or nothing of them
-         (16, 1024, 1024, 2, 2, 1, 2, 0.5), (3, 272, 70, 4, 4, 2, 1, 0.5), (2, 528, 48, 2, 2, 2, 1, 0.5), (5, 304, 96, 5, 4, 1, 1, 0.25)]
+         (16, 1024, 1024, 2, 2, 1, 2, 0.5), (3, 272, 70, 4, 4, 2, 1, 0.5), (2, 528, 48, 2, 2, 2, 1, 0.5), (5, 304, 96, 5, 4, 1, 1, 0.25),
+         # on both sides of the lines to the two stages: workgroups' number, rounds of a wavefront, width of a workgroup
+         (16, 256, 1024, 4, 4, 2, 2, 0.5), (17, 256, 1024, 4, 4, 2, 2, 0.5), (16, 512, 64, 4, 4, 1, 1, 0.5), (66, 512, 96, 4, 4, 1, 1, 0.5),
+         (30, 144, 576, 2, 2, 1, 1, 0.0), (26, 256, 300, 2, 2, 2, 2, 0.25)]
 
 
 def tensors(case, dtype, shift=0):
