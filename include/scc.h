@@ -245,9 +245,7 @@ int scc_depthwise3x3_backward(const void* x, const void* kdw, const void* dz, vo
  * depthwise output of a tile of pixels for all channels on chip and feeds the SCC from there; x is read
  * once, y written once, the intermediate never reaches memory (and is not rounded to the storage type).
  * Two stages (every layer): scc_depthwise3x3_forward into `workspace`, then scc_forward on it; `workspace`
- * then holds the depthwise output (N*Cin*Ho*Wo values of the dtype); or, on layers with few output pixels on maps of 4 x n
- * or 2 x 2, one kernel that computes it again for every group of filters (rounded to the storage type as the two stages round
- * it) and leaves the workspace alone.
+ * then holds the depthwise output (N*Cin*Ho*Wo values of the dtype).
  * scc_dw_forward_workspace_bytes(...) returns 0 for the layers the library runs fused by its own choice
  * (fusable and at least 16384 output pixels over the batch, where fusing is the faster path) and the size
  * of the depthwise output for all others.  A call with a workspace of at least that size (256-byte aligned,
@@ -264,6 +262,15 @@ int scc_dw_forward_fusable(int N, int Cin, int Cout, int H, int W, int dw_stride
 int scc_dw_forward(const void* x, const void* kdw, const void* w, void* y,
                    int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co,
                    scc_dtype dtype, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
+ * The same for callers that want y alone: same arguments, workspace size and errors, but the workspace is scratch and holds
+ * nothing in particular afterwards.  On layers with few output pixels on maps of 4 x n or 2 x 2 one kernel then computes the
+ * depthwise output again for every group of filters, in bf16 rounded as the two stages round it, and leaves the workspace alone.
+ */
+int scc_dw_forward_scratch(const void* x, const void* kdw, const void* w, void* y,
+                           int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co,
+                           scc_dtype dtype, void* workspace, size_t workspace_bytes, void* stream);
 
 /*
  * All gradients of that block in one call (the depthwise output is computed again, never kept):

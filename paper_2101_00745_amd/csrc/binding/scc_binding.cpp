@@ -185,8 +185,8 @@ PyObject* dw_forward(PyObject*, PyObject* const* args, Py_ssize_t n)
     const size_t need = scc_dw_forward_workspace_bytes(l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg, a.co, l.dtype);
     const at::Tensor ws = scratch(need, x);
     const int rc = launch(x, [&](void* st) {
-        return scc_dw_forward(x.data_ptr(), k.data_ptr(), w.data_ptr(), y.data_ptr(), l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg,
-                              a.co, l.dtype, address(ws), need, st);
+        return scc_dw_forward_scratch(x.data_ptr(), k.data_ptr(), w.data_ptr(), y.data_ptr(), l.N, l.Cin, l.Cout, l.H, l.W,
+                                      a.stride, a.cg, a.co, l.dtype, address(ws), need, st);
     });
     if (rc != SCC_OK) Py_RETURN_NONE;
     return THPVariable_Wrap(std::move(y));

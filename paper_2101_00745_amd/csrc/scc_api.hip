@@ -434,9 +434,10 @@ int scc_dw_forward_fusable(int N, int Cin, int Cout, int H, int W, int dw_stride
     return dtype == SCC_F32 && scc::dw_forward_fused_eligible(p) ? 1 : 0;
 }
 
-int scc_dw_forward(const void* x, const void* kdw, const void* w, void* y, int N, int Cin, int Cout, int H, int W,
-                   int dw_stride, int cg, double co, scc_dtype dtype, void* workspace, size_t workspace_bytes,
-                   void* stream)
+// keep: a workspace that two stages would run in holds the depthwise output afterwards
+static int dw_forward(const void* x, const void* kdw, const void* w, void* y, int N, int Cin, int Cout, int H, int W,
+                      int dw_stride, int cg, double co, scc_dtype dtype, void* workspace, size_t workspace_bytes,
+                      void* stream, bool keep)
 {
     if (!x || !kdw || !w || !y) return SCC_ERR_NULL;
     Problem p;
@@ -449,7 +450,7 @@ int scc_dw_forward(const void* x, const void* kdw, const void* w, void* y, int N
     const bool fused = dtype == SCC_F32 && (need == 0 || (!workspace && scc::dw_forward_fused_eligible(p)));
     if (!fused && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0))
         return SCC_ERR_WORKSPACE;
-    if (scc::dw_forward_few_preferred(p, g, dtype == SCC_F32 ? 4 : 2, fused)) {      // one kernel as well; the workspace it could do without stays as it is
+    if ((fused || !keep) && scc::dw_forward_few_preferred(p, g, dtype == SCC_F32 ? 4 : 2, fused)) {   // touches no workspace
         drop_stale_error();
         return with_type(dtype, [&](auto t) {
             typedef decltype(t) T;
@@ -466,6 +467,20 @@ int scc_dw_forward(const void* x, const void* kdw, const void* w, void* y, int N
     const int r1 = scc_depthwise3x3_forward(x, kdw, workspace, N, Cin, H, W, dw_stride, dtype, stream);
     if (r1 != SCC_OK) return r1;
     return scc_forward(workspace, w, y, N, Cin, Cout, g.Ho, g.Wo, cg, co, dtype, stream);
+}
+
+int scc_dw_forward(const void* x, const void* kdw, const void* w, void* y, int N, int Cin, int Cout, int H, int W,
+                   int dw_stride, int cg, double co, scc_dtype dtype, void* workspace, size_t workspace_bytes,
+                   void* stream)
+{
+    return dw_forward(x, kdw, w, y, N, Cin, Cout, H, W, dw_stride, cg, co, dtype, workspace, workspace_bytes, stream, true);
+}
+
+int scc_dw_forward_scratch(const void* x, const void* kdw, const void* w, void* y, int N, int Cin, int Cout, int H, int W,
+                           int dw_stride, int cg, double co, scc_dtype dtype, void* workspace, size_t workspace_bytes,
+                           void* stream)
+{
+    return dw_forward(x, kdw, w, y, N, Cin, Cout, H, W, dw_stride, cg, co, dtype, workspace, workspace_bytes, stream, false);
 }
 
 // The workspace of scc_dw_backward: the depthwise output, its gradient, then the scratch of whichever stage runs.

@@ -22,6 +22,7 @@ SYMBOLS = ("scc_window_params", "scc_forward", "scc_forward_workspace_bytes", "s
            "scc_backward_workspace_bytes", "scc_backward", "scc_backward_weight_path", "scc_backward_path",
            "scc_depthwise3x3_out", "scc_depthwise3x3_forward", "scc_depthwise3x3_backward_workspace_bytes",
            "scc_depthwise3x3_backward", "scc_dw_forward_workspace_bytes", "scc_dw_forward_fusable", "scc_dw_forward",
+           "scc_dw_forward_scratch",
            "scc_dw_backward_workspace_bytes", "scc_dw_backward", "scc_dw_backward_as_workspace_bytes", "scc_dw_backward_as",
            "scc_status_string")
 STATIC_SCRATCH_BYTES = 32 << 20    # SCC_STATIC_SCRATCH_BYTES of include/scc.h
@@ -85,6 +86,8 @@ def load():
     lib.scc_dw_forward_fusable.restype = c_int
     lib.scc_dw_forward.argtypes = [c_vp] * 4 + dw_shape + [c_vp, c_sz, c_vp]
     lib.scc_dw_forward.restype = c_int
+    lib.scc_dw_forward_scratch.argtypes = lib.scc_dw_forward.argtypes
+    lib.scc_dw_forward_scratch.restype = c_int
     lib.scc_dw_backward_workspace_bytes.argtypes = dw_shape
     lib.scc_dw_backward_workspace_bytes.restype = c_sz
     lib.scc_dw_backward.argtypes = [c_vp] * 7 + dw_shape + [c_vp, c_sz, c_vp]
@@ -398,7 +401,8 @@ def scc_dw_forward(x, kdw, w, cg, co, dw_stride=1, out=None, workspace=None, fus
     """y = SCC(DW3x3(x; kdw); w), the forward of a DW + SCC block: x [N,Cin,H,W], kdw [Cin,3,3], w [Cout,Cin//cg]
     -> y [N,Cout,Ho,Wo].  fused=None: the path the library prefers (a workspace is allocated when it asks for
     one); fused=True: no workspace is passed, so the fused kernel runs or the call is refused; fused=False: the
-    two stages through a workspace, also where the library would fuse."""
+    two stages through a workspace, also where the library would fuse.  A `workspace` that is given holds the depthwise
+    output afterwards wherever the library asks for one."""
     if fused is None and out is None and workspace is None:
         y = (_native or _load_native()).dw_forward(x, kdw, w, cg, co, dw_stride)
         if y is not None:
@@ -418,17 +422,19 @@ def scc_dw_forward(x, kdw, w, cg, co, dw_stride=1, out=None, workspace=None, fus
         return scc_forward(z, w, cg, co, out=x.new_empty((N, Cout, Ho, Wo)) if out is None else out)
     shape = (N, Cin, Cout, H, W, dw_stride, cg, float(co), _dtype_code(x))
     need = _workspace_need("scc_dw_forward_workspace_bytes", *shape)
+    call = load().scc_dw_forward
     if fused:
         workspace = None
     elif workspace is None and need > 0:
         workspace = torch.empty(need, dtype=torch.uint8, device=dev)
+        call = load().scc_dw_forward_scratch
     y = x.new_empty((N, Cout, Ho, Wo)) if out is None else out
     if out is not None:
         _dev(out)
         assert out.shape == (N, Cout, Ho, Wo) and out.dtype == x.dtype
     ws_ptr = workspace.data_ptr() if workspace is not None else None
     ws_len = workspace.numel() * workspace.element_size() if workspace is not None else 0
-    _launch(dev, load().scc_dw_forward, x.data_ptr(), kdw.data_ptr(), w.data_ptr(), y.data_ptr(), *shape, ws_ptr, ws_len)
+    _launch(dev, call, x.data_ptr(), kdw.data_ptr(), w.data_ptr(), y.data_ptr(), *shape, ws_ptr, ws_len)
     return y
 
 

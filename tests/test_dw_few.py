@@ -49,3 +49,22 @@ def test_against_the_oracle(case, dtype, shift):
         two = S.scc_dw_forward(x, k, w, cg, co, s, fused=False)
         err = [float((t.double().cpu() - torch.from_numpy(np.asarray(ref, dtype=np.float64))).norm()) for t in (y, two)]
         assert err[0] <= 1.1 * err[1]                                          # no further from binary64 than the two stages
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_a_given_workspace_holds_the_depthwise_output(dtype):
+    case = (16, 512, 512, 4, 4, 1, 2, 0.5)
+    N, Cin, Cout, Ho, Wo, s, cg, co = case
+    x, k, w = tensors(case, dtype)
+    need = S.scc_dw_forward_workspace_bytes(N, Cin, Cout, Ho * s, Wo * s, s, cg, co, dtype)
+    assert need == N * Cin * Ho * Wo * x.element_size()
+    ws = torch.zeros(need, dtype=torch.uint8, device="cuda")
+    y = S.scc_dw_forward(x, k, w, cg, co, s, workspace=ws)
+    z = S.scc_depthwise3x3_forward(x, k, s)
+    assert torch.equal(ws.view(dtype).view(z.shape), z)
+    assert torch.equal(y, S.scc_dw_forward(x, k, w, cg, co, s, fused=False))
+    # binary32 sums in another order; bf16 results rounded to 2^-9 of themselves
+    own = S.scc_dw_forward(x, k, w, cg, co, s, out=torch.empty_like(y))
+    assert torch.equal(own, S.scc_dw_forward(x, k, w, cg, co, s))                # one kernel, with and without an out tensor
+    assert (own.float() - y.float()).abs().max() <= (2e-5 if dtype == torch.float32 else 1e-2) * y.float().abs().max()
