@@ -102,17 +102,30 @@ def load():
     return lib
 
 
+class _NoNative:
+    """Finds no call plain."""
+
+    @staticmethod
+    def forward(*args):
+        return None
+
+    backward = dw_forward = dw_backward = forward
+
+
 def _load_native():
-    """The plain calls: each answers None where a call is not plain (or fails), and the general way below it then goes on."""
+    """The plain calls: each answers None where a call is not plain (or fails), and the general way below it then goes on.  Where
+    the module is not built, or not for this torch, every call takes that way: the same kernels, some microseconds more of host time."""
     global _native
     load()
     try:
         from . import _binding
+        _native = _binding
     except ImportError as e:
-        raise ImportError("_binding.so is not built for this torch (%s): run `python -m paper_2101_00745_amd.build` "
-                          "(or __graft_entry__.build()) first; there is no fallback path" % e) from e
-    _native = _binding
-    return _binding
+        import warnings
+        _native = _NoNative
+        warnings.warn("plain calls go through ctypes: the binding's native part is not built for this torch (%s); "
+                      "`python -m paper_2101_00745_amd.build` builds it" % e, RuntimeWarning, stacklevel=3)
+    return _native
 
 
 def scc_status_string(status):
