@@ -2,6 +2,8 @@
 import glob
 import os
 import subprocess
+import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
@@ -11,7 +13,8 @@ MEMBW_SRC = os.path.join(CSRC, "membw", "membw.hip")
 MEMBW_LIB = os.path.join(HERE, "libscc_membw.so")   # streaming kernels of the benchmark's copy ceiling; not the SCC ABI
 
 BINDING_SRC = os.path.join(CSRC, "binding", "scc_binding.cpp")
-BINDING_LIB = os.path.join(HERE, "_binding.so")     # the Python binding's plain calls (host code, against torch's C++ API)
+# the Python binding's plain calls (host code against torch's C++ API, so for one interpreter and one torch: binding_tag)
+BINDING_LIB = os.path.join(HERE, "_binding" + sysconfig.get_config_var("EXT_SUFFIX"))
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 COMPILE_FLAGS = ["-O3", "-std=c++17", "--offload-arch=gfx950", "-fPIC", "-fno-gpu-rdc",
@@ -25,9 +28,18 @@ def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
 
 
+def binding_tag():
+    """What the native part of the binding is built for; it holds this text (`built_for`)."""
+    import torch
+    return "%s torch %s %s" % (sys.implementation.cache_tag, torch.__version__, torch.version.git_version)
+
+
 def stale():
     if not os.path.exists(LIB) or not os.path.exists(BINDING_LIB):
         return True
+    with open(BINDING_LIB, "rb") as f:
+        if binding_tag().encode() not in f.read():
+            return True
     t = min(os.path.getmtime(LIB), os.path.getmtime(BINDING_LIB))
     deps = sources() + [BINDING_SRC] + glob.glob(os.path.join(CSRC, "*.h")) + glob.glob(os.path.join(INCLUDE, "*.h"))
     return any(os.path.getmtime(f) > t for f in deps)
@@ -73,9 +85,7 @@ def build(force=True, verbose=False):
 
 
 def build_binding(verbose=False):
-    """Build _binding.so, which calls libscc_hip.so beside it."""
-    import sysconfig
-
+    """Build the native part of the binding, which calls libscc_hip.so beside it."""
     import torch
     root = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(HIPCC))
@@ -83,7 +93,7 @@ def build_binding(verbose=False):
                 os.path.join(rocm, "include"), sysconfig.get_paths()["include"], INCLUDE]
     tmp = BINDING_LIB + ".tmp.%d" % os.getpid()
     _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI] + ["-I" + i for i in includes] +
+          "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DSCC_BUILT_FOR="%s"' % binding_tag()] + ["-I" + i for i in includes] +
          [BINDING_SRC, "-o", tmp, "-L" + os.path.join(root, "lib"), "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python",
           "-L" + HERE, "-lscc_hip", "-Wl,-rpath,$ORIGIN"], verbose)
     os.replace(tmp, BINDING_LIB)

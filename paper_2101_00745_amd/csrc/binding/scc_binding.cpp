@@ -225,4 +225,10 @@ PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, n
 
 }  // namespace
 
-PyMODINIT_FUNC PyInit__binding() { return PyModule_Create(&module); }
+// built_for: the torch (and interpreter) whose inlined types this code was compiled with; scc.py compares it before the first call
+PyMODINIT_FUNC PyInit__binding()
+{
+    PyObject* m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", SCC_BUILT_FOR) < 0) Py_CLEAR(m);
+    return m;
+}

@@ -119,6 +119,9 @@ def _load_native():
     load()
     try:
         from . import _binding
+        from .build import binding_tag
+        if getattr(_binding, "built_for", None) != binding_tag():
+            raise ImportError("built for " + getattr(_binding, "built_for", "another one"))
         _native = _binding
     except ImportError as e:
         import warnings

@@ -1,11 +1,14 @@
 """The native part of the binding is the plain calls' shorter way, not a condition: without it every call takes the general way through
 ctypes, on the same kernels."""
+import os
 import sys
+import types
 
 import pytest
 import torch
 
 import paper_2101_00745_amd as S
+from paper_2101_00745_amd import build
 from paper_2101_00745_amd import scc as B
 
 
@@ -46,3 +49,27 @@ def test_results_are_the_same(absent, monkeypatch):
     for a, b in zip(without, [c() for c in calls(*args)]):
         for s, t in zip(a if isinstance(a, tuple) else (a,), b if isinstance(b, tuple) else (b,)):
             assert torch.equal(s, t)
+
+
+def never(*args):
+    raise AssertionError("called into a module of another torch")
+
+
+@pytest.mark.parametrize("built_for", [None, "cpython-310 torch 2.4.0 0000"])
+def test_a_module_of_another_torch_is_not_called(absent, monkeypatch, built_for):
+    other = types.ModuleType("paper_2101_00745_amd._binding")
+    other.forward = other.backward = other.dw_forward = other.dw_backward = never
+    if built_for:
+        other.built_for = built_for
+    monkeypatch.setitem(sys.modules, other.__name__, other)
+    with pytest.warns(RuntimeWarning, match="not built for this torch"):
+        with pytest.raises(ValueError, match="must live on the GPU"):
+            S.scc_forward(torch.zeros(1, 8, 4, 4), torch.zeros(8, 4), 2, 0.5)
+
+
+def test_the_built_module_is_for_this_torch(monkeypatch):
+    B.load()
+    from paper_2101_00745_amd import _binding
+    assert _binding.built_for == build.binding_tag() and os.path.samefile(_binding.__file__, build.BINDING_LIB)
+    monkeypatch.setattr(build, "binding_tag", lambda: "cpython-310 torch 2.4.0 0000")
+    assert build.stale()                                     # built again where torch changed
