@@ -1,6 +1,7 @@
 """Compile the HIP sources in csrc/ into libscc_hip.so (gfx950 only) and the Python binding's native part, in-tree."""
 import glob
 import os
+import shutil
 import subprocess
 import sys
 import sysconfig
@@ -26,6 +27,14 @@ LINK_FLAGS = ["--offload-arch=gfx950", "-fPIC", "-shared", "-fno-gpu-rdc", "-Wno
 
 def sources():
     return sorted(glob.glob(os.path.join(CSRC, "*.hip")))
+
+
+def rocm_root():
+    """The ROCm tree that HIPCC, a path or a command name, belongs to."""
+    hipcc = shutil.which(HIPCC)
+    if hipcc is None:
+        raise RuntimeError("no compiler %r (set HIPCC)" % HIPCC)
+    return os.path.dirname(os.path.dirname(os.path.realpath(hipcc)))
 
 
 def binding_tag():
@@ -61,7 +70,6 @@ def build(force=True, verbose=False):
     if not force and not stale():
         return LIB
     import concurrent.futures
-    import shutil
     import tempfile
     work = tempfile.mkdtemp(prefix="scc_build_")
     try:
@@ -88,9 +96,8 @@ def build_binding(verbose=False):
     """Build the native part of the binding, which calls libscc_hip.so beside it."""
     import torch
     root = os.path.dirname(torch.__file__)
-    rocm = os.path.dirname(os.path.dirname(HIPCC))
     includes = [os.path.join(root, "include"), os.path.join(root, "include", "torch", "csrc", "api", "include"),
-                os.path.join(rocm, "include"), sysconfig.get_paths()["include"], INCLUDE]
+                os.path.join(rocm_root(), "include"), sysconfig.get_paths()["include"], INCLUDE]
     tmp = BINDING_LIB + ".tmp.%d" % os.getpid()
     _run([os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
           "-D_GLIBCXX_USE_CXX11_ABI=%d" % torch._C._GLIBCXX_USE_CXX11_ABI, '-DSCC_BUILT_FOR="%s"' % binding_tag()] + ["-I" + i for i in includes] +

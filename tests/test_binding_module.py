@@ -73,3 +73,15 @@ def test_the_built_module_is_for_this_torch(monkeypatch):
     assert _binding.built_for == build.binding_tag() and os.path.samefile(_binding.__file__, build.BINDING_LIB)
     monkeypatch.setattr(build, "binding_tag", lambda: "cpython-310 torch 2.4.0 0000")
     assert build.stale()                                     # built again where torch changed
+
+
+@pytest.mark.parametrize("hipcc", ["hipcc", "/opt/rocm/bin/hipcc"])
+def test_the_headers_of_a_compiler_named_by_command(monkeypatch, hipcc):
+    """HIPCC may be a path or a name on PATH; the ROCm headers are those beside it either way."""
+    monkeypatch.setattr(build, "HIPCC", hipcc)
+    monkeypatch.setenv("PATH", "/opt/rocm/bin" + os.pathsep + os.environ["PATH"])
+    seen = []
+    monkeypatch.setattr(build, "_run", lambda cmd, verbose: seen.extend(cmd))
+    monkeypatch.setattr(build.os, "replace", lambda a, b: None)
+    build.build_binding()
+    assert any(c.startswith("-I") and os.path.exists(os.path.join(c[2:], "hip", "hip_runtime_api.h")) for c in seen)
