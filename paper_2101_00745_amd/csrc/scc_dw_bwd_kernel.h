@@ -68,10 +68,12 @@ __device__ __forceinline__ void input_s2_body(const T_* __restrict__ dz, const T
         tvec r0, r1;
 #pragma unroll
         for (int j = 0; j < 2; ++j) {
+            // spelled out, as in columns_body: three kernels hold this body and their results are the same bit for bit
             r0[2 * j] = from_f32<T_>(k[4] * ga[j]);
-            r0[2 * j + 1] = from_f32<T_>(k[3] * ga[j + 1] + k[5] * ga[j]);
-            r1[2 * j] = from_f32<T_>(k[1] * gb[j] + k[7] * ga[j]);
-            r1[2 * j + 1] = from_f32<T_>(k[0] * gb[j + 1] + k[2] * gb[j] + k[6] * ga[j + 1] + k[8] * ga[j]);
+            r0[2 * j + 1] = from_f32<T_>(__builtin_fmaf(k[5], ga[j], k[3] * ga[j + 1]));
+            r1[2 * j] = from_f32<T_>(__builtin_fmaf(k[7], ga[j], k[1] * gb[j]));
+            const float up = __builtin_fmaf(k[2], gb[j], k[0] * gb[j + 1]);
+            r1[2 * j + 1] = from_f32<T_>(__builtin_fmaf(k[8], ga[j], __builtin_fmaf(k[6], ga[j + 1], up)));
         }
         T_* o = dx + t * HWi + (size_t)(2 * m) * G.W + 2 * q0;
         __builtin_nontemporal_store(r0, (tvec*)o);

@@ -124,3 +124,26 @@ def test_depthwise_gradients_in_one_launch_are_those_of_two(N, C, H, W, s, dtype
     ref_dx, ref_dk = O.depthwise3x3_backward(*(t.float().cpu().numpy() for t in (x, kdw, dz)), s)
     assert np.max(np.abs(dx.float().cpu().numpy() - ref_dx)) <= (2e-5 if dtype == torch.float32 else 1e-2) * np.max(np.abs(ref_dx))
     assert np.max(np.abs(dk.cpu().numpy() - ref_dk)) <= 2e-5 * np.max(np.abs(ref_dk))
+
+
+@pytest.mark.gpu
+def test_products_of_the_gradient_at_stride_2():
+    """A pixel's sum of two or four products: the first is rounded, each that follows is added with one rounding, in the order of the
+    rows from below, in every kernel (alone, beside the filter's gradient, in a block's backward)."""
+    import numpy as np
+    N, C, Ho = 3, 32, 4
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x, kdw, dz = (torch.randn(*d, generator=gen, device="cuda") for d in ((N, C, 2 * Ho, 2 * Ho), (C, 3, 3), (N, C, Ho, Ho)))
+    g = np.zeros((N, C, Ho + 1, Ho + 1), dtype=np.longdouble)              # rows and columns past the map are zero
+    g[:, :, :Ho, :Ho] = dz.cpu().numpy()
+    k = kdw.cpu().numpy().astype(np.longdouble).reshape(C, 9, 1, 1)
+    a, right, down, both = g[:, :, :-1, :-1], g[:, :, :-1, 1:], g[:, :, 1:, :-1], g[:, :, 1:, 1:]
+    one = lambda s: s.astype(np.float32).astype(np.longdouble)             # a binary32 rounding (64 bits hold the exact sum but for ties)
+    want = np.empty((N, C, 2 * Ho, 2 * Ho), dtype=np.float32)
+    want[:, :, ::2, ::2] = k[:, 4] * a
+    want[:, :, ::2, 1::2] = k[:, 5] * a + one(k[:, 3] * right)
+    want[:, :, 1::2, ::2] = k[:, 7] * a + one(k[:, 1] * down)
+    want[:, :, 1::2, 1::2] = k[:, 8] * a + one(k[:, 6] * right + one(k[:, 2] * down + one(k[:, 0] * both)))
+    want = torch.from_numpy(want).cuda()
+    assert torch.equal(S.scc_depthwise3x3_backward(x, kdw, dz, 2)[0], want)
+    assert torch.equal(S.scc_depthwise3x3_backward(x, kdw, dz, 2, need_dk=False)[0], want)
