@@ -211,12 +211,16 @@ __device__ __forceinline__ void filter_columns_body(const T_* __restrict__ x, co
 }
 
 // On planes (output maps of 2 x 2 read from maps of S times that): a lane owns one channel, whose planes are 16 (16 * S * S) bytes
-// next to its neighbours', and the four wavefronts of a workgroup of 64 channels share the samples.  Lanes on samples of one channel,
-// as in the bodies above, fetch a cache line for every 16 bytes here (all gradients of a block, us: 1024 -> 1024 on 2x2 at batch 128
-// 38.8 -> 28.7, at 16 20.0 -> 13.5, 512 -> 1024 from 4x4 at 128 28.3 -> 24.2).  kBatch samples are in flight, each with sums of its own, added as a tree behind the loop.
+// next to its neighbours'.  Lanes on samples of one channel, as in the bodies above, fetch a cache line for every 16 bytes here.
+// A workgroup takes eight channels, a cache line of binary32 planes, and its 32 groups of eight lanes share the samples: there are
+// C / 8 workgroups per slice, and no more than 1024 / C slices.  (64 channels per workgroup leave 16 to 32 workgroups whatever the
+// batch.)  The filter gradient, us, lanes on samples / 64 channels per workgroup / 8: f32 1024 channels, batch 128 13.8 / 6.3 / 3.5, batch 1024 55 /
+// 32 / 9.0 and at stride 2 76 / 142 / 24; 512 channels, batch 1024, stride 2 40 / 50 / 12; bf16 1024 channels, batch 1024 49 / 74 / 12; 64 channels,
+// batch 16 7.2 / 5.1 / 5.1; 16 channels, one sample 4.6 / 2.7 / 3.0.
+// kBatch samples are in flight, each with sums of its own, added as a tree behind the loop.
 // `red`: kPlanesLds bytes of LDS.
-constexpr int kPlaneChannels = 64;
-constexpr size_t kPlanesLds = (kDkThreads / 64) * kPlaneChannels * 9 * sizeof(float);
+constexpr int kPlaneChannels = 8, kPlaneShares = kDkThreads / kPlaneChannels;
+constexpr size_t kPlanesLds = kDkThreads * 9 * sizeof(float);
 
 inline __host__ __device__ bool filter_on_planes(const DwGeom& g)
 {
@@ -228,20 +232,20 @@ __device__ __forceinline__ void filter_planes_body(const T_* __restrict__ x, con
                                                    int N, int C, int per, int group, int slice, float* red)
 {
     typedef T_ plane4 __attribute__((ext_vector_type(4), aligned(sizeof(T_))));
-    constexpr int kBatch = S == 1 ? 8 : 4, kWaves = kDkThreads / 64, W = 2 * S;
-    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6)), lane = threadIdx.x & 63;
-    const int a0 = group * kPlaneChannels, a = a0 + lane < C ? a0 + lane : C - 1;      // past the end: the last one again, not stored
+    constexpr int kBatch = S == 1 ? 8 : 4, W = 2 * S;
+    const int a0 = group * kPlaneChannels, own_a = a0 + (int)(threadIdx.x % kPlaneChannels);
+    const int a = own_a < C ? own_a : C - 1;           // past the end: the last one again, not stored
     const int n0 = slice * per, n1 = n0 + per < N ? n0 + per : N;
     float s[kBatch][9];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u)
 #pragma unroll
         for (int t = 0; t < 9; ++t) s[u][t] = 0.f;
-    for (int n = n0 + wave; n < n1; n += kWaves * kBatch) {
+    for (int n = n0 + (int)(threadIdx.x / kPlaneChannels); n < n1; n += kPlaneShares * kBatch) {
         plane4 gv[kBatch], xv[kBatch][S * S];
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const int nu = n + kWaves * u;
+            const int nu = n + kPlaneShares * u;
             const size_t plane = (size_t)(nu < n1 ? nu : n) * C + a;
             gv[u] = *(const plane4*)(dz + plane * 4);
 #pragma unroll
@@ -249,7 +253,7 @@ __device__ __forceinline__ void filter_planes_body(const T_* __restrict__ x, con
         }
 #pragma unroll
         for (int u = 0; u < kBatch; ++u) {
-            const bool live = n + kWaves * u < n1;
+            const bool live = n + kPlaneShares * u < n1;
             float own[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int o = 0; o < 4; ++o)
@@ -273,15 +277,17 @@ __device__ __forceinline__ void filter_planes_body(const T_* __restrict__ x, con
 #pragma unroll
             for (int t = 0; t < 9; ++t) s[u][t] += s[u + d][t];
 #pragma unroll
-    for (int t = 0; t < 9; ++t) red[(wave * kPlaneChannels + lane) * 9 + t] = s[0][t];
+    for (int t = 0; t < 9; ++t) red[threadIdx.x * 9 + t] = s[0][t];
     __syncthreads();
-    const int count = (a0 + kPlaneChannels < C ? kPlaneChannels : C - a0) * 9;
-    float* out = part + ((size_t)slice * C + a0) * 9;
-    for (int e = threadIdx.x; e < count; e += kDkThreads) {
-        float v[kWaves];
+    const int count = ((a0 + kPlaneChannels < C ? a0 + kPlaneChannels : C) - a0) * 9;
+    if ((int)threadIdx.x < count) {
+        constexpr int kStep = 9 * kPlaneChannels;
+        float sum[4] = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) v[w] = red[w * kPlaneChannels * 9 + e];
-        out[e] = (v[0] + v[1]) + (v[2] + v[3]);
+        for (int w = 0; w < kPlaneShares; w += 4)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) sum[u] += red[(w + u) * kStep + threadIdx.x];
+        part[((size_t)slice * C + a0) * 9 + threadIdx.x] = (sum[0] + sum[1]) + (sum[2] + sum[3]);
     }
 }
 
@@ -337,8 +343,8 @@ __device__ __forceinline__ void filter_reduce_body(const float* __restrict__ par
     dk[e] = from_f32<T_>(s);
 }
 
-// slices of the samples per channel: about 1024 workgroups in all, at least one sample for each and, on strips, one strip per
-// thread; at most 65535.  Maps of 4x4 at batch 128 have 128 strips per channel: with two slices three quarters of the
+// slices of the samples per channel: about 1024 workgroups of one channel in all (128 of eight on planes), at least one sample for each and,
+// on strips, one strip per thread; at most 65535.  Maps of 4x4 at batch 128 have 128 strips per channel: with two slices three quarters of the
 // threads had none and the slices' sums took another launch (512 channels: 10.4 + 3.9 us, 9.6 with one).
 inline int filter_slices(int N, int C, const DwGeom& g)
 {

@@ -93,8 +93,8 @@ def test_host_checks():
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("N,C,s", [(1, 1, 1), (3, 64, 1), (31, 65, 1), (32, 63, 2), (33, 130, 1), (130, 64, 2), (67, 200, 2), (128, 1024, 1), (5, 2000, 2)])
 def test_filter_gradient_of_2x2_maps(N, C, s, dtype):
-    """A lane per channel: groups of 64 channels whole and partial, samples that fill no, one and several batches of the four
-    wavefronts, one and more slices; alone and in a block's backward."""
+    """A lane per channel: groups of channels whole and partial, samples that fill no, one and several batches of the lanes that
+    share them, one and more slices; alone and in a block's backward."""
     gen = torch.Generator(device="cuda").manual_seed(6)
     x, kdw, dz = (torch.randn(*d, generator=gen, device="cuda").to(dtype) for d in ((N, C, 2 * s, 2 * s), (C, 3, 3), (N, C, 2, 2)))
     import numpy as np
@@ -105,6 +105,14 @@ def test_filter_gradient_of_2x2_maps(N, C, s, dtype):
     assert torch.equal(dk, S.scc_depthwise3x3_backward(x, kdw, dz, s, need_dx=False)[1])
     if C % 16 == 0 and N >= 16:
         test_one_call_is_its_three_stages((N, C, 24, 2 * s, 2 * s, s, 2, 0.5), dtype)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N,C,s", [(1024, 7, 1), (1024, 8, 2), (255, 9, 1), (256, 17, 2), (257, 1031, 1), (129, 1024, 2), (1024, 1024, 1), (1024, 1025, 2)])
+def test_filter_gradient_of_2x2_maps_of_large_batches(N, C, s, dtype):
+    """Eight channels per workgroup, whole and not, and samples that fill one and several batches of its 32 groups of lanes."""
+    test_filter_gradient_of_2x2_maps(N, C, s, dtype)
 
 
 @pytest.mark.gpu
