@@ -35,7 +35,8 @@ DwGrads plan_gradients(const T_* x, const T_* dz, const T_* dx, int N, int C, co
     DwGrads d;
     d.slices = dw::filter_slices(N, C, g);
     d.per = (N + d.slices - 1) / d.slices;
-    d.filter = dw::filter_on_strips(x, dz, g, d.per) ? 8 * g.s + dw::strip_rows_of(g) : g.s == 1 ? dw::strip_rows_of(g) : 0;
+    d.filter = dw::filter_on_strips(x, dz, g, d.per) ? 8 * g.s + dw::strip_rows_of(g)
+               : dw::filter_on_columns(g, d.per) ? dw::strip_rows_of(g) : 0;
     uint32_t channels = (uint32_t)C;                  // or groups of them
     if (dw::filter_on_planes(g)) {
         d.filter = 32 + g.s;

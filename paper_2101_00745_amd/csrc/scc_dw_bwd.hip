@@ -213,7 +213,7 @@ hipError_t launch_depthwise3x3_backward(const T* x, const T* kdw, const T* dz, T
                 depthwise3x3_backward_filter_planes<T, 1><<<grid, dim3(kDkThreads), 0, st>>>(x, dz, part, N, C, per);
             else
                 depthwise3x3_backward_filter_planes<T, 2><<<grid, dim3(kDkThreads), 0, st>>>(x, dz, part, N, C, per);
-        } else if (g.s == 1)
+        } else if (dw::filter_on_columns(g, per))
             launch_filter_columns<T>(x, dz, part, N, C, g, slices, per, st);
         else
             depthwise3x3_backward_filter_generic<T><<<dim3((unsigned)C, (unsigned)slices), dim3(kDkThreads), 0, st>>>(

@@ -155,3 +155,13 @@ def test_products_of_the_gradient_at_stride_2():
     want = torch.from_numpy(want).cuda()
     assert torch.equal(S.scc_depthwise3x3_backward(x, kdw, dz, 2)[0], want)
     assert torch.equal(S.scc_depthwise3x3_backward(x, kdw, dz, 2, need_dk=False)[0], want)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N,C,H,W", [(38, 1024, 4, 5), (39, 1024, 4, 5), (31, 1030, 2, 6), (32, 1030, 2, 6), (200, 1024, 1, 9), (300, 1024, 4, 1),
+                                     (9, 1024, 7, 7), (5, 3, 9, 9), (1, 700, 13, 6), (2, 1100, 13, 14)])
+def test_filter_gradient_on_columns_or_pixels(N, C, H, W, dtype):
+    """On both sides of the line of 192 columns of one, two and four rows to a workgroup; maps of one row and of one column."""
+    test_depthwise_gradients_in_one_launch_are_those_of_two(N, C, H, W, 1, dtype)
+    test_one_call_is_its_three_stages((N, C, 24, H, W, 1, 1, 0.5), dtype)
