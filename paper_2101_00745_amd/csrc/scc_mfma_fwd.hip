@@ -362,20 +362,32 @@ __global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void forward_m
     int krow[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) krow[v] = __shfl(kv, 8 * (v >> 2) + 4 * h + (v & 3), 64);
-    auto store_row = [&](int v) {
-        bvec o;
+    // Rows are written past the caches (once, not re-read here) where they are whole pieces of 64 bytes.  On other planes neighbouring rows
+    // share such a piece, which the caches have to put together: forward, us, past them / through them, 953 x 256 -> 256 on 5x5, cg 4, f32
+    // 22.9 / 13.6, 840 x 256 -> 512 on 2x2, cg 8 10.5 / 6.1; over 12000 layers 1.03 to 1.13 times as fast through them by size of the plane, on planes of
+    // whole pieces 0.96 to 1.0.
+    auto store_rows = [&](auto past, auto whole) {
+        // the marks keep the compiler from making one of the stores of both ways, which would all go through the caches
+        if constexpr (decltype(past)::value) asm volatile("; rows past the caches");
 #pragma unroll
-        for (int c = 0; c < CT; ++c) o[c] = from_f32<T_>(acc[c][v]);
-        __builtin_nontemporal_store(o, (bvec*)((char*)y + (ycol + (uint32_t)krow[v] * plane)));  // written once, not re-read here
+        for (int v = 0; v < 16; ++v) {
+            if (!decltype(whole)::value && !(krow[v] >= 0 && live)) continue;
+            bvec o;
+#pragma unroll
+            for (int c = 0; c < CT; ++c) o[c] = from_f32<T_>(acc[c][v]);
+            bvec* at = (bvec*)((char*)y + (ycol + (uint32_t)krow[v] * plane));
+            if constexpr (decltype(past)::value)
+                __builtin_nontemporal_store(o, at);
+            else
+                *at = o;
+        }
+        if constexpr (decltype(past)::value) asm volatile("; end of rows past the caches");
     };
-    if (__all((int)(live && fvalid))) {              // a whole tile: no row and no column is asked for
-#pragma unroll
-        for (int v = 0; v < 16; ++v) store_row(v);
-    } else {
-#pragma unroll
-        for (int v = 0; v < 16; ++v)
-            if (krow[v] >= 0 && live) store_row(v);
-    }
+    const bool whole = __all((int)(live && fvalid));     // a whole tile: no row and no column is asked for
+    if (plane % 64 == 0)
+        whole ? store_rows(std::true_type(), std::true_type()) : store_rows(std::true_type(), std::false_type());
+    else
+        whole ? store_rows(std::false_type(), std::true_type()) : store_rows(std::false_type(), std::false_type());
 }
 
 int pow2_floor(int v)
