@@ -374,20 +374,28 @@ inline int choose(const Problem& p, int es)
     const double fetches = fetches_without_sharing<FWD>(p, b, &again);
     const bool odd = uneven(p, b), banded = FWD && b.F < 32 && b.P > 1;
     // Layers of whole groups of 4 pixels and weights and one window per tile, forward: the kernels without a workspace lose least
-    // there (fp32 has forward_shared32), so it counts how much longer the row groups' walks are than their windows.  Of 220
-    // fp32 layers from 5 fetches on, null / packed: below 1.2 from 60e6 fetches 1.06 to 1.19 by class of fetches, above 1.2 from 120e6 1.09 (60e6
-    // to 120e6 0.97 to 1.1, single layers 0.7); 120 bf16 layers: from 7 fetches 1.01 to 1.18 from 80e6 on (below 0.72 to 1.0), walks
-    // no longer than the windows 1.11 from 60e6 on.
+    // there (fp32 has forward_shared32), so it counts how much longer the row groups' walks are than their windows, and whether the
+    // rows fill their groups: where they do not, the others' tiles of 32 filters have empty rows as well.  Null / packed over 7330 fp32
+    // and 11415 bf16 layers from 2.5 fetches and 30e6 on, geometric mean: of those taken here 1.17 and 1.09, of those left 1.00 and 0.89.  fp32 whose
+    // walks are long is left to forward_shared32 where that shares nearly all four tiles' planes (0.96: 141 x 800 -> 800 on 12x12, cg 4 62 us
+    // and 75); bf16 that fills its groups is taken from 7 fetches on only (256 -> 1088 .. 3328 from 70e6 0.5 to 0.9).
     if (FWD && !odd && !banded && (es == 2 || p.L < 300)) {
         double walks = 0;
-        const int rows = b.P * b.F;
-        for (int ng = 0; 128 * ng < rows; ++ng) {
+        const int rows = b.P * b.F, groups = (rows + 127) / 128;
+        int longest = 0;
+        for (int ng = 0; ng < groups; ++ng) {
             int first, len;
             walk_of<true>(p, b, rows, ng, first, len);
             walks += len;
+            longest = len > longest ? len : longest;
         }
         const double longer = walks * 128 / ((double)rows * p.L);
-        if (es == 2) return again >= 7.0 && fetches >= (longer < 1.05 ? 60e6 : 80e6) ? ct : 0;
+        if (es == 2) {
+            if (again >= 7.0 && fetches >= (longer < 1.05 ? 60e6 : 80e6)) return ct;
+            const bool partial = 1000ll * rows <= 976ll * 128 * groups;
+            return partial && again >= 3.0 && fetches >= 55e6 && (b.P <= 2 || p.L > 236 || fetches >= 114e6) ? ct : 0;
+        }
+        if (longest > 300 && forward_shared_gain(p) >= 3.4) return 0;
         return (again >= 5.0 && longer < 1.2 && fetches >= 60e6) || (again >= 7.0 && fetches >= 120e6) ? ct : 0;
     }
     if (es == 2) return again >= 3.0 && fetches >= (odd ? 20e6 : 55e6) ? ct : 0;
