@@ -152,17 +152,30 @@ hipError_t launch_second(const T_* x, const T_* kdw, const T_* dy, const T_* z, 
 
 }  // namespace
 
-// Layers that gain: those small enough that launches and latencies count.  The depthwise ranges share the matrix kernels'
-// registers and LDS and so run with fewer wavefronts than in kernels of their own, which larger maps feel.  Values of x and z
-// together, us of the call before -> now (f32 unless said): 64 -> 128 on 32x32 stride 2: 2.5M 25.5 -> 18.5, 6.2M 31.5 -> 25.8, 10M 40.5 -> 38.6;
-// 32 -> 64 on 32x32: 4M 43 -> 35, 10M 58 -> 55; 128 on 28x28, cg 4: 4M 35.3 -> 35.8, 10M 54 -> 58, 25M 127 -> 139, bf16 4M 32 -> 28,
-// 10M 49 -> 48, 16M 64 -> 68; 256 on 12x12: 4M 35 -> 37, bf16 32 -> 30; 512 on 4x4, batch 128: 2M 32 -> 31.  Rows that are no multiple of
-// 4 run on columns, whose many small loads need the wavefronts: 256 on 7x7, cg 4: 1M 30 -> 24, 4M 67 -> 68, 8M 111 -> 168.
+// Layers that gain: those small enough that launches and latencies count.  The depthwise ranges share the matrix kernels' registers and
+// LDS and so run with fewer wavefronts than in kernels of their own, which larger maps feel, and the matrix ranges wait for one another's
+// workgroups, which long binary32 contractions feel.  One stage after the other (sums in one launch) / paired over 3415 drawn layers, geometric mean
+// and least, by the depthwise range: stride 2 on even maps and 2x2 maps, taken up to 2^23 values of x and z (rows of 4 pixels; 2^22 others) f32 1.12
+// (0.87), bf16 1.17 (0.94); rows of 4 at stride 1, f32, taken up to 150e6 multiply-adds and 2^22 values 1.09 (0.86), left 0.96; bf16, up to 2^23
+// values, 1.11 (0.82); columns, f32, up to 150e6 and 2^21 1.13 (0.79), left 0.95; bf16, up to 2^21, 1.22 (0.89), left 1.00; the gather of odd
+// maps, f32, up to 15e6 and 2^20 1.18 (0.84), left 0.92; bf16, up to 2^21, 1.21 (1.00).
 template <typename T_>
 bool block_backward_applicable(const Problem& p, const DwGeom& g)
 {
     const long long values = (long long)p.Cin * p.N * ((long long)g.H * g.W + p.HW);
-    return values <= (g.Wo % 4 == 0 ? 1ll << 23 : 1ll << 22) && backward_merged_applicable<T_>(p);
+    const double products = (double)p.NQ * p.Cout * p.L;
+    const bool wide = sizeof(T_) == 4, fours = g.Wo % 4 == 0;
+    const bool sized = (g.s == 1 || g.s == 2) && g.H == g.s * g.Ho && g.W == g.s * g.Wo;
+    long long most;
+    if (sized && (dw::filter_on_planes(g) || (g.s == 2 && g.Wo % 2 == 0)))
+        most = fours ? 1ll << 23 : 1ll << 22;
+    else if (sized && fours)
+        most = !wide ? 1ll << 23 : products <= 150e6 ? 1ll << 22 : 0;
+    else if (g.s == 1)
+        most = !wide || products <= 150e6 ? 1ll << 21 : 0;
+    else
+        most = !wide ? 1ll << 21 : products <= 15e6 ? 1ll << 20 : 0;
+    return values <= most && backward_merged_applicable<T_>(p);
 }
 
 template <typename T_>

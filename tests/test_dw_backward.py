@@ -165,3 +165,41 @@ def test_filter_gradient_on_columns_or_pixels(N, C, H, W, dtype):
     """On both sides of the line of 192 columns of one, two and four rows to a workgroup; maps of one row and of one column."""
     test_depthwise_gradients_in_one_launch_are_those_of_two(N, C, H, W, 1, dtype)
     test_one_call_is_its_three_stages((N, C, 24, H, W, 1, 1, 0.5), dtype)
+
+
+# paired and not, on either side of the lines: rows of 4 at both strides, columns, pixels, the gather, 2x2 maps
+LINES = [(128, 64, 64, 16, 16, 1, 2, 0.5), (129, 64, 64, 16, 16, 1, 2, 0.5), (71, 512, 512, 4, 4, 1, 2, 0.5), (72, 512, 512, 4, 4, 1, 2, 0.5), (83, 256, 256, 7, 7, 1, 8, 0.5),
+         (84, 256, 256, 7, 7, 1, 8, 0.5), (107, 64, 96, 13, 9, 2, 2, 0.5), (108, 64, 96, 13, 9, 2, 2, 0.5), (30, 96, 48, 12, 12, 2, 2, 0.5), (16, 256, 64, 2, 2, 1, 2, 0.5)]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("shift", [(0, 0, 0, 0), (1, 0, 0, 0), (0, 1, 0, 0), (0, 0, 1, 0), (1, 1, 1, 1)])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("shape", LINES)
+def test_tensors_at_any_address(shape, dtype, shift):
+    """x, dy, dx and the weights one element off 16 bytes: other bodies run beside the SCC gradients, with the bits of the stages given
+    the same addresses."""
+    N, Cin, Cout, H, W, s, cg, co = shape
+    Ho, Wo = (H - 1) // s + 1, (W - 1) // s + 1
+    gen = torch.Generator(device="cuda").manual_seed(8)
+
+    def at(off, *d, fill=True):
+        n = 1
+        for v in d:
+            n *= v
+        t = torch.full((n + 2,), 7.0, dtype=dtype, device="cuda")[off:off + n].view(d)
+        return t.copy_(torch.randn(*d, generator=gen, device="cuda")) if fill else t
+
+    x, dy, dx = at(shift[0], N, Cin, H, W), at(shift[1], N, Cout, Ho, Wo), at(shift[2], N, Cin, H, W, fill=False)
+    kdw, w = at(shift[3], Cin, 3, 3), at(shift[3], Cout, Cin // cg)
+    z = S.scc_depthwise3x3_forward(x, kdw, s)
+    dz, dw = S.scc_backward(z, dy, w, cg, co)
+    ref_dx, dk = S.scc_depthwise3x3_backward(x, kdw, dz, s, out_dx=at(shift[2], N, Cin, H, W, fill=False))
+    lib, code = S.load(), 0 if dtype == torch.float32 else 1
+    shape_c = (N, Cin, Cout, H, W, s, cg, co, code)
+    need = int(lib.scc_dw_backward_as_workspace_bytes(*shape_c, 0))
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda")
+    got_k, got_w = torch.empty_like(dk), torch.empty_like(dw)
+    args = [t.data_ptr() for t in (x, kdw, w, dy, dx, got_k, got_w)]
+    assert lib.scc_dw_backward(*args, *shape_c, ws.data_ptr(), need, torch.cuda.current_stream().cuda_stream) == 0
+    assert torch.equal(dx, ref_dx) and torch.equal(got_k, dk) and torch.equal(got_w, dw)
