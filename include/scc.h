@@ -241,16 +241,17 @@ int scc_depthwise3x3_backward(const void* x, const void* kdw, const void* dz, vo
  *     y = scc_forward(scc_depthwise3x3_forward(x, kdw), w)
  * on the Ho x Wo map the depthwise stage produces.  x: in, N*Cin*H*W.  kdw: in, Cin*9.  w: in, Cout*L.
  * y: out, N*Cout*Ho*Wo.
- * Two paths.  Fused (fp32 layers with Cin a multiple of 16 and at most 1104 channels): one kernel keeps the
- * depthwise output of a tile of pixels for all channels on chip and feeds the SCC from there; x is read
- * once, y written once, the intermediate never reaches memory (and is not rounded to the storage type).
- * Two stages (every layer): scc_depthwise3x3_forward into `workspace`, then scc_forward on it; `workspace`
- * then holds the depthwise output (N*Cin*Ho*Wo values of the dtype).
+ * Three paths (scc_dw_forward_path).  Fused (fp32 layers with Cin a multiple of 16 and at most 1104 channels): one kernel keeps
+ * the depthwise output of a tile of pixels for all channels on chip and feeds the SCC from there; x is read once, y written once,
+ * the intermediate never reaches memory (and is not rounded to the storage type).  Few columns (Cin a multiple of 16, windows and
+ * their starts of 4, maps of rows of 4 or of 2 x 2, few output pixels): the same for a group of filters and the channels they reach, in
+ * as many workgroups as there are groups; in bf16 the intermediate is rounded as two stages round it.  Two stages (every layer):
+ * scc_depthwise3x3_forward into `workspace`, then scc_forward on it.
  * scc_dw_forward_workspace_bytes(...) returns 0 for the layers the library runs fused by its own choice
  * (fusable and at least 16384 output pixels over the batch, where fusing is the faster path) and the size
- * of the depthwise output for all others.  A call with a workspace of at least that size (256-byte aligned,
- * owned by the caller, contents undefined afterwards) takes the path the library prefers.  A call with
- * workspace == NULL runs fused whenever scc_dw_forward_fusable(...) returns 1, also where two stages would
+ * of the depthwise output (N*Cin*Ho*Wo values of the dtype) for all others.  On these a call with a workspace of at least that size
+ * (256-byte aligned, owned by the caller) runs the two stages, and the workspace holds the depthwise output afterwards.  A call with
+ * workspace == NULL runs one of the other two wherever scc_dw_forward_fusable(...) returns 1, also where two stages would
  * be faster, and is refused with SCC_ERR_WORKSPACE otherwise.
  * scc_dw_forward_fusable: 1 or 0, or a negative scc_status for invalid arguments.
  * Errors: as scc_forward and scc_depthwise3x3_forward, SCC_ERR_WORKSPACE.
@@ -265,12 +266,26 @@ int scc_dw_forward(const void* x, const void* kdw, const void* w, void* y,
 
 /*
  * The same for callers that want y alone: same arguments, workspace size and errors, but the workspace is scratch and holds
- * nothing in particular afterwards.  On layers with few output pixels on maps of 4 x n or 2 x 2 one kernel then computes the
- * depthwise output again for every group of filters, in bf16 rounded as the two stages round it, and leaves the workspace alone.
+ * nothing in particular afterwards: layers with few columns on which that kernel is faster than the two stages run it and leave
+ * the workspace alone.
  */
 int scc_dw_forward_scratch(const void* x, const void* kdw, const void* w, void* y,
                            int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co,
                            scc_dtype dtype, void* workspace, size_t workspace_bytes, void* stream);
+
+/*
+ * Which of the paths scc_dw_forward and scc_dw_forward_scratch run a layer on, given a workspace of that many bytes (256-byte
+ * aligned; 0: NULL): the decision the calls themselves take.  Host only; a negative scc_status where the call would be refused.
+ */
+typedef enum {
+    SCC_DW_FORWARD_TWO_STAGES = 0,
+    SCC_DW_FORWARD_FUSED = 1,
+    SCC_DW_FORWARD_FEW = 2         /* few columns */
+} scc_dw_forward_paths;
+int scc_dw_forward_path(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype,
+                        size_t workspace_bytes);
+int scc_dw_forward_scratch_path(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype,
+                                size_t workspace_bytes);
 
 /*
  * All gradients of that block in one call (the depthwise output is computed again, never kept):

@@ -414,14 +414,20 @@ static int make_dw_problem(int N, int Cin, int Cout, int H, int W, int dw_stride
     return make_problem(N, Cin, Cout, g->Ho, g->Wo, cg, co, p);
 }
 
+// The depthwise stage's output, or nothing where one kernel keeps it on chip by the library's own choice.
+static size_t dw_forward_need(const Problem& p, scc_dtype dtype)
+{
+    if (dtype == SCC_F32 && scc::dw_forward_fused_preferred(p)) return 0;
+    return (size_t)p.NQ * p.Cin * size_of(dtype);
+}
+
 size_t scc_dw_forward_workspace_bytes(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co,
                                       scc_dtype dtype)
 {
     Problem p;
     scc::DwGeom g;
     if (make_dw_problem(N, Cin, Cout, H, W, dw_stride, cg, co, &p, &g) != SCC_OK || !dtype_ok(dtype)) return 0;
-    if (dtype == SCC_F32 && scc::dw_forward_fused_preferred(p)) return 0;
-    return (size_t)p.NQ * Cin * (dtype == SCC_F32 ? 4 : 2);   // the depthwise stage's output
+    return dw_forward_need(p, dtype);
 }
 
 int scc_dw_forward_fusable(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype)
@@ -434,7 +440,41 @@ int scc_dw_forward_fusable(int N, int Cin, int Cout, int H, int W, int dw_stride
     return dtype == SCC_F32 && scc::dw_forward_fused_eligible(p) ? 1 : 0;
 }
 
-// keep: a workspace that two stages would run in holds the depthwise output afterwards
+// SCC_DW_FORWARD_*, or SCC_ERR_WORKSPACE.  keep: a workspace that two stages would run in holds the depthwise output afterwards.
+static int dw_forward_path(const Problem& p, const scc::DwGeom& g, scc_dtype dtype, bool keep, const void* workspace,
+                           size_t workspace_bytes)
+{
+    const size_t need = dw_forward_need(p, dtype);
+    // without a workspace the fused kernel runs wherever it can, also where the two stages would be faster
+    const bool fused = dtype == SCC_F32 && (need == 0 || (!workspace && scc::dw_forward_fused_eligible(p)));
+    if (!fused && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0)) return SCC_ERR_WORKSPACE;
+    if ((fused || !keep) && scc::dw_forward_few_preferred(p, g, size_of(dtype), fused)) return SCC_DW_FORWARD_FEW;   // touches no workspace
+    return fused ? SCC_DW_FORWARD_FUSED : SCC_DW_FORWARD_TWO_STAGES;
+}
+
+static int dw_forward_path_of(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype, bool keep,
+                              size_t workspace_bytes)
+{
+    Problem p;
+    scc::DwGeom g;
+    const int rc = make_dw_problem(N, Cin, Cout, H, W, dw_stride, cg, co, &p, &g);
+    if (rc != SCC_OK) return rc;
+    if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
+    return dw_forward_path(p, g, dtype, keep, workspace_bytes ? (const void*)256 : nullptr, workspace_bytes);   // any aligned address
+}
+
+int scc_dw_forward_path(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype,
+                        size_t workspace_bytes)
+{
+    return dw_forward_path_of(N, Cin, Cout, H, W, dw_stride, cg, co, dtype, true, workspace_bytes);
+}
+
+int scc_dw_forward_scratch_path(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype,
+                                size_t workspace_bytes)
+{
+    return dw_forward_path_of(N, Cin, Cout, H, W, dw_stride, cg, co, dtype, false, workspace_bytes);
+}
+
 static int dw_forward(const void* x, const void* kdw, const void* w, void* y, int N, int Cin, int Cout, int H, int W,
                       int dw_stride, int cg, double co, scc_dtype dtype, void* workspace, size_t workspace_bytes,
                       void* stream, bool keep)
@@ -445,24 +485,19 @@ static int dw_forward(const void* x, const void* kdw, const void* w, void* y, in
     const int rc = make_dw_problem(N, Cin, Cout, H, W, dw_stride, cg, co, &p, &g);
     if (rc != SCC_OK) return rc;
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
-    const size_t need = scc_dw_forward_workspace_bytes(N, Cin, Cout, H, W, dw_stride, cg, co, dtype);
-    // without a workspace the fused kernel runs wherever it can, also where the two stages would be faster
-    const bool fused = dtype == SCC_F32 && (need == 0 || (!workspace && scc::dw_forward_fused_eligible(p)));
-    if (!fused && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0))
-        return SCC_ERR_WORKSPACE;
-    if ((fused || !keep) && scc::dw_forward_few_preferred(p, g, dtype == SCC_F32 ? 4 : 2, fused)) {   // touches no workspace
-        drop_stale_error();
+    const int path = dw_forward_path(p, g, dtype, keep, workspace, workspace_bytes);
+    if (path < 0) return path;
+    drop_stale_error();
+    if (path == SCC_DW_FORWARD_FEW) {
         return with_type(dtype, [&](auto t) {
             typedef decltype(t) T;
             return launch_status(scc::launch_dw_forward_few((const T*)x, (const T*)kdw, (const T*)w, (T*)y, p, g,
                                                             (hipStream_t)stream));
         });
     }
-    if (fused) {
-        drop_stale_error();
+    if (path == SCC_DW_FORWARD_FUSED)
         return launch_status(scc::launch_dw_forward_fused((const float*)x, (const float*)kdw, (const float*)w, (float*)y,
                                                           p, g, (hipStream_t)stream));
-    }
     // every other layer: the depthwise stage into the workspace, then the SCC forward on it
     const int r1 = scc_depthwise3x3_forward(x, kdw, workspace, N, Cin, H, W, dw_stride, dtype, stream);
     if (r1 != SCC_OK) return r1;

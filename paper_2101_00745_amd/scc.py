@@ -22,7 +22,7 @@ SYMBOLS = ("scc_window_params", "scc_forward", "scc_forward_workspace_bytes", "s
            "scc_backward_workspace_bytes", "scc_backward", "scc_backward_weight_path", "scc_backward_path",
            "scc_depthwise3x3_out", "scc_depthwise3x3_forward", "scc_depthwise3x3_backward_workspace_bytes",
            "scc_depthwise3x3_backward", "scc_dw_forward_workspace_bytes", "scc_dw_forward_fusable", "scc_dw_forward",
-           "scc_dw_forward_scratch",
+           "scc_dw_forward_scratch", "scc_dw_forward_path", "scc_dw_forward_scratch_path",
            "scc_dw_backward_workspace_bytes", "scc_dw_backward", "scc_dw_backward_as_workspace_bytes", "scc_dw_backward_as",
            "scc_status_string")
 STATIC_SCRATCH_BYTES = 32 << 20    # SCC_STATIC_SCRATCH_BYTES of include/scc.h
@@ -88,6 +88,9 @@ def load():
     lib.scc_dw_forward.restype = c_int
     lib.scc_dw_forward_scratch.argtypes = lib.scc_dw_forward.argtypes
     lib.scc_dw_forward_scratch.restype = c_int
+    for query in (lib.scc_dw_forward_path, lib.scc_dw_forward_scratch_path):
+        query.argtypes = dw_shape + [c_sz]
+        query.restype = c_int
     lib.scc_dw_backward_workspace_bytes.argtypes = dw_shape
     lib.scc_dw_backward_workspace_bytes.restype = c_sz
     lib.scc_dw_backward.argtypes = [c_vp] * 7 + dw_shape + [c_vp, c_sz, c_vp]
@@ -416,9 +419,9 @@ def scc_dw_forward_fusable(N, Cin, Cout, H, W, dw_stride, cg, co, dtype=torch.fl
 def scc_dw_forward(x, kdw, w, cg, co, dw_stride=1, out=None, workspace=None, fused=None):
     """y = SCC(DW3x3(x; kdw); w), the forward of a DW + SCC block: x [N,Cin,H,W], kdw [Cin,3,3], w [Cout,Cin//cg]
     -> y [N,Cout,Ho,Wo].  fused=None: the path the library prefers (a workspace is allocated when it asks for
-    one); fused=True: no workspace is passed, so the fused kernel runs or the call is refused; fused=False: the
-    two stages through a workspace, also where the library would fuse.  A `workspace` that is given holds the depthwise
-    output afterwards wherever the library asks for one."""
+    one); fused=True: no workspace is passed, so a kernel that needs none runs (the fused one, or the one for few columns) or
+    the call is refused; fused=False: the two stages through a workspace, also where the library would fuse.  A `workspace`
+    that is given holds the depthwise output afterwards wherever the library asks for one."""
     if fused is None and out is None and workspace is None:
         y = (_native or _load_native()).dw_forward(x, kdw, w, cg, co, dw_stride)
         if y is not None:

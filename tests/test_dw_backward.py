@@ -203,3 +203,21 @@ def test_tensors_at_any_address(shape, dtype, shift):
     args = [t.data_ptr() for t in (x, kdw, w, dy, dx, got_k, got_w)]
     assert lib.scc_dw_backward(*args, *shape_c, ws.data_ptr(), need, torch.cuda.current_stream().cuda_stream) == 0
     assert torch.equal(dx, ref_dx) and torch.equal(got_k, dk) and torch.equal(got_w, dw)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("N,C,s", [(3, 9, 1), (300, 64, 2), (1024, 20, 1)])
+def test_infinity_and_nan_in_2x2_maps(N, C, s, dtype, value):
+    """They stay in the filter of their channel, as one sample of many."""
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    x, kdw, dz = (torch.randn(*d, generator=gen, device="cuda").to(dtype) for d in ((N, C, 2 * s, 2 * s), (C, 3, 3), (N, C, 2, 2)))
+    clean = S.scc_depthwise3x3_backward(x, kdw, dz, s)[1]
+    for t, at in ((x, (N - 1, C - 2, 0, 0)), (dz, (N // 2, C - 2, 0, 0))):
+        kept = t[at].clone()
+        t[at] = value
+        dk = S.scc_depthwise3x3_backward(x, kdw, dz, s)[1]
+        t[at] = kept
+        other = torch.arange(C, device="cuda") != C - 2
+        assert torch.equal(dk[other], clean[other]) and not bool(torch.isfinite(dk[C - 2, 1, 1]))

@@ -6,18 +6,25 @@ import torch
 import paper_2101_00745_amd as S
 from oracle import scc_oracle as O
 
+FUSED, FEW = 1, 2          # SCC_DW_FORWARD_* of include/scc.h
+
 # (N, Cin, Cout, Ho, Wo, stride, cg, co): one image (fewer columns than a tile), column counts below, at and above tiles of 32, 64 and
 # 128, one / two / four column groups per workgroup (spans from 64 to 1024 channels), one and two filter tiles per workgroup, partial
 # tiles of filters, windows that start off the groups of 16 channels and wrap, rows of 4 on maps that are not square
 CASES = [(1, 64, 40, 4, 4, 1, 2, 0.5), (1, 512, 512, 4, 4, 1, 2, 0.5), (1, 512, 96, 2, 2, 2, 2, 0.5), (9, 1024, 200, 2, 2, 1, 2, 0.5),
-         (2, 256, 33, 4, 4, 2, 1, 0.0), (3, 256, 64, 4, 4, 1, 4, 0.25), (7, 176, 61, 5, 4, 1, 2, 0.5), (5, 80, 90, 1, 4, 2, 1, 0.75),
-         (12, 240, 130, 3, 4, 2, 4, 0.4), (33, 64, 128, 2, 2, 1, 1, 0.5), (128, 512, 512, 4, 4, 1, 2, 0.5), (110, 512, 500, 4, 4, 1, 2, 0.5),
-         (70, 256, 768, 4, 4, 2, 2, 0.5), (6, 1600, 64, 4, 4, 1, 2, 0.5), (40, 128, 128, 2, 2, 2, 8, 0.5), (8, 96, 24, 4, 4, 1, 3, 1.0),
+         (2, 256, 33, 4, 4, 2, 1, 0.0), (3, 256, 64, 4, 4, 1, 4, 0.25), (3, 176, 61, 5, 4, 1, 2, 0.5), (5, 80, 90, 1, 4, 2, 1, 0.75),
+         (5, 240, 130, 3, 4, 2, 4, 0.4), (33, 64, 128, 2, 2, 1, 1, 0.5), (128, 512, 512, 4, 4, 1, 2, 0.5), (110, 512, 500, 4, 4, 1, 2, 0.5),
+         (3, 256, 768, 4, 4, 2, 2, 0.5), (2, 1600, 64, 4, 4, 1, 2, 0.5), (15, 128, 128, 2, 2, 2, 8, 0.5), (8, 96, 24, 4, 4, 1, 3, 1.0),
          # eight wavefronts: spans of 272 to 1024 channels, the last wavefronts with little or nothing of them
          (16, 1024, 1024, 2, 2, 1, 2, 0.5), (3, 272, 70, 4, 4, 2, 1, 0.5), (2, 528, 48, 2, 2, 2, 1, 0.5), (5, 304, 96, 5, 4, 1, 1, 0.25),
-         # on both sides of the lines to the two stages: workgroups' number, rounds of a wavefront, width of a workgroup
+         # up to the lines to the two stages: workgroups' number, rounds of a wavefront, width of a workgroup
          (16, 256, 1024, 4, 4, 2, 2, 0.5), (17, 256, 1024, 4, 4, 2, 2, 0.5), (16, 512, 64, 4, 4, 1, 1, 0.5), (66, 512, 96, 4, 4, 1, 1, 0.5),
-         (30, 144, 576, 2, 2, 1, 1, 0.0), (26, 256, 300, 2, 2, 2, 2, 0.25)]
+         (15, 144, 576, 2, 2, 1, 1, 0.0), (26, 256, 300, 2, 2, 2, 2, 0.25)]
+
+
+def path(case, dtype, workspace):
+    N, Cin, Cout, Ho, Wo, s, cg, co = case
+    return S.load().scc_dw_forward_scratch_path(N, Cin, Cout, Ho * s, Wo * s, s, cg, co, 0 if dtype == torch.float32 else 1, workspace)
 
 
 def tensors(case, dtype, shift=0):
@@ -32,23 +39,96 @@ def tensors(case, dtype, shift=0):
     return out
 
 
+def check(case, dtype, shift, fused=None):
+    N, Cin, Cout, Ho, Wo, s, cg, co = case
+    x, k, w = tensors(case, dtype, shift)
+    y = S.scc_dw_forward(x, k, w, cg, co, s, fused=fused)
+    ref = O.depthwise_scc_forward(*(t.float().cpu().numpy() for t in (x, k, w)), cg, co, s)
+    # bf16: the depthwise output and the result are rounded to 2^-9 of themselves at most
+    bar = 2e-5 if dtype == torch.float32 else 1e-2
+    assert np.max(np.abs(y.float().cpu().numpy() - ref)) <= bar * np.max(np.abs(ref))
+    assert torch.equal(y, S.scc_dw_forward(x, k, w, cg, co, s, fused=fused))   # fixed order of the sums
+    if dtype == torch.float32:
+        two = S.scc_dw_forward(x, k, w, cg, co, s, fused=False)
+        assert not torch.equal(two, y) or N * Ho * Wo < 32                      # another kernel's sums
+        err = [float((t.double().cpu() - torch.from_numpy(np.asarray(ref, dtype=np.float64))).norm()) for t in (y, two)]
+        assert err[0] <= 1.1 * err[1]                                          # no further from binary64 than the two stages
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("case", CASES)
+def test_these_layers_take_the_kernel(case, dtype):
+    assert path(case, dtype, 1 << 40) == FEW and path(case, torch.float32, 0) == (FEW if case[1] <= 1104 else -5)
+    N, Cin, Cout, Ho, Wo, s, cg, co = case
+    args = (N, Cin, Cout, Ho * s, Wo * s, s, cg, co, 0 if dtype == torch.float32 else 1)
+    need = S.load().scc_dw_forward_workspace_bytes(*args)
+    assert S.load().scc_dw_forward_path(*args, need) == 0 and S.load().scc_dw_forward_path(*args, need - 1) == -5     # two stages, or refused
+    assert path(case, torch.bfloat16, 0) == -5
+
+
+# layers past the lines: (case, path of fp32 with a workspace, of bf16, of fp32 without one)
+@pytest.mark.parametrize("case,f32,bf16,null", [
+    ((12, 240, 130, 3, 4, 2, 4, 0.4), 0, 0, FEW), ((70, 256, 768, 4, 4, 2, 2, 0.5), 0, FEW, FEW), ((30, 144, 576, 2, 2, 1, 1, 0.0), 0, 0, FEW),
+    ((7, 176, 61, 5, 4, 1, 2, 0.5), 0, 0, FEW), ((128, 512, 1024, 2, 2, 2, 2, 0.5), 0, FEW, FEW), ((900, 208, 45, 4, 4, 1, 1, 0.0), FEW, FEW, FUSED),
+    ((1024, 512, 512, 4, 4, 1, 2, 0.5), FUSED, 0, FUSED), ((3, 72, 64, 4, 4, 1, 2, 0.5), 0, 0, -5), ((3, 64, 64, 8, 8, 1, 2, 0.5), 0, 0, FUSED)])
+def test_lines(case, f32, bf16, null):
+    assert (path(case, torch.float32, 1 << 40), path(case, torch.bfloat16, 1 << 40), path(case, torch.float32, 0)) == (f32, bf16, null)
+    assert path((0,) + case[1:], torch.float32, 0) == -2
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("shift", [0, 1])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 @pytest.mark.parametrize("case", CASES)
 def test_against_the_oracle(case, dtype, shift):
+    check(case, dtype, shift)
+
+
+# Every form of the kernel: rows of 4 and 2x2 at both strides by one, two and four column groups, one and two filter tiles, four and eight
+# wavefronts of a workgroup (fp32 at stride 2 takes two filter tiles in calls without a workspace only)
+FORMS = [(n, c, k, m, m, s, 1, co) for (s, m), ns in (((1, 2), (3, 5, 900, 7, 900, 33)), ((1, 4), (3, 5, 900, 7, 900, 9)), ((2, 2), (3, 5, 900, 7, 900, 15)),
+                                                      ((2, 4), (3, 3, 240, 3, 240, 3)))
+         for n, (c, k, co) in zip(ns, ((208, 72, 0.0), (288, 40, 0.5), (208, 45 if (s, m) == (1, 4) else 250, 0.0), (80, 61, 0.0),
+                                       (80, 45 if (s, m) == (1, 4) else 250, 0.0), (64, 100, 0.5)))]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("case", FORMS)
+def test_every_form(case, dtype):
+    without = path(case, dtype, 1 << 40) != FEW
+    assert path(case, dtype, 0 if without else 1 << 40) == FEW
+    check(case, dtype, 0, fused=True if without else None)
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+@pytest.mark.parametrize("case", [(1, 64, 40, 4, 4, 1, 2, 0.5), (16, 512, 64, 4, 4, 1, 1, 0.5), (9, 1024, 200, 2, 2, 1, 2, 0.5), (5, 240, 130, 3, 4, 2, 4, 0.4)])
+def test_infinity_and_nan(case, dtype, value):
+    """They reach the pixels of their own sample whose stencils hold them, all filters whose windows hold the channel among the filters there,
+    and no other sample or pixel; in a filter, that filter alone."""
     N, Cin, Cout, Ho, Wo, s, cg, co = case
-    x, k, w = tensors(case, dtype, shift)
-    y = S.scc_dw_forward(x, k, w, cg, co, s)
-    ref = O.depthwise_scc_forward(*(t.float().cpu().numpy() for t in (x, k, w)), cg, co, s)
-    # bf16: the depthwise output and the result are rounded to 2^-9 of themselves at most
-    bar = 2e-5 if dtype == torch.float32 else 1e-2
-    assert np.max(np.abs(y.float().cpu().numpy() - ref)) <= bar * np.max(np.abs(ref))
-    assert torch.equal(y, S.scc_dw_forward(x, k, w, cg, co, s))                # fixed order of the sums
-    if dtype == torch.float32:
-        two = S.scc_dw_forward(x, k, w, cg, co, s, fused=False)
-        err = [float((t.double().cpu() - torch.from_numpy(np.asarray(ref, dtype=np.float64))).norm()) for t in (y, two)]
-        assert err[0] <= 1.1 * err[1]                                          # no further from binary64 than the two stages
+    x, k, w = tensors(case, dtype)
+    clean = S.scc_dw_forward(x, k, w, cg, co, s)
+    n, a, r, c = N - 1, Cin // 2 + 1, 0, Wo * s - 1
+    bad = x.clone()
+    bad[n, a, r, c] = value
+    y = S.scc_dw_forward(bad, k, w, cg, co, s)
+    hit = torch.zeros(N, 1, Ho, Wo, dtype=torch.bool, device="cuda")
+    for m in range(Ho):
+        for q in range(Wo):
+            hit[n, 0, m, q] = abs(s * m - r) <= 1 and abs(s * q - c) <= 1
+    hit = hit.expand_as(y)
+    assert bool(hit.any()) and torch.equal(torch.where(hit, 0, y), torch.where(hit, 0, clean))
+    L, stride, _ = S.scc_window_params(Cin, Cout, cg, co)
+    holds = torch.tensor([(a - f * stride) % Cin < L for f in range(Cout)], device="cuda").view(1, Cout, 1, 1).expand_as(y)
+    assert bool(holds.any()) and not bool(torch.isfinite(y[hit & holds]).any())
+    bad = w.clone()
+    bad[Cout - 3, 5] = value
+    y = S.scc_dw_forward(x, k, bad, cg, co, s)
+    other = torch.arange(Cout, device="cuda") != Cout - 3
+    assert torch.equal(y[:, other], clean[:, other]) and not bool(torch.isfinite(y[:, Cout - 3]).any())
 
 
 @pytest.mark.gpu
