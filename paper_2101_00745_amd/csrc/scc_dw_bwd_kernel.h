@@ -370,13 +370,13 @@ inline bool filter_on_strips(const T_* x, const T_* dz, const DwGeom& g, int per
 inline int strip_rows_of(const DwGeom& g) { return g.Ho % 4 == 0 ? 4 : g.Ho % 2 == 0 ? 2 : 1; }
 
 // Whether the filter gradient of a layer that does not run on strips (or planes) runs on columns (rows of a column: strip_rows_of),
-// `per` samples to a slice, and not pixel by pixel: where at least three quarters of a workgroup's threads have one, on maps of two
-// rows and columns.  With fewer, a thread's rows one after another cost what the loads save, and a map of one row or column
-// has no neighbours to share.  Over 5252 layers of 1 to 32 rows of 1 to 30 pixels, both types, pixels / columns, geometric mean and least: the
-// layers this takes 1.47 (0.92), the others 0.98 (0.61).
+// `per` samples to a slice, and not pixel by pixel: where a workgroup has 350 pixels, on maps of two rows and columns.  With fewer, its threads
+// have a pixel or two each, and a column's rows one after another cost what the loads save; a map of one row or column has no neighbours
+// to share.  Over 5252 layers of 1 to 32 rows of 1 to 30 pixels, both types, pixels / columns, geometric mean and least: the layers this takes
+// 1.41 (0.92), the others 0.96 (0.61).
 inline bool filter_on_columns(const DwGeom& g, int per)
 {
-    return g.s == 1 && g.H > 1 && g.W > 1 && (long long)per * g.W * (g.H / strip_rows_of(g)) >= 192;
+    return g.s == 1 && g.H > 1 && g.W > 1 && (long long)per * g.H * g.W >= 350;
 }
 
 // Whether grad-input at stride 2 runs on input_s2_body.

@@ -159,17 +159,17 @@ def test_products_of_the_gradient_at_stride_2():
 
 @pytest.mark.gpu
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
-@pytest.mark.parametrize("N,C,H,W", [(38, 1024, 4, 5), (39, 1024, 4, 5), (31, 1030, 2, 6), (32, 1030, 2, 6), (200, 1024, 1, 9), (300, 1024, 4, 1),
+@pytest.mark.parametrize("N,C,H,W", [(17, 1024, 4, 5), (18, 1024, 4, 5), (29, 1030, 2, 6), (30, 1030, 2, 6), (7, 1024, 5, 10), (38, 1024, 4, 5), (200, 1024, 1, 9), (300, 1024, 4, 1),
                                      (9, 1024, 7, 7), (5, 3, 9, 9), (1, 700, 13, 6), (2, 1100, 13, 14)])
 def test_filter_gradient_on_columns_or_pixels(N, C, H, W, dtype):
-    """On both sides of the line of 192 columns of one, two and four rows to a workgroup; maps of one row and of one column."""
+    """On both sides of the line of 350 pixels to a workgroup, in columns of one, two and four rows; maps of one row and of one column."""
     test_depthwise_gradients_in_one_launch_are_those_of_two(N, C, H, W, 1, dtype)
     test_one_call_is_its_three_stages((N, C, 24, H, W, 1, 1, 0.5), dtype)
 
 
 # paired and not, on either side of the lines: rows of 4 at both strides, columns, pixels, the gather, 2x2 maps
-LINES = [(128, 64, 64, 16, 16, 1, 2, 0.5), (129, 64, 64, 16, 16, 1, 2, 0.5), (71, 512, 512, 4, 4, 1, 2, 0.5), (72, 512, 512, 4, 4, 1, 2, 0.5), (83, 256, 256, 7, 7, 1, 8, 0.5),
-         (84, 256, 256, 7, 7, 1, 8, 0.5), (107, 64, 96, 13, 9, 2, 2, 0.5), (108, 64, 96, 13, 9, 2, 2, 0.5), (30, 96, 48, 12, 12, 2, 2, 0.5), (16, 256, 64, 2, 2, 1, 2, 0.5)]
+LINES = [(128, 64, 64, 16, 16, 1, 2, 0.5), (129, 64, 64, 16, 16, 1, 2, 0.5), (192, 512, 512, 4, 4, 1, 2, 0.5), (193, 512, 512, 4, 4, 1, 2, 0.5), (83, 256, 256, 7, 7, 1, 8, 0.5),
+         (84, 256, 256, 7, 7, 1, 8, 0.5), (125, 256, 256, 7, 7, 1, 8, 0.5), (126, 256, 256, 7, 7, 1, 8, 0.5), (107, 64, 96, 13, 9, 2, 2, 0.5), (108, 64, 96, 13, 9, 2, 2, 0.5), (30, 96, 48, 12, 12, 2, 2, 0.5), (16, 256, 64, 2, 2, 1, 2, 0.5)]
 
 
 @pytest.mark.gpu
