@@ -156,8 +156,9 @@ hipError_t launch_second(const T_* x, const T_* kdw, const T_* dy, const T_* z, 
 // LDS and so run with fewer wavefronts than in kernels of their own, which larger maps feel, and the matrix ranges wait for one another's
 // workgroups, which long binary32 contractions feel.  One stage after the other (sums in one launch) / paired over 3415 drawn layers, geometric mean
 // and least, by the depthwise range: stride 2 on even maps and 2x2 maps, taken up to 2^23 values of x and z (rows of 4 pixels; 2^22 others) f32 1.12
-// (0.87), bf16 1.17 (0.94); rows of 4 at stride 1, f32, taken up to 150e6 multiply-adds and 2^22 values 1.09 (0.86), left 0.96; bf16, up to 2^23
-// values, 1.11 (0.82); columns, f32, up to 150e6 and 2^21 1.13 (0.79), left 0.95; bf16, up to 2^21, 1.22 (0.89), left 1.00; the gather of odd
+// (0.87), bf16 1.17 (0.94); rows of 4 at stride 1, f32, taken up to 150e6 multiply-adds and 2^22 values 1.09 (0.86), on one group of 4 pixels per row
+// with more up to 3 x 2^20 values 1.02 (0.93; 128 x 512 -> 512 on 4x4 1.03), left 0.96; bf16, up to 2^23
+// values, 1.11 (0.82); columns, f32, up to 250e6 and 2^21 1.12 (0.79), left 0.94; bf16, up to 3 x 2^20, 1.21 (0.89), left 1.00; the gather of odd
 // maps, f32, up to 15e6 and 2^20 1.18 (0.84), left 0.92; bf16, up to 2^21, 1.21 (1.00).
 template <typename T_>
 bool block_backward_applicable(const Problem& p, const DwGeom& g)
@@ -170,9 +171,9 @@ bool block_backward_applicable(const Problem& p, const DwGeom& g)
     if (sized && (dw::filter_on_planes(g) || (g.s == 2 && g.Wo % 2 == 0)))
         most = fours ? 1ll << 23 : 1ll << 22;
     else if (sized && fours)
-        most = !wide ? 1ll << 23 : products <= 150e6 ? 1ll << 22 : 0;
+        most = !wide ? 1ll << 23 : products <= 150e6 ? 1ll << 22 : g.Wo == 4 ? 3ll << 20 : 0;
     else if (g.s == 1)
-        most = !wide || products <= 150e6 ? 1ll << 21 : 0;
+        most = !wide ? 3ll << 20 : products <= 250e6 ? 1ll << 21 : 0;
     else
         most = !wide ? 1ll << 21 : products <= 15e6 ? 1ll << 20 : 0;
     return values <= most && backward_merged_applicable<T_>(p);
