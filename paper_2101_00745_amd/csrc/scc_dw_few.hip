@@ -398,15 +398,14 @@ static FewPlan few_plan(const Problem& p)
     return f;
 }
 
-// Against the two stages, of which the second reaches its tiled kernels from 64 columns up; below, this kernel is at least 1.37 times as
-// fast over 706 layers (one image of 512 -> 512 on 4x4 96 -> 6.4 us).  From 64 up its time goes with the rounds that a CU walks one after
-// another: rounds of a wavefront x generations of 256 workgroups, wider workgroups somewhat longer ones (3 + column groups x filter tiles
-// quarters of the narrowest's).  Over 4324 layers of up to 1100 tiles, warm and cold buffers, two stages / this kernel, geometric mean
-// and extremes of those it takes, mean of those it leaves: stride 1, rows of 4, fp32 1.20 (0.85 .. 1.67), 0.92, bf16 1.11 (0.72 .. 1.59),
-// 0.78; 2x2 maps, whose depthwise stage alone is slow, fp32 1.20, 0.96, bf16 1.17, 1.25 (few); stride 2, where every tile recomputes from four
-// times the input, fp32 1.12 (0.79 .. 1.74), 0.83, bf16 1.11 (0.79 .. 1.79), 0.81.  Without the rule 2.5 times slower at worst (18 x 1984 -> 5948 on
-// 4x4, cg 1: 46 -> 118).  us at the lines: 128 x 512 -> 512 on 4x4 13.2 -> 12.1, 128 x 1024 -> 1024 on 2x2 15.5 -> 14.9, left: 128 x 512 -> 1024
-// from 4x4 14.0 (16.0 here), 128 x 256 -> 512 from 8x8 11.8 (12.5).
+// Against the two stages, of which the second reaches its tiled kernels from 64 columns up; below, this kernel is as fast or faster over 1338
+// layers, three times as fast on average (one image of 512 -> 512 on 4x4 43 -> 6.4 us).  From 64 up its time goes with the rounds that a CU
+// walks one after another: rounds of a wavefront x generations of 256 workgroups, wider workgroups somewhat longer ones (3 + column groups x
+// filter tiles quarters of the narrowest's).  The lines were drawn on 4324 layers of up to 1100 tiles, warm and cold buffers; over 1924 layers that
+// they take, two stages / this kernel, geometric mean and extremes: stride 1, rows of 4, fp32 1.17 (0.86 .. 1.81), bf16 1.10 (0.77 .. 1.57); 2x2 maps, fp32 1.23
+// (0.86 .. 1.84), bf16 1.23 (0.91 .. 1.73); stride 2, where every tile recomputes from four times the input, fp32 1.10 (0.69 .. 1.50), bf16
+// 1.11 (0.78 .. 1.52).  Without the rule 2.5 times slower at worst (18 x 1984 -> 5948 on 4x4, cg 1: 46 -> 118).  us at the lines: 128 x 512 -> 512 on
+// 4x4 13.2 -> 12.1, 128 x 1024 -> 1024 on 2x2 15.5 -> 14.9, left: 128 x 512 -> 1024 from 4x4 14.0 (16.0 here), 128 x 256 -> 512 from 8x8 11.8 (12.5).
 // Against the kernel that computes all channels once per tile of 64 columns, which a call without workspace would take (fp32, 2507 layers):
 // median 2.5 times as fast, as few columns leave that one most of the chip idle; from 4096 columns up it can lose (291 x 64 -> 96 from 8x8 9.1 to 10.8).
 bool dw_forward_few_preferred(const Problem& p, const DwGeom& g, int es, bool against_fused)
