@@ -394,18 +394,25 @@ static FewPlan few_plan(const Problem& p)
     f.tf = f.cp <= 2 && f.units > 768 ? 2 : 1;
     f.t = few_tiling(p, f.cp, f.tf);
     f.wv = f.cp == 1 && f.tf == 1 && f.t.U > 256 && f.t.total <= 256 ? 8 : 4;
-    f.rounds = ((f.t.U + 64 / f.cp - 1) / (64 / f.cp) + f.wv - 1) / f.wv;
+    // a tile starts g * TM channels behind the one before it: at any multiple of that step's common factor with 16 into a group
+    int align = 16;
+    while (f.t.TM < f.t.b.P && (f.t.b.g * f.t.TM) % align != 0) align /= 2;
+    const int all = (f.t.U + 16 - align + 15) / 16, own = (all + f.wv - 1) / f.wv, kr = 4 / f.cp;      // groups of 16: a tile's, a wavefront's, a round's
+    f.rounds = (own + kr - 1) / kr;
     return f;
 }
 
 // Against the two stages, of which the second reaches its tiled kernels from 64 columns up; below, this kernel is as fast or faster over 1338
 // layers, three times as fast on average (one image of 512 -> 512 on 4x4 43 -> 6.4 us).  From 64 up its time goes with the rounds that a CU
 // walks one after another: rounds of a wavefront x generations of 256 workgroups, wider workgroups somewhat longer ones (3 + column groups x
-// filter tiles quarters of the narrowest's).  The lines were drawn on 4324 layers of up to 1100 tiles, warm and cold buffers; over 1924 layers that
-// they take, two stages / this kernel, geometric mean and extremes: stride 1, rows of 4, fp32 1.17 (0.86 .. 1.81), bf16 1.10 (0.77 .. 1.57); 2x2 maps, fp32 1.23
-// (0.86 .. 1.84), bf16 1.23 (0.91 .. 1.73); stride 2, where every tile recomputes from four times the input, fp32 1.10 (0.69 .. 1.50), bf16
-// 1.11 (0.78 .. 1.52).  Without the rule 2.5 times slower at worst (18 x 1984 -> 5948 on 4x4, cg 1: 46 -> 118).  us at the lines: 128 x 512 -> 512 on
-// 4x4 13.2 -> 12.1, 128 x 1024 -> 1024 on 2x2 15.5 -> 14.9, left: 128 x 512 -> 1024 from 4x4 14.0 (16.0 here), 128 x 256 -> 512 from 8x8 11.8 (12.5).
+// filter tiles quarters of the narrowest's).  Left to the two stages besides, over 46814 layers of up to 1100 tiles, two stages / this kernel, geometric mean: maps
+// of one row of 4, where a lane's pixels share a cache line with no neighbour's, 0.86; a second generation at stride 2 in fp32 0.91, or of two column
+// groups by two filter tiles 0.96; bf16, whose second stage is cheaper, in more than one round 0.94 (from 2x2 to 2x2 1.14); fp32 from 4x4 to 2x2 on
+// two column groups 1.00 (0.66 at worst).
+// Those taken: stride 1, rows of 4, fp32 1.20 (one in 50 below 0.94), bf16 1.14 (0.90); 2x2 maps, fp32 1.27 (0.96), bf16 1.25 (0.89); stride 2, where every tile
+// recomputes from four times the input, rows of 4, fp32 1.13 (0.89), bf16 1.13 (0.90); 2x2, fp32 1.16 (0.88), bf16 1.10 (0.85).  Without the rules 2.5 times slower at
+// worst (18 x 1984 -> 5948 on 4x4, cg 1: 46 -> 118).  us at the lines: 128 x 512 -> 512 on 4x4 13.2 -> 12.1, 128 x 1024 -> 1024 on 2x2 15.5 -> 14.9, left: 128 x 512 ->
+// 1024 from 4x4 14.0 (16.0 here), 128 x 256 -> 512 from 8x8 11.8 (12.5), 18 x 608 -> 1216 on 1x4, cg 1, bf16 9.0 (17.6).
 // Against the kernel that computes all channels once per tile of 64 columns, which a call without workspace would take (fp32, 2507 layers):
 // median 2.5 times as fast, as few columns leave that one most of the chip idle; from 4096 columns up it can lose (291 x 64 -> 96 from 8x8 9.1 to 10.8).
 bool dw_forward_few_preferred(const Problem& p, const DwGeom& g, int es, bool against_fused)
@@ -415,10 +422,14 @@ bool dw_forward_few_preferred(const Problem& p, const DwGeom& g, int es, bool ag
     const FewPlan f = few_plan(p);
     if (f.units > 1100) return false;                                           // not measured above
     if (against_fused) return p.NQ < 4096;
-    if (g.s == 2 && es == 4 && f.wv == 8) return false;
+    const bool planes = g.Wo == 2, second = f.t.total > 256;
+    if (!planes && g.Ho == 1) return false;
+    if (second && f.cp == 2 && f.tf == 2) return false;
+    if (es == 4 && g.s == 2 && (second || f.wv == 8 || (planes && f.cp == 2))) return false;
+    if (es == 2 && !(planes && g.s == 1) && f.rounds > 1) return false;
     const long long width = f.cp == 1 ? 4 : 3 + f.cp * f.tf;
     const long long walked = width * f.rounds * (f.t.total < 256 ? 256 : f.t.total);
-    return walked <= (g.s == 2 ? (es == 4 ? 1280 : 2048) : g.Wo == 2 && f.cp == 1 ? 4096 : 2048);
+    return walked <= (g.s == 2 ? (es == 4 ? 1280 : 2048) : planes && f.cp == 1 ? 4096 : 2048);
 }
 
 template <typename T_>
