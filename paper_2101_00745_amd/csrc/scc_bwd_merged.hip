@@ -61,7 +61,9 @@ hipError_t launch_variant(const T_* x, const T_* dy, const T_* w, T_* dx, float*
         if (allowed != hipSuccess) return allowed;
     }
     const long long nbww = (long long)8 * tw.chunk;
-    backward_merged<T_, CT, S, NPT, SMALL><<<dim3((unsigned)(nbww + nbwi)), dim3(256), kLds, st>>>(x, dy, w, dx, out, p, ti,
+    bwi::BwiTiling beside = ti;
+    beside.deal = in_eighths(ti.deal);
+    backward_merged<T_, CT, S, NPT, SMALL><<<dim3((unsigned)(nbww + nbwi)), dim3(256), kLds, st>>>(x, dy, w, dx, out, p, beside,
                                                                                                tw, (int)nbww);
     return hipGetLastError();
 }

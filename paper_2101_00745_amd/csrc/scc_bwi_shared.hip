@@ -55,8 +55,7 @@ struct BwiSharedTiling {
     Band b;
     int CB;        // channel blocks of 32
     int FG;        // workgroups per column tile: ceil(CB / 4)
-    int total;     // workgroups with work
-    int chunk;     // consecutive workgroups given to one XCD
+    Deal deal;     // (column tile, group of workgroups that read its planes)
     Groups q;      // column groups of 4 pixels; a workgroup owns 32 of them
 };
 
@@ -82,12 +81,10 @@ __global__ __launch_bounds__(kWavesG * 64, 2) void backward_input_shared32(const
     char* const b_lds = lds_g;                              // two B buffers
     i32x4* const table = (i32x4*)(lds_g + 2 * kGBuf);       // per walk position: {k*L or -1, window start, byte offset of dy plane k, 0}
 
-    // workgroup -> (column tile, group of four channel blocks), group fastest; each XCD takes a contiguous run
+    // workgroup -> (column tile, group of four channel blocks)
     const int bid = blockIdx.x;
-    const int xcd = bid & 7, slot = bid >> 3;
-    const int logical = xcd * T.chunk + slot;
-    if (slot >= T.chunk || logical >= T.total) return;      // the whole workgroup leaves
-    const int ct = logical / T.FG, fg = logical % T.FG;
+    int ct, fg;
+    if (!dealt(T.deal, bid, ct, fg)) return;          // the whole workgroup leaves
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int tid = threadIdx.x;
     const int lane = tid & 63;
@@ -292,8 +289,7 @@ BwiSharedTiling make_bwi_shared_tiling(const Problem& p)
     t.FG = (t.CB + kWavesG - 1) / kWavesG;
     t.q = column_groups(p, 4);
     const long long nct = (t.q.count + 31) / 32;
-    t.total = (int)(nct * t.FG);
-    t.chunk = (t.total + 7) / 8;
+    t.deal = make_deal(nct, t.FG);
     return t;
 }
 
@@ -349,7 +345,7 @@ bool backward_input_shared_preferred(const Problem& p)
     int longest;
     double gain;
     walk_stats(p, t, &longest, &gain);
-    return t.total >= 512 && (gain >= 3.5 || (gain >= 2.9 && t.b.g < 32));
+    return t.deal.total >= 512 && (gain >= 3.5 || (gain >= 2.9 && t.b.g < 32));
 #endif
 }
 
@@ -359,7 +355,7 @@ hipError_t launch_backward_input_shared(const float* dy, const float* w, float* 
     static const hipError_t allowed =
         hipFuncSetAttribute((const void*)backward_input_shared32, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsG);
     if (allowed != hipSuccess) return allowed;
-    backward_input_shared32<<<dim3((unsigned)(8 * t.chunk)), dim3(kWavesG * 64), kLdsG, st>>>(dy, w, dx, p, t);
+    backward_input_shared32<<<dim3((unsigned)(8 * t.deal.chunk)), dim3(kWavesG * 64), kLdsG, st>>>(dy, w, dx, p, t);
     return hipGetLastError();
 }
 

@@ -38,8 +38,7 @@ struct FewTiling {
     int GM;         // workgroups per column tile and window group: ceil(IB / TF)
     int FG;         // workgroups per column tile: GM * ceil(P / TM)
     int U;          // channels a tile spans: L + g * (TM - 1)
-    int total;      // workgroups with work: column tiles * FG, filter group fastest
-    int chunk;      // consecutive workgroups of that order given to one XCD: ceil(total / 8)
+    Deal deal;      // (column tile, filter group)
 };
 
 // LDS of a wavefront: a round's pieces and taps (binary32), then its partial tiles in their place.
@@ -65,10 +64,8 @@ __global__ __launch_bounds__(64 * WV, 2) void dw_scc_forward_few(const T_* __res
     extern __shared__ __attribute__((aligned(16))) char lds[];     // WV * kBlockB
     typedef T_ w4 __attribute__((ext_vector_type(4), aligned(sizeof(T_))));
 
-    const int xcd = (int)blockIdx.x & 7, slot = (int)blockIdx.x >> 3;
-    const int logical = xcd * T.chunk + slot;
-    if (slot >= T.chunk || logical >= T.total) return;
-    const int ct = logical / T.FG, fg = logical - ct * T.FG;
+    int ct, fg;
+    if (!dealt(T.deal, (int)blockIdx.x, ct, fg)) return;
     const int mb = fg / T.GM, ib0 = (fg - mb * T.GM) * TF;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63, f = lane & 31, h = lane >> 5;
@@ -349,8 +346,7 @@ FewTiling few_tiling(const Problem& p, int cp, int tf)
     t.FG = t.GM * ((t.b.P + t.TM - 1) / t.TM);
     t.U = p.L + t.b.g * (t.TM - 1);
     const long long nct = (p.NQ + 32 * cp - 1) / (32 * cp);
-    t.total = (int)(nct * t.FG);
-    t.chunk = (t.total + 7) / 8;
+    t.deal = make_deal(nct, t.FG);
     return t;
 }
 
@@ -389,11 +385,11 @@ static FewPlan few_plan(const Problem& p)
 {
     FewPlan f;
     f.t = few_tiling(p, 1, 1);
-    f.units = f.t.total;
+    f.units = f.t.deal.total;
     f.cp = few_cp(f.t);
     f.tf = f.cp <= 2 && f.units > 768 ? 2 : 1;
     f.t = few_tiling(p, f.cp, f.tf);
-    f.wv = f.cp == 1 && f.tf == 1 && f.t.U > 256 && f.t.total <= 256 ? 8 : 4;
+    f.wv = f.cp == 1 && f.tf == 1 && f.t.U > 256 && f.t.deal.total <= 256 ? 8 : 4;
     // a tile starts g * TM channels behind the one before it: at any multiple of that step's common factor with 16 into a group
     int align = 16;
     while (f.t.TM < f.t.b.P && (f.t.b.g * f.t.TM) % align != 0) align /= 2;
@@ -422,13 +418,13 @@ bool dw_forward_few_preferred(const Problem& p, const DwGeom& g, int es, bool ag
     const FewPlan f = few_plan(p);
     if (f.units > 1100) return false;                                           // not measured above
     if (against_fused) return p.NQ < 4096;
-    const bool planes = g.Wo == 2, second = f.t.total > 256;
+    const bool planes = g.Wo == 2, second = f.t.deal.total > 256;
     if (!planes && g.Ho == 1) return false;
     if (second && f.cp == 2 && f.tf == 2) return false;
     if (es == 4 && g.s == 2 && (second || f.wv == 8 || (planes && f.cp == 2))) return false;
     if (es == 2 && !(planes && g.s == 1) && f.rounds > 1) return false;
     const long long width = f.cp == 1 ? 4 : 3 + f.cp * f.tf;
-    const long long walked = width * f.rounds * (f.t.total < 256 ? 256 : f.t.total);
+    const long long walked = width * f.rounds * (f.t.deal.total < 256 ? 256 : f.t.deal.total);
     return walked <= (g.s == 2 ? (es == 4 ? 1280 : 2048) : planes && f.cp == 1 ? 4096 : 2048);
 }
 
@@ -449,7 +445,7 @@ hipError_t launch_dw_forward_few(const T_* x, const T_* kdw, const T_* w, T_* y,
             e = allowed;
             if (e != hipSuccess) return;
         }
-        dw_scc_forward_few<T_, S, MAP, CP, TF, WV><<<dim3(8u * (unsigned)f.t.chunk), dim3(64 * WV), kLds, st>>>(x, kdw, w, y, p, g, f.t);
+        dw_scc_forward_few<T_, S, MAP, CP, TF, WV><<<dim3(8u * (unsigned)f.t.deal.chunk), dim3(64 * WV), kLds, st>>>(x, kdw, w, y, p, g, f.t);
         e = hipGetLastError();
     };
     const integral_constant<int, 4> four;

@@ -50,8 +50,7 @@ struct SharedTiling {
     int IB, MB;    // tiles along the filter and the window axis; tile index = mb*IB + ib
     int U;         // channels a tile spans: L + g*(TM-1)
     int FG;        // workgroups per column tile: ceil(IB*MB / 4)
-    int total;     // workgroups with work
-    int chunk;     // consecutive workgroups given to one XCD
+    Deal deal;     // (column tile, group of workgroups that read its planes)
     Groups q;      // column groups of 4 pixels; a workgroup owns 32 of them
 };
 
@@ -65,12 +64,10 @@ __global__ __launch_bounds__(kWavesS * 64, 2) void forward_shared32(const float*
     char* const b_lds = lds_s;                   // two B buffers
     char* const a_lds = lds_s + 2 * kBBuf;       // then one A block per wavefront
 
-    // workgroup -> (column tile, group of four tiles), group fastest; each XCD takes a contiguous run of that order
+    // workgroup -> (column tile, group of four tiles)
     const int bid = blockIdx.x;
-    const int xcd = bid & 7, slot = bid >> 3;
-    const int logical = xcd * T.chunk + slot;
-    if (slot >= T.chunk || logical >= T.total) return;         // the whole workgroup leaves
-    const int ct = logical / T.FG, fg = logical % T.FG;
+    int ct, fg;
+    if (!dealt(T.deal, bid, ct, fg)) return;          // the whole workgroup leaves
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int ntiles = T.IB * T.MB;
     const int tile = fg * kWavesS + wave;
@@ -318,8 +315,7 @@ SharedTiling make_shared_tiling(const Problem& p)
     t.FG = (t.IB * t.MB + kWavesS - 1) / kWavesS;
     t.q = column_groups(p, 4);
     const long long nct = (t.q.count + 31) / 32;
-    t.total = (int)(nct * t.FG);
-    t.chunk = (t.total + 7) / 8;
+    t.deal = make_deal(nct, t.FG);
     return t;
 }
 
@@ -359,7 +355,7 @@ bool forward_shared_preferred(const Problem& p)
 #else
     if (!forward_shared_eligible(p)) return false;
     const SharedTiling t = make_shared_tiling(p);
-    return t.total >= 512 && forward_shared_gain(p) >= 3.0;
+    return t.deal.total >= 512 && forward_shared_gain(p) >= 3.0;
 #endif
 }
 
@@ -367,7 +363,7 @@ hipError_t launch_forward_shared(const float* x, const float* w, float* y, const
 {
     const SharedTiling t = make_shared_tiling(p);
     const bool al4 = (t.b.g % 4 == 0) && (p.L % 4 == 0);
-    const dim3 grid((unsigned)(8 * t.chunk)), block(kWavesS * 64);
+    const dim3 grid((unsigned)(8 * t.deal.chunk)), block(kWavesS * 64);
     static const hipError_t allowed[2] = {
         hipFuncSetAttribute((const void*)forward_shared32<false>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsS),
         hipFuncSetAttribute((const void*)forward_shared32<true>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsS)};

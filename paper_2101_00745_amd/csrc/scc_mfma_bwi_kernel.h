@@ -28,8 +28,7 @@ struct BwiTiling {
     Band b;
     int CB;   // channel blocks of 32
     int FG;     // workgroups per column tile = ceil(CB / 4)
-    int total;  // workgroups with work: column tiles * FG, channel-block group fastest
-    int chunk;  // consecutive workgroups of that order given to one XCD: ceil(total / 8)
+    Deal deal;     // (column tile, group of workgroups that read its planes)
     int even;   // every window start has F filters and F is a multiple of a chunk: see the walk below
     Groups q;   // column groups of CT pixels
 };
@@ -58,13 +57,10 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
 {
     typedef T_ bvec __attribute__((ext_vector_type(CT), aligned(sizeof(T_))));   // CT consecutive columns of one plane
     constexpr uint32_t ES = sizeof(T_);
-    // bid is the workgroup's index in a launch whose first workgroup is a multiple of 8: bid % 8 names the XCD; each XCD takes a contiguous run of the (column tile, group) order, so the
-    // channel blocks of a column tile, which re-read the same dy planes, share an XCD and its L2
-    const int xcd = bid & 7, slot = bid >> 3;
-    const int logical = xcd * T.chunk + slot;
-    if (slot >= T.chunk || logical >= T.total) return;
-    const int ct = logical / T.FG;
-    const int fg = logical % T.FG;
+    // bid is the workgroup's index in a launch whose first workgroup is a multiple of 8: bid % 8 names the XCD; the
+    // channel blocks of a column tile, which re-read the same dy planes, share one and its L2
+    int ct, fg;
+    if (!dealt(T.deal, bid, ct, fg)) return;          // the whole workgroup leaves
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int cb = fg * (WPB / S) + wave / S, split = wave % S;
     const bool tvalid = cb < T.CB;
@@ -277,9 +273,8 @@ inline BwiTiling make_tiling(const Problem& p, long long* blocks)
     t.q = column_groups(p, CT);
     const long long nct = (t.q.count + 31) / 32;
     t.FG = (t.CB * S + WPB - 1) / WPB;
-    t.total = (int)(nct * t.FG);
-    t.chunk = (t.total + 7) / 8;
-    *blocks = (long long)8 * t.chunk;
+    t.deal = make_deal(nct, t.FG);
+    *blocks = (long long)8 * t.deal.chunk;
     return t;
 }
 

@@ -34,8 +34,7 @@ struct FwdTiling {
     int Uh;        // K-steps per tile (multiple of the chunk length); each half-wave covers Uh channels
     int Us;        // K-steps of one wavefront when S wavefronts share a tile: ceil(Uh / S) rounded to rounds
     int FG;        // workgroups per column tile = ceil(IB*MB * S / wavefronts per workgroup)
-    int total;     // workgroups with work: column tiles (of 32*CT columns) * FG, filter-tile group fastest
-    int chunk;     // consecutive workgroups of that order given to one XCD: ceil(total / 8)
+    Deal deal;     // (column tile, group of workgroups that read its planes)
     int stagger;   // ticks of the 100 MHz clock the second half of an 8-wavefront workgroup waits after kernel start
     Groups q;      // column groups of CT pixels
 };
@@ -79,16 +78,12 @@ __global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void forward_m
     constexpr int KA = 2 * KC;   // K-steps per round: two chunks of B loads
     constexpr int kAB = 2 * KA;  // K-steps per staged block of A operands: two rounds
 
-    // workgroup -> (column tile, filter-tile group).  blockIdx % 8 names the XCD; each XCD takes a
-    // contiguous run of the (column tile, group) order, so the groups of a column tile, which re-read
-    // the same channel planes, share one XCD and its L2 whenever there are enough column tiles.
+    // workgroup -> (column tile, filter-tile group); the groups of a column tile, which re-read the same channel planes, share one
+    // XCD and its L2 whenever there are enough column tiles
     const uint64_t t_start = WPB == 8 ? __builtin_amdgcn_s_memrealtime() : 0;   // 100 MHz, independent of core clocks
     const int bid = blockIdx.x;
-    const int xcd = bid & 7, slot = bid >> 3;
-    const int logical = xcd * T.chunk + slot;
-    if (slot >= T.chunk || logical >= T.total) return;
-    const int ct = logical / T.FG;
-    const int fg = logical % T.FG;
+    int ct, fg;
+    if (!dealt(T.deal, bid, ct, fg)) return;          // the whole workgroup leaves
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int tile = fg * (WPB / S) + wave / S, split = wave % S;
     const bool tvalid = tile < T.IB * T.MB;
@@ -421,7 +416,7 @@ FwdTiling filter_tiling(const Problem& p)
     t.Uh = (((U + 1) / 2) + 2 * kc - 1) / (2 * kc) * (2 * kc);
     t.Us = t.Uh;
     t.FG = (t.IB * t.MB + 3) / 4;
-    t.total = t.chunk = 0;
+    t.deal = Deal();
     t.stagger = kStaggerTicks;
     return t;
 }
@@ -434,9 +429,8 @@ void launch_wpb(const T_* x, const T_* w, T_* y, const Problem& p, hipStream_t s
     const long long nct = (t.q.count + 31) / 32;
     t.Us = ((t.Uh + S - 1) / S + 2 * KC - 1) / (2 * KC) * (2 * KC);
     t.FG = (t.IB * t.MB * S + WPB - 1) / WPB;
-    t.total = (int)(nct * t.FG);
-    t.chunk = (t.total + 7) / 8;
-    const long long blocks = (long long)8 * t.chunk;
+    t.deal = make_deal(nct, t.FG);
+    const long long blocks = (long long)8 * t.deal.chunk;
     const bool al4 = (t.b.g % 4 == 0) && (p.L % 4 == 0);
     const bool ch8 = al4 && p.Cin % KC == 0 && (t.b.g * t.TM % KC == 0 || t.MB == 1);
     const dim3 grid((unsigned)blocks), block(WPB * 64);

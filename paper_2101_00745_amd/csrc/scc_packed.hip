@@ -134,7 +134,7 @@ hipError_t launch_variant(const T_* src, const T_* w, T_* out, char* ws, const P
                                                           lds_bytes((int)sizeof(T_), CT) + kMaxGroups * 16 * 4);
     if (allowed != hipSuccess) return allowed;
     launch_pack<T_, FWD>(w, ws, p, t, st);
-    packed_product<T_, CT, FWD><<<dim3((unsigned)(8 * t.chunk)), dim3(256), lds, st>>>(src, ws, out, p, t);
+    packed_product<T_, CT, FWD><<<dim3((unsigned)(8 * t.deal.chunk)), dim3(256), lds, st>>>(src, ws, out, p, t);
     return hipGetLastError();
 }
 

@@ -48,8 +48,7 @@ struct Packed {
     int NG;          // row groups of 128: one tile of 32 rows per wavefront
     int KG;          // K groups of 16 positions per round
     int nround;      // rounds of the longest walk; shorter walks are padded with empty positions
-    int total;       // workgroups with work: column tiles * NG, row group fastest
-    int chunk;       // consecutive workgroups of that order given to one XCD
+    Deal deal;       // (column tile, row group)
     uint32_t tab_group;   // table entries per row group: nround rounds
     uint32_t act_at, a_at;   // byte offsets of the activity bytes and of A in the workspace
     size_t bytes;    // of the workspace
@@ -103,10 +102,8 @@ __device__ __forceinline__ void packed_body(const T_* __restrict__ src, const ch
     constexpr int kBuf = NP * kPiece;
     uint32_t* const tab = (uint32_t*)(lds_p + 2 * kBuf);
 
-    const int xcd = bid & 7, slot = bid >> 3;
-    const int logical = xcd * T.chunk + slot;
-    if (slot >= T.chunk || logical >= T.total) return;  // the whole workgroup leaves
-    const int ct = logical / T.NG, ng = logical % T.NG;
+    int ct, ng;
+    if (!dealt(T.deal, bid, ct, ng)) return;            // the whole workgroup leaves
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, f = lane & 31, h = lane >> 5;
@@ -298,8 +295,7 @@ inline Packed make_packed(const Problem& p, int es, int CT)
     }
     t.nround = (longest + 16 * t.KG - 1) / (16 * t.KG);
     t.q = column_groups(p, CT);
-    t.total = (int)((t.q.count + 31) / 32 * t.NG);
-    t.chunk = (t.total + 7) / 8;
+    t.deal = make_deal((t.q.count + 31) / 32, t.NG);
     t.tab_group = (uint32_t)(t.nround * 16 * t.KG);
     const long long np = es == 2 ? 1 : 3, nkg = (long long)t.nround * t.KG;
     long long at = (long long)t.NG * t.tab_group * 4;
@@ -348,7 +344,7 @@ inline int tile_width(const Problem& p, int es)
     // 7x7 layer: 100 workgroups of 128 columns 44 us, 200 of 64 30 us)
     const int ct = wide < 384 ? 2 : 4;
     const Packed t = make_packed<FWD>(p, es, ct);
-    return t.nround * t.KG <= kMaxGroups && t.bytes <= (1u << 28) && t.total < (1 << 28) ? ct : 0;
+    return t.nround * t.KG <= kMaxGroups && t.bytes <= (1u << 28) && (t.q.count + 31) / 32 * t.NG < (1 << 28) ? ct : 0;
 }
 
 // tile_width where the pass on its own is faster this way, else 0.

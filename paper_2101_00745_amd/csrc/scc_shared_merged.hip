@@ -38,7 +38,7 @@ hipError_t launch_variant(const T_* x, const T_* dy, const char* packed_w, T_* d
                                                           hipFuncAttributeMaxDynamicSharedMemorySize, kMost);
     if (allowed != hipSuccess) return allowed;
     const int need = kI + ti.nround * 16 * ti.KG * 4, nweight = 8 * tw.chunk;
-    backward_shared<T_, CT, PT><<<dim3((unsigned)(nweight + 8 * ti.chunk)), dim3(256), need > kW ? need : kW, st>>>(
+    backward_shared<T_, CT, PT><<<dim3((unsigned)(nweight + 8 * ti.deal.chunk)), dim3(256), need > kW ? need : kW, st>>>(
         x, dy, packed_w, dx, part, p, ti, tw, nweight);
     return hipGetLastError();
 }
@@ -86,7 +86,8 @@ hipError_t launch_backward_shared(const T_* x, const T_* dy, const T_* w, T_* dx
     const shared_bww::WeightTiling tw = shared_bww::make_weight_tiling(p, es, &pt, true);
     const int ct = packed::tile_width<false>(p, es);
     if (ct == 0 || tw.KS == 0) return hipErrorInvalidValue;
-    const packed::Packed ti = packed::make_packed<false>(p, es, ct);
+    packed::Packed ti = packed::make_packed<false>(p, es, ct);
+    ti.deal = in_eighths(ti.deal);
     float* part = (float*)workspace;
     char* packed_w = (char*)workspace + partial_bytes(p, tw);
     hipError_t e = pack_only<T_, false>(w, packed_w, p, ct, st);
