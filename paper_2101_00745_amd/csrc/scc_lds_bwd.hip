@@ -67,7 +67,7 @@ struct FusedTiling {
     Band b;       // g == 32: window m starts at channel 32*m; P windows and P channel blocks
     int KS;       // K-splits (workgroups per channel block)
     int NQ4;      // groups of 4 consecutive columns: N*HW / 4
-    int per_ks;   // column groups per K-split: ceil(NQ4 / KS)
+    int nchunk;   // chunks of 32 column groups; K-split ks takes the chunks ks, ks + KS, ...
     int chunk;    // consecutive workgroups of the (K-split, block) order given to one XCD: ceil(KS * P / 8)
 };
 
@@ -125,12 +125,13 @@ __global__ __launch_bounds__(kWaves * 64) void backward_fused_lds32(const float*
         }
     }
 
-    // column groups [ks_b, ks_e) of this K-split; chunk c is groups [ks_b + 32c, +32), this wavefront's
-    // sub-chunk the 8 groups from ks_b + 32c + 8*sub
-    const int ks_b = ks * T.per_ks < T.NQ4 ? ks * T.per_ks : T.NQ4;
-    const int ks_e = ks_b + T.per_ks < T.NQ4 ? ks_b + T.per_ks : T.NQ4;
-    const int nchunk = (ks_e - ks_b + 31) / 32;
-    const int q0 = ks_b + 8 * sub;
+    // This K-split's chunks are KS apart, so that the chip sweeps the tensors on one front.  (With a stretch of the columns each,
+    // the K-splits are a fraction of a tensor apart, for many sizes on the same memory channels at the same time: operands from HBM,
+    // 128 x 256 -> 256 on 16x16, cg 4, co 0.5 31.5 us with stretches, 28.7 so; 77 x 512 -> 509 on 12x12, cg 8 26.5 and 24.6; operands
+    // still on the chip: the same.)  Its chunk c is the column groups from q0 - 8*sub + 32*KS*c on, this
+    // wavefront's sub-chunk the 8 of them from q0 + 32*KS*c on.
+    const int nchunk = (T.nchunk - ks + T.KS - 1) / T.KS;      // at least one
+    const int q0 = 32 * ks + 8 * sub, ahead = 32 * T.KS;
 
     // load view: this lane's column group in chunk 0 (piece lc ^ lr of the sub-chunk's 128 bytes per row)
     const uint32_t tensor_rows = dx_role ? (uint32_t)P.Cout : (uint32_t)P.Cin;   // planes per sample of what is loaded
@@ -151,7 +152,7 @@ __global__ __launch_bounds__(kWaves * 64) void backward_fused_lds32(const float*
         cps = col % (uint32_t)P.HW;
         offD = (cn * (uint32_t)P.Cin * (uint32_t)P.HW + cps) * 4u;
     }
-    const uint32_t dn = 128u / (uint32_t)P.HW, dp = 128u % (uint32_t)P.HW;   // a chunk further: 128 columns
+    const uint32_t dn = 4u * (uint32_t)ahead / (uint32_t)P.HW, dp = 4u * (uint32_t)ahead % (uint32_t)P.HW;   // this K-split's next chunk
     const uint32_t stepL = (dn * tensor_rows * (uint32_t)P.HW + dp) * 4u, wrapL = (tensor_rows - 1u) * plane;
     const uint32_t stepD = (dn * (uint32_t)P.Cin * (uint32_t)P.HW + dp) * 4u, wrapD = ((uint32_t)P.Cin - 1u) * plane;
 
@@ -165,14 +166,14 @@ __global__ __launch_bounds__(kWaves * 64) void backward_fused_lds32(const float*
     typedef __attribute__((address_space(3))) void* lptr_t;
     const char* const zeros = (const char*)zero16;
     auto issue = [&](int buf) {                // this wavefront's 64 rows of one chunk: global -> LDS buffer `buf`
-        const bool gin = qload < ks_e;
+        const bool gin = qload < T.NQ4;
         const char* const base = gin ? lb + offL : zeros;      // one 64-bit select per chunk, no branches
         const uint32_t keep = gin ? 0xffffffffu : 0u;
         char* sb = (char*)lds + buf * kBufB + ld_ofs;
 #pragma unroll
         for (int it = 0; it < kInstr; ++it)
             __builtin_amdgcn_global_load_lds((gptr_t)(base + (rowoff[it] & keep)), (lptr_t)(sb + it * 1024), 16, 0, 0);
-        qload += 32;
+        qload += ahead;
         cpl += dp;
         const bool wr = cpl >= (uint32_t)P.HW;  // crossed into the next sample
         cpl -= wr ? (uint32_t)P.HW : 0u;
@@ -196,7 +197,7 @@ __global__ __launch_bounds__(kWaves * 64) void backward_fused_lds32(const float*
             wv[gk][e] = (dx_role && k < P.Cout) ? w[(size_t)k * 64 + j] : 0.f;
         }
     __builtin_amdgcn_sched_barrier(0);
-    if (nchunk > 0) issue(0);
+    issue(0);
     __builtin_amdgcn_sched_barrier(0);
     uint32_t a_hi[4][4], a_mid[4][4], a_lo[4][4];
 #pragma unroll
@@ -245,8 +246,8 @@ __global__ __launch_bounds__(kWaves * 64) void backward_fused_lds32(const float*
         }
 #pragma unroll
         for (int v = 0; v < 16; ++v) acc[v] += acc2[v];
-        const bool any = __builtin_amdgcn_readfirstlane(qstore - (f >> 2)) < ks_e;   // the sub-chunk's first group exists
-        if (qstore < ks_e) {
+        const bool any = __builtin_amdgcn_readfirstlane(qstore - (f >> 2)) < T.NQ4;   // the sub-chunk's first group exists
+        if (qstore < T.NQ4) {
             // accumulator register v holds channel 32b + 8*(v/4) + 4*h + v%4, column f of the sub-chunk
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -254,7 +255,7 @@ __global__ __launch_bounds__(kWaves * 64) void backward_fused_lds32(const float*
                 __builtin_nontemporal_store(acc[v], (float*)(db + (offD + ch * plane)));   // written once, never re-read
             }
         }
-        qstore += 32;
+        qstore += ahead;
         cps += dp;
         const bool wr = cps >= (uint32_t)P.HW;
         cps -= wr ? (uint32_t)P.HW : 0u;
@@ -371,7 +372,7 @@ FusedTiling make_fused_tiling(const Problem& p)
     if (ks > ks_max) ks = ks_max;
     if (ks < 1) ks = 1;
     t.KS = (int)ks;
-    t.per_ks = (t.NQ4 + t.KS - 1) / t.KS;
+    t.nchunk = (t.NQ4 + 31) / 32;
     t.chunk = (int)(((long long)t.KS * t.b.P + 7) / 8);
     return t;
 }
