@@ -90,22 +90,42 @@ int with_type(scc_dtype dtype, F&& f)
     return dtype == SCC_F32 ? f(float()) : f(scc::bf16_t());
 }
 
-// Forward (FWD) or grad-input: with a workspace, the layers that packed_workspace names take the product with packed
-// weights; without one, and every other layer, the kernels that need none.
-template <typename T, bool FWD>
-int run_product(const T* src, const T* w, T* out, const Problem& p, void* workspace, size_t workspace_bytes, hipStream_t st)
+// SCC_FORWARD_*, or SCC_ERR_WORKSPACE.  bf16 layers that gain from it keep their weights in registers and leave a workspace they are
+// given alone; else, with a workspace, the layers that packed_workspace names take the product with packed weights.
+int forward_path(const Problem& p, int es, const void* y, const void* workspace, size_t workspace_bytes)
 {
-    const size_t need = workspace ? scc::packed_workspace<FWD>(p, (int)sizeof(T)) : 0;
+    const size_t need = workspace ? scc::packed_workspace<true>(p, es) : 0;
+    if (need > 0 && (workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0)) return SCC_ERR_WORKSPACE;
+    if (scc::forward_resident_preferred(p, es, y)) return SCC_FORWARD_RESIDENT;
+    if (need > 0) return SCC_FORWARD_PACKED;
+    return scc::forward_mfma_eligible(p) ? SCC_FORWARD_TILE : SCC_FORWARD_ANY;
+}
+
+template <typename T>
+int run_forward(const T* x, const T* w, T* y, const Problem& p, void* workspace, size_t workspace_bytes, hipStream_t st)
+{
+    const int path = forward_path(p, (int)sizeof(T), y, workspace, workspace_bytes);
+    if (path < 0) return path;
+    drop_stale_error();
+    if constexpr (sizeof(T) == 2) {
+        if (path == SCC_FORWARD_RESIDENT) return launch_status(scc::launch_forward_resident(x, w, y, p, st));
+    }
+    if (path == SCC_FORWARD_PACKED) return launch_status(scc::launch_packed<T, true>(x, w, y, workspace, p, st));
+    if (path == SCC_FORWARD_TILE) return launch_status(scc::launch_forward_mfma(x, w, y, p, st));
+    return launch_status(scc::launch_forward_generic(x, w, y, p, st));
+}
+
+// Grad-input: with a workspace, the layers that packed_workspace names take the product with packed weights; without one, and
+// every other layer, the kernels that need none.
+template <typename T>
+int run_backward_input(const T* dy, const T* w, T* dx, const Problem& p, void* workspace, size_t workspace_bytes, hipStream_t st)
+{
+    const size_t need = workspace ? scc::packed_workspace<false>(p, (int)sizeof(T)) : 0;
     if (need > 0 && (workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0)) return SCC_ERR_WORKSPACE;
     drop_stale_error();
-    if (need > 0) return launch_status(scc::launch_packed<T, FWD>(src, w, out, workspace, p, st));
-    if constexpr (FWD) {
-        if (scc::forward_mfma_eligible(p)) return launch_status(scc::launch_forward_mfma(src, w, out, p, st));
-        return launch_status(scc::launch_forward_generic(src, w, out, p, st));
-    } else {
-        if (scc::backward_input_mfma_eligible(p)) return launch_status(scc::launch_backward_input_mfma(src, w, out, p, st));
-        return launch_status(scc::launch_backward_input_generic(src, w, out, p, st));
-    }
+    if (need > 0) return launch_status(scc::launch_packed<T, false>(dy, w, dx, workspace, p, st));
+    if (scc::backward_input_mfma_eligible(p)) return launch_status(scc::launch_backward_input_mfma(dy, w, dx, p, st));
+    return launch_status(scc::launch_backward_input_generic(dy, w, dx, p, st));
 }
 
 int size_of(scc_dtype dtype) { return dtype == SCC_F32 ? 4 : 2; }
@@ -187,8 +207,17 @@ int scc_forward_ws(const void* x, const void* w, void* y, int N, int Cin, int Co
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
     return with_type(dtype, [&](auto t) {
         typedef decltype(t) T;
-        return run_product<T, true>((const T*)x, (const T*)w, (T*)y, p, workspace, workspace_bytes, (hipStream_t)stream);
+        return run_forward<T>((const T*)x, (const T*)w, (T*)y, p, workspace, workspace_bytes, (hipStream_t)stream);
     });
+}
+
+int scc_forward_path(int N, int Cin, int Cout, int H, int W, int cg, double co, scc_dtype dtype, size_t workspace_bytes)
+{
+    Problem p;
+    const int rc = make_problem(N, Cin, Cout, H, W, cg, co, &p);
+    if (rc != SCC_OK) return rc;
+    if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
+    return forward_path(p, dtype == SCC_F32 ? 4 : 2, nullptr, workspace_bytes ? (const void*)256 : nullptr, workspace_bytes);   // aligned addresses
 }
 
 int scc_forward(const void* x, const void* w, void* y, int N, int Cin, int Cout, int H, int W, int cg, double co,
@@ -214,7 +243,7 @@ int scc_backward_input_ws(const void* dy, const void* w, void* dx, int N, int Ci
     if (!dtype_ok(dtype)) return SCC_ERR_DTYPE;
     return with_type(dtype, [&](auto t) {
         typedef decltype(t) T;
-        return run_product<T, false>((const T*)dy, (const T*)w, (T*)dx, p, workspace, workspace_bytes, (hipStream_t)stream);
+        return run_backward_input<T>((const T*)dy, (const T*)w, (T*)dx, p, workspace, workspace_bytes, (hipStream_t)stream);
     });
 }
 

@@ -65,14 +65,14 @@ struct Deal {
     int chunk;   // workgroups of one XCD: ceil(total / 8)
     int even;    // of these, the first, which are dealt in runs; what then is left goes in eighths ...
     int rest;    // ... from this outer index on
+    int run;     // tiles of a run
 };
-constexpr int kRun = 16;
 
-inline Deal make_deal(long long outer, int inner)
+inline Deal make_runs(long long outer, int inner, int run = 16)
 {
     const long long total = outer * inner;
-    const int runs = total >= 1024 && inner > 1 ? (int)(outer / (8 * kRun)) : 0;   // of each XCD
-    return {(int)total, inner, (int)((total + 7) / 8), runs * kRun * inner, 8 * runs * kRun};
+    const int runs = (int)(outer / (8 * run));   // of each XCD
+    return {(int)total, inner, (int)((total + 7) / 8), runs * run * inner, 8 * runs * run, run};
 }
 
 // An eighth of the order for each XCD, whatever the grid: where grad-weight's workgroups, which keep to slices of the columns, run
@@ -84,6 +84,12 @@ inline Deal in_eighths(Deal d)
     return d;
 }
 
+inline Deal make_deal(long long outer, int inner)
+{
+    const Deal d = make_runs(outer, inner);
+    return d.total >= 1024 && inner > 1 ? d : in_eighths(d);
+}
+
 // false: no work, the whole workgroup leaves
 __device__ __forceinline__ bool dealt(const Deal& d, int bid, int& outer, int& inner)
 {
@@ -93,8 +99,20 @@ __device__ __forceinline__ bool dealt(const Deal& d, int bid, int& outer, int& i
     if (slot >= d.chunk || (!runs && left >= d.total - 8 * d.even)) return false;
     const int at = runs ? slot : left, tile = at / d.inner;
     inner = at - tile * d.inner;
-    outer = runs ? tile + (7 * (tile / kRun) + xcd) * kRun : tile + d.rest;
+    outer = runs ? tile + (7 * (tile / d.run) + xcd) * d.run : tile + d.rest;
     return true;
+}
+
+// For workgroups that take several tiles (inner == 1): tiles of an XCD, and the i-th of them
+__device__ __forceinline__ int tiles_of(const Deal& d, int xcd)
+{
+    const int each = d.chunk - d.even, left = d.total - 8 * d.even - xcd * each;
+    return d.even + (left < 0 ? 0 : left < each ? left : each);
+}
+
+__device__ __forceinline__ int nth_tile(const Deal& d, int xcd, int i)
+{
+    return i < d.even ? i + (7 * (i / d.run) + xcd) * d.run : d.rest + xcd * (d.chunk - d.even) + i - d.even;
 }
 
 typedef uint16_t bf16_t;  // bfloat16 storage: the upper 16 bits of a binary32
@@ -175,6 +193,9 @@ bool forward_shared_eligible(const Problem& p);
 double forward_shared_gain(const Problem& p);   // channel fetches saved: own spans / shared walks
 bool forward_shared_preferred(const Problem& p);   // ... and faster
 hipError_t launch_forward_shared(const float* x, const float* w, float* y, const Problem& p, hipStream_t st);
+// Forward with the weights resident in registers, bf16 (scc_fwd_resident.hip); es is the storage type's size
+bool forward_resident_preferred(const Problem& p, int es, const void* y);
+hipError_t launch_forward_resident(const bf16_t* x, const bf16_t* w, bf16_t* y, const Problem& p, hipStream_t st);
 bool backward_input_mfma_eligible(const Problem& p);
 template <typename T> hipError_t launch_backward_input_mfma(const T* dy, const T* w, T* dx, const Problem& p, hipStream_t st);
 // Grad-input with the dy operand shared by four channel blocks through LDS, fp32 (scc_bwi_shared.hip)

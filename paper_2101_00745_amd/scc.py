@@ -19,7 +19,7 @@ SCC_F32, SCC_BF16 = 0, 1
 SYMBOLS = ("scc_window_params", "scc_forward", "scc_forward_workspace_bytes", "scc_forward_ws", "scc_backward_input",
            "scc_backward_input_workspace_bytes", "scc_backward_input_ws",
            "scc_backward_weight_workspace_bytes", "scc_backward_weight", "scc_backward_weight_static",
-           "scc_backward_workspace_bytes", "scc_backward", "scc_backward_weight_path", "scc_backward_path",
+           "scc_backward_workspace_bytes", "scc_backward", "scc_forward_path", "scc_backward_weight_path", "scc_backward_path",
            "scc_depthwise3x3_out", "scc_depthwise3x3_forward", "scc_depthwise3x3_backward_workspace_bytes",
            "scc_depthwise3x3_backward", "scc_dw_forward_workspace_bytes", "scc_dw_forward_fusable", "scc_dw_forward",
            "scc_dw_forward_scratch", "scc_dw_forward_path", "scc_dw_forward_scratch_path",
@@ -67,7 +67,7 @@ def load():
     lib.scc_backward_workspace_bytes.restype = c_sz
     lib.scc_backward.argtypes = [c_vp] * 5 + shape + [c_vp, c_sz, c_vp]
     lib.scc_backward.restype = c_int
-    for name in ("scc_backward_weight_path", "scc_backward_path"):
+    for name in ("scc_forward_path", "scc_backward_weight_path", "scc_backward_path"):
         getattr(lib, name).argtypes, getattr(lib, name).restype = shape + [c_sz], c_int
     lib.scc_backward_weight_static.argtypes = [c_vp, c_vp, c_vp] + shape + [c_vp]
     lib.scc_backward_weight_static.restype = c_int

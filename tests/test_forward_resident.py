@@ -1,0 +1,59 @@
+"""The bf16 forward that keeps its weights in registers: which layers take it, and every element against the fp32 forward of the same
+values (itself held to the oracle), with samples against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2101_00745_amd as S
+from oracle import scc_oracle as O
+
+RESIDENT = 3    # SCC_FORWARD_RESIDENT
+LAYERS = [(128, 128, 512, 32, 32, 2, 0.33),      # a filter group's walk of 95 channels, some across channel 0
+          (150, 128, 512, 31, 30, 2, 0.33),      # planes of 930 pixels: a sample's last columns overlap; tiles left over
+          (703, 448, 448, 12, 12, 8, 0.33),      # walk of 182; windows on most channels, last filter group of 64 rows
+          (852, 56, 221, 12, 12, 1, 0.75),       # once around the circle of 56 channels; filters without number in the last group
+          (363, 160, 317, 20, 20, 4, 0.33),      # walk of 103, 16 starts to a tile
+          (592, 96, 144, 20, 18, 4, 0.5),        # two filter groups, the second of 16 rows
+          (310, 192, 768, 12, 13, 4, 0.75)]      # rows of 312 bytes
+
+
+def path(layer, code, workspace=1 << 30):
+    return S.load().scc_forward_path(*layer, code, workspace)
+
+
+@pytest.mark.parametrize("layer", LAYERS)
+def test_lines(layer):
+    N, Cin, Cout, H, W, cg, co = layer
+    assert path(layer, 1) == path(layer, 1, 0) == RESIDENT and path(layer, 0) != RESIDENT
+    for other in ((N // 16, Cin, Cout, H, W, cg, co), (N, Cin, 40, H, W, cg, co), (N, Cin, Cout, 7, 7, cg, co)):      # few columns, few filters, odd planes
+        assert path(other, 1) != RESIDENT
+    assert path((N, Cin, Cout, H, W, 0, co), 1) == -2
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer", LAYERS)
+def test_parity(layer):
+    N, Cin, Cout, H, W, cg, co = layer
+    gen = torch.Generator(device="cuda").manual_seed(21)
+    x, w = (torch.randn(*d, generator=gen, device="cuda").bfloat16() for d in ((N, Cin, H, W), (Cout, Cin // cg)))
+    y = torch.full((N, Cout, H, W), float("nan"), dtype=torch.bfloat16, device="cuda")
+    S.scc_forward(x, w, cg, co, out=y)
+    assert torch.equal(y, S.scc_forward(x, w, cg, co))          # with and without a workspace
+    wide = S.scc_forward(x.float(), w.float(), cg, co)
+    # bf16 keeps 8 bits, so half a unit of its last place is at most 2**-8 of a value; both sums are binary32
+    bound = wide.abs() * 2.0 ** -8 + 2e-5 * float(wide.abs().max())
+    assert bool(((y.float() - wide).abs() <= bound).all())
+    some = torch.tensor([0, N // 3, N - 1], device="cuda")
+    ref = O.forward(x[some].float().cpu().numpy(), w.float().cpu().numpy(), cg, co)
+    assert np.max(np.abs(y[some].float().cpu().numpy() - ref)) <= 4e-3 * np.max(np.abs(ref))
+
+
+@pytest.mark.gpu
+def test_an_output_on_odd_addresses_takes_another_kernel():
+    N, Cin, Cout, H, W, cg, co = LAYERS[3]
+    gen = torch.Generator(device="cuda").manual_seed(22)
+    x, w = (torch.randn(*d, generator=gen, device="cuda").bfloat16() for d in ((N, Cin, H, W), (Cout, Cin // cg)))
+    odd = torch.zeros(N * Cout * H * W + 1, dtype=torch.bfloat16, device="cuda")[1:].view(N, Cout, H, W)
+    S.scc_forward(x, w, cg, co, out=odd)
+    want = S.scc_forward(x, w, cg, co).float()                  # both rounded: a unit of the last place, 2**-7, apart at most
+    assert bool(((odd.float() - want).abs() <= want.abs() * 2.0 ** -7 + 2e-5 * float(want.abs().max())).all())
