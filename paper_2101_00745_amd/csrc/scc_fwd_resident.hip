@@ -31,7 +31,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int CT = 8;   // columns per lane and plane
 constexpr int KA = 6;   // K groups of 16 positions whose weights a wavefront keeps
-constexpr int kSpan = 80;   // positions a tile's filters span at most where the layer takes this path
 
 struct Resident {
     Band b;
@@ -264,13 +263,13 @@ hipError_t launch_variant(const bf16_t* x, const bf16_t* w, bf16_t* y, const Pro
 
 // Layers that gain, of 95 measured against the per-tile and the packed forward.  A workgroup's start takes 3 us: 64 MB of x and y, and at least
 // four tiles of 256 columns per workgroup, five where a tile's filters start together (four of them 0.85 to 1.12: 855 x 64 -> 256 on 12x12, cg 2 23.4
-// and 25.2 us).  Windows whose 32 filters span at most 80 positions (the walks get long: 0.74 to 0.92 against the per-tile kernel from a span of 88
-// on, but for one of 1.0).  Row groups filled to more than half (64 x 64 and 32 x 64 channels 0.72 to 0.98).  And tiles of the others that
+// and 25.2 us).  Windows whose 32 filters span at most KA K groups and, where they start together, 80 positions
+// (the walks get long: from 88 on 0.74 to 0.92 against the per-tile kernel, but for one of 1.0).  Row groups filled to more than half (64 x 64 and 32 x 64 channels 0.72 to 0.98).  And tiles of the others that
 // fetch planes again: 1.7 times with differing starts in a tile, 2.5 times without (below 0.8 to 1.05).  Layers taken run 1.02 to 1.58 times as
 // fast.  Stores take rows of whole words.
 bool forward_resident_preferred(const Problem& p, int es, const void* y)
 {
-    if (es != 2 || p.L > kSpan || p.HW < CT || p.HW % 2 != 0 || ((uintptr_t)y & 3u) != 0 || !forward_mfma_eligible(p)) return false;
+    if (es != 2 || p.L > 16 * KA || p.HW < CT || p.HW % 2 != 0 || ((uintptr_t)y & 3u) != 0 || !forward_mfma_eligible(p)) return false;
     if ((double)(p.Cin + p.Cout) * (double)p.NQ < 32e6) return false;
     const Band b = make_band(p);
     if (4ll * b.P * b.F > 5ll * p.Cout) return false;       // few filters on many starts: too many empty rows
@@ -278,10 +277,10 @@ bool forward_resident_preferred(const Problem& p, int es, const void* y)
     if (t.deal.chunk <= (b.F < 32 ? 3 : 4) * t.lanes || 100ll * p.Cout < 55ll * 128 * t.NG || t.NG > 32) return false;
     double again;
     packed::fetches_without_sharing<true>(p, b, &again);
-    if (again < (b.F < 32 ? 1.7 : 2.5)) return false;
+    if (b.F < 32 ? again < 1.7 : again < 2.5 || p.L > 80) return false;
     int octets, longest;
     reach(p, b, t.rows, &octets, &longest);
-    return octets <= (kSpan + 7 + 7) / 8 && longest <= 192;
+    return octets <= 2 * KA && longest <= 192;
 }
 
 hipError_t launch_forward_resident(const bf16_t* x, const bf16_t* w, bf16_t* y, const Problem& p, hipStream_t st)

@@ -11,7 +11,7 @@ RESIDENT = 3    # SCC_FORWARD_RESIDENT
 LAYERS = [(128, 128, 512, 32, 32, 2, 0.33),      # a filter group's walk of 95 channels, some across channel 0
           (150, 128, 512, 31, 30, 2, 0.33),      # planes of 930 pixels: a sample's last columns overlap; tiles left over
           (703, 448, 448, 12, 12, 8, 0.33),      # walk of 182; windows on most channels, last filter group of 64 rows
-          (852, 56, 221, 12, 12, 1, 0.75),       # once around the circle of 56 channels; filters without number in the last group
+          (1100, 56, 221, 12, 12, 1, 0.75),       # once around the circle of 56 channels; filters without number in the last group
           (363, 160, 317, 20, 20, 4, 0.33),      # walk of 103, 16 starts to a tile
           (592, 96, 144, 20, 18, 4, 0.5),        # two filter groups, the second of 16 rows
           (310, 192, 768, 12, 13, 4, 0.75)]      # rows of 312 bytes
