@@ -65,14 +65,14 @@ struct Deal {
     int chunk;   // workgroups of one XCD: ceil(total / 8)
     int even;    // of these, the first, which are dealt in runs; what then is left goes in eighths ...
     int rest;    // ... from this outer index on
-    int run;     // tiles of a run
 };
+constexpr int kRun = 16;   // a constant: nothing to divide by in a workgroup's first instructions
 
-inline Deal make_runs(long long outer, int inner, int run = 16)
+inline Deal make_runs(long long outer, int inner)
 {
     const long long total = outer * inner;
-    const int runs = (int)(outer / (8 * run));   // of each XCD
-    return {(int)total, inner, (int)((total + 7) / 8), runs * run * inner, 8 * runs * run, run};
+    const int runs = (int)(outer / (8 * kRun));   // of each XCD
+    return {(int)total, inner, (int)((total + 7) / 8), runs * kRun * inner, 8 * runs * kRun};
 }
 
 // An eighth of the order for each XCD, whatever the grid: where grad-weight's workgroups, which keep to slices of the columns, run
@@ -90,17 +90,18 @@ inline Deal make_deal(long long outer, int inner)
     return d.total >= 1024 && inner > 1 ? d : in_eighths(d);
 }
 
-// false: no work, the whole workgroup leaves
+// false: no work, the whole workgroup leaves.  RUNS: false where the deal is one of in_eighths.  Without a branch in here: behind one, the
+// kernel's other arguments are fetched after the deal's (1 us for each generation of workgroups).
+template <bool RUNS = true>
 __device__ __forceinline__ bool dealt(const Deal& d, int bid, int& outer, int& inner)
 {
     const int xcd = bid & 7, slot = bid >> 3;
-    const bool runs = slot < d.even;
-    const int left = xcd * (d.chunk - d.even) + slot - d.even;
-    if (slot >= d.chunk || (!runs && left >= d.total - 8 * d.even)) return false;
+    const bool runs = RUNS && slot < d.even;
+    const int left = RUNS ? xcd * (d.chunk - d.even) + slot - d.even : xcd * d.chunk + slot;
     const int at = runs ? slot : left, tile = at / d.inner;
     inner = at - tile * d.inner;
-    outer = runs ? tile + (7 * (tile / d.run) + xcd) * d.run : tile + d.rest;
-    return true;
+    outer = runs ? tile + (7 * (tile / kRun) + xcd) * kRun : RUNS ? tile + d.rest : tile;
+    return (slot < d.chunk) & (runs | (left < (RUNS ? d.total - 8 * d.even : d.total)));
 }
 
 // For workgroups that take several tiles (inner == 1): tiles of an XCD, and the i-th of them
@@ -112,7 +113,7 @@ __device__ __forceinline__ int tiles_of(const Deal& d, int xcd)
 
 __device__ __forceinline__ int nth_tile(const Deal& d, int xcd, int i)
 {
-    return i < d.even ? i + (7 * (i / d.run) + xcd) * d.run : d.rest + xcd * (d.chunk - d.even) + i - d.even;
+    return i < d.even ? i + (7 * (i / kRun) + xcd) * kRun : d.rest + xcd * (d.chunk - d.even) + i - d.even;
 }
 
 typedef uint16_t bf16_t;  // bfloat16 storage: the upper 16 bits of a binary32

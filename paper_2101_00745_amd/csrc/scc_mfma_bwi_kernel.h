@@ -60,7 +60,7 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
     // bid is the workgroup's index in a launch whose first workgroup is a multiple of 8: bid % 8 names the XCD; the
     // channel blocks of a column tile, which re-read the same dy planes, share one and its L2
     int ct, fg;
-    if (!dealt(T.deal, bid, ct, fg)) return;          // the whole workgroup leaves
+    if (!dealt<!LENT>(T.deal, bid, ct, fg)) return;          // the whole workgroup leaves
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int cb = fg * (WPB / S) + wave / S, split = wave % S;
     const bool tvalid = cb < T.CB;

@@ -87,7 +87,7 @@ __device__ __forceinline__ int filter_of(const Band& b, int m, int i, int Cout)
 }
 
 // bid: the workgroup's index in a launch whose first workgroup is a multiple of 8 (bid % 8 names the XCD)
-template <typename T_, int CT, bool FWD>
+template <typename T_, int CT, bool FWD, bool RUNS = true>
 __device__ __forceinline__ void packed_body(const T_* __restrict__ src, const char* __restrict__ ws, T_* __restrict__ out,
                                             const Problem& P, const Packed& T, const int bid, char* const lds_p)
 {
@@ -103,7 +103,7 @@ __device__ __forceinline__ void packed_body(const T_* __restrict__ src, const ch
     uint32_t* const tab = (uint32_t*)(lds_p + 2 * kBuf);
 
     int ct, ng;
-    if (!dealt(T.deal, bid, ct, ng)) return;            // the whole workgroup leaves
+    if (!dealt<RUNS>(T.deal, bid, ct, ng)) return;            // the whole workgroup leaves
     const int tid = threadIdx.x;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int lane = tid & 63, f = lane & 31, h = lane >> 5;

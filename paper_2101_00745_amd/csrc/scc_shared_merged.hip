@@ -25,7 +25,7 @@ __global__ __launch_bounds__(256, 3) void backward_shared(const T_* __restrict__
     if (bid < nweight)
         shared_bww::weight_body<T_, PT>(x, dy, part, P, TW, bid, lds_b);
     else
-        packed::packed_body<T_, CT, false>(dy, packed_w, dx, P, TI, bid - nweight, lds_b);
+        packed::packed_body<T_, CT, false, false>(dy, packed_w, dx, P, TI, bid - nweight, lds_b);
 }
 
 template <typename T_, int CT, int PT>
