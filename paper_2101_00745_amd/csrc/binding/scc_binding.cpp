@@ -17,6 +17,7 @@
 #include <c10/hip/HIPFunctions.h>
 #include <c10/hip/HIPStream.h>
 #include <torch/csrc/Exceptions.h>
+#include <torch/csrc/autograd/custom_function.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include <climits>
@@ -117,10 +118,12 @@ struct Unlocked {
     ~Unlocked() { PyEval_RestoreThread(save); }
 };
 
+void* stream_of(const at::Tensor& x) { return (void*)c10::hip::getCurrentHIPStream(x.get_device()).stream(); }
+
 template <typename F>
 int launch(const at::Tensor& x, F&& f)
 {
-    void* stream = (void*)c10::hip::getCurrentHIPStream(x.get_device()).stream();
+    void* stream = stream_of(x);
     Unlocked unlocked;
     return f(stream);
 }
@@ -173,6 +176,38 @@ PyObject* backward(PyObject*, PyObject* const* args, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
+// y of a block; undefined where the call failed
+template <typename F>
+at::Tensor block_forward(const at::Tensor& x, const at::Tensor& k, const at::Tensor& w, const Args& a, const Layer& l, F&& run)
+{
+    at::Tensor y = at::empty({l.N, l.Cout, l.Ho, l.Wo}, x.options());
+    const size_t need = scc_dw_forward_workspace_bytes(l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg, a.co, l.dtype);
+    const at::Tensor ws = scratch(need, x);
+    const int rc = run([&](void* st) {
+        return scc_dw_forward_scratch(x.data_ptr(), k.data_ptr(), w.data_ptr(), y.data_ptr(), l.N, l.Cin, l.Cout, l.H, l.W,
+                                      a.stride, a.cg, a.co, l.dtype, address(ws), need, st);
+    });
+    return rc == SCC_OK ? y : at::Tensor();
+}
+
+// dx, dkdw, dw of a block; none where the call failed
+template <typename F>
+std::vector<at::Tensor> block_backward(const at::Tensor& x, const at::Tensor& k, const at::Tensor& w, const at::Tensor& dy,
+                                       const Args& a, const Layer& l, scc_dtype grad, F&& run)
+{
+    const at::TensorOptions of = x.options().dtype(grad == SCC_F32 ? at::kFloat : at::kBFloat16);
+    at::Tensor dx = at::empty_like(x), dk = at::empty(k.sizes(), of), dw = at::empty(w.sizes(), of);
+    const size_t need = scc_dw_backward_as_workspace_bytes(l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg, a.co, l.dtype, grad);
+    const at::Tensor ws = scratch(need, x);
+    const int rc = run([&](void* st) {
+        return scc_dw_backward_as(x.data_ptr(), k.data_ptr(), w.data_ptr(), dy.data_ptr(), dx.data_ptr(), dk.data_ptr(),
+                                  dw.data_ptr(), l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg, a.co, l.dtype, grad, address(ws), need,
+                                  st);
+    });
+    if (rc != SCC_OK) return {};
+    return {dx, dk, dw};
+}
+
 PyObject* dw_forward(PyObject*, PyObject* const* args, Py_ssize_t n)
 {
     HANDLE_TH_ERRORS
@@ -181,14 +216,8 @@ PyObject* dw_forward(PyObject*, PyObject* const* args, Py_ssize_t n)
     if (!parse(args, n, 3, true, &a) || !layer(a, *a.t[0], *a.t[2], &l)) Py_RETURN_NONE;
     const at::Tensor &x = *a.t[0], &k = *a.t[1], &w = *a.t[2];
     if (!taps(k, x, l)) Py_RETURN_NONE;
-    at::Tensor y = at::empty({l.N, l.Cout, l.Ho, l.Wo}, x.options());
-    const size_t need = scc_dw_forward_workspace_bytes(l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg, a.co, l.dtype);
-    const at::Tensor ws = scratch(need, x);
-    const int rc = launch(x, [&](void* st) {
-        return scc_dw_forward_scratch(x.data_ptr(), k.data_ptr(), w.data_ptr(), y.data_ptr(), l.N, l.Cin, l.Cout, l.H, l.W,
-                                      a.stride, a.cg, a.co, l.dtype, address(ws), need, st);
-    });
-    if (rc != SCC_OK) Py_RETURN_NONE;
+    at::Tensor y = block_forward(x, k, w, a, l, [&](auto&& f) { return launch(x, f); });
+    if (!y.defined()) Py_RETURN_NONE;
     return THPVariable_Wrap(std::move(y));
     END_HANDLE_TH_ERRORS
 }
@@ -201,24 +230,98 @@ PyObject* dw_backward(PyObject*, PyObject* const* args, Py_ssize_t n)
     if (n != 8 || !PyBool_Check(args[7]) || !parse(args, 7, 4, true, &a) || !layer(a, *a.t[0], *a.t[2], &l)) Py_RETURN_NONE;
     const at::Tensor &x = *a.t[0], &k = *a.t[1], &w = *a.t[2], &dy = *a.t[3];
     if (!taps(k, x, l) || !outputs(dy, x, l)) Py_RETURN_NONE;
-    const scc_dtype grad = args[7] == Py_True ? l.dtype : SCC_F32;
-    const at::TensorOptions of = x.options().dtype(grad == SCC_F32 ? at::kFloat : at::kBFloat16);
-    at::Tensor dx = at::empty_like(x), dk = at::empty(k.sizes(), of), dw = at::empty(w.sizes(), of);
-    const size_t need = scc_dw_backward_as_workspace_bytes(l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg, a.co, l.dtype, grad);
-    const at::Tensor ws = scratch(need, x);
-    const int rc = launch(x, [&](void* st) {
-        return scc_dw_backward_as(x.data_ptr(), k.data_ptr(), w.data_ptr(), dy.data_ptr(), dx.data_ptr(), dk.data_ptr(),
-                                  dw.data_ptr(), l.N, l.Cin, l.Cout, l.H, l.W, a.stride, a.cg, a.co, l.dtype, grad, address(ws), need,
-                                  st);
-    });
-    if (rc != SCC_OK) Py_RETURN_NONE;
-    return tuple_of({dx, dk, dw});
+    const std::vector<at::Tensor> g = block_backward(x, k, w, dy, a, l, args[7] == Py_True ? l.dtype : SCC_F32,
+                                                     [&](auto&& f) { return launch(x, f); });
+    if (g.empty()) Py_RETURN_NONE;
+    return tuple_of({g[0], g[1], g[2]});
+    END_HANDLE_TH_ERRORS
+}
+
+// A block under autograd: nn.DWSCCFunction for the training step of a plain call, all of whose tensors want gradients.  Through the Python function
+// a block costs 40 us of host time more, forward and backward, than its launches take (128 x 128 -> 256 on 32x32, stride 2, bf16, one
+// step: 95 us of which the kernels are 62).
+struct Block : torch::autograd::Function<Block> {
+    struct Refused {};
+
+    // from a call of the interpreter, whose lock is held
+    static at::Tensor forward(torch::autograd::AutogradContext* ctx, const at::Tensor& x, const at::Tensor& k, const at::Tensor& w,
+                              int64_t cg, double co, int64_t stride)
+    {
+        const Args a = {{&x, &k, &w, nullptr}, (int)cg, (int)stride, co};
+        Layer l;
+        at::Tensor y;
+        if (layer(a, x, w, &l)) y = block_forward(x, k, w, a, l, [&](auto&& f) { return launch(x, f); });
+        if (!y.defined()) throw Refused();
+        ctx->save_for_backward({x, k, w});
+        ctx->saved_data["cg"] = cg;
+        ctx->saved_data["co"] = co;
+        ctx->saved_data["stride"] = stride;
+        return y;
+    }
+
+    // The engine's thread: the interpreter's lock is not held.
+    static torch::autograd::variable_list backward(torch::autograd::AutogradContext* ctx, torch::autograd::variable_list grads)
+    {
+        const torch::autograd::variable_list saved = ctx->get_saved_variables();
+        const at::Tensor &x = saved[0], &k = saved[1], &w = saved[2];
+        const at::Tensor dy = grads[0].contiguous();
+        Args a = {{&x, &k, &w, &dy}, (int)ctx->saved_data["cg"].toInt(), (int)ctx->saved_data["stride"].toInt(),
+                  ctx->saved_data["co"].toDouble()};
+        Layer l;
+        std::vector<at::Tensor> g;
+        if (layer(a, x, w, &l) && taps(k, x, l) && outputs(dy, x, l))
+            g = block_backward(x, k, w, dy, a, l, l.dtype, [&](auto&& f) { return f(stream_of(x)); });
+        if (g.empty()) g = general(a);
+        return {g[0], g[1], g[2], at::Tensor(), at::Tensor(), at::Tensor()};
+    }
+
+    // what is not plain any more (tensors that saved-tensor hooks brought back, say), and errors: scc._dw_backward
+    static std::vector<at::Tensor> general(const Args& a)
+    {
+        struct Locked {
+            PyGILState_STATE s = PyGILState_Ensure();
+            ~Locked() { PyGILState_Release(s); }
+        } locked;
+        std::vector<at::Tensor> g;
+        PyObject* m = PyImport_ImportModule("paper_2101_00745_amd.scc");
+        PyObject* t[4] = {};
+        for (int i = 0; i < 4; ++i) t[i] = THPVariable_Wrap(*a.t[i]);
+        PyObject* r = m ? PyObject_CallMethod(m, "_dw_backward", "OOOOidiO", t[0], t[1], t[2], t[3], a.cg, a.co, a.stride, Py_True) : nullptr;
+        for (int i = 0; r && i < 3; ++i) g.push_back(THPVariable_Unpack(PyTuple_GetItem(r, i)));
+        for (int i = 0; i < 4; ++i) Py_XDECREF(t[i]);
+        Py_XDECREF(r);
+        Py_XDECREF(m);
+        if (!r) {
+            python_error e;
+            e.persist();
+            throw e;
+        }
+        return g;
+    }
+};
+
+PyObject* dw_block(PyObject*, PyObject* const* args, Py_ssize_t n)
+{
+    HANDLE_TH_ERRORS
+    Args a;
+    Layer l;
+    if (!at::GradMode::is_enabled() || !parse(args, n, 3, true, &a) || !layer(a, *a.t[0], *a.t[2], &l)) Py_RETURN_NONE;
+    const at::Tensor &x = *a.t[0], &k = *a.t[1], &w = *a.t[2];
+    if (!taps(k, x, l)) Py_RETURN_NONE;
+    for (int i = 0; i < 3; ++i)
+        if (!a.t[i]->requires_grad() || a.t[i]->is_inference() || a.t[i]->_fw_grad(0).defined()) Py_RETURN_NONE;
+    try {
+        return THPVariable_Wrap(Block::apply(x, k, w, (int64_t)a.cg, a.co, (int64_t)a.stride));
+    } catch (const Block::Refused&) {
+        Py_RETURN_NONE;
+    }
     END_HANDLE_TH_ERRORS
 }
 
 #define METHOD(name, doc) {#name, (PyCFunction)(void (*)(void))name, METH_FASTCALL, doc}
 PyMethodDef methods[] = {METHOD(forward, "(x, w, cg, co) -> y or None"), METHOD(backward, "(x, dy, w, cg, co) -> (dx, dw) or None"),
                          METHOD(dw_forward, "(x, kdw, w, cg, co, stride) -> y or None"),
+                         METHOD(dw_block, "(x, kdw, w, cg, co, stride) -> y under autograd, or None"),
                          METHOD(dw_backward, "(x, kdw, w, dy, cg, co, stride, stored) -> (dx, dkdw, dw) or None"),
                          {nullptr, nullptr, 0, nullptr}};
 PyModuleDef module = {PyModuleDef_HEAD_INIT, "_binding", nullptr, -1, methods, nullptr, nullptr, nullptr, nullptr};

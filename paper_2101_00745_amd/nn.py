@@ -18,6 +18,11 @@ import torch
 from . import scc as _scc
 
 
+# where a torch lacks one of these, every call goes the general way
+_transforms_active = getattr(torch._C, "_are_functorch_transforms_active", lambda: True)
+_tracing_state = getattr(torch._C, "_get_tracing_state", lambda: True)
+
+
 class SCCFunction(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, weight, cg, co):
@@ -116,8 +121,13 @@ class DWSCCFunction(torch.autograd.Function):
 
 
 def dw_scc(x, kdw, weight, cg, co, dw_stride=1, bias=None):
-    """Functional form of the block: y = SCC(DW3x3(x; kdw); weight) (+ bias per output channel)."""
-    y = DWSCCFunction.apply(x, kdw, weight, cg, co, dw_stride)
+    """Functional form of the block: y = SCC(DW3x3(x; kdw); weight) (+ bias per output channel).  A plain training call (dense tensors that all
+    want gradients, no tracing, no functional transform) is DWSCCFunction in native code; every other one is DWSCCFunction."""
+    y = None
+    if not (torch.compiler.is_compiling() or _transforms_active() or _tracing_state() is not None):
+        y = (_scc._native or _scc._load_native()).dw_block(x, kdw, weight, cg, co, dw_stride)
+    if y is None:
+        y = DWSCCFunction.apply(x, kdw, weight, cg, co, dw_stride)
     if bias is not None:
         y = y + bias.view(1, -1, 1, 1)
     return y

@@ -112,7 +112,7 @@ class _NoNative:
     def forward(*args):
         return None
 
-    backward = dw_forward = dw_backward = forward
+    backward = dw_forward = dw_backward = dw_block = forward
 
 
 def _load_native():
