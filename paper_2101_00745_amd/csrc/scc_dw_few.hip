@@ -65,7 +65,7 @@ __global__ __launch_bounds__(64 * WV, 2) void dw_scc_forward_few(const T_* __res
     typedef T_ w4 __attribute__((ext_vector_type(4), aligned(sizeof(T_))));
 
     int ct, fg;
-    if (!dealt(T.deal, (int)blockIdx.x, ct, fg)) return;
+    if (!dealt<false>(T.deal, (int)blockIdx.x, ct, fg)) return;
     const int mb = fg / T.GM, ib0 = (fg - mb * T.GM) * TF;
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int lane = threadIdx.x & 63, f = lane & 31, h = lane >> 5;
@@ -346,7 +346,7 @@ FewTiling few_tiling(const Problem& p, int cp, int tf)
     t.FG = t.GM * ((t.b.P + t.TM - 1) / t.TM);
     t.U = p.L + t.b.g * (t.TM - 1);
     const long long nct = (p.NQ + 32 * cp - 1) / (32 * cp);
-    t.deal = make_deal(nct, t.FG);
+    t.deal = in_eighths(make_deal(nct, t.FG));
     return t;
 }
 
