@@ -259,7 +259,8 @@ int scc_depthwise3x3_backward(const void* x, const void* kdw, const void* dz, vo
  * as many workgroups as there are groups; in bf16 the intermediate is rounded as two stages round it.  Two stages (every layer):
  * scc_depthwise3x3_forward into `workspace`, then scc_forward on it.
  * scc_dw_forward_workspace_bytes(...) returns 0 for the layers the library runs fused by its own choice
- * (fusable and at least 16384 output pixels over the batch, where fusing is the faster path) and the size
+ * (fusable, at least 16384 output pixels over the batch, stride 1 or 2 and rows of 4, 8, 16, 32, 64 or 128 output pixels that the kernel
+ * cuts into strips: there fusing is the faster path) and the size
  * of the depthwise output (N*Cin*Ho*Wo values of the dtype) for all others.  On these a call with a workspace of at least that size
  * (256-byte aligned, owned by the caller) runs the two stages, and the workspace holds the depthwise output afterwards.  A call with
  * workspace == NULL runs one of the other two wherever scc_dw_forward_fusable(...) returns 1, also where two stages would

@@ -444,9 +444,9 @@ static int make_dw_problem(int N, int Cin, int Cout, int H, int W, int dw_stride
 }
 
 // The depthwise stage's output, or nothing where one kernel keeps it on chip by the library's own choice.
-static size_t dw_forward_need(const Problem& p, scc_dtype dtype)
+static size_t dw_forward_need(const Problem& p, const scc::DwGeom& g, scc_dtype dtype)
 {
-    if (dtype == SCC_F32 && scc::dw_forward_fused_preferred(p)) return 0;
+    if (dtype == SCC_F32 && scc::dw_forward_fused_preferred(p, g)) return 0;
     return (size_t)p.NQ * p.Cin * size_of(dtype);
 }
 
@@ -456,7 +456,7 @@ size_t scc_dw_forward_workspace_bytes(int N, int Cin, int Cout, int H, int W, in
     Problem p;
     scc::DwGeom g;
     if (make_dw_problem(N, Cin, Cout, H, W, dw_stride, cg, co, &p, &g) != SCC_OK || !dtype_ok(dtype)) return 0;
-    return dw_forward_need(p, dtype);
+    return dw_forward_need(p, g, dtype);
 }
 
 int scc_dw_forward_fusable(int N, int Cin, int Cout, int H, int W, int dw_stride, int cg, double co, scc_dtype dtype)
@@ -473,7 +473,7 @@ int scc_dw_forward_fusable(int N, int Cin, int Cout, int H, int W, int dw_stride
 static int dw_forward_path(const Problem& p, const scc::DwGeom& g, scc_dtype dtype, bool keep, const void* workspace,
                            size_t workspace_bytes)
 {
-    const size_t need = dw_forward_need(p, dtype);
+    const size_t need = dw_forward_need(p, g, dtype);
     // without a workspace the fused kernel runs wherever it can, also where the two stages would be faster
     const bool fused = dtype == SCC_F32 && (need == 0 || (!workspace && scc::dw_forward_fused_eligible(p)));
     if (!fused && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0)) return SCC_ERR_WORKSPACE;

@@ -87,6 +87,10 @@ __global__ __launch_bounds__(256) void dw_scc_forward_lds(const float* __restric
     float* zl = (float*)lds_raw;
     constexpr int TP = 32 * CP;
     constexpr int TPP = TP + 1;          // padded row of a channel quad, in columns
+    // On strips a lane of phase 2 owns CP consecutive columns and stores them together: column t of the tile is LDS column
+    // 32*(t % CP) + t / CP, and a row leaves in pieces of 128*CP bytes, which is what bounds the kernel: 512 x 64 -> 128 on 32x32, cg 2 119 us
+    // with a store per column (pieces of 128 bytes), 112 with two columns, 99.5 with four (4.1 TB/s).
+    constexpr bool ROWS = S > 0;
 
     // workgroup -> column tile; blockIdx % 8 names the XCD, and every XCD takes a contiguous run of column
     // tiles, so the rows of x that neighbouring tiles of one sample both need meet in one L2
@@ -183,11 +187,11 @@ __global__ __launch_bounds__(256) void dw_scc_forward_lds(const float* __restric
             dw::load_taps(kdw, c, false, k);
             float out[RB][4];
             dw_strip<S, RB>(xb + (size_t)c * HWi, G.W, k, rowmask, left, right, false, false, out);
-            float* zo = zl + ((size_t)(c >> 2) * TPP + colbase) * 4 + (c & 3);
+            float* zo = zl + ((size_t)(c >> 2) * TPP + colbase / CP) * 4 + (c & 3);
 #pragma unroll
             for (int rr = 0; rr < RB; ++rr)
 #pragma unroll
-                for (int i = 0; i < 4; ++i) zo[(rr * G.Wo + i) * 4] = out[rr][i];
+                for (int i = 0; i < 4; ++i) zo[(32 * (i % CP) + rr * G.Wo / CP + i / CP) * 4] = out[rr][i];
         }
     } else {
         // any stride and map size: each of the thread's 4 columns has its own sample and pixel
@@ -242,7 +246,7 @@ __global__ __launch_bounds__(256) void dw_scc_forward_lds(const float* __restric
     bool live[CP];
 #pragma unroll
     for (int c = 0; c < CP; ++c) {
-        const long long q = q0 + 32 * c + col;
+        const long long q = q0 + (ROWS ? CP * col + c : 32 * c + col);
         live[c] = q < P.NQ;
         const long long qs = live[c] ? q : 0;
         ycol[c] = (qs / P.HW) * (long long)P.Cout * P.HW + qs % P.HW;
@@ -290,6 +294,14 @@ __global__ __launch_bounds__(256) void dw_scc_forward_lds(const float* __restric
                 const int row = (v >> 2) * 8 + kg * 4 + (v & 3);
                 const int kr = __shfl(kmine, row, 64);   // lane `row` computed that filter's index
                 if (kr < 0) continue;
+                if constexpr (ROWS) {
+                    typedef float yvec __attribute__((ext_vector_type(CP), aligned(4)));
+                    yvec o;
+#pragma unroll
+                    for (int c = 0; c < CP; ++c) o[c] = acc[c][v];
+                    if (live[0]) __builtin_nontemporal_store(o, (yvec*)(y + ycol[0] + (long long)kr * P.HW));
+                    continue;
+                }
 #pragma unroll
                 for (int c = 0; c < CP; ++c)
                     if (live[c]) __builtin_nontemporal_store(acc[c][v], y + ycol[c] + (long long)kr * P.HW);
@@ -336,11 +348,13 @@ int strip_rows(const DwGeom& g, int cp, const float* x)
     return 0;
 }
 
-// Columns per workgroup, in groups of 32 (2 or 1): two workgroups per CU where the LDS tile allows it (80 KiB each),
-// the wider tile when it still leaves every CU two workgroups, and a width on which phase 1 can run on strips
-// if there is one.
+// Columns per workgroup, in groups of 32 (4, 2 or 1): two workgroups per CU where the LDS tile allows it (80 KiB each),
+// the widest tile when it still leaves every CU two workgroups, and a width on which phase 1 can run on strips
+// if there is one.  Four groups only there: fewer halo rows and longer stores (128 x 32 -> 64 on 32x32, cg 2 21.6 -> 19.2 us; 256 x 128 ->
+// 128 on 16x16, cg 2 26.3 -> 20.4; 1000 x 32 -> 61 on 32x32, stride 2 64.5 -> 50.2).
 int pick_cp(const Problem& p, const DwGeom& g, const float* x)
 {
+    if (fused_lds_bytes(p, 4) <= 80 * 1024 && (p.NQ + 127) / 128 >= 512 && strip_rows(g, 4, x) > 0) return 4;
     int first = 0;
     for (int cp = 2; cp >= 1; --cp) {
         const bool fits = fused_lds_bytes(p, cp) <= 80 * 1024 || cp == 1;
@@ -417,15 +431,27 @@ bool dw_forward_fused_eligible(const Problem& p)
     return p.Cin % 16 == 0 && fused_lds_bytes(p, 1) <= 144 * 1024 && p.Cin < 65536;
 }
 
-// Where it also pays: a workgroup computes every filter tile of its columns, so the grid has one workgroup per 32
-// or 64 columns; measured against the two stages run one after the other it wins from 16384 columns up (two
-// workgroups per CU) and loses below (the deep layers of the MobileNet-shaped stack: 512 to 8192 columns).
-bool dw_forward_fused_preferred(const Problem& p) { return dw_forward_fused_eligible(p) && p.NQ >= 16384; }
+// Where it also pays: a workgroup computes every filter tile of its columns, so the grid has one workgroup per 32 to 128
+// columns; measured against the two stages run one after the other it wins from 16384 columns up (two
+// workgroups per CU) and loses below (the deep layers of the MobileNet-shaped stack: 512 to 8192 columns).  And only where its first phase runs on
+// strips: tap by tap (28x28, 14x14, 7x7 maps) 26 drawn layers from 16384 columns on take 1.25 to 3.85 times as long as in two stages (256 x 96 -> 96 on
+// 28x28, cg 1 257 us against 87; 103 x 256 -> 512 on 14x14, cg 1 125 and 70; 801 x 64 -> 64 on 5x5, cg 4 21.4 and 17.2).
+bool dw_forward_fused_preferred(const Problem& p, const DwGeom& g)
+{
+    if (!dw_forward_fused_eligible(p) || p.NQ < 16384) return false;
+    return strip_rows(g, pick_cp(p, g, nullptr), nullptr) > 0;
+}
 
 hipError_t launch_dw_forward_fused(const float* x, const float* kdw, const float* w, float* y, const Problem& p,
                                    const DwGeom& g, hipStream_t st)
 {
-    if (pick_cp(p, g, x) == 2) return launch_fused_cp<2>(x, kdw, w, y, p, g, st);
+    const int cp = pick_cp(p, g, x);
+    if (cp == 4) {
+        const int rb = strip_rows(g, 4, x);
+        if (g.s == 1) return rb == 4 ? launch_fused<4, 1, 4>(x, kdw, w, y, p, g, st) : launch_fused<4, 1, 2>(x, kdw, w, y, p, g, st);
+        return rb == 4 ? launch_fused<4, 2, 4>(x, kdw, w, y, p, g, st) : launch_fused<4, 2, 2>(x, kdw, w, y, p, g, st);
+    }
+    if (cp == 2) return launch_fused_cp<2>(x, kdw, w, y, p, g, st);
     return launch_fused_cp<1>(x, kdw, w, y, p, g, st);
 }
 

@@ -1,0 +1,44 @@
+"""The block's forward: tiles of 128, 64 and 32 columns in one kernel, whose rows leave in one piece per lane, and two stages on maps that
+are not cut into strips.  Which path a layer takes; every sample finite, some against the fp64 oracle."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2101_00745_amd as S
+from oracle import scc_oracle as O
+
+TWO_STAGES, FUSED = 0, 1          # scc_dw_forward_paths of include/scc.h
+# (N, Cin, Cout, H, W, stride, cg, co), path
+LAYERS = [((65, 32, 61, 32, 32, 1, 2, 0.33), FUSED),      # 520 tiles of 128 columns; filters without number
+          ((257, 64, 96, 32, 32, 2, 4, 0.5), FUSED),      # stride 2: rows of 16; the last tile of a sample's own
+          ((1030, 144, 40, 8, 8, 1, 2, 0.5), FUSED),      # 128 columns are two samples; 74 KB of z
+          ((33, 160, 64, 32, 32, 1, 2, 0.5), FUSED),      # 80 KB are too many for 128 columns: 64
+          ((64, 256, 128, 16, 16, 1, 8, 0.5), FUSED),     # one group of 32 or two
+          ((103, 64, 96, 14, 14, 1, 2, 0.5), TWO_STAGES), ((26, 48, 96, 28, 28, 1, 1, 0.33), TWO_STAGES),
+          ((336, 32, 48, 14, 14, 2, 2, 0.25), TWO_STAGES), ((661, 32, 48, 5, 5, 1, 2, 0.5), TWO_STAGES)]
+
+
+@pytest.mark.parametrize("layer,path", LAYERS)
+def test_paths(layer, path):
+    need = S.load().scc_dw_forward_workspace_bytes(*layer, 0)
+    N, Cin, Cout, H, W, s, cg, co = layer
+    assert need == (0 if path == FUSED else N * Cin * ((H - 1) // s + 1) * ((W - 1) // s + 1) * 4)
+    assert S.load().scc_dw_forward_path(*layer, 0, need) == path
+    assert S.load().scc_dw_forward_path(*layer, 0, 0) == FUSED          # a call without a workspace is served as before
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer,path", LAYERS)
+def test_parity(layer, path):
+    N, Cin, Cout, H, W, s, cg, co = layer
+    gen = torch.Generator(device="cuda").manual_seed(12)
+    x, k, w = (torch.randn(*d, generator=gen, device="cuda") for d in ((N, Cin, H, W), (Cin, 3, 3), (Cout, Cin // cg)))
+    some = torch.tensor([0, 1, N // 2, N - 2, N - 1], device="cuda")
+    host = lambda t: t.cpu().numpy()
+    ref = O.depthwise_scc_forward(host(x[some]), host(k), host(w), cg, co, s)
+    plain, fused = S.scc_dw_forward(x, k, w, cg, co, s), S.scc_dw_forward(x, k, w, cg, co, s, fused=True)
+    for y in (plain, fused):
+        assert bool(torch.isfinite(y).all())
+        # binary32: one rounding per value of z and sums of up to 160 products
+        assert np.max(np.abs(host(y[some]) - ref)) <= 2e-6 * np.max(np.abs(ref))
+    assert float((plain - fused).abs().max()) <= 4e-6 * float(plain.abs().max())
