@@ -264,7 +264,8 @@ int scc_depthwise3x3_backward(const void* x, const void* kdw, const void* dz, vo
  * of the depthwise output (N*Cin*Ho*Wo values of the dtype) for all others.  On these a call with a workspace of at least that size
  * (256-byte aligned, owned by the caller) runs the two stages, and the workspace holds the depthwise output afterwards.  A call with
  * workspace == NULL runs one of the other two wherever scc_dw_forward_fusable(...) returns 1, also where two stages would
- * be faster, and is refused with SCC_ERR_WORKSPACE otherwise.
+ * be faster, and is refused with SCC_ERR_WORKSPACE otherwise.  A workspace that is too small or not aligned is refused too, but for
+ * fusable layers of at least 16384 output pixels, which then run fused and leave it alone.
  * scc_dw_forward_fusable: 1 or 0, or a negative scc_status for invalid arguments.
  * Errors: as scc_forward and scc_depthwise3x3_forward, SCC_ERR_WORKSPACE.
  */

@@ -474,9 +474,12 @@ static int dw_forward_path(const Problem& p, const scc::DwGeom& g, scc_dtype dty
                            size_t workspace_bytes)
 {
     const size_t need = dw_forward_need(p, g, dtype);
-    // without a workspace the fused kernel runs wherever it can, also where the two stages would be faster
-    const bool fused = dtype == SCC_F32 && (need == 0 || (!workspace && scc::dw_forward_fused_eligible(p)));
-    if (!fused && (!workspace || workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0)) return SCC_ERR_WORKSPACE;
+    const bool room = workspace && workspace_bytes >= need && ((uintptr_t)workspace & 255u) == 0;
+    // without a workspace the fused kernel runs wherever it can, also where the two stages would be faster; from kFusedPixels on a workspace
+    // that does not do is none
+    const bool fused = dtype == SCC_F32 && (need == 0 || (scc::dw_forward_fused_eligible(p) &&
+                                                          (!workspace || (!room && p.NQ >= scc::kFusedPixels))));
+    if (!fused && !room) return SCC_ERR_WORKSPACE;
     if ((fused || !keep) && scc::dw_forward_few_preferred(p, g, size_of(dtype), fused)) return SCC_DW_FORWARD_FEW;   // touches no workspace
     return fused ? SCC_DW_FORWARD_FUSED : SCC_DW_FORWARD_TWO_STAGES;
 }

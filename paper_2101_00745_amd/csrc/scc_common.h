@@ -281,6 +281,7 @@ hipError_t launch_block_backward(const T* x, const T* kdw, const T* w, const T* 
 template <typename T>
 hipError_t launch_gradient_sums(const SliceSum& w, T* dw, const SliceSum& k, T* dk, hipStream_t st);
 bool dw_forward_fused_eligible(const Problem& p);    // the fused kernel can run the layer
+constexpr int kFusedPixels = 16384;                  // output pixels of a batch from which it may be the faster path
 bool dw_forward_fused_preferred(const Problem& p, const DwGeom& g);   // ... and is the faster path for it
 hipError_t launch_dw_forward_fused(const float* x, const float* kdw, const float* w, float* y, const Problem& p,
                                    const DwGeom& g, hipStream_t st);

@@ -438,7 +438,7 @@ bool dw_forward_fused_eligible(const Problem& p)
 // 28x28, cg 1 257 us against 87; 103 x 256 -> 512 on 14x14, cg 1 125 and 70; 801 x 64 -> 64 on 5x5, cg 4 21.4 and 17.2).
 bool dw_forward_fused_preferred(const Problem& p, const DwGeom& g)
 {
-    if (!dw_forward_fused_eligible(p) || p.NQ < 16384) return false;
+    if (!dw_forward_fused_eligible(p) || p.NQ < kFusedPixels) return false;
     return strip_rows(g, pick_cp(p, g, nullptr), nullptr) > 0;
 }
 

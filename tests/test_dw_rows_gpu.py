@@ -25,6 +25,8 @@ def test_paths(layer, path):
     assert need == (0 if path == FUSED else N * Cin * ((H - 1) // s + 1) * ((W - 1) // s + 1) * 4)
     assert S.load().scc_dw_forward_path(*layer, 0, need) == path
     assert S.load().scc_dw_forward_path(*layer, 0, 0) == FUSED          # a call without a workspace is served as before
+    if need:                                                            # ... and so is one whose workspace is too small
+        assert S.load().scc_dw_forward_path(*layer, 0, need - 1) == S.load().scc_dw_forward_scratch_path(*layer, 0, 1) == FUSED
 
 
 @pytest.mark.gpu
