@@ -65,6 +65,7 @@ struct Deal {
     int chunk;   // workgroups of one XCD: ceil(total / 8)
     int even;    // of these, the first, which are dealt in runs; what then is left goes in eighths ...
     int rest;    // ... from this outer index on
+    uint32_t recip;   // floor(2^32 / inner), 2^32 - 1 for 1
 };
 constexpr int kRun = 16;   // a constant: nothing to divide by in a workgroup's first instructions
 
@@ -72,7 +73,8 @@ inline Deal make_runs(long long outer, int inner)
 {
     const long long total = outer * inner;
     const int runs = (int)(outer / (8 * kRun));   // of each XCD
-    return {(int)total, inner, (int)((total + 7) / 8), runs * kRun * inner, 8 * runs * kRun};
+    return {(int)total, inner, (int)((total + 7) / 8), runs * kRun * inner, 8 * runs * kRun,
+            inner == 1 ? 0xffffffffu : (uint32_t)((1ull << 32) / (uint32_t)inner)};
 }
 
 // An eighth of the order for each XCD, whatever the grid: where grad-weight's workgroups, which keep to slices of the columns, run
@@ -90,6 +92,8 @@ inline Deal make_deal(long long outer, int inner)
     return d.total >= 1024 && inner > 1 ? d : in_eighths(d);
 }
 
+// The tile is a product with the reciprocal and one correction: a division is 0.1 us of every launch (forward of 1 x 32 -> 32 on 8x8 3.72 -> 3.61 us,
+// 16 x 128 -> 128 on 14x14, bf16 3.49 -> 3.36).
 // false: no work, the whole workgroup leaves.  RUNS: false where the deal is one of in_eighths.  Without a branch in here: behind one, the
 // kernel's other arguments are fetched after the deal's (1 us for each generation of workgroups).
 template <bool RUNS = true>
@@ -98,8 +102,12 @@ __device__ __forceinline__ bool dealt(const Deal& d, int bid, int& outer, int& i
     const int xcd = bid & 7, slot = bid >> 3;
     const bool runs = RUNS && slot < d.even;
     const int left = RUNS ? xcd * (d.chunk - d.even) + slot - d.even : xcd * d.chunk + slot;
-    const int at = runs ? slot : left, tile = at / d.inner;
+    const int at = runs ? slot : left;
+    int tile = (int)__umulhi((uint32_t)at, d.recip);   // the quotient or one less
     inner = at - tile * d.inner;
+    const bool more = inner >= d.inner;
+    tile += more ? 1 : 0;
+    inner -= more ? d.inner : 0;
     outer = runs ? tile + (7 * (tile / kRun) + xcd) * kRun : RUNS ? tile + d.rest : tile;
     return (slot < d.chunk) & (runs | (left < (RUNS ? d.total - 8 * d.even : d.total)));
 }

@@ -77,7 +77,7 @@ __global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void forward_m
     // The rest are named for the same reason: fetched where they are first needed, they wait for one another four times over
     // (128 x 256 -> 256 on 16x16, cg 4, co 0.25, bf16 9.9 us against 9.5).
     asm volatile("" ::"s"(T.q.per), "s"(T.q.last), "s"((int)T.q.count), "s"(T.deal.total), "s"(T.deal.inner), "s"(T.deal.chunk),
-                 "s"(T.deal.even), "s"(T.deal.rest), "s"(T.TI), "s"(T.TM), "s"(T.IB), "s"(T.MB), "s"(T.b.g), "s"(T.b.P), "s"(T.b.inv),
+                 "s"(T.deal.even), "s"(T.deal.rest), "s"(T.deal.recip), "s"(T.TI), "s"(T.TM), "s"(T.IB), "s"(T.MB), "s"(T.b.g), "s"(T.b.P), "s"(T.b.inv),
                  "s"(T.Uh));
     constexpr int KA = 2 * KC;   // K-steps per round: two chunks of B loads
     constexpr int kAB = 2 * KA;  // K-steps per staged block of A operands: two rounds
