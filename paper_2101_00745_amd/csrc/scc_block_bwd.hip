@@ -87,7 +87,7 @@ __device__ __forceinline__ void gradients_body(const T_* __restrict__ x, const T
     if (D.input == kInputStage)
         dw::stage_body<T_>(dz, kdw, dx, C, G, D.stage, bid);
     else if (D.input == kInputS2)
-        dw::input_s2_body<T_>(dz, kdw, dx, C, G, (uint32_t)D.items, bid, D.blocks);
+        dw::input_s2_body<T_, 2>(dz, kdw, dx, C, G, (uint32_t)D.items, bid, D.blocks);
     else
         dw::input_gather_body<T_>(dz, kdw, dx, C, G, D.items, bid, D.blocks);
 }

@@ -34,7 +34,7 @@ template <typename T_>
 __global__ __launch_bounds__(256) void depthwise3x3_backward_input_s2(const T_* __restrict__ dz, const T_* __restrict__ kdw,
                                                                       T_* __restrict__ dx, int C, DwGeom G, uint32_t items)
 {
-    dw::input_s2_body<T_>(dz, kdw, dx, C, G, items, blockIdx.x, gridDim.x);
+    dw::input_s2_body<T_, 2>(dz, kdw, dx, C, G, items, blockIdx.x, gridDim.x);
 }
 
 template <typename T_, int S, int RB>
@@ -49,6 +49,7 @@ __global__ __launch_bounds__(kDkThreads) void depthwise3x3_backward_filter_strip
 // Both gradients in one launch where both run on strips: the filter's workgroups (channel fastest) are the first range of the
 // grid, grad-input's the second.  Neither computation changes; small maps, whose kernels take about as long as a launch, gain
 // most (13-block stack at batch 128, training step: kernels 810 -> 737 us with the sums and slices above, 11 of 13 blocks take it).
+// RBX: rows of grad-input's strips; at stride 2, outputs of a row under which a thread writes.
 template <typename T_, int S, int RB, int RBX>
 __global__ __launch_bounds__(256) void depthwise3x3_backward_strips(const T_* __restrict__ x, const T_* __restrict__ kdw,
                                                                     const T_* __restrict__ dz, T_* __restrict__ dx,
@@ -61,7 +62,7 @@ __global__ __launch_bounds__(256) void depthwise3x3_backward_strips(const T_* __
     else if constexpr (S == 1)
         dw::strips_body<T_, 1, RBX>(dz, kdw, dx, C, G, items, 1, bid - nfilter, gridDim.x - nfilter);
     else
-        dw::input_s2_body<T_>(dz, kdw, dx, C, G, (uint32_t)items, bid - nfilter, gridDim.x - nfilter);
+        dw::input_s2_body<T_, RBX>(dz, kdw, dx, C, G, (uint32_t)items, bid - nfilter, gridDim.x - nfilter);
 }
 
 template <typename T_>
@@ -132,10 +133,14 @@ bool launch_both_strips(const T* x, const T* kdw, const T* dz, T* dx, float* par
     long long items, blocks;
     int rbx = dw::strip_rows(N, C, g, &items, &blocks);
     if (S == 2) {
-        items = (long long)N * C * g.Ho * (g.Wo / 2);
+        // no strips on that side.  bf16: stores of 16 bytes, and half the workgroups to go through beside the filter's, from 3072 of them on.
+        // Both gradients, us, two outputs / four: 128 x 128 on 32x32 24.6 / 20.9 (4.0 TB/s), 100 x 96 on 64x64 51.6 / 41.1, 64 x 128 on 40x40
+        // 23.8 / 21.7; the same or slower with fewer workgroups (128 x 256 on 16x16 15.0 / 15.4, 128 x 256 on 14x24 19.9 / 22.2), and alone
+        // (128 x 128 on 32x32 9.9 / 10.3)
+        rbx = sizeof(T) == 2 && (long long)N * C * g.Ho * (g.Wo / 4) >= 3072 * 256 ? 4 : 2;
+        items = (long long)N * C * g.Ho * (g.Wo / rbx);
         blocks = (items + 255) / 256;
         if (blocks > (1ll << 20)) blocks = 1ll << 20;
-        rbx = 1;                                              // no strips on that side
     }
     const long long nfilter = (long long)C * slices;
     if (items >= (1ll << 31) || nfilter + blocks >= (1ll << 31)) return false;
@@ -147,11 +152,16 @@ bool launch_both_strips(const T* x, const T* kdw, const T* dz, T* dx, float* par
     };
     auto with_rb = [&](auto r) {                              // rbx divides rb
         constexpr int RB = decltype(r)::value;
+        if constexpr (S == 2) {
+            if constexpr (sizeof(T) == 2)
+                if (rbx == 4) return go(r, std::integral_constant<int, 4>{});
+            return go(r, std::integral_constant<int, 2>{});
+        }
         if constexpr (S == 1 && RB >= 4)
             if (rbx == 4) return go(r, std::integral_constant<int, 4>{});
         if constexpr (S == 1 && RB >= 2)
             if (rbx == 2) return go(r, std::integral_constant<int, 2>{});
-        go(r, std::integral_constant<int, 1>{});
+        if constexpr (S == 1) go(r, std::integral_constant<int, 1>{});
     };
     rb == 4 ? with_rb(std::integral_constant<int, 4>{})
     : rb == 2 ? with_rb(std::integral_constant<int, 2>{}) : with_rb(std::integral_constant<int, 1>{});
