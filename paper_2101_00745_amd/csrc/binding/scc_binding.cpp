@@ -237,6 +237,21 @@ PyObject* dw_backward(PyObject*, PyObject* const* args, Py_ssize_t n)
     END_HANDLE_TH_ERRORS
 }
 
+// nn._FirstOrder: gradients under create_graph, which only differentiating them makes an error of
+struct FirstOrder : torch::autograd::Function<FirstOrder> {
+    static torch::autograd::variable_list forward(torch::autograd::AutogradContext*, const at::Tensor& dx, const at::Tensor& dk,
+                                                  const at::Tensor& dw, const at::Tensor&, const at::Tensor&, const at::Tensor&,
+                                                  const at::Tensor&)
+    {
+        return {dx.detach(), dk.detach(), dw.detach()};
+    }
+
+    static torch::autograd::variable_list backward(torch::autograd::AutogradContext*, torch::autograd::variable_list)
+    {
+        TORCH_CHECK(false, "sliding-channel convolution has no second derivative");
+    }
+};
+
 // A block under autograd: nn.DWSCCFunction for the training step of a plain call, all of whose tensors want gradients.  Through the Python function
 // a block costs 40 us of host time more, forward and backward, than its launches take (128 x 128 -> 256 on 32x32, stride 2, bf16, one
 // step: 95 us of which the kernels are 62).
@@ -272,6 +287,7 @@ struct Block : torch::autograd::Function<Block> {
         if (layer(a, x, w, &l) && taps(k, x, l) && outputs(dy, x, l))
             g = block_backward(x, k, w, dy, a, l, l.dtype, [&](auto&& f) { return f(stream_of(x)); });
         if (g.empty()) g = general(a);
+        if (at::GradMode::is_enabled()) g = FirstOrder::apply(g[0], g[1], g[2], x, k, w, dy);
         return {g[0], g[1], g[2], at::Tensor(), at::Tensor(), at::Tensor()};
     }
 

@@ -23,6 +23,28 @@ _transforms_active = getattr(torch._C, "_are_functorch_transforms_active", lambd
 _tracing_state = getattr(torch._C, "_get_tracing_state", lambda: True)
 
 
+class _FirstOrder(torch.autograd.Function):
+    """Gradients, as a function of the tensors they were computed from, that cannot be differentiated."""
+
+    @staticmethod
+    def forward(ctx, count, *tensors):
+        return tuple(t.detach() for t in tensors[:count])
+
+    @staticmethod
+    def backward(ctx, *grads):
+        raise RuntimeError("sliding-channel convolution has no second derivative")
+
+
+def _first_order(grads, *used):
+    """What a backward pass returns.  Under create_graph plain results would be constants, and a loss on them would lose its derivative
+    without a word; so they are marked, and only differentiating them is an error."""
+    if not torch.is_grad_enabled():
+        return grads
+    there = [g for g in grads if g is not None]
+    marked = iter(_FirstOrder.apply(len(there), *there, *used))
+    return tuple(None if g is None else next(marked) for g in grads)
+
+
 class SCCFunction(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, weight, cg, co):
@@ -45,7 +67,7 @@ class SCCFunction(torch.autograd.Function):
             dw = _scc.scc_backward_weight(x, dy, ctx.cg, ctx.co)
         if dw is not None:
             dw = dw.to(weight.dtype)                                        # dw comes back as float32
-        return dx, dw, None, None
+        return (*_first_order((dx, dw), dy, x, weight), None, None)
 
 
 def scc(x, weight, cg, co, bias=None):
@@ -100,8 +122,8 @@ class DWSCCFunction(torch.autograd.Function):
         dy = dy.contiguous()
         need_x, need_k, need_w = ctx.needs_input_grad[:3]
         if need_x and need_k and need_w:                                    # the training step: the three stages in one call
-            dx, dk, dw = _scc._dw_backward(x, kdw, weight, dy, ctx.cg, ctx.co, ctx.s, True)   # the gradients in the weights' type
-            return dx, dk, dw, None, None, None
+            grads = _scc._dw_backward(x, kdw, weight, dy, ctx.cg, ctx.co, ctx.s, True)   # the gradients in the weights' type
+            return (*_first_order(grads, dy, x, kdw, weight), None, None, None)
         z = _scc.scc_depthwise3x3_forward(x, kdw, ctx.s)
         dz = dw = None
         if (need_x or need_k) and need_w:
@@ -117,7 +139,7 @@ class DWSCCFunction(torch.autograd.Function):
             dw = dw.to(weight.dtype)
         if dk is not None:
             dk = dk.to(kdw.dtype)
-        return dx, dk, dw, None, None, None
+        return (*_first_order((dx, dk, dw), dy, x, kdw, weight), None, None, None)
 
 
 def dw_scc(x, kdw, weight, cg, co, dw_stride=1, bias=None):
