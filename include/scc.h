@@ -258,10 +258,11 @@ int scc_depthwise3x3_backward(const void* x, const void* kdw, const void* dz, vo
  * their starts of 4, maps of rows of 4 or of 2 x 2, few output pixels): the same for a group of filters and the channels they reach, in
  * as many workgroups as there are groups; in bf16 the intermediate is rounded as two stages round it.  Two stages (every layer):
  * scc_depthwise3x3_forward into `workspace`, then scc_forward on it.
- * scc_dw_forward_workspace_bytes(...) returns 0 for the layers the library runs fused by its own choice
- * (fusable, at least 16384 output pixels over the batch, stride 1 or 2 and rows of 4, 8, 16, 32, 64 or 128 output pixels that the kernel
- * cuts into strips: there fusing is the faster path) and the size
- * of the depthwise output (N*Cin*Ho*Wo values of the dtype) for all others.  On these a call with a workspace of at least that size
+ * scc_dw_forward_workspace_bytes(...) returns 0 for the layers the library runs fused by its own choice, where that is the faster
+ * path: fusable, at least 16384 output pixels over the batch, and maps that the kernel's tiles cut into strips (stride 1 or 2, H and W
+ * that many times Ho and Wo, Ho even, rows of 4, 8 or 16 output pixels; of 32 with at most 304 channels; of 64 with at most 144
+ * and 65409 output pixels or more).  For all others it returns the size of the depthwise output, N*Cin*Ho*Wo values of the dtype:
+ * scratch as large as an activation, which a call with NULL does without.  On these a call with a workspace of at least that size
  * (256-byte aligned, owned by the caller) runs the two stages, and the workspace holds the depthwise output afterwards.  A call with
  * workspace == NULL runs one of the other two wherever scc_dw_forward_fusable(...) returns 1, also where two stages would
  * be faster, and is refused with SCC_ERR_WORKSPACE otherwise.  A workspace that is too small or not aligned is refused too, but for

@@ -363,7 +363,7 @@ int pick_cp(const Problem& p, const DwGeom& g, const float* x)
         if (!first) first = cp;
         if (strip_rows(g, cp, x) > 0) return cp;
     }
-    // no width of that choice runs on strips: a wider tile may (rows of 64 pixels need 64 columns)
+    // no width of that choice runs on strips: a wider tile may (rows of 32 pixels need 64 columns)
     if (fused_lds_bytes(p, 2) <= 80 * 1024 && strip_rows(g, 2, x) > 0) return 2;
     return first;
 }

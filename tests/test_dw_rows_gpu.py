@@ -14,7 +14,13 @@ LAYERS = [((65, 32, 61, 32, 32, 1, 2, 0.33), FUSED),      # 520 tiles of 128 col
           ((1030, 144, 40, 8, 8, 1, 2, 0.5), FUSED),      # 128 columns are two samples; 74 KB of z
           ((33, 160, 64, 32, 32, 1, 2, 0.5), FUSED),      # 80 KB are too many for 128 columns: 64
           ((64, 256, 128, 16, 16, 1, 8, 0.5), FUSED),     # one group of 32 or two
+          ((300, 32, 48, 14, 16, 1, 2, 0.5), FUSED),      # 128 columns, strips of two rows: 8 rows of maps of 14
+          ((300, 32, 48, 28, 32, 2, 2, 0.5), FUSED), ((16, 144, 64, 64, 64, 1, 2, 0.5), FUSED),     # the same at stride 2; rows of 64
+          ((17, 32, 48, 128, 128, 2, 2, 0.33), FUSED),
           ((103, 64, 96, 14, 14, 1, 2, 0.5), TWO_STAGES), ((26, 48, 96, 28, 28, 1, 1, 0.33), TWO_STAGES),
+          ((15, 144, 64, 64, 64, 1, 2, 0.5), TWO_STAGES), ((16, 160, 64, 64, 64, 1, 2, 0.5), TWO_STAGES),     # rows of 64: too few pixels, too many channels
+          ((2, 64, 64, 128, 128, 1, 2, 0.5), TWO_STAGES), ((32, 320, 64, 16, 32, 1, 2, 0.5), TWO_STAGES),
+          ((124, 32, 48, 9, 16, 1, 2, 0.5), TWO_STAGES), ((40, 32, 48, 31, 64, 2, 2, 0.5), TWO_STAGES),     # odd numbers of rows
           ((336, 32, 48, 14, 14, 2, 2, 0.25), TWO_STAGES), ((661, 32, 48, 5, 5, 1, 2, 0.5), TWO_STAGES)]
 
 
@@ -27,6 +33,21 @@ def test_paths(layer, path):
     assert S.load().scc_dw_forward_path(*layer, 0, 0) == FUSED          # a call without a workspace is served as before
     if need:                                                            # ... and so is one whose workspace is too small
         assert S.load().scc_dw_forward_path(*layer, 0, need - 1) == S.load().scc_dw_forward_scratch_path(*layer, 0, 1) == FUSED
+
+
+@pytest.mark.parametrize("s", [1, 2])
+@pytest.mark.parametrize("Wo", [4, 8, 12, 16, 28, 32, 48, 64, 128])
+def test_layers_that_ask_for_no_workspace(Wo, s):
+    """The rule as include/scc.h states it."""
+    query = S.load().scc_dw_forward_workspace_bytes
+    for Cin in (16, 144, 160, 304, 320, 1104, 24, 1120):
+        for Ho in (1, 2, 7, 14, 16, 64):
+            for pixels in (16383, 16384, 65408, 65409):
+                for short in (0, 1) if s == 2 else (0,):                # of an odd input map
+                    N = -(-pixels // (Ho * Wo)) if pixels % 2 == 0 else pixels // (Ho * Wo) + (pixels > 65408)
+                    fused = Cin % 16 == 0 and Cin <= 1104 and N * Ho * Wo >= 16384 and not short and Ho % 2 == 0 and \
+                        (Wo <= 16 and Wo != 12 or Wo == 32 and Cin <= 304 or Wo == 64 and Cin <= 144 and N * Ho * Wo >= 65409)
+                    assert query(N, Cin, 48, s * Ho, s * Wo - short, s, 2, 0.5, 0) == (0 if fused else 4 * N * Cin * Ho * Wo)
 
 
 @pytest.mark.gpu
