@@ -103,7 +103,8 @@ int scc_forward(const void* x, const void* w, void* y,
 /*
  * The same with device scratch: layers with enough arithmetic per byte pack their weights into it in the operand
  * layout of the matrix cores first, which pays for itself; on these layers, and only there, the query is not 0
- * (bf16 layers among them whose weights stay in registers leave the workspace alone: scc_forward_path).
+ * (bf16 layers among them whose weights stay in registers leave the workspace alone: scc_forward_path).  Those layers need y aligned
+ * to 4 bytes: with y on an odd element the other kernels run them, with another order of the sums.
  * workspace: at least scc_forward_workspace_bytes(...) bytes, 256-byte aligned, owned by the caller, contents
  * undefined before and after; NULL runs the kernels that need none, as scc_forward does.  The results of the two
  * differ by the order of their binary32 sums.
@@ -184,7 +185,7 @@ int scc_backward(const void* x, const void* dy, const void* w, void* dx, void* d
                  int N, int Cin, int Cout, int H, int W, int cg, double co,
                  scc_dtype dtype, void* workspace, size_t workspace_bytes, void* stream);
 
-/* Which kernel scc_forward_ws runs a layer on: as scc_backward_path, below, for the backward passes. */
+/* Which kernel scc_forward_ws runs a layer on: as scc_backward_path, below, for the backward passes (y aligned to 4 bytes). */
 typedef enum {
     SCC_FORWARD_ANY = 0,      /* the kernel for any shape */
     SCC_FORWARD_TILE = 1,     /* a filter tile per wavefront, or its planes shared by four of them */
