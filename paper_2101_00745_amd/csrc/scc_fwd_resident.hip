@@ -42,9 +42,10 @@ struct Resident {
     uint32_t bytes;   // of y
 };
 
-constexpr uint32_t kDropped = 0xffffffffu;
+// Past the end of any y (these layers' has less than 2^31 bytes, forward_mfma_eligible), and 16 bytes from there do not wrap around 2^32.
+constexpr uint32_t kDropped = 0x80000000u;
 
-// A row without a filter is stored past the end of y, where the hardware drops it: with a branch around a store the next tile's
+// A row without a filter is stored there and the hardware drops it: with a branch around a store the next tile's
 // loads could not be waited for without the stores.
 template <bool PAST>
 __device__ __forceinline__ void store_row(u32x4 v, __amdgpu_buffer_rsrc_t to, uint32_t at)

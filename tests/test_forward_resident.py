@@ -30,6 +30,14 @@ def test_lines(layer):
     assert path((N, Cin, Cout, H, W, 0, co), 1) == -2
 
 
+def test_outputs_end_before_the_offset_that_is_dropped():
+    """Stores of rows without a filter go to byte 2**31 of y."""
+    N, Cin, Cout, H, W, cg, co = LAYERS[0]
+    last = (2**32 - 1) // (4 * Cout * H * W)
+    assert path((last, Cin, Cout, H, W, cg, co), 1) == RESIDENT and last * Cout * H * W * 2 < 2**31
+    assert path((last + 1, Cin, Cout, H, W, cg, co), 1) != RESIDENT
+
+
 @pytest.mark.gpu
 @pytest.mark.parametrize("layer", LAYERS)
 def test_parity(layer):
@@ -57,3 +65,23 @@ def test_an_output_on_odd_addresses_takes_another_kernel():
     S.scc_forward(x, w, cg, co, out=odd)
     want = S.scc_forward(x, w, cg, co).float()                  # both rounded: a unit of the last place, 2**-7, apart at most
     assert bool(((odd.float() - want).abs() <= want.abs() * 2.0 ** -7 + 2e-5 * float(want.abs().max())).all())
+
+
+def inputs(layer, seed):
+    N, Cin, Cout, H, W, cg, co = layer
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    return [torch.randn(*d, generator=gen, device="cuda").bfloat16() for d in ((N, Cin, H, W), (Cout, Cin // cg))] + [gen]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer", LAYERS)
+def test_nothing_is_written_outside_the_output(layer):
+    """Rows without a filter are stored past the end of y, where the hardware drops them; a sample's last columns are stored twice."""
+    N, Cin, Cout, H, W, cg, co = layer
+    x, w, _ = inputs(layer, 24)
+    size, guard = N * Cout * H * W, 1 << 20
+    buf = torch.full((size + 2 * guard,), 3.0, dtype=torch.bfloat16, device="cuda")
+    y = buf[guard:guard + size].view(N, Cout, H, W)
+    S.scc_forward(x, w, cg, co, out=y)
+    assert torch.equal(y, S.scc_forward(x, w, cg, co))
+    assert bool((buf[:guard] == 3.0).all()) and bool((buf[guard + size:] == 3.0).all())
