@@ -74,6 +74,28 @@ def inputs(layer, seed):
 
 
 @pytest.mark.gpu
+@pytest.mark.parametrize("layer", [LAYERS[1], LAYERS[2], LAYERS[3], LAYERS[5]])
+@pytest.mark.parametrize("value", [float("inf"), float("nan")])
+def test_non_finite_values_stay_in_their_column(layer, value):
+    """They reach every filter whose window has the channel, and may reach others at the same sample and pixel: a wavefront multiplies 96
+    positions of the walk, those past a window by zero."""
+    N, Cin, Cout, H, W, cg, co = layer
+    x, w, _ = inputs(layer, 23)
+    clean = S.scc_forward(x, w, cg, co)
+    places = [(0, 0, 0, 0), (N // 2, Cin // 2, H - 1, W - 1), (N - 1, Cin - 1, H - 1, W - 2)]      # the last pixels: where groups of columns overlap
+    column = torch.zeros(N, H, W, dtype=torch.bool, device="cuda")
+    for n, c, h, v in places:
+        x[n, c, h, v] = value
+        column[n, h, v] = True
+    got = S.scc_forward(x, w, cg, co)
+    assert torch.equal(torch.where(column[:, None], 0, got), torch.where(column[:, None], 0, clean))
+    L, step, _ = S.scc_window_params(Cin, Cout, cg, co)
+    for n, c, h, v in places:
+        reads = (c - torch.arange(Cout, device="cuda") * step) % Cin < L
+        assert not bool(torch.isfinite(got[n, reads, h, v]).any())
+
+
+@pytest.mark.gpu
 @pytest.mark.parametrize("layer", LAYERS)
 def test_nothing_is_written_outside_the_output(layer):
     """Rows without a filter are stored past the end of y, where the hardware drops them; a sample's last columns are stored twice."""
@@ -85,3 +107,24 @@ def test_nothing_is_written_outside_the_output(layer):
     S.scc_forward(x, w, cg, co, out=y)
     assert torch.equal(y, S.scc_forward(x, w, cg, co))
     assert bool((buf[:guard] == 3.0).all()) and bool((buf[guard + size:] == 3.0).all())
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("layer", [LAYERS[1], LAYERS[3]])
+def test_calls_in_a_graph(layer):
+    """Every replay against the eager result, with other work and new inputs in between."""
+    N, Cin, Cout, H, W, cg, co = layer
+    x, w, gen = inputs(layer, 25)
+    out = torch.empty(N, Cout, H, W, dtype=torch.bfloat16, device="cuda")
+    S.scc_forward(x, w, cg, co, out=out)                        # code objects are loaded before the capture
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        S.scc_forward(x, w, cg, co, out=out)
+    for _ in range(3):
+        x.copy_(torch.randn(x.shape, generator=gen, device="cuda"))
+        w.copy_(torch.randn(w.shape, generator=gen, device="cuda"))
+        out.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out, S.scc_forward(x, w, cg, co))
