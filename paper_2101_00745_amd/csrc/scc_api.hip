@@ -96,7 +96,7 @@ int forward_path(const Problem& p, int es, const void* y, const void* workspace,
 {
     const size_t need = workspace ? scc::packed_workspace<true>(p, es) : 0;
     if (need > 0 && (workspace_bytes < need || ((uintptr_t)workspace & 255u) != 0)) return SCC_ERR_WORKSPACE;
-    if (scc::forward_resident_preferred(p, es, y)) return SCC_FORWARD_RESIDENT;
+    if (scc::forward_resident_preferred(p, es, y, workspace != nullptr)) return SCC_FORWARD_RESIDENT;
     if (need > 0) return SCC_FORWARD_PACKED;
     return scc::forward_mfma_eligible(p) ? SCC_FORWARD_TILE : SCC_FORWARD_ANY;
 }

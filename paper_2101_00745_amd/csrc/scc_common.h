@@ -130,7 +130,7 @@ double forward_shared_gain(const Problem& p);   // channel fetches saved: own sp
 bool forward_shared_preferred(const Problem& p);   // ... and faster
 hipError_t launch_forward_shared(const float* x, const float* w, float* y, const Problem& p, hipStream_t st);
 // Forward with the weights resident in registers, bf16 (scc_fwd_resident.hip); es is the storage type's size
-bool forward_resident_preferred(const Problem& p, int es, const void* y);
+bool forward_resident_preferred(const Problem& p, int es, const void* y, bool workspace);
 hipError_t launch_forward_resident(const bf16_t* x, const bf16_t* w, bf16_t* y, const Problem& p, hipStream_t st);
 bool backward_input_mfma_eligible(const Problem& p);
 template <typename T> hipError_t launch_backward_input_mfma(const T* dy, const T* w, T* dx, const Problem& p, hipStream_t st);

@@ -9,12 +9,14 @@
 // its registers: per tile it reads B operands from LDS, multiplies and stores 512 contiguous bytes of a row per half-wave.  The planes of
 // the next tile are in flight meanwhile.
 //
-// What bounds it: HBM.  The kernels with a workgroup per tile spend most of a tile on its first loads (weights, table, planes) and its
-// last stores; here a CU holds one workgroup (more put more columns in flight and are slower: 128 x 128 -> 512 on 32x32, cg 2, co 0.33
-// 37.5 us, 40.7 with two), the tiles' loads and stores are in flight together, and the chip sweeps the tensors on one front in pieces of 512 bytes (loads
-// and stores alone, in this pattern: 32 us).  That layer 45 us with packed weights, 37.5 here (4.5 TB/s); 256 x 128 -> 256 on 32x32, cg 2
-// 52 -> 40.5; 312 x 224 -> 893 on 14x14, cg 4, co 0.33 65 -> 41; 434 x 448 -> 1792 on 12x6, cg 8, co 0.25 83 -> 48.  Binary32 layers, whose
-// three pieces and six products per value leave no room for 256 columns, gained 4 % at most and stay with the other kernels.
+// What bounds it: HBM where x is not on the chip, else a tile's chain of load, barrier, product and store.  The kernels with a workgroup
+// per tile spend most of a tile on its first loads (weights, table, planes) and its last stores; here a CU holds one workgroup (more put
+// more columns in flight and are slower: 128 x 128 -> 512 on 32x32, cg 2, co 0.33 37.5 us, 40.7 with two), the tiles' loads and
+// stores are in flight together, and the chip sweeps the tensors on one front in pieces of 512 bytes (loads and stores alone, in this
+// pattern: 32 us; x is read once, 33 of 32 MiB: the groups' reads meet in the L2s).  us, packed weights and their packing launch -> this,
+// x cold / x in three buffers in turn: that layer 44 -> 39 / 36.7 -> 33-35; 312 x 224 -> 893 on 14x14, cg 4, co 0.33 65 -> 39 / 59 -> 32;
+// 434 x 448 -> 1792 on 12x6, cg 8, co 0.25 82 -> 44 / 75 -> 35.  Binary32 layers, whose three pieces and six products per
+// value leave no room for 256 columns, gained 4 % at most and stay with the other kernels.
 //
 // Products and sums are those of the kernels with packed weights (scc_packed_kernel.h).
 #include "scc_packed_kernel.h"
@@ -243,6 +245,21 @@ Resident make_resident(const Problem& p)
     return t;
 }
 
+// What the kernel takes: a workgroup's start costs 3 us, so 64 MB of x and y, and more than three tiles of 256 columns per workgroup,
+// more than four where a tile's filters start together; windows whose 32 filters span at most KA K groups and, where they start
+// together, 80 positions (the walks get long: from 88 on 0.74 to 0.92 of the per-tile kernel's speed); row groups filled to more than
+// half; tiles of the others that fetch planes again, 1.7 times with differing starts in a tile, 2.5 times without.
+bool resident_eligible(const Problem& p, const Band& b, const Resident& t, int* longest)
+{
+    if (t.deal.chunk <= (b.F < 32 ? 3 : 4) * t.lanes || 100ll * p.Cout < 55ll * 128 * t.NG || t.NG > 32) return false;
+    double again;
+    packed::fetches_without_sharing<true>(p, b, &again);
+    if (b.F < 32 ? again < 1.7 : again < 2.5 || p.L > 80) return false;
+    int octets;
+    reach(p, b, t.rows, &octets, longest);
+    return octets <= 2 * KA && *longest <= 192;
+}
+
 template <int NQ>
 hipError_t launch_variant(const bf16_t* x, const bf16_t* w, bf16_t* y, const Problem& p, const Resident& t, hipStream_t st)
 {
@@ -262,26 +279,35 @@ hipError_t launch_variant(const bf16_t* x, const bf16_t* w, bf16_t* y, const Pro
 
 }  // namespace
 
-// Layers that gain, of 95 measured against the per-tile and the packed forward.  A workgroup's start takes 3 us: 64 MB of x and y, and at least
-// four tiles of 256 columns per workgroup, five where a tile's filters start together (four of them 0.85 to 1.12: 855 x 64 -> 256 on 12x12, cg 2 23.4
-// and 25.2 us).  Windows whose 32 filters span at most KA K groups and, where they start together, 80 positions
-// (the walks get long: from 88 on 0.74 to 0.92 against the per-tile kernel, but for one of 1.0).  Row groups filled to more than half (64 x 64 and 32 x 64 channels 0.72 to 0.98).  And tiles of the others that
-// fetch planes again: 1.7 times with differing starts in a tile, 2.5 times without (below 0.8 to 1.05).  Layers taken run 1.02 to 1.58 times as
-// fast.  Stores take rows of whole words.
-bool forward_resident_preferred(const Problem& p, int es, const void* y)
+// Which of these gain: of 1300 drawn layers that the kernel takes, and 250 more of those chosen here, times of the packed kernel with its
+// packing launch where that is preferred, else of the per-tile kernel, over this one's, mean (least), with x in three buffers in turn or
+// just written by another kernel, the lower of the two | with x cold.  Cold operands alone (1.16, least 0.79, over all of them) do not
+// show what is lost: this kernel waits for a tile's planes wherever they come from, the others are faster with planes that the last
+// level cache still holds.
+//   No packed weights: with starts or windows off multiples of four, whose weights the per-tile kernel loads one by one, at least eight
+//   starts to a tile and windows of more than 8 channels 1.26 (0.95) | 1.34; shorter windows 1.11 (0.94), fewer starts 0.83 (0.74);
+//   even weights 0.89 (0.67) | 1.06 (258 x 128 -> 512 on 16x16, cg 4, co 0.5 20.4 us, per tile 14.3).
+//   Packed weights, planes that are no whole pieces of 64 bytes, which that kernel writes past the caches: below 600 bytes 1.33 (0.85,
+//   0.97 in turn) | 1.40; larger ones with Cout >= 3 Cin 1.24 (0.95) | 1.23, others of less than 70e6 values of x and y 1.07 (0.93) | 1.23,
+//   of more 0.95 (0.76) | 1.33.
+//   Packed weights, whole pieces: with workgroups on 7/8 of the CUs and walks past 64 positions that end by 96, or whose groups are
+//   filled to three quarters at most (the other kernel multiplies the empty rows as well), 1.06 (0.90) | 1.21; the rest 0.98 (0.71) | 1.10.
+// Without a workspace even weights stay with the per-tile kernel (0.72 to 1.3 here), uneven ones gain more than with one (1.10 to 3.1).
+// Stores take rows of whole words.
+bool forward_resident_preferred(const Problem& p, int es, const void* y, bool workspace)
 {
     if (es != 2 || p.L > 16 * KA || p.HW < CT || p.HW % 2 != 0 || ((uintptr_t)y & 3u) != 0 || !forward_mfma_eligible(p)) return false;
     if ((double)(p.Cin + p.Cout) * (double)p.NQ < 32e6) return false;
     const Band b = make_band(p);
     if (4ll * b.P * b.F > 5ll * p.Cout) return false;       // few filters on many starts: too many empty rows
     const Resident t = make_resident(p);
-    if (t.deal.chunk <= (b.F < 32 ? 3 : 4) * t.lanes || 100ll * p.Cout < 55ll * 128 * t.NG || t.NG > 32) return false;
-    double again;
-    packed::fetches_without_sharing<true>(p, b, &again);
-    if (b.F < 32 ? again < 1.7 : again < 2.5 || p.L > 80) return false;
-    int octets, longest;
-    reach(p, b, t.rows, &octets, &longest);
-    return octets <= 2 * KA && longest <= 192;
+    int longest;
+    if (!resident_eligible(p, b, t, &longest)) return false;
+    const bool uneven = b.g % 4 != 0 || p.L % 4 != 0, packs = packed::choose<true>(p, es) > 0;
+    if (!uneven && !(packs && workspace)) return false;
+    if (!packs) return b.F < 8 && b.P >= 8 && p.L > 8;
+    if (p.HW % 32 != 0) return p.HW < 300 || p.Cout >= 3 * p.Cin || (double)(p.Cin + p.Cout) * (double)p.NQ < 70e6;
+    return 8 * t.lanes * t.NG >= 224 && longest > 64 && (longest <= 96 || 4 * p.Cout <= 3 * 128 * t.NG);
 }
 
 hipError_t launch_forward_resident(const bf16_t* x, const bf16_t* w, bf16_t* y, const Problem& p, hipStream_t st)
