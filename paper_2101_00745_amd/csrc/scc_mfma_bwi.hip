@@ -24,7 +24,7 @@ template <typename T_, int CT, int KC, int S, int WPB>
 __global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void backward_input_mfma32(const T_* __restrict__ dy, const T_* __restrict__ w,
                                                              T_* __restrict__ dx, Problem P, bwi::BwiTiling T)
 {
-    bwi::backward_input_body<T_, CT, KC, S, WPB>(dy, w, dx, P, T, (int)blockIdx.x);
+    bwi::backward_input_body<T_, CT, KC, S, WPB, false, true>(dy, w, dx, P, T, (int)blockIdx.x);
 }
 
 }  // namespace

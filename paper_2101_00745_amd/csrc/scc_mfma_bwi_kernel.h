@@ -49,18 +49,29 @@ template <int CT, int S, int WPB>
 constexpr size_t reduce_bytes() { return S > 1 ? (size_t)(WPB / S) * (S - 1) * CT * 16 * 64 * sizeof(float) : 0; }
 
 // `shared_red`: LDS of at least reduce_bytes<CT, S, WPB>() that the caller provides for that sum (a kernel that
-// holds dynamic LDS for other workgroups of its grid lends it); null: the body declares its own.
-template <typename T_, int CT, int KC, int S, int WPB, bool LENT = false>
+// holds dynamic LDS for other workgroups of its grid lends it); null: the body declares its own.  ALONE: the whole kernel is this body.
+template <typename T_, int CT, int KC, int S, int WPB, bool LENT = false, bool ALONE = false>
 __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, const T_* __restrict__ w,
                                                     T_* __restrict__ dx, const Problem& P, const BwiTiling& T,
                                                     const int bid, float* shared_red = nullptr)
 {
     typedef T_ bvec __attribute__((ext_vector_type(CT), aligned(sizeof(T_))));   // CT consecutive columns of one plane
     constexpr uint32_t ES = sizeof(T_);
+    // Alone and with one column per lane: few columns, one generation of workgroups at most, and a tile's time is that of its loads, chunk
+    // after chunk.  The compiler does not see that: with anything changed around it, it packs the bf16 of a chunk pair by pair as they
+    // come, with one load in flight, or cuts binary32 values before it asks for the next.  HELD spells the order out (below), and names all
+    // arguments here, so that they are fetched together.  Grad-input, us, left to itself -> so: 2 x 208 -> 832 on 16x16, cg 1, co 0.25, bf16
+    // 14.6 -> 6.9; 46 x 256 -> 1024 on 2x2, cg 2, co 0.25, bf16 8.1 -> 5.3; 1 x 736 -> 1472 on 16x16, cg 4, co 0.33, f32 6.9 -> 6.1.  (Binary32
+    // tiles of one wavefront, and wider ones, have the right order by themselves.)
+    constexpr bool HELD = CT == 1 && ALONE && (ES == 2 || S > 1), WIDE = HELD && ES == 2;
+    if constexpr (HELD)
+        asm volatile("" ::"s"(T.deal.total), "s"(T.deal.inner), "s"(T.deal.chunk), "s"(T.deal.recip), "s"(T.b.g), "s"(T.b.P), "s"(T.b.inv),
+                     "s"(T.b.F), "s"(T.CB), "s"(T.even), "s"(T.q.per), "s"(T.q.last), "s"((int)T.q.count), "s"(P.L), "s"(P.HW), "s"(P.Cin),
+                     "s"(P.Cout));
     // bid is the workgroup's index in a launch whose first workgroup is a multiple of 8: bid % 8 names the XCD; the
     // channel blocks of a column tile, which re-read the same dy planes, share one and its L2
     int ct, fg;
-    if (!dealt<!LENT>(T.deal, bid, ct, fg)) return;          // the whole workgroup leaves
+    if (!dealt<!LENT && !HELD>(T.deal, bid, ct, fg)) return;          // the whole workgroup leaves
     const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     const int cb = fg * (WPB / S) + wave / S, split = wave % S;
     const bool tvalid = cb < T.CB;
@@ -138,22 +149,48 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
         }
     };
 
-    // Software pipelined over an even number n of chunks, which load(a, in, b) requests one after the other.
+    // Software pipelined over an even number n of chunks, which load(a, in, b) requests one after the other.  HELD: nothing of a chunk moves
+    // past the next one's loads; WIDE: its bf16 stay in a register each until they are multiplied.
+    typedef std::conditional_t<WIDE, uint32_t, T_> aheld;
+    typedef std::conditional_t<WIDE, uint32_t, bvec> bheld;
+    typedef std::conditional_t<WIDE, T_, bvec> bmem;
+    auto use_chunk = [&](const aheld (&ah)[KC], uint32_t am, const bheld (&bh)[KC]) __attribute__((always_inline)) {
+        if constexpr (HELD) {
+            __builtin_amdgcn_sched_barrier(0);
+            T_ as[KC];
+            bvec bs[KC];
+#pragma unroll
+            for (int e = 0; e < KC; ++e) {
+                if constexpr (WIDE) {
+                    as[e] = (T_)ah[e];
+                    bs[e][0] = (T_)bh[e];
+                } else {
+                    as[e] = ah[e];
+                    float v = bh[e][0];
+                    asm volatile("" : "+v"(as[e]), "+v"(v));
+                    bs[e][0] = v;
+                }
+            }
+            mma_chunk(as, am, bs);
+        } else {
+            mma_chunk(ah, am, bh);
+        }
+    };
     auto pipeline = [&](int n, auto&& load) __attribute__((always_inline)) {
-        T_ a0[KC], a1[KC];
-        bvec b0[KC], b1[KC];
+        aheld a0[KC], a1[KC];
+        bheld b0[KC], b1[KC];
         uint32_t m0, m1;
         if (n <= 0) return;
         load(a0, m0, b0);
         for (int cix = 0; cix + 2 < n; cix += 2) {
             load(a1, m1, b1);
-            mma_chunk(a0, m0, b0);
+            use_chunk(a0, m0, b0);
             load(a0, m0, b0);
-            mma_chunk(a1, m1, b1);
+            use_chunk(a1, m1, b1);
         }
         load(a1, m1, b1);
-        mma_chunk(a0, m0, b0);
-        mma_chunk(a1, m1, b1);
+        use_chunk(a0, m0, b0);
+        use_chunk(a1, m1, b1);
     };
     // K-steps: each half-wave walks Uh (window, filter) slots; an even number of chunks
     const int Uh = ((M * T.b.F + 1) / 2 + 2 * KC - 1) / (2 * KC) * (2 * KC);
@@ -184,20 +221,36 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
         // what a bf16 tile executes: 226 per chunk of 4 matrix instructions (fp32: 345 of 24), 45 (fp32: 160) here; same
         // operands in the same order.
         const uint32_t wstep = (uint32_t)T.b.P * (uint32_t)P.L * ES, gstep = (uint32_t)T.b.P * plane;
-        pipeline((t1 - t0) / KC, [&](T_(&ad)[KC], uint32_t& am, bvec(&bd)[KC]) __attribute__((always_inline)) {
+        // WIDE: these bases in scalar registers, not added up again for every chunk
+        typedef const __attribute__((address_space(1))) char* gptr;
+        gptr wat[KC], gat[KC];
+        if constexpr (WIDE) {
+#pragma unroll
+            for (int s = 0; s < KC; ++s) {
+                wat[s] = (gptr)(wb + (size_t)(s * wstep));
+                gat[s] = (gptr)(gb + (size_t)(s * gstep));
+                asm("" : "+s"(wat[s]), "+s"(gat[s]));
+            }
+        }
+        pipeline((t1 - t0) / KC, [&](aheld(&ad)[KC], uint32_t& am, bheld(&bd)[KC]) __attribute__((always_inline)) {
             const int k = mm < M ? r + T.b.P * i : 0;
             const bool in = (mm < M) & cvalid & (ju >= 0) & (ju < P.L);
             am = in ? 0xffffffffu : 0u;
             const uint32_t wofs = (uint32_t)(k * P.L + (in ? ju : 0)) * ES, gofs = gcol + (uint32_t)k * plane;
 #pragma unroll
             for (int s = 0; s < KC; ++s) {
-                ad[s] = *(const T_*)(wb + (size_t)(s * wstep) + wofs);
-                bd[s] = *(const bvec*)(gb + (size_t)(s * gstep) + gofs);
+                if constexpr (WIDE) {
+                    ad[s] = *(const __attribute__((address_space(1))) T_*)(wat[s] + wofs);
+                    bd[s] = *(const __attribute__((address_space(1))) T_*)(gat[s] + gofs);
+                } else {
+                    ad[s] = *(const T_*)(wb + (size_t)(s * wstep) + wofs);
+                    bd[s] = *(const bvec*)(gb + (size_t)(s * gstep) + gofs);
+                }
             }
             advance(KC);
         });
     } else {
-        pipeline((t1 - t0) / KC, [&](T_(&ad)[KC], uint32_t& am, bvec(&bd)[KC]) {
+        pipeline((t1 - t0) / KC, [&](aheld(&ad)[KC], uint32_t& am, bheld(&bd)[KC]) {
             am = 0;
 #pragma unroll
             for (int s = 0; s < KC; ++s) {
@@ -209,7 +262,7 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
                 ad[s] = *(const T_*)(wb + (uint32_t)(in ? at : 0) * ES);
                 am |= in ? (1u << s) : 0u;
                 const uint32_t rowofs = (uint32_t)(kvalid ? k : 0) * plane;
-                bd[s] = *(const bvec*)(gb + (uint32_t)(gcol + rowofs));
+                bd[s] = *(const bmem*)(gb + (uint32_t)(gcol + rowofs));
                 advance(1);                      // next filter of this window, or the first filter of the next window
             }
         });
