@@ -6,15 +6,16 @@
 namespace scc {
 
 // Workgroups of a launch as (outer, inner) pairs, inner fastest: outer is a column tile, inner the groups of rows that read its
-// planes.  Consecutive workgroups go to consecutive XCDs, so blockIdx % 8 names the XCD, and an XCD takes runs of that order, so that
-// the groups of a column tile meet in its L2.  A grid of several generations (from 1024 workgroups on) is dealt out in runs of 16 column
-// tiles, so that the chip sweeps the tensors on one front.  With an eighth of the columns each, the XCDs are an eighth of a tensor
-// apart, which for many sizes (powers of two) puts them on the same memory channels at the same time.  Forward, us, eighths -> runs of
-// 16: 1024 x 256 -> 256 on 16x16, cg 4, f32 102 -> 101 (no more than noise), bf16 63.4 -> 53.4; 128 x 128 -> 512 on 32x32, cg 2, co 0.33, bf16 50 -> 45; 512 x 512 ->
-// 512 on 8x8, cg 8, bf16 17.2 -> 16.1; grad-input of 256 x 512 -> 512 on 14x14, cg 4, bf16 42.2 -> 38.0; of 66 drawn layers 0.98 to 1.07.  Shorter
-// runs put tiles that share cache lines on two XCDs: 256 x 512 -> 512 on 14x14, cg 4, bf16 41.5 in eighths, 43.7 with runs of one, 41.4 with 16.
-// Grids of one generation are everywhere at once (64 x 512 -> 512 on 14x14, cg 8, bf16 11.2 in eighths, 12.7 and 11.2 with runs of one
-// and 16), and where a tile has one group only, neither order is better (0.91 to 1.07).
+// planes.  Consecutive workgroups go to consecutive XCDs, so blockIdx % 8 names the XCD, and an XCD takes runs of that order, so
+// that the groups of a column tile meet in its L2.  A grid of several generations (from 1024 workgroups on) is dealt out in runs of
+// 16 column tiles, so that the chip sweeps the tensors on one front.  With an eighth of the columns each, the XCDs are an eighth of
+// a tensor apart, which for many sizes (powers of two) puts them on the same memory channels at the same time.  Forward, us,
+// eighths -> runs of 16: 1024 x 256 -> 256 on 16x16, cg 4, f32 102 -> 101 (no more than noise), bf16 63.4 -> 53.4; 128 x 128 -> 512
+// on 32x32, cg 2, co 0.33, bf16 50 -> 45; 512 x 512 -> 512 on 8x8, cg 8, bf16 17.2 -> 16.1; grad-input of 256 x 512 -> 512 on
+// 14x14, cg 4, bf16 42.2 -> 38.0; of 66 drawn layers 0.98 to 1.07.  Shorter runs put tiles that share cache lines on two XCDs: 256
+// x 512 -> 512 on 14x14, cg 4, bf16 41.5 in eighths, 43.7 with runs of one, 41.4 with 16. Grids of one generation are everywhere at
+// once (64 x 512 -> 512 on 14x14, cg 8, bf16 11.2 in eighths, 12.7 and 11.2 with runs of one and 16), and where a tile has one
+// group only, neither order is better (0.91 to 1.07).
 struct Deal {
     int total;   // workgroups with work: outer * inner
     int inner;
@@ -48,9 +49,9 @@ inline Deal make_deal(long long outer, int inner)
     return d.total >= 1024 && inner > 1 ? d : in_eighths(d);
 }
 
-// The tile is a product with the reciprocal and one correction: a division is 0.1 us of every launch (forward of 1 x 32 -> 32 on 8x8 3.72 -> 3.61 us,
-// 16 x 128 -> 128 on 14x14, bf16 3.49 -> 3.36).
-// false: no work, the whole workgroup leaves.  RUNS: false where the deal is one of in_eighths.  Without a branch in here: behind one, the
+// The tile is a product with the reciprocal and one correction: a division is 0.1 us of every launch (forward of 1 x 32 -> 32 on
+// 8x8 3.72 -> 3.61 us, 16 x 128 -> 128 on 14x14, bf16 3.49 -> 3.36).  Returns false where there is no work and the whole
+// workgroup leaves.  RUNS false: the deal, whatever it is, is read as one of in_eighths.  Without a branch in here: behind one, the
 // kernel's other arguments are fetched after the deal's (1 us for each generation of workgroups).
 template <bool RUNS = true>
 __host__ __device__ __forceinline__ bool dealt(const Deal& d, int bid, int& outer, int& inner)

@@ -150,7 +150,7 @@ bool launch_both_strips(const T* x, const T* kdw, const T* dz, T* dx, float* par
             <<<dim3((unsigned)(nfilter + blocks)), dim3(kDkThreads), 0, st>>>(x, kdw, dz, dx, part, N, C, g, per,
                                                                               (uint32_t)nfilter, items);
     };
-    auto with_rb = [&](auto r) {                              // rbx divides rb
+    auto with_rb = [&](auto r) {                              // stride 1: rbx divides rb
         constexpr int RB = decltype(r)::value;
         if constexpr (S == 2) {
             if constexpr (sizeof(T) == 2)

@@ -272,8 +272,8 @@ hipError_t launch_variant(const bf16_t* x, const bf16_t* w, bf16_t* y, const Pro
         forward_resident<NQ, PAST><<<dim3((unsigned)(8 * t.lanes * t.NG)), dim3(256), kLds, st>>>(x, w, y, p, t);
         return hipGetLastError();
     };
-    // past the caches where rows are whole pieces of 64 bytes, as in the per-tile forward (512 x 128 -> 128 on 28x28, cg 2, co 0.25: 51.3 us past
-    // them, 49.1 through them; 128 x 128 -> 512 on 32x32 37.4 and 38.3)
+    // past the caches where rows are whole pieces of 64 bytes, as in the per-tile forward (512 x 128 -> 128 on 28x28, cg 2, co
+    // 0.25: 51.3 us past them, 49.1 through them; 128 x 128 -> 512 on 32x32 37.4 and 38.3)
     return p.HW * sizeof(bf16_t) % 64 == 0 ? launch(std::true_type()) : launch(std::false_type());
 }
 

@@ -126,10 +126,12 @@ __global__ __launch_bounds__(kWaves * 64) void backward_fused_lds32(const float*
     }
 
     // This K-split's chunks are KS apart, so that the chip sweeps the tensors on one front.  (With a stretch of the columns each,
-    // the K-splits are a fraction of a tensor apart, for many sizes on the same memory channels at the same time: operands from HBM,
-    // 128 x 256 -> 256 on 16x16, cg 4, co 0.5 31.5 us with stretches, 28.7 so; 77 x 512 -> 509 on 12x12, cg 8 26.5 and 24.6; operands
-    // still on the chip: the same.)  Its chunk c is the column groups from q0 - 8*sub + 32*KS*c on, this
-    // wavefront's sub-chunk the 8 of them from q0 + 32*KS*c on.
+    // the K-splits are a fraction of a tensor apart, for many sizes on the same memory channels at the same time: operands from
+    // HBM, 128 x 256 -> 256 on 16x16, cg 4, co 0.5 31.5 us with stretches, 28.7 so; 256 x 512 -> 512 on 14x14, cg 8, three buffers
+    // in turn, 94 and 86; operands still on the chip: the same, 0.97 to 1.02.  An accumulator adds as many chunks as before, since
+    // rounding up twice is rounding up once, ceil(ceil(NQ4 / KS) / 32) = ceil(nchunk / KS); its last chunk may be whole where a
+    // stretch's was not.  dw's error against binary64 over eight layers: 0.993 to 1.007 of what it was, 0.998 on average.)  Its
+    // chunk c is the column groups from q0 - 8*sub + 32*KS*c on, this wavefront's sub-chunk the 8 of them from q0 + 32*KS*c on.
     const int nchunk = (T.nchunk - ks + T.KS - 1) / T.KS;      // at least one
     const int q0 = 32 * ks + 8 * sub, ahead = 32 * T.KS;
 

@@ -57,12 +57,12 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
 {
     typedef T_ bvec __attribute__((ext_vector_type(CT), aligned(sizeof(T_))));   // CT consecutive columns of one plane
     constexpr uint32_t ES = sizeof(T_);
-    // Alone and with one column per lane: few columns, one generation of workgroups at most, and a tile's time is that of its loads, chunk
-    // after chunk.  The compiler does not see that: with anything changed around it, it packs the bf16 of a chunk pair by pair as they
-    // come, with one load in flight, or cuts binary32 values before it asks for the next.  HELD spells the order out (below), and names all
-    // arguments here, so that they are fetched together.  Grad-input, us, left to itself -> so: 2 x 208 -> 832 on 16x16, cg 1, co 0.25, bf16
-    // 14.6 -> 6.9; 46 x 256 -> 1024 on 2x2, cg 2, co 0.25, bf16 8.1 -> 5.3; 1 x 736 -> 1472 on 16x16, cg 4, co 0.33, f32 6.9 -> 6.1.  (Binary32
-    // tiles of one wavefront, and wider ones, have the right order by themselves.)
+    // Alone and with one column per lane: few columns, one generation of workgroups at most, and a tile's time is that of its
+    // loads, chunk after chunk.  The compiler does not see that: with anything changed around it, it packs the bf16 of a chunk pair
+    // by pair as they come, with one load in flight, or cuts binary32 values before it asks for the next.  HELD spells the order
+    // out (below), and names all arguments here, so that they are fetched together.  Grad-input, us, left to itself -> so: 2 x 208
+    // -> 832 on 16x16, cg 1, co 0.25, bf16 14.6 -> 6.9; 46 x 256 -> 1024 on 2x2, cg 2, co 0.25, bf16 8.1 -> 5.3; 1 x 736 -> 1472 on
+    // 16x16, cg 4, co 0.33, f32 6.9 -> 6.1.  (Binary32 tiles of one wavefront, and wider ones, have the right order by themselves.)
     constexpr bool HELD = CT == 1 && ALONE && (ES == 2 || S > 1), WIDE = HELD && ES == 2;
     if constexpr (HELD)
         asm volatile("" ::"s"(T.deal.total), "s"(T.deal.inner), "s"(T.deal.chunk), "s"(T.deal.recip), "s"(T.b.g), "s"(T.b.P), "s"(T.b.inv),
@@ -149,8 +149,8 @@ __device__ __forceinline__ void backward_input_body(const T_* __restrict__ dy, c
         }
     };
 
-    // Software pipelined over an even number n of chunks, which load(a, in, b) requests one after the other.  HELD: nothing of a chunk moves
-    // past the next one's loads; WIDE: its bf16 stay in a register each until they are multiplied.
+    // Software pipelined over an even number n of chunks, which load(a, in, b) requests one after the other.  HELD: nothing of a
+    // chunk moves past the next one's loads; WIDE: its bf16 stay in a register each until they are multiplied.
     typedef std::conditional_t<WIDE, uint32_t, T_> aheld;
     typedef std::conditional_t<WIDE, uint32_t, bvec> bheld;
     typedef std::conditional_t<WIDE, T_, bvec> bmem;

@@ -75,7 +75,7 @@ __global__ __launch_bounds__(WPB * 64, CT == 4 && S == 4 ? 2 : 1) void forward_m
     // fetched only there, and the first planes' addresses wait for them (27 x 384 -> 384 on 16x16, cg 2: 17.6 us against 17.2;
     // 128 x 256 -> 256 on 8x8: 9.8 against 9.5; 0.2 to 0.5 us a pass on layers of one generation of workgroups).
     // The rest are named for the same reason: fetched where they are first needed, they wait for one another four times over
-    // (128 x 256 -> 256 on 16x16, cg 4, co 0.25, bf16 9.9 us against 9.5).
+    // (128 x 256 -> 256 on 16x16, cg 4, co 0.25, bf16 8.45 us against 8.25; 16 x 128 -> 128 on 14x14, cg 4 3.33 and 3.28).
     asm volatile("" ::"s"(T.q.per), "s"(T.q.last), "s"((int)T.q.count), "s"(T.deal.total), "s"(T.deal.inner), "s"(T.deal.chunk),
                  "s"(T.deal.even), "s"(T.deal.rest), "s"(T.deal.recip), "s"(T.TI), "s"(T.TM), "s"(T.IB), "s"(T.MB), "s"(T.b.g), "s"(T.b.P), "s"(T.b.inv),
                  "s"(T.Uh));
